@@ -14,6 +14,18 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 __device__ __forceinline__ int wave_id() { return threadIdx.x >> 6; }
 __device__ __forceinline__ uint64_t lanes_below() { return (1ull << lane_id()) - 1ull; }
 
+// Inclusive prefix sum over the 64 lanes, in registers: row shifts inside 16 lanes, then the row totals are
+// broadcast into the following rows (six vector instructions against six LDS round trips for shuffles).
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);            // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);            // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);            // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);            // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);            // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);            // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 // For the lanes with `valid`, the number of lower lanes holding the same key; `total` receives the
 // number of lanes holding it.  Keys are < 2^bits.  One ballot per key bit: the lanes that agree with
 // mine on every bit are the lanes with my key (no loop over the distinct keys of the wave).
@@ -158,12 +170,7 @@ __device__ __forceinline__ void build_token_lists(KeyFn key_of, const int* prese
     __syncthreads();
     if (threadIdx.x < kWave) {                          // exclusive scan of the slot counts
         const int c = (int)threadIdx.x < spr ? s_cnt[threadIdx.x] : 0;
-        int incl = c;
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-            const int up = __shfl_up(incl, d);
-            if (lane_id() >= d) incl += up;
-        }
+        const int incl = wave_inclusive_sum(c);
         if ((int)threadIdx.x < spr) {
             s_off[threadIdx.x] = incl - c;
             group_offsets[threadIdx.x] = incl - c;

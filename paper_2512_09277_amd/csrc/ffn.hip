@@ -20,107 +20,17 @@
 #include <type_traits>
 #include <utility>
 
-#include "device_utils.h"
+#include "ffn_common.h"
+#include "ffn_split.h"
 #include "host_utils.h"
 #include "metro.h"
 
 namespace metro {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int kThreads = 256;
-constexpr int kMaxSpr = 64;
 constexpr int kWideRows = 128;              // rows of a full wide tile
 constexpr int kStreamRows = 128;            // largest remainder that may become a stream tile
-
-struct Tile {
-    int slot, row0, rows, col;              // rows [row0, row0 + rows) of a slot x column tile `col`
-};
-
-// Upper bound of the tile count (the launch grid; workgroups past the real count exit after locating
-// nothing): cap / tile_rows full tiles, and per slot one remainder -- or two tiles where one-tile slots
-// are cut finer (each at least half a tile).
-inline int max_tiles(int cap, int spr, int tile_rows, bool finer_singles) {
-    return (finer_singles ? 2 : 1) * spr + cap / tile_rows;
-}
-
-// ------------------------------------------------------------------------------------------ work items
-// A slot of m rows gives m / tile_rows full tiles and one tile for the remainder; a tile is wide if it has
-// more than `stream_rows` rows.  Tile order: full tiles, then the remainders by rows descending
-// (ties: lower slot first); the first n_wide of them are the wide ones.  Work item = (tile, column
-// tile), tile-major, wide items first, `ntw` column tiles per wide tile and `nts` per stream tile.
-// Every workgroup derives its own item from group_offsets (65 integers, one memory round trip, a few
-// hundred scalar-ish instructions): no planning kernel, no list in memory.  Each wave computes the
-// same result with lane = local slot; everything returned is uniform.
-struct Item {
-    Tile tile;
-    bool valid, wide;
-};
-
-__device__ __forceinline__ Item locate_item(const int32_t* __restrict__ group_offsets, int spr, int cap,
-                                            int tile_rows, int single_rows, int stream_rows, int ntw, int nts,
-                                            int id) {
-    const int l = lane_id();
-    int begin = 0, m = 0;
-    if (l < spr) {                              // offsets that are not a partition of [0, cap] are clamped
-        begin = min(max(group_offsets[l], 0), cap);
-        m = min(max(group_offsets[l + 1], begin), cap) - begin;
-    }
-    // one-tile slots may be cut finer than the slots that re-read their weights once per tile
-    const int th = (single_rows > 0 && m <= tile_rows) ? single_rows : tile_rows;
-    const int full = m / th, part = m % th;
-    int incl = full;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int up = __shfl_up(incl, d);
-        if (l >= d) incl += up;
-    }
-    const int n_full = __builtin_amdgcn_readlane(incl, kWave - 1);
-    int rank = 0;                               // remainders: more rows first, then lower slot
-#pragma unroll
-    for (int j = 0; j < kWave; ++j) {
-        const int pj = __builtin_amdgcn_readlane(part, j);
-        rank += (pj > part || (pj == part && j < l)) ? 1 : 0;
-    }
-    const int n_part_wide = __popcll(__ballot(part > stream_rows));
-    const int n_part = __popcll(__ballot(part > 0));
-    // stream_rows >= 128: no wide class at all, full tiles take the stream path too
-    const int n_wide = stream_rows >= tile_rows ? 0 : n_full + n_part_wide;
-    const int n_stream = n_full + n_part - n_wide;
-    const int wide_items = n_wide * ntw, n_items = wide_items + n_stream * nts;
-
-    Item it;
-    it.valid = id < n_items;
-    it.wide = id < wide_items;
-    it.tile = Tile{0, 0, 0, 0};
-    if (!it.valid) return it;
-    const int nt = it.wide ? ntw : nts, r = it.wide ? id : id - wide_items;
-    const int tl = r / nt;
-    const int ti = it.wide ? tl : n_wide + tl;
-    it.tile.col = r - tl * nt;
-    if (ti < n_full) {
-        const uint64_t owner = __ballot(incl - full <= ti && ti < incl);      // exactly one lane
-        const int o = __ffsll((unsigned long long)owner) - 1;
-        const int first = __builtin_amdgcn_readlane(incl - full, o);
-        it.tile.slot = o;
-        const int th_o = __builtin_amdgcn_readlane(th, o);
-        it.tile.row0 = __builtin_amdgcn_readlane(begin, o) + (ti - first) * th_o;
-        it.tile.rows = th_o;
-    } else {
-        const uint64_t owner = __ballot(part > 0 && n_full + rank == ti);     // exactly one lane
-        const int o = __ffsll((unsigned long long)owner) - 1;
-        it.tile.slot = o;
-        it.tile.row0 = __builtin_amdgcn_readlane(begin + full * th, o);
-        it.tile.rows = __builtin_amdgcn_readlane(part, o);
-    }
-    it.valid = it.tile.rows > 0;                // always true here; keeps a broken invariant from indexing row -1
-    return it;
-}
 
 // ------------------------------------------------------------------------------------------ MFMA path
 struct FfnArgs {
@@ -137,16 +47,6 @@ struct FfnArgs {
     int stream_rows;          // tiles with more rows are wide
     int ntw, nts;             // column tiles per wide / stream tile
 };
-
-__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
-    uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-    const uint32_t ra = ua + 0x7fffu + ((ua >> 16) & 1u);       // round to nearest even
-    const uint32_t rb = ub + 0x7fffu + ((ub >> 16) & 1u);
-    // NaN stays a (quiet) NaN: the rounding add could carry its mantissa into Inf or -0
-    ua = (a != a) ? (ua | 0x00400000u) : ra;
-    ub = (b != b) ? (ub | 0x00400000u) : rb;
-    return (ua >> 16) | (ub & 0xffff0000u);
-}
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }
 
@@ -185,17 +85,6 @@ __device__ __forceinline__ void store_tile(const FfnArgs& a, const Tile& t, cons
             }
         }
     }
-}
-
-// do_step(U, s) for U = 0..n-1 with compile-time U (buffer indices), s = s0 + U.
-template <int... Us, typename F>
-__device__ __forceinline__ void run_steps(std::integer_sequence<int, Us...>, F& f, int s0) {
-    (f(std::integral_constant<int, Us>{}, s0 + Us), ...);
-}
-template <int... Us, typename F>
-__device__ __forceinline__ void run_steps_tail(std::integer_sequence<int, Us...>, F& f, int s0, int n_steps) {
-    // short-circuit: once a step is past the end nothing after it is tested, the paths join only at the end
-    (void)((s0 + Us < n_steps && (f(std::integral_constant<int, Us>{}, s0 + Us), true)) && ...);
 }
 
 // One tile x one column tile.
@@ -363,187 +252,56 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_mfma_kernel(FfnArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------ general path
-// Any shape, fp32 or bf16 storage, fp32 arithmetic on the vector ALUs (the matrix-core path needs bf16 and
-// H, I multiples of 128).  One workgroup = 16 rows of one slot x 64 output columns; both operands go through LDS
-// in K steps of 32 (the loads of the next step in flight in registers meanwhile), so a weight element is
-// fetched once per 16 rows and an activation element once per 64 columns (not once per output element); a
-// thread owns 4 outputs of one row and adds its products in ascending k with fused multiply-adds.
-template <typename T>
-__device__ __forceinline__ float to_f32(T v);
-template <>
-__device__ __forceinline__ float to_f32<float>(float v) { return v; }
-template <>
-__device__ __forceinline__ float to_f32<__bf16>(__bf16 v) { return (float)v; }
+// fp32 storage, and 16-bit shapes whose H or I is no multiple of 128 (activations between the stages in fp32): K-split
+// tiles (ffn_split.h) of at most 32 rows x 16 gate/up columns or 32 down columns.  What bounds it is HBM latency times
+// occupancy (fp32 matrix instructions take about a third of the time at 32 rows), so the tiles are small -- many
+// workgroups -- and registers are kept low enough for three workgroups per CU.  Measured on the 17-slot, 362-row
+// fp32 rank of the 2048 x 768 shape, gate/up + down: 94 + 42 us with 64 rows x 32/64 columns at two workgroups per CU,
+// 71 + 39 us with 32 rows x 16/32 columns, 73 + 35 us with three per CU (this one); on 2000 x 712 in bf16
+// 30 + 21 us against 33 + 28 us.  (The vector-ALU kernels these replaced: 328 + 119 and 440 + 137 us.)
+constexpr int kGenRows = 32;
+constexpr int kGenBlocks = 2;               // 16-row weight blocks of a workgroup
+constexpr int kGenGateUpCols = kGenBlocks * 8, kGenDownCols = kGenBlocks * 16;
+constexpr int kGenLds = 4 * kGenBlocks * (kGenRows / 16) * 64 * (int)sizeof(floatx4);
+// Two rounds of the 768 resident workgroups; more items loop.  (The grid can only be sized for a rank that gets every
+// pair of the batch; a workgroup that finds no item costs about 2 ns.)
+constexpr int kGenGrid = 1536;
 
-template <typename T>
-__device__ __forceinline__ T from_f32(float v);
-template <>
-__device__ __forceinline__ float from_f32<float>(float v) { return v; }
-template <>
-__device__ __forceinline__ __bf16 from_f32<__bf16>(float v) {
-    const uint16_t bits = (uint16_t)(pack_bf16x2(v, 0.f) & 0xffffu);
-    return __builtin_bit_cast(__bf16, bits);
-}
-
-constexpr int kGenRows = 16, kGenCols = 64, kGenK = 32;
-
-// Row tile `b` (counted over the slots' tiles of 16 rows, slot by slot) -> slot, first row, rows; rows = 0 past
-// the last tile.  One thread walks the <= 64 slots, the result reaches the workgroup through LDS.
-__device__ __forceinline__ void general_locate(const int32_t* __restrict__ group_offsets, int spr, int cap, int b,
-                                               int* s_tile) {
-    if (threadIdx.x == 0) {
-        int slot = 0, row0 = 0, rows = 0;
-        for (int l = 0; l < spr; ++l) {
-            const int begin = min(max(group_offsets[l], 0), cap);
-            const int m = min(max(group_offsets[l + 1], begin), cap) - begin;
-            const int nt = (m + kGenRows - 1) / kGenRows;
-            if (b < nt) {
-                slot = l;
-                row0 = begin + b * kGenRows;
-                rows = min(kGenRows, m - b * kGenRows);
-                break;
-            }
-            b -= nt;
-        }
-        s_tile[0] = slot;
-        s_tile[1] = row0;
-        s_tile[2] = rows;
+template <bool kGateUp, typename WT, bool kTinyK>
+__global__ __launch_bounds__(kThreads, 3) void general_ffn_kernel(SplitArgs a, const int32_t* __restrict__ group_offsets,
+                                                                  int spr, int n_cols, int64_t n_items) {
+    __shared__ __attribute__((aligned(16))) char lds[kGenLds];
+    using XT = std::conditional_t<kGateUp, WT, float>;
+    using OT = std::conditional_t<kGateUp, float, WT>;
+    for (int64_t id = blockIdx.x; id < n_items; id += gridDim.x) {
+        const Item it = locate_in_order(group_offsets, spr, a.T * a.k, kGenRows, n_cols, id);
+        if (!it.valid) return;                                       // uniform; items are consecutive
+        if constexpr (kTinyK) split_tile<kGateUp, WT, XT, OT, kGenBlocks, 2, 1, true>(a, it.tile, lds);
+        else if (it.tile.rows <= 16) split_tile<kGateUp, WT, XT, OT, kGenBlocks, 1, 3, false>(a, it.tile, lds);
+        else split_tile<kGateUp, WT, XT, OT, kGenBlocks, 2, 2, false>(a, it.tile, lds);
+        __syncthreads();                                             // the next item's sums reuse the LDS
     }
-    __syncthreads();
 }
 
-template <typename T>
-__global__ __launch_bounds__(kThreads) void general_gate_up_kernel(const T* __restrict__ x,
-                                                                   const int32_t* __restrict__ perm_pair,
-                                                                   const int32_t* __restrict__ group_offsets, int Tn,
-                                                                   int k, int spr, int H, int I,
-                                                                   const T* __restrict__ w13, int ldw,
-                                                                   float* __restrict__ act) {
-    __shared__ float xs[kGenRows][kGenK + 1], wg[kGenCols][kGenK + 1], wu[kGenCols][kGenK + 1];
-    __shared__ int s_tile[3], s_tok[kGenRows];
-    general_locate(group_offsets, spr, Tn * k, blockIdx.x, s_tile);
-    const int slot = s_tile[0], row0 = s_tile[1], rows = s_tile[2];
-    if (rows == 0) return;                                           // uniform
-    const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-    const int col0 = blockIdx.y * kGenCols;
-    if (tid < kGenRows) s_tok[tid] = min(max(perm_pair[row0 + min(tid, rows - 1)] / k, 0), Tn - 1);
-    __syncthreads();
-    const T* wslot = w13 + (size_t)slot * 2 * I * ldw;
-    float g[4] = {0.f, 0.f, 0.f, 0.f}, u[4] = {0.f, 0.f, 0.f, 0.f};
-    // the global loads of step s + 1 are in flight (in registers) while step s is multiplied out of LDS
-    constexpr int NX = kGenRows * kGenK / kThreads, NW = kGenCols * kGenK / kThreads;
-    float rx[NX], rg[NW], ru[NW];
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int j = 0; j < NX; ++j) {
-            const int e = tid + j * kThreads, r = e / kGenK, kk = e % kGenK;
-            rx[j] = (r < rows && k0 + kk < H) ? to_f32<T>(x[(size_t)s_tok[r] * H + k0 + kk]) : 0.f;
-        }
-#pragma unroll
-        for (int j = 0; j < NW; ++j) {
-            const int e = tid + j * kThreads, c = e / kGenK, kk = e % kGenK;
-            const bool in = col0 + c < I && k0 + kk < H;
-            const size_t at = (size_t)(col0 + c) * ldw + k0 + kk;
-            rg[j] = in ? to_f32<T>(wslot[at]) : 0.f;
-            ru[j] = in ? to_f32<T>(wslot[(size_t)I * ldw + at]) : 0.f;
-        }
+template <bool kGateUp>
+int launch_general(const SplitArgs& a, const int32_t* group_offsets, int spr, int dtype, hipStream_t st) {
+    const int n_out = kGateUp ? a.I : a.H, K = kGateUp ? a.H : a.I;
+    const int cols = kGateUp ? kGenGateUpCols : kGenDownCols, n_cols = (n_out + cols - 1) / cols;
+    const int64_t n_items = (int64_t)max_tiles(a.T * a.k, spr, kGenRows, false) * n_cols;
+    const uint32_t grid = (uint32_t)(n_items < kGenGrid ? n_items : kGenGrid);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, st, a, group_offsets, spr, n_cols, n_items);
     };
-    fetch(0);
-    for (int k0 = 0; k0 < H; k0 += kGenK) {
-#pragma unroll
-        for (int j = 0; j < NX; ++j) {
-            const int e = tid + j * kThreads;
-            xs[e / kGenK][e % kGenK] = rx[j];
-        }
-#pragma unroll
-        for (int j = 0; j < NW; ++j) {
-            const int e = tid + j * kThreads;
-            wg[e / kGenK][e % kGenK] = rg[j];
-            wu[e / kGenK][e % kGenK] = ru[j];
-        }
-        __syncthreads();
-        if (k0 + kGenK < H) fetch(k0 + kGenK);                       // uniform
-#pragma unroll 8
-        for (int kk = 0; kk < kGenK; ++kk) {
-            const float xv = xs[ty][kk];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                g[c] = fmaf(xv, wg[tx + 16 * c][kk], g[c]);
-                u[c] = fmaf(xv, wu[tx + 16 * c][kk], u[c]);
-            }
-        }
-        __syncthreads();
+    // vectors of 16 bytes need a row of at least one
+    if (dtype == METRO_DTYPE_F32) {
+        if (K < 4) go(general_ffn_kernel<kGateUp, float, true>);
+        else go(general_ffn_kernel<kGateUp, float, false>);
+    } else {
+        if (K < 8) go(general_ffn_kernel<kGateUp, __bf16, true>);
+        else go(general_ffn_kernel<kGateUp, __bf16, false>);
     }
-    if (ty < rows) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int col = col0 + tx + 16 * c;
-            if (col < I) act[(size_t)(row0 + ty) * I + col] = g[c] / (1.0f + expf(-g[c])) * u[c];
-        }
-    }
+    return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP;
 }
-
-template <typename T>
-__global__ __launch_bounds__(kThreads) void general_down_kernel(const float* __restrict__ act,
-                                                                const int32_t* __restrict__ group_offsets, int cap,
-                                                                int spr, int H, int I, const T* __restrict__ w2, int ldw,
-                                                                T* __restrict__ y) {
-    __shared__ float as[kGenRows][kGenK + 1], ws[kGenCols][kGenK + 1];
-    __shared__ int s_tile[3];
-    general_locate(group_offsets, spr, cap, blockIdx.x, s_tile);
-    const int slot = s_tile[0], row0 = s_tile[1], rows = s_tile[2];
-    if (rows == 0) return;                                           // uniform
-    const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-    const int col0 = blockIdx.y * kGenCols;
-    const T* wslot = w2 + (size_t)slot * H * ldw;
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    constexpr int NX = kGenRows * kGenK / kThreads, NW = kGenCols * kGenK / kThreads;
-    float ra[NX], rw[NW];
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int j = 0; j < NX; ++j) {
-            const int e = tid + j * kThreads, r = e / kGenK, kk = e % kGenK;
-            ra[j] = (r < rows && k0 + kk < I) ? act[(size_t)(row0 + r) * I + k0 + kk] : 0.f;
-        }
-#pragma unroll
-        for (int j = 0; j < NW; ++j) {
-            const int e = tid + j * kThreads, c = e / kGenK, kk = e % kGenK;
-            rw[j] = (col0 + c < H && k0 + kk < I) ? to_f32<T>(wslot[(size_t)(col0 + c) * ldw + k0 + kk]) : 0.f;
-        }
-    };
-    fetch(0);
-    for (int k0 = 0; k0 < I; k0 += kGenK) {
-#pragma unroll
-        for (int j = 0; j < NX; ++j) {
-            const int e = tid + j * kThreads;
-            as[e / kGenK][e % kGenK] = ra[j];
-        }
-#pragma unroll
-        for (int j = 0; j < NW; ++j) {
-            const int e = tid + j * kThreads;
-            ws[e / kGenK][e % kGenK] = rw[j];
-        }
-        __syncthreads();
-        if (k0 + kGenK < I) fetch(k0 + kGenK);                       // uniform
-#pragma unroll 8
-        for (int kk = 0; kk < kGenK; ++kk) {
-            const float av = as[ty][kk];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc[c] = fmaf(av, ws[tx + 16 * c][kk], acc[c]);
-        }
-        __syncthreads();
-    }
-    if (ty < rows) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int col = col0 + tx + 16 * c;
-            if (col < H) y[(size_t)(row0 + ty) * H + col] = from_f32<T>(acc[c]);
-        }
-    }
-}
-
-// Row tiles of the general path: every slot may end with a partial tile.
-inline int general_row_tiles(int cap, int spr) { return cap / kGenRows + spr; }
 
 inline bool mfma_shape(int H, int I, int dtype) {
     return dtype == METRO_DTYPE_BF16 && H % 128 == 0 && I % 128 == 0;
@@ -646,14 +404,8 @@ extern "C" int moe_grouped_ffn_gate_up(const void* x, const int32_t* perm_pair, 
     hipStream_t st = (hipStream_t)stream;
     char* act = act_of(ws);
     if (!use_mfma(T, k, H, I, dtype)) {
-        const dim3 grid(general_row_tiles(cap, spr), (I + kGenCols - 1) / kGenCols);
-        if (dtype == METRO_DTYPE_F32)
-            hipLaunchKernelGGL(general_gate_up_kernel<float>, grid, dim3(kThreads), 0, st, (const float*)x,
-                               perm_pair, group_offsets, T, k, spr, H, I, (const float*)w13, ldw13, (float*)act);
-        else
-            hipLaunchKernelGGL(general_gate_up_kernel<__bf16>, grid, dim3(kThreads), 0, st, (const __bf16*)x,
-                               perm_pair, group_offsets, T, k, spr, H, I, (const __bf16*)w13, ldw13, (float*)act);
-        return launched();
+        const SplitArgs g{x, perm_pair, w13, act, T, k, H, I, ldw13};
+        return launch_general<true>(g, group_offsets, spr, dtype, st);
     }
     if (enable_large_lds() != METRO_OK) return METRO_ERR_HIP;
     FfnArgs a;
@@ -690,14 +442,8 @@ extern "C" int moe_grouped_ffn_down(const int32_t* group_offsets, int T, int k, 
     hipStream_t st = (hipStream_t)stream;
     char* act = act_of(ws);
     if (!use_mfma(T, k, H, I, dtype)) {
-        const dim3 grid(general_row_tiles(cap, spr), (H + kGenCols - 1) / kGenCols);
-        if (dtype == METRO_DTYPE_F32)
-            hipLaunchKernelGGL(general_down_kernel<float>, grid, dim3(kThreads), 0, st, (const float*)act,
-                               group_offsets, cap, spr, H, I, (const float*)w2, ldw2, (float*)y_perm);
-        else
-            hipLaunchKernelGGL(general_down_kernel<__bf16>, grid, dim3(kThreads), 0, st, (const float*)act,
-                               group_offsets, cap, spr, H, I, (const __bf16*)w2, ldw2, (__bf16*)y_perm);
-        return launched();
+        const SplitArgs g{act, nullptr, w2, y_perm, T, k, H, I, ldw2};
+        return launch_general<false>(g, group_offsets, spr, dtype, st);
     }
     if (enable_large_lds() != METRO_OK) return METRO_ERR_HIP;
     FfnArgs a;

@@ -1,0 +1,64 @@
+"""Grouped FFN at the sizes where its kernels change path or end inside a tile, every row against the CPU oracle.
+
+Tolerance: max|gpu - ref| / max|ref|.  fp32: sums of n products in any order err by at most n * 2^-24 of the sum of
+magnitudes, which for random signs is about sqrt(n) of the result's scale: below 1e-5 for n <= 2048.  bf16: two roundings
+of 2^-9 relative (the intermediate and the output), 2e-2 over the tensor."""
+import numpy as np
+import pytest
+
+from paper_2512_09277_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"bf16": 2e-2, "f32": 1e-5}
+
+
+def dev(a):
+    import torch
+
+    t = torch.from_numpy(np.ascontiguousarray(a))
+    return (t.view(torch.bfloat16) if a.dtype == np.uint16 else t).cuda()
+
+
+def weights(a, pitch):
+    """[slots, rows, K] on the device, rows `pitch` elements apart, the gap filled with NaN."""
+    import torch
+
+    t = dev(a)
+    buf = torch.full((t.shape[0], t.shape[1], pitch), float("nan"), dtype=t.dtype, device="cuda")
+    view = buf[:, :, :t.shape[2]]
+    view.copy_(t)
+    return view
+
+
+def check(oracle, dtype, H, I, sizes, T=256, k=2, extra=0):
+    from paper_2512_09277_amd import api
+
+    api.load()
+    print(f"edges {dtype} H={H} I={I} sizes={sizes}", flush=True)
+    spr = len(sizes)
+    rng = np.random.default_rng(H * 7 + I)
+    pairs = rng.permutation(T * k)[:sum(sizes)]
+    ps = np.full(T * k, -1, np.int32)
+    ps[pairs] = np.repeat(np.arange(spr), sizes)
+    ps = ps.reshape(T, k)
+    x = W.activations(T, H, 5, dtype)
+    w13, w2 = W.expert_weights(spr, H, I, 6, dtype)
+    pm = api.moe_permute(dev(ps), 0, spr)
+    up8 = lambda n: (n + 7) // 8 * 8 + extra  # noqa: E731
+    y = api.moe_grouped_ffn(dev(x), pm["perm_pair"], pm["group_offsets"], k, weights(w13, up8(H)), weights(w2, up8(I)))
+    ref = oracle.permute(ps, 0, spr)
+    want = oracle.ffn(x, ref["perm_pair"], ref["group_offsets"], k, w13, w2)
+    got = y[:ref["n_pairs"]].float().cpu().numpy().astype(np.float64)
+    assert np.isfinite(got).all()
+    err = np.abs(got - want).max() / np.abs(want).max()
+    assert err <= TOL[dtype], err
+
+
+# the last K step of either stage whole, one element short or long, shorter than a vector, a multiple of no vector; output
+# columns ending inside a 16-row block and inside a vector; rows at the edges of the 16-row sub-tiles
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("H,I", [(1, 1), (3, 5), (7, 2), (4, 8), (8, 9), (9, 16), (31, 33), (32, 64), (63, 127), (65, 130),
+                                 (129, 31), (250, 96), (257, 66), (1023, 255)])
+def test_general_path_edges(oracle, dtype, H, I):
+    check(oracle, dtype, H, I, [1, 16, 0, 17, 32, 33, 15, 65])
