@@ -1,15 +1,15 @@
 // moe_grouped_ffn for gfx950: SwiGLU expert FFN over one rank's per-slot token lists.
 //
 // Decode is HBM-bound: runtime follows the bytes of the activated experts' weights (Sec. 3.2 of
-// arxiv 2512.09277).  Every activated weight row is streamed from HBM once, with 128-bit loads that
-// land directly in the matrix-core operand layout (16 rows x 64 contiguous bytes per instruction);
-// the small, heavily reused activations are staged through LDS.  Work is cut into tiles of one
-// slot's rows (at most 128; 32 on the smallest shapes):
-//   stream tiles (<= 32 rows at large shapes, the bulk of the bytes): per wave 2 x 16 weight rows, K steps of 128,
-//       loads issued two steps ahead so that ~128 KB per CU are in flight at 2 waves per SIMD;
-//   wide tiles (33..128 rows at large shapes, the few popular experts): per wave 4 x 16 weight rows, K steps of 64,
-//       so that each activation fragment read from LDS feeds four MFMAs and the matrix cores,
-//       not LDS, bound the tile; they are listed first so that they spread over the chip early.
+// arxiv 2512.09277).  Every activated weight row is streamed from HBM once per tile, with 128-bit loads that
+// land directly in the matrix-core operand layout (16 rows x 64 contiguous bytes per instruction).
+// Work is cut into tiles of one slot's rows (at most 128; 64 on the smallest shapes):
+//   narrow tiles (<= 64 rows, 32 at large shapes; the bulk of the bytes): ffn_split.h -- K split over the four waves, 64 weight rows per
+//       workgroup, activations straight into registers, no barrier in the K loop;
+//   tall tiles (up to 128 rows, the popular experts), activations staged through LDS: wide ones (large shapes) with 4 x 16
+//       weight rows per wave and K steps of 64, so that each activation fragment read from LDS feeds four MFMAs;
+//       stream ones (mid shapes) with 2 x 16 weight rows per wave.  They are listed first so that they spread over
+//       the chip early.
 //   gate/up: a wave owns gate rows and the matching up rows, so silu(gate)*up is formed in
 //            registers and written once as bf16;   down: same structure over K = I.
 // A slot with no rows produces no tile and its weights are never touched.  There is no planning pass:
@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -30,7 +31,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWideRows = 128;              // rows of a full wide tile
-constexpr int kStreamRows = 128;            // largest remainder that may become a stream tile
 
 // ------------------------------------------------------------------------------------------ MFMA path
 struct FfnArgs {
@@ -43,9 +43,10 @@ struct FfnArgs {
     int ldw;                  // elements between consecutive weight rows (>= K)
     int tile_rows;            // rows of a full tile (<= 128)
     int single_rows;          // > 0: slots of at most tile_rows rows are cut into tiles of this many rows
-    int bk256;                // <= 32-row tiles take K steps of 256 with one step of prefetch
     int stream_rows;          // tiles with more rows are wide
     int ntw, nts;             // column tiles per wide / stream tile
+    int narrow_rows;          // tiles of at most this many rows are narrow (<= 64)
+    int ntn;                  // column tiles per narrow tile
 };
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }
@@ -221,34 +222,68 @@ __device__ __forceinline__ void ffn_tile(const FfnArgs& a, const Tile t, const i
     store_tile<kGateUp, NB, MT>(a, t, acc, col0, n_out, mt_count, r16, q);
 }
 
+constexpr int kLdsSplit = 4 * 4 * (kNarrowMost / 16) * 64 * (int)sizeof(floatx4);      // partial sums of four waves
 constexpr int kLdsStream = 2 * 64 * (128 * 2 + 16);
 constexpr int kLdsWide = 2 * 128 * (64 * 2 + 16);
-constexpr int kLdsBytes = kLdsWide > kLdsStream ? kLdsWide : kLdsStream;
+constexpr int kLdsBytes = std::max(kLdsSplit, std::max(kLdsWide, kLdsStream));
+
+// Narrow tiles.  Measured against tiles staged through LDS with a barrier per K step (gate/up + down, us): 8 tokens of the
+// 2048 x 768 shape 21 + 10 -> 13 + 6.5 (twice the workgroups for the same bytes, nobody waits for a sibling wave's loads);
+// 256 tokens of it 38 + 18 -> 30 + 16; 97 tokens of the 7168 x 2048 shape (token-balanced) 288 + 152 -> 268 + 138; 1024
+// tokens of it (METRO, whose time is in the tall tiles) 384 + 205 -> 383 + 201.
+//   Blocks: 2 instead of 4 weight blocks per workgroup re-read the activations twice as often and lose everywhere (97 tokens:
+//   276 + 177).
+//   Depth: what 256 registers hold.
+constexpr int kNarrowBlocks = 4;
+// Workgroups of the narrow tiles at most; a workgroup past the last item costs about 2 ns, so the grid is not sized for
+// the most tiles a rank could have, and the rest is taken in turns.  Three times the 512 resident ones: with fewer, who
+// gets one item more is decided at launch and not by who is free (512: 287 us, 1024: 269, 1536 and more: 268; 97
+// tokens, gate/up).
+constexpr int kNarrowGrid = 1536;
 
 template <bool kGateUp>
 __global__ __launch_bounds__(kThreads, 2) void ffn_mfma_kernel(FfnArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     // Work items = (tile, column tile), wide items first: a wide workgroup lives several times longer
-    // than a stream one, so it has to start early for the stream items to fill in around it.
+    // than a stream one, so it has to start early for the other items to fill in around it.
     // (Measured alternatives that lost: spreading the wide items through the launch order,
     // alternating wide and stream items, and per-XCD work queues.)  Everything here is uniform per
     // workgroup.
-    const Item it = locate_item(a.group_offsets, a.spr, a.T * a.k, a.tile_rows, a.single_rows, a.stream_rows, a.ntw, a.nts, blockIdx.x);
-    if (!it.valid) return;
-    const Tile t = it.tile;
+    WorkList wl;
+    wl.read(a.group_offsets, a.spr, a.T * a.k, a.tile_rows, a.single_rows, a.stream_rows, a.narrow_rows);
+    const int wide_items = wl.n_wide * a.ntw, tall_items = wide_items + (wl.n_tall - wl.n_wide) * a.nts;
+    if ((int)blockIdx.x >= tall_items) {
+        const SplitArgs sa{a.src, a.perm_pair, a.w, a.dst, a.T, a.k, a.H, a.I, a.ldw};
+        const int n = (wl.n_tiles - wl.n_tall) * a.ntn, stride = gridDim.x - tall_items;
+        for (int id = blockIdx.x - tall_items; id < n; id += stride) {
+            const int ti = id / a.ntn;
+            const Tile t = wl.tile(wl.n_tall + ti, id - ti * a.ntn);
+            if (t.rows <= 16) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 1, 4, KRows::kWhole>(sa, t, lds);
+            else if (t.rows <= 32) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 2, 3, KRows::kWhole>(sa, t, lds);
+            else if (t.rows <= 48) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 3, 2, KRows::kWhole>(sa, t, lds);
+            else split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 4, 2, KRows::kWhole>(sa, t, lds);
+            __syncthreads();                                             // the next item's sums reuse the LDS
+        }
+        return;
+    }
+    const int id = blockIdx.x;
+    const bool wide = id < wide_items;
+    const int nt = wide ? a.ntw : a.nts, r = wide ? id : id - wide_items, tl = r / nt;
+    const Tile t = wl.tile(wide ? tl : wl.n_wide + tl, r - tl * nt);
     // partial wide tiles stage only the rows they have; with half the accumulators the 64-row variant
     // also affords a second K step of weights in flight (token-balanced rank: gate/up 401 -> 390 us)
-    if (it.wide && t.rows <= 64) ffn_tile<kGateUp, 4, 4, 64, 2>(a, t, t.col, lds);
-    else if (it.wide && t.rows <= 96) ffn_tile<kGateUp, 4, 6, 64, 1>(a, t, t.col, lds);
-    else if (it.wide) ffn_tile<kGateUp, 4, 8, 64, 1>(a, t, t.col, lds);
-    else if (t.rows <= 32 && a.bk256) {
-        if (t.rows <= 16) ffn_tile<kGateUp, 2, 1, 256, 1>(a, t, t.col, lds);
-        else ffn_tile<kGateUp, 2, 2, 256, 1>(a, t, t.col, lds);
-    }
-    else if (t.rows <= 16) ffn_tile<kGateUp, 2, 1, 128, 2>(a, t, t.col, lds);
-    else if (t.rows <= 32) ffn_tile<kGateUp, 2, 2, 128, 2>(a, t, t.col, lds);
+    if (wide && t.rows <= 64) ffn_tile<kGateUp, 4, 4, 64, 2>(a, t, t.col, lds);
+    else if (wide && t.rows <= 96) ffn_tile<kGateUp, 4, 6, 64, 1>(a, t, t.col, lds);
+    else if (wide) ffn_tile<kGateUp, 4, 8, 64, 1>(a, t, t.col, lds);
     else if (t.rows <= 64) ffn_tile<kGateUp, 2, 4, 128, 2>(a, t, t.col, lds);
     else ffn_tile<kGateUp, 2, 8, 64, 3>(a, t, t.col, lds);
+}
+
+// Tall workgroups for the most tall tiles `cap` rows can make, and the narrow ones.
+inline int mfma_grid(const FfnArgs& a, int cap, int spr) {
+    const int tall = a.tile_rows > a.narrow_rows ? std::min(cap / a.narrow_rows, max_tiles(cap, spr, a.tile_rows, a.single_rows > 0)) : 0;
+    const int narrow = std::min(a.ntn * (std::min(spr, cap) + cap / a.narrow_rows), kNarrowGrid);
+    return tall * std::max(a.ntw, a.nts) + narrow;
 }
 
 // ------------------------------------------------------------------------------------------ general path
@@ -267,7 +302,7 @@ constexpr int kGenLds = 4 * kGenBlocks * (kGenRows / 16) * 64 * (int)sizeof(floa
 // pair of the batch; a workgroup that finds no item costs about 2 ns.)
 constexpr int kGenGrid = 1536;
 
-template <bool kGateUp, typename WT, bool kTinyK>
+template <bool kGateUp, typename WT, KRows kRows>
 __global__ __launch_bounds__(kThreads, 3) void general_ffn_kernel(SplitArgs a, const int32_t* __restrict__ group_offsets,
                                                                   int spr, int n_cols, int64_t n_items) {
     __shared__ __attribute__((aligned(16))) char lds[kGenLds];
@@ -276,9 +311,9 @@ __global__ __launch_bounds__(kThreads, 3) void general_ffn_kernel(SplitArgs a, c
     for (int64_t id = blockIdx.x; id < n_items; id += gridDim.x) {
         const Item it = locate_in_order(group_offsets, spr, a.T * a.k, kGenRows, n_cols, id);
         if (!it.valid) return;                                       // uniform; items are consecutive
-        if constexpr (kTinyK) split_tile<kGateUp, WT, XT, OT, kGenBlocks, 2, 1, true>(a, it.tile, lds);
-        else if (it.tile.rows <= 16) split_tile<kGateUp, WT, XT, OT, kGenBlocks, 1, 3, false>(a, it.tile, lds);
-        else split_tile<kGateUp, WT, XT, OT, kGenBlocks, 2, 2, false>(a, it.tile, lds);
+        if constexpr (kRows == KRows::kTiny) split_tile<kGateUp, WT, XT, OT, kGenBlocks, 2, 1, kRows>(a, it.tile, lds);
+        else if (it.tile.rows <= 16) split_tile<kGateUp, WT, XT, OT, kGenBlocks, 1, 3, kRows>(a, it.tile, lds);
+        else split_tile<kGateUp, WT, XT, OT, kGenBlocks, 2, 2, kRows>(a, it.tile, lds);
         __syncthreads();                                             // the next item's sums reuse the LDS
     }
 }
@@ -294,11 +329,11 @@ int launch_general(const SplitArgs& a, const int32_t* group_offsets, int spr, in
     };
     // vectors of 16 bytes need a row of at least one
     if (dtype == METRO_DTYPE_F32) {
-        if (K < 4) go(general_ffn_kernel<kGateUp, float, true>);
-        else go(general_ffn_kernel<kGateUp, float, false>);
+        if (K < 4) go(general_ffn_kernel<kGateUp, float, KRows::kTiny>);
+        else go(general_ffn_kernel<kGateUp, float, KRows::kRagged>);
     } else {
-        if (K < 8) go(general_ffn_kernel<kGateUp, __bf16, true>);
-        else go(general_ffn_kernel<kGateUp, __bf16, false>);
+        if (K < 8) go(general_ffn_kernel<kGateUp, __bf16, KRows::kTiny>);
+        else go(general_ffn_kernel<kGateUp, __bf16, KRows::kRagged>);
     }
     return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP;
 }
@@ -343,19 +378,26 @@ int enable_large_lds() {                            // opt in to > 64 KB of dyna
     });
 }
 
-// Remainders of at most this many rows become stream tiles.  A wide workgroup prefetches one step
+// Tall remainders of at most this many rows become stream tiles.  A wide workgroup prefetches one step
 // ahead, so its K loop runs at about one memory latency per step: at large shapes that hides behind
-// the stream items, at small ones (short launches, HBM not saturated) it is the critical path.  Small
-// FFNs therefore keep every tile on the deep-prefetch stream path, whose narrower column tile costs
-// more activation re-reads -- which is what decides at large shapes, where only <= 32 rows go there.
-inline int stream_rows_for(int H, int I) { return (size_t)H * I >= (size_t)4096 * 2048 ? 32 : kStreamRows; }
+// the narrow items, at mid ones (short launches, HBM not saturated) it is the critical path, and they keep tall tiles on
+// the deep-prefetch stream path, whose narrower column tile costs more activation re-reads.
+inline bool large_shape(int H, int I) { return (size_t)H * I >= (size_t)4096 * 2048; }
+inline int stream_rows_for(int H, int I) { return large_shape(H, I) ? 32 : kWideRows; }
 
-// Rows of a full tile.  128 amortises a slot's weights over the most rows (one HBM pass per 128 rows).
+// Tiles above this many rows stage their activations through LDS.  A narrow tile reads each activation once per 64 weight
+// rows, which at 33..64 rows is as much L2 traffic as the weights themselves: large shapes, at the fabric's rate
+// already, lose by it (7168 x 2048, 1024 tokens, METRO rank: 399 + 205 us with 64, 383 + 201 with 32); shorter launches
+// gain from the smaller work items (4096 x 1536: 103 + 57 with 64, 107 + 57 with 32; 2048 x 768 has only these tiles).
+inline int narrow_rows_for(int H, int I) { return large_shape(H, I) ? 32 : kNarrowMost; }
+
+// Rows of a full tile.  128 amortises a slot's weights over the most rows (one HBM pass per 128 rows; all
+// tiles narrow at 4096 x 1536: 116 + 59 instead of 103 + 57 us).
 // The smallest FFNs finish in a few tens of microseconds and are bound by their longest workgroup, not
 // by bytes: a 128-row tile spends longer in its matrix instructions than the whole launch should take,
-// while re-reading a small slot's weights from L2 is cheap, so they cut groups into 32-row tiles
-// (Qwen3-30B-shaped METRO rank: 60 -> 52 us; at 4096 x 1536 the same cut loses, 194 -> 250 us).
-inline int tile_rows_for(int H, int I) { return (size_t)H * I < (size_t)2048 * 1024 ? 32 : kWideRows; }
+// while re-reading a small slot's weights from L2 is cheap, so they cut groups into narrow tiles (2048 x 768: 256 tokens
+// 30 + 16 us with 64 rows, 35 + 16 with 32; 4096 tokens 110 + 63 with 64, 159 + 83 with 32).
+inline int tile_rows_for(int H, int I) { return (size_t)H * I < (size_t)2048 * 1024 ? kNarrowMost : kWideRows; }
 
 inline int launched() { return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP; }
 
@@ -418,14 +460,15 @@ extern "C" int moe_grouped_ffn_gate_up(const void* x, const int32_t* perm_pair, 
     a.T = T; a.k = k; a.spr = spr; a.H = H; a.I = I;
     a.stream_rows = stream_rows_for(H, I);
     a.tile_rows = tile_rows_for(H, I);
+    a.narrow_rows = narrow_rows_for(H, I);
     // mid shapes (every tile on the stream path, 128-row tiles): a one-tile slot of 65..128 rows is the
     // longest workgroup of a launch that has fewer workgroups than the chip has slots; two 64-row tiles
     // balance it (token-balanced rank of the 4096 x 1536 shape: gate/up 109 -> 101 us; no gain for down)
     a.single_rows = (a.stream_rows >= kWideRows && a.tile_rows == kWideRows) ? 64 : 0;
-    a.bk256 = 0;
     a.ntw = I / 128;
     a.nts = I / 64;
-    hipLaunchKernelGGL(ffn_mfma_kernel<true>, dim3(max_tiles(cap, spr, a.tile_rows, a.single_rows > 0) * a.nts), dim3(kThreads), kLdsBytes, st, a);
+    a.ntn = I / (kNarrowBlocks * 8);
+    hipLaunchKernelGGL(ffn_mfma_kernel<true>, dim3(mfma_grid(a, cap, spr)), dim3(kThreads), kLdsBytes, st, a);
     return launched();
 }
 
@@ -456,18 +499,17 @@ extern "C" int moe_grouped_ffn_down(const int32_t* group_offsets, int T, int k, 
     a.T = T; a.k = k; a.spr = spr; a.H = H; a.I = I;
     a.stream_rows = stream_rows_for(H, I);
     a.tile_rows = tile_rows_for(H, I);
+    a.narrow_rows = narrow_rows_for(H, I);
     a.single_rows = 0;
     // mid shapes: the full 128-row tiles of a several-tile slot take the wide path in this stage (half
     // the column tiles, each activation fragment feeding four matrix instructions); smaller tiles stay
     // on the stream path (METRO rank of the 4096 x 1536 shape: down 71 -> 60 us; a 113-row one-tile
     // slot on the wide path costs the token-balanced rank 8 us, hence "full tiles only")
     if (a.stream_rows >= kWideRows && a.tile_rows == kWideRows) a.stream_rows = kWideRows - 1;
-    // a short K (few steps): half as many barriers for the same bytes in flight (Qwen3-30B-shaped
-    // down stage 23.2 -> 20.6 us; no gain on the gate/up stage or at I = 2048)
-    a.bk256 = I % 256 == 0 && I <= 1536;
     a.ntw = (H + 255) / 256;
     a.nts = H / 128;
-    hipLaunchKernelGGL(ffn_mfma_kernel<false>, dim3(max_tiles(cap, spr, a.tile_rows, a.single_rows > 0) * a.nts), dim3(kThreads), kLdsBytes, st, a);
+    a.ntn = H / (kNarrowBlocks * 16);
+    hipLaunchKernelGGL(ffn_mfma_kernel<false>, dim3(mfma_grid(a, cap, spr)), dim3(kThreads), kLdsBytes, st, a);
     return launched();
 }
 

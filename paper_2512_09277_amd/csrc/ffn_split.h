@@ -53,8 +53,10 @@ __device__ __forceinline__ uint32_t keep_mask(int drop, int e) {
     return drop <= 2 * e ? 0xffffffffu : drop == 2 * e + 1 ? 0xffff0000u : 0u;
 }
 
-// WT weights, XT activations, OT output.  kTinyK: K < kVec, element-wise guarded loads.
-template <bool kGateUp, typename WT, typename XT, typename OT, int NB, int MT, int DEPTH, bool kTinyK>
+enum class KRows { kWhole, kRagged, kTiny };  // K a multiple of a step; any K >= kVec; K < kVec (element-wise loads)
+
+// WT weights, XT activations, OT output.
+template <bool kGateUp, typename WT, typename XT, typename OT, int NB, int MT, int DEPTH, KRows kRows>
 __device__ __forceinline__ void split_tile(const SplitArgs& a, const Tile t, char* lds) {
     constexpr int kVec = 16 / (int)sizeof(WT);              // k per lane and load
     constexpr int kStep = 8 * kVec;                         // k per step
@@ -70,19 +72,26 @@ __device__ __forceinline__ void split_tile(const SplitArgs& a, const Tile t, cha
     const int mt_count = (t.rows + 15) >> 4;
     const int col0 = t.col * kUnits * 16;
 
+    // Whole rows (the host checks that activation offsets fit): a uniform base per block and 32-bit lane offsets, which
+    // leaves the vector registers to the data in flight.  Otherwise a pointer per lane, rows past the last column
+    // repeating it.
+    constexpr bool kWhole = kRows == KRows::kWhole;
     const WT* wslot = reinterpret_cast<const WT*>(a.w) + (size_t)t.slot * (kGateUp ? 2 * a.I : a.H) * a.ldw;
     const WT* pw[NB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {                          // rows past the last column repeat it
-        const int col = min(col0 + (b % kUnits) * 16 + r16, n_out - 1);
+    for (int b = 0; b < NB; ++b) {
+        const int at = col0 + (b % kUnits) * 16, col = kWhole ? at : min(at + r16, n_out - 1);
         pw[b] = wslot + (size_t)((kGateUp && b >= kUnits) ? a.I + col : col) * a.ldw;
     }
+    const uint32_t w_lane = (uint32_t)(r16 * a.ldw + q * kVec);
     const XT* px[MT];
+    uint32_t x_lane[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         const int row = t.row0 + min(mt * 16 + r16, t.rows - 1);    // rows past the tile repeat its last row
         const int src = kGateUp ? min(max(a.perm_pair[row] / a.k, 0), a.T - 1) : row;
-        px[mt] = reinterpret_cast<const XT*>(a.src) + (size_t)src * K;
+        px[mt] = reinterpret_cast<const XT*>(a.src) + (kWhole ? 0 : (size_t)src * K);
+        x_lane[mt] = (uint32_t)src * (uint32_t)K + q * kVec;
     }
 
     floatx4 acc[NB][MT];
@@ -103,30 +112,39 @@ __device__ __forceinline__ void split_tile(const SplitArgs& a, const Tile t, cha
     };
     // Every lane's vector stays inside its row: one that would pass the end is moved back to end with the row, and
     // the elements it then repeats are zeroed (in both operands) when the partial step is consumed.
-    auto load = [&](auto B, int step) {
+    auto load = [&](auto B, int s) {
         constexpr int buf = decltype(B)::value;
+        const int step = wv + 4 * min(s, mine - 1);
+        // past the wave's last step: every lane the same 16 bytes of a line that is there already
+        const uint32_t w_off = s < mine ? w_lane : 0u;
+        uint32_t x_off[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) x_off[mt] = s < mine ? x_lane[mt] : 0u;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int k = step * kStep + j * 4 * kVec + q * kVec;
             const int at = min(k, K - kVec);
+            const size_t whole_at = (size_t)step * kStep + j * 4 * kVec;      // uniform
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int v = 0; v < XV; ++v) {
                     constexpr int n = 16 / (int)sizeof(XT);
-                    if constexpr (kTinyK) x[buf][j][mt][v] = guarded(px[mt], k + v * n);
+                    if constexpr (kRows == KRows::kTiny) x[buf][j][mt][v] = guarded(px[mt], k + v * n);
+                    else if constexpr (kWhole) x[buf][j][mt][v] = *reinterpret_cast<const u32x4*>(px[mt] + whole_at + x_off[mt] + v * n);
                     else x[buf][j][mt][v] = *reinterpret_cast<const u32x4_any*>(px[mt] + at + v * n);
                 }
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                if constexpr (kTinyK) w[buf][j][b] = guarded(pw[b], k);
+                if constexpr (kRows == KRows::kTiny) w[buf][j][b] = guarded(pw[b], k);
+                else if constexpr (kWhole) w[buf][j][b] = *reinterpret_cast<const u32x4*>(pw[b] + whole_at + w_off);
                 else w[buf][j][b] = *reinterpret_cast<const u32x4_any*>(pw[b] + at);
             }
         }
     };
     auto consume = [&](auto B, int step, auto Masked) {
         constexpr int buf = decltype(B)::value;
-        constexpr bool masked = decltype(Masked)::value && !kTinyK;
+        constexpr bool masked = decltype(Masked)::value && kRows == KRows::kRagged;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             u32x4 xv[MT][XV], wm = {}, xm[XV] = {};
@@ -168,14 +186,15 @@ __device__ __forceinline__ void split_tile(const SplitArgs& a, const Tile t, cha
     };
 
     if (mine > 0) {
-        const int last = mine - 1;
         // Buffer s % DEPTH holds the wave's step s.  Loads are unconditional (past the end: the last step again) so
         // that the compiler counts what is outstanding exactly and waits for the consumed step only; the last
         // DEPTH steps load nothing.
-        run_steps(std::make_integer_sequence<int, DEPTH>{}, [&](auto U, int s) { load(U, wv + 4 * min(s, last)); }, 0);
+        run_steps(std::make_integer_sequence<int, DEPTH>{}, [&](auto U, int s) { load(U, s); }, 0);
         auto step = [&](auto U, int s) {
             consume(U, wv + 4 * s, std::false_type{});
-            load(U, wv + 4 * min(s + DEPTH, last));
+            __builtin_amdgcn_sched_barrier(0);              // the loads refill the registers just read, none earlier
+            load(U, s + DEPTH);
+            __builtin_amdgcn_sched_barrier(0);
         };
         auto final_step = [&](auto U, int s) { consume(U, wv + 4 * s, std::true_type{}); };
         int s = 0;
@@ -207,7 +226,7 @@ __device__ __forceinline__ void split_tile(const SplitArgs& a, const Tile t, cha
         if (kGateUp) {
             const floatx4 up = total(b + kUnits, mt);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) o[v] = g[v] / (1.0f + expf(-g[v])) * up[v];
+            for (int v = 0; v < 4; ++v) o[v] = g[v] / (1.0f + (sizeof(OT) == 4 ? expf(-g[v]) : __expf(-g[v]))) * up[v];
         } else {
 #pragma unroll
             for (int v = 0; v < 4; ++v) o[v] = g[v];
