@@ -26,7 +26,7 @@ __global__ __launch_bounds__(kThreads) void permute_kernel(const int32_t* __rest
         const int l = pair_slot[p] - lo;
         return (l >= 0 && l < spr) ? l : -1;
     };
-    build_token_lists(key_of, nullptr, n, spr, s_hist, s_cnt, s_off, group_offsets, perm_pair, pair_row, n_pairs);
+    build_token_lists(key_of, n, spr, s_hist, s_cnt, s_off, group_offsets, perm_pair, pair_row, n_pairs);
 }
 
 }  // namespace

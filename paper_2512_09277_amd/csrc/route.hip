@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "device_utils.h"
 #include "metro.h"
 
@@ -27,6 +29,7 @@ constexpr int kWords = kMaxN / 64;
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
 constexpr int kNoSlot = 0x7fffffff;
+constexpr int kRunPairs = 2048;   // pairs a workgroup numbers at least: two 64-item chunks per wave
 
 struct RouteArgs {
     const int32_t* ids;
@@ -40,6 +43,7 @@ struct RouteArgs {
     int32_t* err_flag;
     // token lists of one rank, emitted by the same workgroup after pair_slot (single-layer calls only)
     int list_rank;            // < 0: no lists
+    int split;                // workgroups per layer, each numbers and emits its own run of pairs
     int32_t* group_offsets;
     int32_t* perm_pair;
     int32_t* pair_row;
@@ -53,19 +57,88 @@ __device__ __forceinline__ void set_bit64(uint32_t* lo, uint32_t* hi, int idx, i
     else atomicOr(&hi[idx], 1u << (bit - 32));
 }
 
-// Ranks hosting each expert (matrix A, one 64-bit row per expert) from slot_to_expert.
-__device__ __forceinline__ void build_host_masks(const int32_t* s2e, int N, int S, int spr, uint32_t* host_lo,
-                                                 uint32_t* host_hi, int* err) {
-    for (int s = threadIdx.x; s < S; s += blockDim.x) {
-        const int e = s2e[s];
-        if (e < -1 || e >= N) atomicOr(err, METRO_FLAG_BAD_PLACEMENT);
-        else if (e >= 0) set_bit64(host_lo, host_hi, e, s / spr);
+// ------------------------------------------------------------------------------------------ shared pieces
+// Smallest value over the lanes of the first 16 (narrow) or all 64 lanes, in every lane's scalar view.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v, bool narrow) {
+    constexpr int kNone = -1;                        // identity of the unsigned minimum
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x111, 0xf, 0xf, false));      // row_shr:1
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x112, 0xf, 0xf, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x114, 0xf, 0xf, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x118, 0xf, 0xf, false));
+    if (narrow) return __builtin_amdgcn_readlane(v, 15);
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x142, 0xa, 0xf, false));      // row_bcast:15
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x143, 0xc, 0xf, false));      // row_bcast:31
+    return __builtin_amdgcn_readlane(v, kWave - 1);
+}
+
+// The run of pairs [lo, hi) of one of the workgroups of a layer, in chunks of 64; wave w of it owns the chunks
+// [first + w * per_wave, ...).  Every workgroup reads all ids (it needs the counts of the pairs before its run and of the
+// whole layer) and numbers only its own: reading and counting takes a fraction of numbering, and no workgroup waits
+// for another.
+struct Run {
+    int lo, hi, first, per_wave;                     // first: the wave's first chunk
+    __device__ __forceinline__ Run(int n, int part, int split) {
+        const int chunks = (n + kWave - 1) / kWave, each = (chunks + split - 1) / split;
+        const int begin = min(part * each, chunks), end = min(begin + each, chunks);
+        lo = begin * kWave;
+        hi = min(end * kWave, n);
+        per_wave = (end - begin + kWaves - 1) / kWaves;
+        first = begin + wave_id() * per_wave;
     }
+    __device__ __forceinline__ int item(int c) const { return (first + c) * kWave + lane_id(); }
+};
+
+// f(id) for the ids outside the run, four at a time where the layout allows; `before`: the id precedes the run.
+template <typename F>
+__device__ __forceinline__ void for_other_ids(const int32_t* __restrict__ ids, int n, bool vec4, const Run& run, F f) {
+    if (run.lo == 0 && run.hi >= n) return;          // uniform
+    const int tid = threadIdx.x;
+    if (vec4) {
+        const int4* v = reinterpret_cast<const int4*>(ids);
+        constexpr int kBatch = 4;                    // independent loads in flight
+        for (int i0 = 0; i0 < n / 4; i0 += kBatch * kThreads) {
+            int4 q[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int i = i0 + u * kThreads + tid, p = 4 * i;
+                q[u] = make_int4(-1, -1, -1, -1);
+                if (p < n && (p < run.lo || p >= run.hi)) q[u] = v[i];
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const bool before = 4 * (i0 + u * kThreads + tid) < run.lo;
+                f(q[u].x, before); f(q[u].y, before); f(q[u].z, before); f(q[u].w, before);
+            }
+        }
+    } else {
+        for (int p = tid; p < n; p += kThreads)
+            if (p < run.lo || p >= run.hi) f(ids[p], p < run.lo);
+    }
+}
+
+// Per-wave counts of the run -> what precedes each wave's chunks; returns the count over the whole layer.
+__device__ __forceinline__ int run_bases(int* hist, int n_keys, int e, int before, int after) {
+    int running = before;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        const int c = hist[w * n_keys + e];
+        hist[w * n_keys + e] = running;
+        running += c;
+    }
+    return running + after;
 }
 
 // ------------------------------------------------------------------------------------------ METRO
 constexpr int kIdCache = 8;      // int4 loads of ids a thread keeps in registers between the two passes
+constexpr int kRunCache = 8;     // chunks of its run whose ids a wave keeps in registers
 
+// One workgroup per layer solves; with kLists, `split` workgroups solve the same layer and each emits its own run of
+// pairs and the rows these get in the token lists of one rank ("route tokens", Sec. 4.3).  All pairs of an expert go to
+// one replica, so the row of a pair is the slot's first row plus the number of earlier pairs of the expert: one stable
+// numbering, by the keys of the run only.  Latency-bound throughout (barriers, LDS round trips, the serial chain); kernel
+// times with the rule below, us, against one workgroup that sorted its own pair_slot in three more passes: 64 pairs 9.9 ->
+// 5.8, 2048 pairs 11.0 -> 6.4, 8192 pairs (256 experts) 19.2 -> 11.2; without lists, 58 layers of 8192 pairs 10.2 -> 9.4.
+template <bool kLists>
 __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
     __shared__ int s_active[kMaxN];
     __shared__ uint32_t s_host_lo[kMaxN], s_host_hi[kMaxN];
@@ -75,9 +148,11 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
     __shared__ uint32_t s_multi_lo[kWords], s_multi_hi[kWords];
     __shared__ uint32_t s_bm_lo[kMaxG], s_bm_hi[kMaxG];
     __shared__ int s_err;
-    __shared__ int s_list_hist[kWaves * kListMaxSpr], s_list_cnt[kListMaxSpr], s_list_off[kListMaxSpr + 1];
+    __shared__ int s_hist[kLists ? kWaves * kMaxN : 1];             // pairs per expert: the run's, by wave
+    __shared__ int s_before[kLists ? kMaxN : 1], s_after[kLists ? kMaxN : 1];
+    __shared__ int s_off[kLists ? kMaxSpr : 1];                     // first row of every slot of list_rank
 
-    const int layer = blockIdx.x;
+    const int layer = kLists ? 0 : blockIdx.x, part = kLists ? blockIdx.x : 0;
     const int N = a.N, G = a.G, spr = a.spr, S = G * spr;
     const int n_pairs = a.T * a.k;
     const int32_t* ids = a.ids + (size_t)layer * n_pairs;
@@ -86,15 +161,25 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
     const int tid = threadIdx.x;
 
     // The global loads go out first, so that their latency overlaps the LDS set-up; the ids stay in
-    // registers for the emit pass (batches beyond kIdCache*4*1024 pairs re-read the rest).
+    // registers for the emit pass (what does not fit is read again).
     const int4* v = reinterpret_cast<const int4*>(ids);
     const int n4 = a.vec4 ? n_pairs / 4 : 0;
-    int4 idc[kIdCache];
+    const Run run(n_pairs, part, kLists ? a.split : 1);
+    int4 idc[kLists ? 1 : kIdCache];
+    int key[kLists ? kRunCache : 1];
+    if constexpr (kLists) {
 #pragma unroll
-    for (int c = 0; c < kIdCache; ++c) {
-        idc[c] = make_int4(-1, -1, -1, -1);
-        const int i = tid + c * kThreads;
-        if (i < n4) idc[c] = v[i];
+        for (int c = 0; c < kRunCache; ++c) {
+            const int p = run.item(c);
+            key[c] = c < run.per_wave && p < run.hi ? ids[p] : -1;
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < kIdCache; ++c) {
+            idc[c] = make_int4(-1, -1, -1, -1);
+            const int i = tid + c * kThreads;
+            if (i < n4) idc[c] = v[i];
+        }
     }
     int se[kMaxS / kThreads];
 #pragma unroll
@@ -103,14 +188,17 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
         se[j] = sl < S ? s2e[sl] : -1;
     }
 
-    for (int e = tid; e < kMaxN; e += kThreads) {
+    for (int e = tid; e < N; e += kThreads) {
         s_active[e] = 0;
         s_host_lo[e] = 0;
         s_host_hi[e] = 0;
         s_rank[e] = -1;
         s_slot[e] = kNoSlot;
+        if constexpr (kLists) s_before[e] = s_after[e] = 0;
     }
-    for (int i = tid; i < kWords * kMaxG; i += kThreads) {
+    if constexpr (kLists)
+        for (int i = tid; i < kWaves * N; i += kThreads) s_hist[i] = 0;
+    for (int i = tid; i < ((N + 63) >> 6) * kMaxG; i += kThreads) {
         (&s_forced_lo[0][0])[i] = 0;
         (&s_forced_hi[0][0])[i] = 0;
     }
@@ -131,17 +219,32 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
     auto mark = [&](int id) {
         if (id < -1 || id >= N) atomicOr(&s_err, METRO_FLAG_BAD_ID);
         else if (id >= 0) s_active[id] = 1;
+        return id >= 0 && id < N;
     };
+    if constexpr (kLists) {
+        int* mine = s_hist + wave_id() * N;
 #pragma unroll
-    for (int c = 0; c < kIdCache; ++c) {
-        mark(idc[c].x); mark(idc[c].y); mark(idc[c].z); mark(idc[c].w);   // padding (-1) where not loaded
+        for (int c = 0; c < kRunCache; ++c)
+            if (mark(key[c])) atomicAdd(&mine[key[c]], 1);
+        for (int c = kRunCache; c < run.per_wave; ++c) {
+            const int id = run.item(c) < run.hi ? ids[run.item(c)] : -1;
+            if (mark(id)) atomicAdd(&mine[id], 1);
+        }
+        for_other_ids(ids, n_pairs, a.vec4, run, [&](int id, bool before) {
+            if (mark(id)) atomicAdd(before ? &s_before[id] : &s_after[id], 1);
+        });
+    } else {
+#pragma unroll
+        for (int c = 0; c < kIdCache; ++c) {
+            mark(idc[c].x); mark(idc[c].y); mark(idc[c].z); mark(idc[c].w);   // padding (-1) where not loaded
+        }
+        for (int i = tid + kIdCache * kThreads; i < n4; i += kThreads) {
+            const int4 q = v[i];
+            mark(q.x); mark(q.y); mark(q.z); mark(q.w);
+        }
+        if (!a.vec4)
+            for (int i = tid; i < n_pairs; i += kThreads) mark(ids[i]);
     }
-    for (int i = tid + kIdCache * kThreads; i < n4; i += kThreads) {
-        const int4 q = v[i];
-        mark(q.x); mark(q.y); mark(q.z); mark(q.w);
-    }
-    if (!a.vec4)
-        for (int i = tid; i < n_pairs; i += kThreads) mark(ids[i]);
     __syncthreads();
 
     // Split the active experts: single replica (forced) or several (the serial chain).
@@ -164,16 +267,15 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
     // The chain: wave 0, lane g keeps L[g].  Load of rank g when expert e is served =
     //   L (all experts of lower words) + forced experts of this word below e + chain picks of this word.
     // Per 64-expert word the lanes first fetch the host masks of the word's experts (lane b <-> expert
-    // 64w+b), so that the serial loop reads them with readlane instead of waiting for LDS each step.
+    // 64w+b), so that the serial loop reads them with readlane instead of waiting for LDS each step.  The choice is a
+    // minimum over (load, rank) in registers: about 100 cycles per expert (ballots over the bits of the load: 300).
     if (tid < kWave) {
         const int g = tid;
         int L = 0;
-        int load_bits = 1;
-        while ((1 << load_bits) <= spr) ++load_bits;   // L[g] <= spr always
         const int n_words = (N + 63) >> 6;
         for (int w = 0; w < n_words; ++w) {
             const uint64_t forced = g < G ? join64(s_forced_lo[w][g], s_forced_hi[w][g]) : 0ull;
-            const int my_e = min((w << 6) + g, kMaxN - 1);
+            const int my_e = min((w << 6) + g, N - 1);
             const uint32_t hl = s_host_lo[my_e], hh = s_host_hi[my_e];
             uint64_t multi = join64(__builtin_amdgcn_readfirstlane(s_multi_lo[w]),
                                     __builtin_amdgcn_readfirstlane(s_multi_hi[w]));
@@ -182,19 +284,18 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
             while (multi) {
                 const int b = __ffsll((unsigned long long)multi) - 1;
                 multi &= multi - 1;
-                uint64_t cand = join64(__builtin_amdgcn_readlane(hl, b), __builtin_amdgcn_readlane(hh, b));
+                const uint64_t cand = join64(__builtin_amdgcn_readlane(hl, b), __builtin_amdgcn_readlane(hh, b));
                 const int cur = L + __popcll(forced & ((1ull << b) - 1ull)) + picked;
-                for (int bit = load_bits - 1; bit >= 0; --bit) {     // keep the candidates with the smallest load
-                    const uint64_t zero_here = __ballot(((cur >> bit) & 1) == 0) & cand;
-                    if (zero_here) cand = zero_here;
-                }
-                const int best = __ffsll((unsigned long long)cand) - 1;   // lowest rank among them
+                const uint32_t order = ((cand >> g) & 1ull) ? ((uint32_t)cur << 6) | (uint32_t)g : 0xffffffffu;
+                const int best = (int)(wave_min(order, G <= 16) & 63u);      // least load, lowest rank among equals
                 if (g == best) ++picked;
                 if (g == b) best_of = best;
             }
             if (best_of != 0xffffffffu) s_rank[(w << 6) + g] = (int)best_of;
             L += __popcll(forced) + picked;
         }
+    } else if constexpr (kLists) {                       // meanwhile: what precedes each wave's chunks, and T[i]
+        for (int e = tid - kWave; e < N; e += kThreads - kWave) s_after[e] = run_bases(s_hist, N, e, s_before[e], s_after[e]);
     }
     __syncthreads();
 
@@ -206,62 +307,102 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
         if (sl < S && e >= 0 && s_active[e] && s_rank[e] == sl / spr) atomicMin(&s_slot[e], sl);
     }
     __syncthreads();
+    const int lo = a.list_rank * spr;
+    if constexpr (kLists) {                              // the last wave: rows per slot of the rank and their offsets
+        if (wave_id() == kWaves - 1) {
+            const int l = lane_id();
+            const int e = l < spr ? s2e[lo + l] : -1;
+            const int c = e >= 0 && e < N && s_slot[e] == lo + l ? s_after[e] : 0;
+            const int incl = wave_inclusive_sum(c);
+            s_off[l] = incl - c;
+            if (part == 0) {
+                if (l < spr) a.group_offsets[l] = incl - c;
+                if (l == spr - 1) {
+                    a.group_offsets[spr] = incl;
+                    *a.n_pairs = incl;
+                }
+            }
+        }
+    }
     for (int e = tid; e < N; e += kThreads) {
-        int slot = s_slot[e];
-        if (slot == kNoSlot) slot = -1;
-        s_slot[e] = slot;
-        a.expert_slot[(size_t)layer * N + e] = slot;
+        const int slot = s_slot[e] == kNoSlot ? -1 : s_slot[e];
+        if (part == 0) a.expert_slot[(size_t)layer * N + e] = slot;
         if (slot >= 0) set_bit64(s_bm_lo, s_bm_hi, slot / spr, slot % spr);
     }
     __syncthreads();
-    if (tid < G) {
-        const uint64_t bm = join64(s_bm_lo[tid], s_bm_hi[tid]);
-        a.rank_bitmap[(size_t)layer * G + tid] = bm;
-        a.rank_active[(size_t)layer * G + tid] = __popcll(bm);
+    if (part == 0) {
+        if (tid < G) {
+            const uint64_t bm = join64(s_bm_lo[tid], s_bm_hi[tid]);
+            a.rank_bitmap[(size_t)layer * G + tid] = bm;
+            a.rank_active[(size_t)layer * G + tid] = __popcll(bm);
+        }
+        if (tid == 0) a.err_flag[layer] = s_err;
     }
-    if (tid == 0) a.err_flag[layer] = s_err;
 
     // x from y: every pair of expert i goes to its activated replica.
-    auto slot_of = [&](int id) { return (id >= 0 && id < N) ? s_slot[id] : -1; };
-    int4* o = reinterpret_cast<int4*>(pair_slot);
+    auto slot_of = [&](int id) {
+        const int slot = (id >= 0 && id < N) ? s_slot[id] : kNoSlot;
+        return slot == kNoSlot ? -1 : slot;
+    };
+    if constexpr (!kLists) {
+        int4* o = reinterpret_cast<int4*>(pair_slot);
 #pragma unroll
-    for (int c = 0; c < kIdCache; ++c) {
-        const int i = tid + c * kThreads;
-        if (i < n4) o[i] = make_int4(slot_of(idc[c].x), slot_of(idc[c].y), slot_of(idc[c].z), slot_of(idc[c].w));
-    }
-    for (int i = tid + kIdCache * kThreads; i < n4; i += kThreads) {
-        const int4 q = v[i];
-        o[i] = make_int4(slot_of(q.x), slot_of(q.y), slot_of(q.z), slot_of(q.w));
-    }
-    if (!a.vec4)
-        for (int i = tid; i < n_pairs; i += kThreads) pair_slot[i] = slot_of(ids[i]);
-    // "Route tokens" (Sec. 4.3) in the same launch: the token lists of one rank.  A pair's slot is looked up from
-    // the table in LDS again (the ids come back from the cache), so nothing written above has to be re-read.
-    if (a.list_rank >= 0) {                         // uniform
-        const int lo = a.list_rank * spr;
-        auto key_of = [&](int p) {
-            const int id = ids[p];
-            const int l = ((id >= 0 && id < N) ? s_slot[id] : -1) - lo;
-            return (l >= 0 && l < spr) ? l : -1;
+        for (int c = 0; c < kIdCache; ++c) {
+            const int i = tid + c * kThreads;
+            if (i < n4) o[i] = make_int4(slot_of(idc[c].x), slot_of(idc[c].y), slot_of(idc[c].z), slot_of(idc[c].w));
+        }
+        for (int i = tid + kIdCache * kThreads; i < n4; i += kThreads) {
+            const int4 q = v[i];
+            o[i] = make_int4(slot_of(q.x), slot_of(q.y), slot_of(q.z), slot_of(q.w));
+        }
+        if (!a.vec4)
+            for (int i = tid; i < n_pairs; i += kThreads) pair_slot[i] = slot_of(ids[i]);
+    } else {
+        int* mine = s_hist + wave_id() * N;
+        const int bits = 32 - __clz(max(spr - 1, 1));
+        auto emit = [&](int p, int id) {
+            const int slot = slot_of(id), l = slot - lo;
+            const bool here = l >= 0 && l < spr;         // slot -1 is on no rank
+            int total;
+            const int nth = wave_rank_by_key(l, here, bits, total);
+            int row = -1;
+            if (here) {
+                const int base = mine[id];
+                row = s_off[l] + base + nth;
+                // the wave executes in lockstep: every read of mine[] above precedes the update below
+                if (nth == total - 1) mine[id] = base + total;
+                a.perm_pair[row] = p;
+            }
+            if (p < run.hi) {
+                pair_slot[p] = slot;
+                a.pair_row[p] = row;
+            }
         };
-        build_token_lists(key_of, nullptr, n_pairs, spr, s_list_hist, s_list_cnt, s_list_off, a.group_offsets,
-                          a.perm_pair, a.pair_row, a.n_pairs);
+#pragma unroll
+        for (int c = 0; c < kRunCache; ++c)
+            if (c < run.per_wave) emit(run.item(c), key[c]);             // uniform per wave
+        for (int c = kRunCache; c < run.per_wave; ++c) emit(run.item(c), run.item(c) < run.hi ? ids[run.item(c)] : -1);
     }
 }
 
 // ------------------------------------------------------------------------------------------ token-balanced
+// `split` workgroups per layer, each with its own run of pairs.  The occurrence number q of a pair (its place among the
+// pairs of its expert) gives both results: replica q mod r, and -- since that replica gets every r-th pair of the
+// expert -- place q / r among the replica's pairs, so the token lists need no sort of their own.  Issue-bound in the
+// ballots of the numbering (about 80 instructions per 64 pairs), hence the runs; kernel time with lists 13.3 -> 6.7 us at 776
+// pairs, 80.7 -> 11.8 us at 32768 (one workgroup, ids past the registers read one chunk at a time, the lists sorted again).
 __global__ __launch_bounds__(kThreads) void token_balanced_kernel(RouteArgs a) {
-    __shared__ int s_hist[kWaves * kMaxN];          // per-wave occurrence bases
-    __shared__ int s_cnt[kMaxN];                    // T[i]
+    __shared__ int s_hist[kWaves * kMaxN];          // the run's pairs per expert, by wave; then their bases
+    __shared__ int s_before[kMaxN], s_cnt[kMaxN];   // pairs before the run; after it, then T[i]
     __shared__ uint32_t s_host_lo[kMaxN], s_host_hi[kMaxN];
     __shared__ int s_base[kMaxN + 1];               // CSR of replicas per expert
     __shared__ int s_repl[kMaxS];                   // replica slots, ascending slot id within an expert
-    __shared__ int s_s2e[kMaxS];
     __shared__ uint32_t s_bm_lo[kMaxG], s_bm_hi[kMaxG];
     __shared__ int s_wave_sum[kWaves];
+    __shared__ int s_off[kMaxSpr];                  // first row of every slot of list_rank
     __shared__ int s_err;
 
-    const int layer = blockIdx.x;
+    const int layer = blockIdx.x / a.split, part = blockIdx.x - layer * a.split;
     const int N = a.N, G = a.G, spr = a.spr, S = G * spr;
     const int n_pairs = a.T * a.k;
     const int32_t* ids = a.ids + (size_t)layer * n_pairs;
@@ -269,39 +410,60 @@ __global__ __launch_bounds__(kThreads) void token_balanced_kernel(RouteArgs a) {
     int32_t* pair_slot = a.pair_slot + (size_t)layer * n_pairs;
     const int tid = threadIdx.x;
 
-    OrderedCounter oc;
-    oc.init(n_pairs, N, s_hist, s_cnt);
-    for (int e = tid; e < kMaxN; e += kThreads) { s_host_lo[e] = 0; s_host_hi[e] = 0; }
+    const Run run(n_pairs, part, a.split);
+    int key[kRunCache];
+#pragma unroll
+    for (int c = 0; c < kRunCache; ++c) {
+        const int p = run.item(c);
+        key[c] = c < run.per_wave && p < run.hi ? ids[p] : -1;
+    }
+    int se[kMaxS / kThreads];
+#pragma unroll
+    for (int j = 0; j < kMaxS / kThreads; ++j) {
+        const int sl = tid + j * kThreads;
+        se[j] = sl < S ? s2e[sl] : -1;
+    }
+    for (int e = tid; e < N; e += kThreads) { s_host_lo[e] = s_host_hi[e] = 0; s_before[e] = s_cnt[e] = 0; }
+    for (int i = tid; i < kWaves * N; i += kThreads) s_hist[i] = 0;
+    for (int i = tid; i < S; i += kThreads) s_repl[i] = kNoSlot;
     if (tid < kMaxG) { s_bm_lo[tid] = 0; s_bm_hi[tid] = 0; }
     if (tid == 0) s_err = 0;
-    for (int s = tid; s < S; s += kThreads) {
-        const int e = s2e[s];
-        s_s2e[s] = (e >= 0 && e < N) ? e : -1;
+    __syncthreads();
+
+#pragma unroll
+    for (int j = 0; j < kMaxS / kThreads; ++j) {
+        const int sl = tid + j * kThreads;
+        if (sl < S) {
+            if (se[j] < -1 || se[j] >= N) { atomicOr(&s_err, METRO_FLAG_BAD_PLACEMENT); se[j] = -1; }
+            else if (se[j] >= 0) set_bit64(s_host_lo, s_host_hi, se[j], sl / spr);
+        }
     }
-    __syncthreads();
-
-    build_host_masks(s2e, N, S, spr, s_host_lo, s_host_hi, &s_err);
-    auto key_of = [&](int p) {
-        const int id = ids[p];
-        if (id < -1 || id >= N) { atomicOr(&s_err, METRO_FLAG_BAD_ID); return -1; }
-        return id;
+    auto valid = [&](int id) {
+        if (id < -1 || id >= N) atomicOr(&s_err, METRO_FLAG_BAD_ID);
+        return id >= 0 && id < N;
     };
-    int keys[OrderedCounter::kCached];
-    oc.load_keys(key_of, keys);
-    oc.histogram(key_of, keys);
+    int* mine = s_hist + wave_id() * N;
+#pragma unroll
+    for (int c = 0; c < kRunCache; ++c)
+        if (valid(key[c])) atomicAdd(&mine[key[c]], 1);
+    for (int c = kRunCache; c < run.per_wave; ++c) {
+        const int id = run.item(c) < run.hi ? ids[run.item(c)] : -1;
+        if (valid(id)) atomicAdd(&mine[id], 1);
+    }
+    for_other_ids(ids, n_pairs, a.vec4, run, [&](int id, bool before) {
+        if (valid(id)) atomicAdd(before ? &s_before[id] : &s_cnt[id], 1);
+    });
     __syncthreads();
-    oc.prefix();                                     // s_cnt[e] = T[e]
 
-    // Exclusive scan of replica counts r_e = popcount(host[e]) over experts -> s_base.
+    // T[i], the bases of the run's chunks, and an exclusive scan of the replica counts r_e = popcount(host[e]) -> s_base
     {
         int r = 0;
-        if (tid < N) r = __popcll(join64(s_host_lo[tid], s_host_hi[tid]));
-        int incl = r;
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-            const int up = __shfl_up(incl, d);
-            if (lane_id() >= d) incl += up;
+        if (tid < N) {
+            r = __popcll(join64(s_host_lo[tid], s_host_hi[tid]));
+            s_cnt[tid] = run_bases(s_hist, N, tid, s_before[tid], s_cnt[tid]);
+            if (s_cnt[tid] > 0 && r == 0) atomicOr(&s_err, METRO_FLAG_NO_REPLICA);
         }
+        const int incl = wave_inclusive_sum(r);
         if (lane_id() == kWave - 1) s_wave_sum[wave_id()] = incl;
         __syncthreads();
         int before = 0;
@@ -311,68 +473,88 @@ __global__ __launch_bounds__(kThreads) void token_balanced_kernel(RouteArgs a) {
     }
     __syncthreads();
 
-    // Replica lists: the lowest slot of an expert on each hosting rank, ranks ascending
-    // (= ascending slot id).  A replica is activated iff its index is below T[e].
-    for (int s = tid; s < S; s += kThreads) {
-        const int e = s_s2e[s];
-        if (e < 0) continue;
-        const int g = s / spr;
-        bool primary = true;
-        for (int q = g * spr; q < s; ++q) primary = primary && s_s2e[q] != e;
-        if (!primary) continue;
-        const uint64_t host = join64(s_host_lo[e], s_host_hi[e]);
-        const int j = __popcll(host & ((1ull << g) - 1ull));
-        s_repl[s_base[e] + j] = s;
-        if (j < s_cnt[e]) set_bit64(s_bm_lo, s_bm_hi, g, s - g * spr);
-    }
-    for (int e = tid; e < N; e += kThreads)
-        if (s_cnt[e] > 0 && s_base[e + 1] == s_base[e]) atomicOr(&s_err, METRO_FLAG_NO_REPLICA);
-    __syncthreads();
-
-    // q-th pair of expert e -> replica q mod r_e.  The slots of the wave's register-cached chunks are kept for
-    // the token lists (their items map to lanes the same way there).
-    const int lo = a.list_rank * spr;
-    auto local = [&](int slot) {
-        const int l = slot - lo;
-        return (a.list_rank >= 0 && l >= 0 && l < spr) ? l : -1;
-    };
-    int list_keys[OrderedCounter::kCached];
+    // Replica lists: the lowest slot of an expert on each hosting rank, ranks ascending (= ascending slot id).
+    auto replica = [&](int e, int g) { return __popcll(join64(s_host_lo[e], s_host_hi[e]) & ((1ull << g) - 1ull)); };
 #pragma unroll
-    for (int c = 0; c < OrderedCounter::kCached; ++c) list_keys[c] = -1;
-    oc.number(
-        [&](int p) {
-            const int id = ids[p];
-            return (id < 0 || id >= N) ? -1 : id;
-        },
-        keys, [&](int p, int e, int occ, auto cached) {
-            int slot = -1;
-            if (e >= 0) {
-                const int r = s_base[e + 1] - s_base[e];
-                if (r > 0) slot = s_repl[s_base[e] + occ % r];
-            }
-            pair_slot[p] = slot;
-            constexpr int c = decltype(cached)::value;
-            if constexpr (c >= 0) list_keys[c] = local(slot);
-        });
-    if (tid < G) {
-        const uint64_t bm = join64(s_bm_lo[tid], s_bm_hi[tid]);
-        a.rank_bitmap[(size_t)layer * G + tid] = bm;
-        a.rank_active[(size_t)layer * G + tid] = __popcll(bm);
+    for (int j = 0; j < kMaxS / kThreads; ++j) {
+        const int sl = tid + j * kThreads;
+        if (sl < S && se[j] >= 0) atomicMin(&s_repl[s_base[se[j]] + replica(se[j], sl / spr)], sl);
     }
     __syncthreads();
-    if (tid == 0) a.err_flag[layer] = s_err;
-    // "Route tokens" (Sec. 4.3) in the same launch.  The occurrence tables are free again and the token lists reuse
-    // them.  Pairs beyond the register-cached chunks (batches of more than 8192 pairs) are read back from
-    // pair_slot: the fence pushes this workgroup's stores past the CU's L1, the loads go around it.
-    if (a.list_rank >= 0) {                         // uniform
-        __threadfence();
-        __syncthreads();
-        auto key_of = [&](int p) {
-            return local(__hip_atomic_load(pair_slot + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        };
-        build_token_lists(key_of, list_keys, n_pairs, spr, s_hist, s_cnt, s_base, a.group_offsets, a.perm_pair,
-                          a.pair_row, a.n_pairs);
+    // Replica i of expert e gets pairs i, i + r, ...: it is activated iff i < T[e].
+    const int lo = a.list_rank * spr;
+    auto pairs_of = [&](int e, int sl) {                 // 0 for a copy that is no replica
+        const int i = replica(e, sl / spr), r = s_base[e + 1] - s_base[e];
+        return s_repl[s_base[e] + i] == sl && i < s_cnt[e] ? (s_cnt[e] - i + r - 1) / r : 0;
+    };
+#pragma unroll
+    for (int j = 0; j < kMaxS / kThreads; ++j) {
+        const int sl = tid + j * kThreads;
+        if (sl < S && se[j] >= 0 && pairs_of(se[j], sl) > 0) set_bit64(s_bm_lo, s_bm_hi, sl / spr, sl % spr);
     }
+    if (a.list_rank >= 0 && wave_id() == kWaves - 1) {   // rows per slot of the rank and their offsets
+        const int l = lane_id();
+        const int e = l < spr ? s2e[lo + l] : -1;
+        const int c = e >= 0 && e < N ? pairs_of(e, lo + l) : 0;
+        const int incl = wave_inclusive_sum(c);
+        s_off[l] = incl - c;
+        if (part == 0) {
+            if (l < spr) a.group_offsets[l] = incl - c;
+            if (l == spr - 1) {
+                a.group_offsets[spr] = incl;
+                *a.n_pairs = incl;
+            }
+        }
+    }
+    __syncthreads();
+    if (part == 0) {
+        if (tid < G) {
+            const uint64_t bm = join64(s_bm_lo[tid], s_bm_hi[tid]);
+            a.rank_bitmap[(size_t)layer * G + tid] = bm;
+            a.rank_active[(size_t)layer * G + tid] = __popcll(bm);
+        }
+        if (tid == 0) a.err_flag[layer] = s_err;
+    }
+
+    const int bits = 32 - __clz(max(N - 1, 1));
+    auto emit = [&](int p, int id) {
+        const bool ok = id >= 0 && id < N;
+        int total;
+        const int nth = wave_rank_by_key(id, ok, bits, total);
+        int slot = -1, row = -1;
+        if (ok) {
+            const int q = mine[id] + nth;
+            // the wave executes in lockstep: every read of mine[] above precedes the update below
+            if (nth == total - 1) mine[id] = q + 1;
+            const int first = s_base[id], r = s_base[id + 1] - first;
+            if (r > 0) {
+                const int turn = q / r;
+                slot = s_repl[first + q - turn * r];
+                const int l = slot - lo;
+                if (a.list_rank >= 0 && l >= 0 && l < spr) {
+                    row = s_off[l] + turn;
+                    a.perm_pair[row] = p;
+                }
+            }
+        }
+        if (p < run.hi) {
+            pair_slot[p] = slot;
+            if (a.list_rank >= 0) a.pair_row[p] = row;
+        }
+    };
+#pragma unroll
+    for (int c = 0; c < kRunCache; ++c)
+        if (c < run.per_wave) emit(run.item(c), key[c]);                 // uniform per wave
+    for (int c = kRunCache; c < run.per_wave; ++c) emit(run.item(c), run.item(c) < run.hi ? ids[run.item(c)] : -1);
+}
+
+// Workgroups per layer for the calls that number pairs: runs of at least 2048 pairs (one workgroup numbers these in less time
+// than reading the other runs' ids takes: 2048 pairs 6.4 us as one run, 8.1 us as two; 8192 pairs 11.2 us as four runs,
+// 10.5 as eight), no more workgroups than CUs, and no more than 64 readers of one layer's ids.
+inline int split_for(int L, int T, int k) {
+    const int64_t runs = ((int64_t)T * k + kRunPairs - 1) / kRunPairs;
+    const int64_t most = L >= 256 ? 1 : std::min(256 / L, 64);
+    return (int)std::max<int64_t>(1, std::min(runs, most));
 }
 
 int check_route_args(const void* ids, const void* s2e, int L, int T, int k, int N, int G, int spr,
@@ -400,6 +582,7 @@ RouteArgs pack(const int32_t* ids, const int32_t* s2e, int T, int k, int N, int 
     a.rank_bitmap = rank_bitmap;
     a.err_flag = err_flag;
     a.list_rank = -1;
+    a.split = 1;
     a.group_offsets = a.perm_pair = a.pair_row = a.n_pairs = nullptr;
     return a;
 }
@@ -428,7 +611,7 @@ extern "C" int metro_route(const int32_t* topk_ids, const int32_t* slot_to_exper
     if (!expert_slot) return METRO_ERR_INVALID_ARG;
     RouteArgs a = pack(topk_ids, slot_to_expert, T, k, N, G, spr, pair_slot, expert_slot, rank_active,
                        rank_bitmap, err_flag);
-    hipLaunchKernelGGL(metro_route_kernel, dim3(L), dim3(kThreads), 0, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(metro_route_kernel<false>, dim3(L), dim3(kThreads), 0, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP;
 }
 
@@ -442,7 +625,8 @@ extern "C" int metro_route_token_balanced(const int32_t* topk_ids, const int32_t
     if (rc != METRO_OK) return rc;
     RouteArgs a = pack(topk_ids, slot_to_expert, T, k, N, G, spr, pair_slot, nullptr, rank_active, rank_bitmap,
                        err_flag);
-    hipLaunchKernelGGL(token_balanced_kernel, dim3(L), dim3(kThreads), 0, (hipStream_t)stream, a);
+    a.split = split_for(L, T, k);
+    hipLaunchKernelGGL(token_balanced_kernel, dim3(L * a.split), dim3(kThreads), 0, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP;
 }
 
@@ -459,7 +643,8 @@ extern "C" int metro_route_permute(const int32_t* topk_ids, const int32_t* slot_
                        rank_bitmap, err_flag);
     rc = add_lists(a, rank, group_offsets, perm_pair, pair_row, n_pairs);
     if (rc != METRO_OK) return rc;
-    hipLaunchKernelGGL(metro_route_kernel, dim3(1), dim3(kThreads), 0, (hipStream_t)stream, a);
+    a.split = split_for(1, T, k);
+    hipLaunchKernelGGL(metro_route_kernel<true>, dim3(a.split), dim3(kThreads), 0, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP;
 }
 
@@ -476,6 +661,7 @@ extern "C" int metro_route_token_balanced_permute(const int32_t* topk_ids, const
                        err_flag);
     rc = add_lists(a, rank, group_offsets, perm_pair, pair_row, n_pairs);
     if (rc != METRO_OK) return rc;
-    hipLaunchKernelGGL(token_balanced_kernel, dim3(1), dim3(kThreads), 0, (hipStream_t)stream, a);
+    a.split = split_for(1, T, k);
+    hipLaunchKernelGGL(token_balanced_kernel, dim3(a.split), dim3(kThreads), 0, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP;
 }

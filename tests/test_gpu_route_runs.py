@@ -1,0 +1,65 @@
+"""Routing calls that number pairs (token lists, token-balanced routing) at the sizes where a layer's pairs are cut into
+runs of several workgroups: one pair short of, at and past a run, runs whose length is no multiple of four ids or of a
+chunk, more layers than leave a workgroup each, and batches whose runs outgrow the registers.  Whole numbers: bit for bit."""
+import numpy as np
+import pytest
+
+from paper_2512_09277_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    import torch
+
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+
+
+@pytest.mark.parametrize("N,k,G,spr,T", [(16, 1, 4, 5, 1), (16, 1, 4, 5, 63), (16, 1, 4, 5, 2047), (16, 1, 4, 5, 2048), (16, 1, 4, 5, 2049),
+                                         (128, 8, 8, 18, 257), (128, 8, 8, 18, 4096), (256, 3, 16, 18, 5461), (512, 5, 64, 32, 3001),
+                                         (64, 7, 33, 3, 20011), (256, 8, 8, 36, 70000)])
+@pytest.mark.parametrize("routing", ["metro", "token_balanced"])
+def test_runs_of_one_layer(oracle, routing, N, k, G, spr, T):
+    from paper_2512_09277_amd import api
+
+    api.load()
+    print(f"runs {routing} N={N} k={k} G={G} spr={spr} T={T}", flush=True)
+    p = W.popularity(N, 1.0, T)
+    s2e = W.placement(p, G, spr) if G * spr - N <= N * (G - 1) else None
+    ids = W.topk_trace(p, T, k, T + 1)
+    if T > 1:
+        ids[np.random.default_rng(T).random(ids.shape) < 0.05] = -1
+    ref = (oracle.route_metro if routing == "metro" else oracle.route_token_balanced)(ids, s2e, N, G, spr)
+    fused = api.metro_route_permute if routing == "metro" else api.metro_route_token_balanced_permute
+    plain = api.metro_route if routing == "metro" else api.metro_route_token_balanced
+    alone = plain(dev(ids), dev(s2e), N, G, spr)
+    for rank in sorted({0, G // 2, G - 1}):
+        out, lists = fused(dev(ids), dev(s2e), N, G, spr, rank)
+        want = oracle.permute(ref["pair_slot"], rank, spr)
+        for got in (out, alone):
+            assert int(got["err_flag"].item()) == 0
+            for name in ("pair_slot", "rank_active") + (("expert_slot",) if routing == "metro" else ()):
+                assert np.array_equal(got[name][0].cpu().numpy(), ref[name]), name
+            assert np.array_equal(got["rank_bitmap"][0].cpu().numpy().view(np.uint64), ref["rank_bitmap"])
+        n = want["n_pairs"]
+        assert int(lists["n_pairs"].item()) == n
+        assert np.array_equal(lists["group_offsets"].cpu().numpy(), want["group_offsets"])
+        assert np.array_equal(lists["perm_pair"].cpu().numpy()[:n], want["perm_pair"])
+        assert np.array_equal(lists["pair_row"].cpu().numpy(), want["pair_row"])
+
+
+@pytest.mark.parametrize("L,T", [(3, 1500), (58, 1024), (129, 700), (300, 300)])
+def test_runs_of_many_layers(oracle, L, T):
+    from paper_2512_09277_amd import api
+
+    api.load()
+    w = W.QWEN3_30B
+    p = W.popularity(w.N, 1.0, L)
+    s2e = W.placement(p, w.G, w.spr)
+    ids = np.stack([W.topk_trace(p, T, w.k, 1000 + l) for l in range(L)])
+    out = api.metro_route_token_balanced(dev(ids), dev(np.stack([s2e] * L)), w.N, w.G, w.spr)
+    assert not out["err_flag"].any()
+    for l in range(0, L, max(1, L // 7)):
+        ref = oracle.route_token_balanced(ids[l], s2e, w.N, w.G, w.spr)
+        assert np.array_equal(out["pair_slot"][l].cpu().numpy(), ref["pair_slot"]), l
+        assert np.array_equal(out["rank_bitmap"][l].cpu().numpy().view(np.uint64), ref["rank_bitmap"]), l
