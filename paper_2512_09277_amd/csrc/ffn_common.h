@@ -1,21 +1,13 @@
-// Pieces shared by the grouped-FFN kernels: operand types, the work items of a launch, bf16 packing.
+// Pieces shared by the grouped-FFN kernels: the work items of a launch, bf16 packing.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <type_traits>
-#include <utility>
-
 #include "device_utils.h"
+#include "mfma_common.h"
 
 namespace metro {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kMaxSpr = 64;
 
@@ -137,17 +129,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
     ua = (a != a) ? (ua | 0x00400000u) : ra;
     ub = (b != b) ? (ub | 0x00400000u) : rb;
     return (ua >> 16) | (ub & 0xffff0000u);
-}
-
-// do_step(U, s) for U = 0..n-1 with compile-time U (buffer indices), s = s0 + U.
-template <int... Us, typename F>
-__device__ __forceinline__ void run_steps(std::integer_sequence<int, Us...>, F&& f, int s0) {
-    (f(std::integral_constant<int, Us>{}, s0 + Us), ...);
-}
-template <int... Us, typename F>
-__device__ __forceinline__ void run_steps_tail(std::integer_sequence<int, Us...>, F&& f, int s0, int n_steps) {
-    // short-circuit: once a step is past the end nothing after it is tested, the paths join only at the end
-    (void)((s0 + Us < n_steps && (f(std::integral_constant<int, Us>{}, s0 + Us), true)) && ...);
 }
 
 }  // namespace

@@ -14,8 +14,8 @@
 //   2. gate_topk_kernel: one wave per token sums the chunks in a fixed order (deterministic), picks the
 //      top-k by k rounds of a wave-wide arg-max over (logit, -id) and forms the softmax weights;
 //   3. (only when the caller wants expert_count) gate_count_kernel: pairs per expert, one workgroup.
-// Shapes the MFMA kernel does not take (fp32, N not a multiple of 64, H not a multiple of 32) use a
-// plain one-wave-per-logit kernel in fp32.
+// Shapes these kernels do not take (fp32, N not a multiple of 64, H not a multiple of 32, misaligned operands) use
+// gate_logits_split_kernel instead, K split over the waves of a workgroup.
 #include <hip/hip_runtime.h>
 #include <float.h>
 #include <stdint.h>
@@ -25,13 +25,10 @@
 #include "device_utils.h"
 #include "host_utils.h"
 #include "metro.h"
+#include "split_k.h"
 
 namespace metro {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
 constexpr int kMaxN = 512;
@@ -242,33 +239,68 @@ __global__ __launch_bounds__(kThreads, 2) void gate_logits_lds_kernel(GateArgs a
     }
 }
 
-template <typename T>
-__device__ __forceinline__ float elem_f32(const void* p, size_t i);
-template <>
-__device__ __forceinline__ float elem_f32<float>(const void* p, size_t i) { return ((const float*)p)[i]; }
-template <>
-__device__ __forceinline__ float elem_f32<__bf16>(const void* p, size_t i) { return (float)((const __bf16*)p)[i]; }
-
-// Any shape, fp32 arithmetic: one wave per logit, a single chunk.
-template <typename T>
-__global__ __launch_bounds__(kThreads) void gate_logits_general_kernel(GateArgs a) {
-    const int t = blockIdx.x;
-    const int e = blockIdx.y * (kThreads / kWave) + wave_id();
-    if (e >= a.N) return;
-    float acc = 0.f;
-    for (int h = lane_id(); h < a.H; h += kWave)
-        acc = fmaf(elem_f32<T>(a.x, (size_t)t * a.H + h), elem_f32<T>(a.w_gate, (size_t)e * a.ldw + h), acc);
+// Any shape and alignment, fp32 storage among them: a tile of 16 MT tokens x 16 NB experts per workgroup, K split over its
+// waves (split_k.h; fp32 operands in fp32 matrix instructions), a single chunk.  What bounds it is latency and the number
+// of busy CUs; which tile when: launch_general_logits.
+template <typename T, int NB, int MT, int kSplit, int DEPTH, KRows kRows>
+__global__ __launch_bounds__(kSplit * kWave) void gate_logits_split_kernel(GateArgs a) {
+    __shared__ floatx4 part[kSplit][NB * MT][kWave];
+    const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
+    const int r16 = lane & 15, q = lane >> 4;
+    const int t0 = blockIdx.x * (16 * MT), e0 = blockIdx.y * (16 * NB);
+    constexpr int kStep = 8 * (16 / (int)sizeof(T));
+    const int n_steps = (a.H + kStep - 1) / kStep;
+    const T* pw[NB];
 #pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) acc += __shfl_xor(acc, d);
-    if (lane_id() == 0) a.part[(size_t)t * a.N + e] = acc;
+    for (int b = 0; b < NB; ++b) pw[b] = (const T*)a.w_gate + (size_t)min(e0 + b * 16 + r16, a.N - 1) * a.ldw;
+    const T* px[MT];
+    const uint32_t none[MT] = {};
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) px[mt] = (const T*)a.x + (size_t)min(t0 + mt * 16 + r16, a.T - 1) * a.H;
+    floatx4 acc[NB][MT];
+    // fp32 logits decide the top-k: chains of additions about as short as those of one product per lane and a tree
+    constexpr int kChains = sizeof(T) == 2 ? 2 : NB * MT > 4 ? 2 : 8;
+    split_dot<T, T, NB, MT, DEPTH, kRows, kChains>(pw, px, 0u, none, a.H, wv, kSplit, max(n_steps - wv + kSplit - 1, 0) / kSplit, acc);
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) part[wv][b * MT + mt][lane] = acc[b][mt];
+    __syncthreads();
+    for (int u = wv; u < NB * MT; u += kSplit) {
+        floatx4 p[kSplit];
+#pragma unroll
+        for (int o = 0; o < kSplit; ++o) p[o] = part[o][u][lane];
+#pragma unroll
+        for (int h = 1; h < kSplit; h *= 2)                                // pairwise, in a fixed order
+#pragma unroll
+            for (int o = 0; o + h < kSplit; o += 2 * h) p[o] += p[o + h];
+        const floatx4 sum = p[0];
+        const int t = t0 + (u % MT) * 16 + r16, e = e0 + (u / MT) * 16 + q * 4;
+        if (t >= a.T) continue;
+        float* out = a.part + (size_t)t * a.N + e;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (e + v < a.N) out[v] = sum[v];
+    }
 }
 
-struct Cand {
-    float v;
-    int id;
-};
-__device__ __forceinline__ bool better(const Cand& a, const Cand& b) { return a.v > b.v || (a.v == b.v && a.id < b.id); }
+// Position of a float (no NaN) in an order of unsigned integers; 0 comes before all of them.  -0 and +0 are one value.
+__device__ __forceinline__ uint32_t order_of(float v) {
+    const uint32_t u = __float_as_uint(v + 0.0f);
+    return u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
+}
+// Maximum over the wave, in registers (a shuffle through LDS per step costs several times as much).
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));          // row_shr:1
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));          // row_bcast:15
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));          // row_bcast:31
+    return __builtin_amdgcn_readlane(v, kWave - 1);
+}
 
+// (k rounds of shuffles through LDS took most of this kernel: 1024 tokens x 256 experts 11.2 -> 6.6 us, 256 x 128 7.6 -> 4.0.)
 // One wave per token.  Lane l holds the logits of experts l, l + 64, ... (kPerLane = ceil(N / 64) of them).
 // Tokens at or past *n_valid (a padded batch) get ids -1 and weights 0.
 template <int kPerLane>
@@ -309,33 +341,40 @@ __global__ __launch_bounds__(kThreads) void gate_topk_kernel(const float* __rest
                 for (int j = 0; j < kPerLane; ++j) v[j] += p[u][j];
             }
     }
+    uint32_t ord[kPerLane];                                      // 0: no expert, or already selected
 #pragma unroll
     for (int j = 0; j < kPerLane; ++j) {
         if (v[j] != v[j]) v[j] = -FLT_MAX;                       // NaN sorts below every number
-        if (j * kWave + l >= N) v[j] = -INFINITY;                // experts past N never win
+        ord[j] = j * kWave + l < N ? order_of(v[j]) : 0u;
     }
-    uint32_t taken = 0;                                          // bit j: v[j] already selected
-#pragma unroll
-    for (int j = 0; j < kPerLane; ++j)
-        if (j * kWave + l >= N) taken |= 1u << j;
     float my_v = 0.f;
     int my_id = 0;
     for (int r = 0; r < k; ++r) {
-        Cand best{-INFINITY, 0x7fffffff};
+        uint32_t best = 0;
+        int at = 0;
+        float best_v = 0.f;
 #pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {
-            const Cand c{v[j], j * kWave + l};
-            if (!((taken >> j) & 1u) && better(c, best)) best = c;
+        for (int j = 0; j < kPerLane; ++j)
+            if (ord[j] > best) {                                 // equal logits of a lane: the lower id stays
+                best = ord[j];
+                at = j;
+                best_v = v[j];
+            }
+        const uint32_t top = wave_max(best);                     // > 0: k <= N
+        uint64_t who = __ballot(best == top);
+        if (who & (who - 1)) {                                   // the same logit in several lanes (uniform): the lowest id
+            const uint32_t first = ~wave_max(best == top ? ~(uint32_t)(at * kWave + l) : 0u);
+            who = __ballot(best == top && (uint32_t)(at * kWave + l) == first);
         }
+        const int lane = __ffsll((unsigned long long)who) - 1;
+        const float val = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(best_v), lane));
+        const int id = __builtin_amdgcn_readlane(at, lane) * kWave + lane;
 #pragma unroll
-        for (int d = kWave / 2; d > 0; d >>= 1) {
-            const Cand o{__shfl_xor(best.v, d), __shfl_xor(best.id, d)};
-            if (better(o, best)) best = o;
-        }
-        if ((best.id & (kWave - 1)) == l) taken |= 1u << (best.id >> 6);   // k <= N: a real expert
+        for (int j = 0; j < kPerLane; ++j)
+            if (l == lane && at == j) ord[j] = 0u;
         if (l == r) {
-            my_v = best.v;
-            my_id = best.id;
+            my_v = val;
+            my_id = id;
         }
     }
     // lanes 0..k-1 hold the selection in descending order; softmax over it
@@ -362,12 +401,36 @@ __global__ __launch_bounds__(kCountThreads) void gate_count_kernel(const int32_t
     __shared__ int hist[kMaxN];
     for (int e = threadIdx.x; e < N; e += kCountThreads) hist[e] = 0;
     __syncthreads();
-    for (int p = threadIdx.x; p < n_pairs; p += kCountThreads) {
-        const int e = ids[p];
-        if (e >= 0 && e < N) atomicAdd(&hist[e], 1);
+    constexpr int kBatch = 8;                                    // independent loads in flight
+    for (int p0 = threadIdx.x; p0 < n_pairs; p0 += kBatch * kCountThreads) {
+        int e[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) e[u] = p0 + u * kCountThreads < n_pairs ? ids[p0 + u * kCountThreads] : -1;
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            if (e[u] >= 0 && e[u] < N) atomicAdd(&hist[e[u]], 1);
     }
     __syncthreads();
     for (int e = threadIdx.x; e < N; e += kCountThreads) cnt[e] = hist[e];
+}
+
+template <typename T>
+void launch_general_logits(const GateArgs& a, hipStream_t st) {
+    auto tiles = [&](int rows) { return (int64_t)((a.T + rows - 1) / rows) * ((a.N + rows - 1) / rows); };
+    auto go = [&](auto kernel, int rows, int waves) {
+        hipLaunchKernelGGL(kernel, dim3((a.T + rows - 1) / rows, (a.N + rows - 1) / rows), dim3(waves * kWave), 0, st, a);
+    };
+    // The largest tile that gives the chip enough workgroups: larger tiles read each operand fewer times, smaller ones put
+    // more CUs and waves to work.  Measured, logits kernel, us, 64 / 32 / 16 wide tiles: bf16, H = 4000, 200 experts, 4096
+    // tokens (256 / 896 / 3328 tiles) 25 / 42 / 75, 1024 tokens (64 / 224 / 832) 25 / 14 / 24; fp32, H = 2048, 128 experts,
+    // 512 tokens (16 / 64 / 256) 41 / 18 / 11.  The 32-wide tile pays from 64 tiles in bf16 (H = 2000, 200 experts, 512
+    // tokens, 112 tiles: 8.3 against 13.7) and, its fp32 matrix instructions being the longer part, from 256 in fp32.
+    // Short loops want little code: 8 waves two steps deep beat 16 waves four deep at 64 tokens, H = 1000, 5.1 to 7.6.
+    // (One wave per logit, which this replaced: 1887, 460, 83 us for the first, second and third, 93 for the fourth.)
+    if (a.H < 16 / (int)sizeof(T)) go(gate_logits_split_kernel<T, 2, 2, 4, 1, KRows::kTiny>, 32, 4);
+    else if (tiles(64) >= 256) go(gate_logits_split_kernel<T, 4, 4, 4, 1, KRows::kRagged>, 64, 4);
+    else if (tiles(32) >= (sizeof(T) == 2 ? 64 : 256)) go(gate_logits_split_kernel<T, 2, 2, 8, 2, KRows::kRagged>, 32, 8);
+    else go(gate_logits_split_kernel<T, 1, 1, 8, 2, KRows::kRagged>, 16, 8);
 }
 
 inline bool gate_mfma_shape(int H, int N, int dtype) {
@@ -471,11 +534,8 @@ extern "C" int moe_gate_topk(const void* x, const void* w_gate, int ldw, int T, 
     if (!mfma) {
         a.steps_per_chunk = 0;
         n_chunks = 1;
-        const dim3 grid(T, (N + kThreads / kWave - 1) / (kThreads / kWave));
-        if (dtype == METRO_DTYPE_F32)
-            hipLaunchKernelGGL(gate_logits_general_kernel<float>, grid, dim3(kThreads), 0, st, a);
-        else
-            hipLaunchKernelGGL(gate_logits_general_kernel<__bf16>, grid, dim3(kThreads), 0, st, a);
+        if (dtype == METRO_DTYPE_F32) launch_general_logits<float>(a, st);
+        else launch_general_logits<__bf16>(a, st);
     }
     if (hipGetLastError() != hipSuccess) return METRO_ERR_HIP;
     const int per = kThreads / kWave;

@@ -158,3 +158,42 @@ def test_padded_batch(api, oracle, T, n_real):
     if n:
         check(dict(topk_ids=got["topk_ids"][:n], topk_w=got["topk_w"][:n], expert_count=got["expert_count"]), ref, k, N,
               "bf16")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T,H,N,k", [(1, 1, 1, 1), (17, 3, 5, 2), (16, 7, 16, 3), (33, 8, 17, 4), (15, 9, 33, 8), (31, 65, 63, 5),
+                                     (300, 130, 100, 8), (256, 257, 129, 64), (1500, 100, 45, 4), (1300, 200, 131, 8),
+                                     (4100, 72, 200, 8)])
+def test_shapes_beside_the_matrix_tiles(api, oracle, T, H, N, k, dtype):
+    """Sizes the aligned kernels do not take: rows shorter than a vector, K steps and tiles of every width (16, 32, 64 tokens x
+    experts) ending inside, fp32, and an operand at an odd element offset."""
+    import torch
+
+    print(f"gate general T={T} H={H} N={N} k={k} {dtype}", flush=True)
+    x, wg = W.activations(T, H, 91, dtype), W.gate_weights(N, H, 92, dtype)
+    ref = oracle.gate_topk(x, wg, k, want_logits=True)
+    d_wg = dev(wg)
+    buf = torch.full((N * (H + 1) + 1,), 3.0, dtype=d_wg.dtype, device="cuda")     # pitch H + 1, first row one element in
+    odd = buf[1:].as_strided((N, H), (H + 1, 1))
+    odd.copy_(d_wg)
+    for w in (d_wg, odd):
+        got = api.moe_gate_topk(dev(x), w, k)
+        torch.cuda.synchronize()
+        check(got, ref, k, N, dtype)
+
+
+def test_nan_and_infinite_logits(api):
+    """NaN sorts below every number, +-infinity in their places, equal values to the lower id (also across the 64 lanes)."""
+    import torch
+
+    N, k, T = 200, 9, 4
+    row = torch.zeros(N)
+    row[7] = float("nan"); row[100] = float("inf"); row[199] = 5.0; row[3] = 5.0; row[67] = 5.0; row[50] = float("-inf")
+    wg = torch.zeros(N, 4); wg[:, 0] = row
+    x = torch.zeros(T, 4); x[:, 0] = 1.0
+    wg[7, 0] = float("nan")
+    got = api.moe_gate_topk(x.cuda(), wg.cuda(), k)
+    want = [100, 3, 67, 199, 0, 1, 2, 4, 5]
+    assert got["topk_ids"].cpu().tolist() == [want] * T
+    low = api.moe_gate_topk(x[:1].cuda(), wg[[7, 50, 7, 50, 1]].cuda(), 5)
+    assert low["topk_ids"].cpu().tolist() == [[4, 0, 2, 1, 3]]
