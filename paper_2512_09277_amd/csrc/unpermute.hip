@@ -18,32 +18,45 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float v) {
     return u >> 16;
 }
 
-// bf16, H % 8 == 0: every thread owns 8 consecutive columns (one 128-bit load per row).  KMAX > 0:
-// k <= KMAX, the token's rows and weights sit in registers and the row loads of a column go out
-// together; KMAX == 0: any k.
-template <int KMAX>
-__global__ __launch_bounds__(kThreads) void unpermute_bf16x8_kernel(const uint4* __restrict__ y,
-                                                                    const int32_t* __restrict__ pair_row,
-                                                                    const float* __restrict__ topk_w, int k, int H8,
-                                                                    uint4* __restrict__ out) {
-    const int t = blockIdx.x;
-    const int cap = (int)gridDim.x * k;           // rows of y_perm; an entry of pair_row outside [0, cap) is skipped
-    auto add = [](float (&acc)[8], float w, const uint4& v) {
+// A 16-byte vector of one row, in fp32 and packed: 8 bf16 or 4 fp32 columns.
+template <bool kBf16>
+struct Columns {
+    static constexpr int kN = kBf16 ? 8 : 4;
+    static __device__ __forceinline__ void add(float (&acc)[kN], float w, const uint4& v) {
         const uint32_t u[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            acc[2 * i] = fmaf(w, bf16_bits_to_f32(u[i] & 0xffffu), acc[2 * i]);
-            acc[2 * i + 1] = fmaf(w, bf16_bits_to_f32(u[i] >> 16), acc[2 * i + 1]);
+            if constexpr (kBf16) {
+                acc[2 * i] = fmaf(w, bf16_bits_to_f32(u[i] & 0xffffu), acc[2 * i]);
+                acc[2 * i + 1] = fmaf(w, bf16_bits_to_f32(u[i] >> 16), acc[2 * i + 1]);
+            } else {
+                acc[i] = fmaf(w, __uint_as_float(u[i]), acc[i]);
+            }
         }
-    };
-    auto pack = [](const float (&acc)[8]) {
-        uint4 o;
-        o.x = f32_to_bf16_bits(acc[0]) | (f32_to_bf16_bits(acc[1]) << 16);
-        o.y = f32_to_bf16_bits(acc[2]) | (f32_to_bf16_bits(acc[3]) << 16);
-        o.z = f32_to_bf16_bits(acc[4]) | (f32_to_bf16_bits(acc[5]) << 16);
-        o.w = f32_to_bf16_bits(acc[6]) | (f32_to_bf16_bits(acc[7]) << 16);
-        return o;
-    };
+    }
+    static __device__ __forceinline__ uint4 pack(const float (&acc)[kN]) {
+        uint32_t o[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (kBf16) o[i] = f32_to_bf16_bits(acc[2 * i]) | (f32_to_bf16_bits(acc[2 * i + 1]) << 16);
+            else o[i] = __float_as_uint(acc[i]);
+        }
+        return make_uint4(o[0], o[1], o[2], o[3]);
+    }
+};
+
+// Rows of whole 16-byte vectors: every thread owns one vector's columns (one 128-bit load per row).  KMAX > 0:
+// k <= KMAX, the token's rows and weights sit in registers and the row loads of a column go out
+// together; KMAX == 0: any k.  Bound by HBM (1024 tokens x 7168 in bf16: 45 MB in 12.6 us) and, in small batches, by
+// the two dependent loads; fp32 rows took one column per thread and 15 us at 256 tokens x 2048, now 4.8.
+template <bool kBf16, int KMAX>
+__global__ __launch_bounds__(kThreads) void unpermute_vec_kernel(const uint4* __restrict__ y,
+                                                                 const int32_t* __restrict__ pair_row,
+                                                                 const float* __restrict__ topk_w, int k, int HV,
+                                                                 uint4* __restrict__ out) {
+    using C = Columns<kBf16>;
+    const int t = blockIdx.x;
+    const int cap = (int)gridDim.x * k;           // rows of y_perm; an entry of pair_row outside [0, cap) is skipped
     if (KMAX > 0) {
         int rows[KMAX > 0 ? KMAX : 1];
         float ws[KMAX > 0 ? KMAX : 1];
@@ -53,26 +66,26 @@ __global__ __launch_bounds__(kThreads) void unpermute_bf16x8_kernel(const uint4*
             if (rows[j] >= cap) rows[j] = -1;
             ws[j] = j < k ? topk_w[(size_t)t * k + j] : 0.f;
         }
-        for (int c = threadIdx.x; c < H8; c += kThreads) {
+        for (int c = threadIdx.x; c < HV; c += kThreads) {
             uint4 v[KMAX > 0 ? KMAX : 1];
 #pragma unroll
             for (int j = 0; j < KMAX; ++j)
-                if (rows[j] >= 0) v[j] = y[(size_t)rows[j] * H8 + c];     // uniform per workgroup
-            float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                if (rows[j] >= 0) v[j] = y[(size_t)rows[j] * HV + c];     // uniform per workgroup
+            float acc[C::kN] = {};
 #pragma unroll
             for (int j = 0; j < KMAX; ++j)
-                if (rows[j] >= 0) add(acc, ws[j], v[j]);
-            out[(size_t)t * H8 + c] = pack(acc);
+                if (rows[j] >= 0) C::add(acc, ws[j], v[j]);
+            out[(size_t)t * HV + c] = C::pack(acc);
         }
     } else {
-        for (int c = threadIdx.x; c < H8; c += kThreads) {
-            float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int c = threadIdx.x; c < HV; c += kThreads) {
+            float acc[C::kN] = {};
             for (int j = 0; j < k; ++j) {
                 const int r = pair_row[(size_t)t * k + j];
                 if (r < 0 || r >= cap) continue;
-                add(acc, topk_w[(size_t)t * k + j], y[(size_t)r * H8 + c]);
+                C::add(acc, topk_w[(size_t)t * k + j], y[(size_t)r * HV + c]);
             }
-            out[(size_t)t * H8 + c] = pack(acc);
+            out[(size_t)t * HV + c] = C::pack(acc);
         }
     }
 }
@@ -111,18 +124,24 @@ extern "C" int moe_unpermute(const void* y_perm, const int32_t* pair_row, const 
     if (T == 0) return METRO_OK;
     hipStream_t st = (hipStream_t)stream;
     const bool aligned = (((uintptr_t)y_perm | (uintptr_t)out) & 15) == 0;
-    if (dtype == METRO_DTYPE_BF16 && H % 8 == 0 && aligned && k <= 8)
-        hipLaunchKernelGGL(unpermute_bf16x8_kernel<8>, dim3(T), dim3(kThreads), 0, st, (const uint4*)y_perm, pair_row,
-                           topk_w, k, H / 8, (uint4*)out);
-    else if (dtype == METRO_DTYPE_BF16 && H % 8 == 0 && aligned)
-        hipLaunchKernelGGL(unpermute_bf16x8_kernel<0>, dim3(T), dim3(kThreads), 0, st, (const uint4*)y_perm, pair_row,
-                           topk_w, k, H / 8, (uint4*)out);
-    else if (dtype == METRO_DTYPE_BF16)
+    const bool bf16 = dtype == METRO_DTYPE_BF16;
+    const int per = bf16 ? 8 : 4;                 // columns of a 16-byte vector
+    auto vec = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(T), dim3(kThreads), 0, st, (const uint4*)y_perm, pair_row, topk_w, k, H / per,
+                           (uint4*)out);
+    };
+    if (H % per == 0 && aligned) {
+        if (bf16 && k <= 8) vec(unpermute_vec_kernel<true, 8>);
+        else if (bf16) vec(unpermute_vec_kernel<true, 0>);
+        else if (k <= 8) vec(unpermute_vec_kernel<false, 8>);
+        else vec(unpermute_vec_kernel<false, 0>);
+    } else if (bf16) {
         hipLaunchKernelGGL(unpermute_scalar_kernel<true>, dim3(T), dim3(kThreads), 0, st, y_perm, pair_row, topk_w,
                            k, H, out);
-    else
+    } else {
         hipLaunchKernelGGL(unpermute_scalar_kernel<false>, dim3(T), dim3(kThreads), 0, st, y_perm, pair_row, topk_w,
                            k, H, out);
+    }
     return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP;
 }
 

@@ -71,3 +71,27 @@ def test_general_path_edges(oracle, dtype, H, I):
 def test_matrix_path_edges(oracle, H, I):
     check(oracle, "bf16", H, I, [1, 15, 16, 17, 31, 32, 33, 0, 47, 48, 49, 63, 64, 65, 96, 97, 128, 129, 200], T=700,
           extra=128)
+
+
+# combine: vectors of 8 bf16 or 4 fp32 columns, k in registers (<= 8) or not, rows that are no whole vectors, pairs of other
+# ranks.  Sums of k products in fp32 in the oracle's order: fp32 within k * 2^-24 of the sum of magnitudes, bf16 one rounding.
+@pytest.mark.parametrize("dtype,tol", [("f32", 2e-6), ("bf16", 8e-3)])
+@pytest.mark.parametrize("H,k", [(1, 1), (4, 3), (6, 8), (8, 8), (12, 9), (1028, 8), (2048, 12)])
+def test_unpermute_edges(oracle, dtype, tol, H, k):
+    from paper_2512_09277_amd import api
+
+    api.load()
+    T = 37
+    rng = np.random.default_rng(H + k)
+    row = np.full(T * k, -1, np.int32)
+    here = np.flatnonzero(rng.random(T * k) < 0.4)
+    row[here] = rng.permutation(here.size)
+    y = W.activations(max(here.size, 1), H, 3, dtype)
+    tw = W.gating_weights(T, k, 4)
+    full = np.zeros((T * k, H), y.dtype)
+    full[:y.shape[0]] = y
+    out = api.moe_unpermute(dev(full), dev(row.reshape(T, k)), dev(tw))
+    as_f64 = W.bf16_bits_to_f32(full).astype(np.float64) if dtype == "bf16" else full.astype(np.float64)
+    want = oracle.unpermute(as_f64, row.reshape(T, k), tw)
+    got = out.float().cpu().numpy().astype(np.float64)
+    assert np.abs(got - want).max() <= tol * max(np.abs(want).max(), 1e-30)
