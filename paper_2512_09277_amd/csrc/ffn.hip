@@ -3,13 +3,11 @@
 // Decode is HBM-bound: runtime follows the bytes of the activated experts' weights (Sec. 3.2 of
 // arxiv 2512.09277).  Every activated weight row is streamed from HBM once per tile, with 128-bit loads that
 // land directly in the matrix-core operand layout (16 rows x 64 contiguous bytes per instruction).
-// Work is cut into tiles of one slot's rows (at most 128; 64 on the smallest shapes):
-//   narrow tiles (<= 64 rows, 32 at large shapes; the bulk of the bytes): ffn_split.h -- K split over the four waves, 64 weight rows per
-//       workgroup, activations straight into registers, no barrier in the K loop;
-//   tall tiles (up to 128 rows, the popular experts), activations staged through LDS: wide ones (large shapes) with 4 x 16
-//       weight rows per wave and K steps of 64, so that each activation fragment read from LDS feeds four MFMAs;
-//       stream ones (mid shapes) with 2 x 16 weight rows per wave.  They are listed first so that they spread over
-//       the chip early.
+// Work is cut into tiles of one slot's rows:
+//   narrow tiles (at most 32 rows, 64 where the launch is short; the bulk of the bytes): ffn_split.h -- K split over the
+//       four waves, 64 weight rows per workgroup, activations straight into registers, no barrier in the K loop;
+//   tall tiles (up to 128 rows, the popular experts and large batches): dense_k.h -- both operands through LDS, 128 weight
+//       rows per workgroup.  They are listed first.
 //   gate/up: a wave owns gate rows and the matching up rows, so silu(gate)*up is formed in
 //            registers and written once as bf16;   down: same structure over K = I.
 // A slot with no rows produces no tile and its weights are never touched.  There is no planning pass:
@@ -21,6 +19,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "dense_k.h"
 #include "ffn_common.h"
 #include "ffn_split.h"
 #include "host_utils.h"
@@ -30,7 +29,6 @@ namespace metro {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kWideRows = 128;              // rows of a full wide tile
 
 // ------------------------------------------------------------------------------------------ MFMA path
 struct FfnArgs {
@@ -41,191 +39,69 @@ struct FfnArgs {
     const int32_t* group_offsets;
     int T, k, spr, H, I;
     int ldw;                  // elements between consecutive weight rows (>= K)
-    int tile_rows;            // rows of a full tile (<= 128)
-    int single_rows;          // > 0: slots of at most tile_rows rows are cut into tiles of this many rows
-    int stream_rows;          // tiles with more rows are wide
-    int ntw, nts;             // column tiles per wide / stream tile
-    int narrow_rows;          // tiles of at most this many rows are narrow (<= 64)
+    int ntt;                  // column tiles per tall tile
     int ntn;                  // column tiles per narrow tile
 };
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }
 
-// D[i][j] of block b, sub-tile mt: i = output column 4*q + v of the block, j = tile row r16.
-template <bool kGateUp, int NB, int MT>
-__device__ __forceinline__ void store_tile(const FfnArgs& a, const Tile& t, const floatx4 (&acc)[NB][MT], int col0,
-                                           int n_out, int mt_count, int r16, int q) {
-    const int H = a.H, I = a.I;
+constexpr int kLdsSplit = 4 * 4 * (kCutRows / 16) * 64 * (int)sizeof(floatx4);         // partial sums of four waves
+constexpr int kLdsBytes = std::max(kDenseLds, kLdsSplit);
+
+// Tall tile: 32 MT rows x 64 gate/up columns or 128 down columns, both operands through LDS (dense_k.h).  Bound by what the
+// L2s deliver (a 128 x 128 tile reads 32 KB per 2 MFLOP) at large batches and by latency times resident workgroups
+// elsewhere.  It replaced tiles whose weights went straight to registers, every wave reading all activations from
+// LDS: one K step in flight behind 128 accumulator registers, or 64 weight rows per workgroup.  Measured, gate/up + down,
+// us: 4096 tokens at 2048 x 768 111 + 63 -> 54 + 35; 512 tokens at 4096 x 1536 102 + 57 -> 92 + 49; 1024 tokens at
+// 7168 x 2048 (METRO rank) 381 + 200 -> 373 + 195.  Remainders of 33..64 rows are tall too (as narrow tiles 391 + 200 in
+// the last case, 97 + 51 in the one before).  Contiguous runs of items per XCD, so that its L2 sees fewer slots:
+// 395 + 203 in the last case, no gain in the others.
+template <bool kGateUp, int MT>
+__device__ __forceinline__ void dense_tile(const FfnArgs& a, const Tile t, char* lds) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, q = lane >> 4, srow = tid >> 3;
+    const int K = kGateUp ? a.H : a.I, n_out = kGateUp ? a.I : a.H;
+    const int col0 = t.col * (kGateUp ? 64 : 128);
+    uint32_t x_lane[MT];                    // every activation byte offset fits 32 bits on this path
+    const char* wb[4];
+    const __bf16* wslot = a.w + (size_t)t.slot * (kGateUp ? 2 * a.I : a.H) * a.ldw;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const int row = kGateUp ? (p >> 1) * a.I + col0 + (p & 1) * 32 : col0 + p * 32;
+        wb[p] = reinterpret_cast<const char*>(wslot + (size_t)row * a.ldw);
+    }
+#pragma unroll
+    for (int p = 0; p < MT; ++p) {
+        const int row = t.row0 + min(p * 32 + srow, t.rows - 1);          // rows past the tile repeat its last row
+        const int src = kGateUp ? min(max(a.perm_pair[row] / a.k, 0), a.T - 1) : row;
+        x_lane[p] = (uint32_t)src * (uint32_t)(K * 2) + (tid & 7) * 16;
+    }
+    const int ty = wv >> 1, tx = wv & 1;
+    int wave_w[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) wave_w[b] = kGateUp ? (b >> 1) * 64 + tx * 32 + (b & 1) * 16 : tx * 64 + b * 16;
+    floatx4 acc[4][MT];
+    dense_dot<MT>(reinterpret_cast<const char*>(a.src), x_lane, wb, (size_t)srow * a.ldw * 2 + (tid & 7) * 16, ty * 16 * MT, wave_w, 0, K / kDenseBK, lds, acc);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-        const int row = mt * 16 + r16;
-        if (mt < mt_count && row < t.rows) {
-            if (kGateUp) {
+        const int row = (ty * MT + mt) * 16 + r16;
+        if (row >= t.rows) continue;
+        __bf16* out = a.dst + (size_t)(t.row0 + row) * n_out + q * 4;
+        if (kGateUp) {
 #pragma unroll
-                for (int b = 0; b < NB / 2; ++b) {
-                    const int col = col0 + b * 16;
-                    if (col < n_out) {
-                        const floatx4 g = acc[b][mt], u = acc[b + NB / 2][mt];
-                        u32x2 o;
-                        o.x = pack_bf16x2(silu(g[0]) * u[0], silu(g[1]) * u[1]);
-                        o.y = pack_bf16x2(silu(g[2]) * u[2], silu(g[3]) * u[3]);
-                        *reinterpret_cast<u32x2*>(a.dst + (size_t)(t.row0 + row) * I + col + q * 4) = o;
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    const int col = col0 + b * 16;
-                    if (col < n_out) {
-                        u32x2 o;
-                        o.x = pack_bf16x2(acc[b][mt][0], acc[b][mt][1]);
-                        o.y = pack_bf16x2(acc[b][mt][2], acc[b][mt][3]);
-                        *reinterpret_cast<u32x2*>(a.dst + (size_t)(t.row0 + row) * H + col + q * 4) = o;
-                    }
-                }
+            for (int b = 0; b < 2; ++b) {
+                const floatx4 g = acc[b][mt], u = acc[b + 2][mt];
+                *reinterpret_cast<u32x2*>(out + col0 + tx * 32 + b * 16) =
+                    u32x2{pack_bf16x2(silu(g[0]) * u[0], silu(g[1]) * u[1]), pack_bf16x2(silu(g[2]) * u[2], silu(g[3]) * u[3])};
             }
+        } else {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                *reinterpret_cast<u32x2*>(out + col0 + tx * 64 + b * 16) =
+                    u32x2{pack_bf16x2(acc[b][mt][0], acc[b][mt][1]), pack_bf16x2(acc[b][mt][2], acc[b][mt][3])};
         }
     }
 }
-
-// One tile x one column tile.
-//   NB    16-row weight blocks per wave (gate/up: NB/2 gate blocks + the matching up blocks)
-//   MT    16-row activation sub-tiles (tile rows <= 16*MT)
-//   BK    K elements per step;  DEPTH  steps the loads run ahead
-// Lane (r16, q) of a wave supplies, for MFMA j of a step, the 8 elements k = j*32 + q*8 .. +8 of
-// weight row r16 (A operand) and of tile row r16 (B operand): one load instruction reads 64
-// contiguous bytes of each of 16 rows.  D[i][j]: i = weight row 4*q + v, j = tile row r16.
-template <bool kGateUp, int NB, int MT, int BK, int DEPTH>
-__device__ __forceinline__ void ffn_tile(const FfnArgs& a, const Tile t, const int nt, char* lds) {
-    constexpr int NJ = BK / 32;                 // MFMAs per block per step
-    constexpr int NW = DEPTH + 1;               // weight register buffers
-    constexpr int kLdsRow = BK * 2 + 16;        // bytes per staged row (+16 spreads the banks)
-    constexpr int kChunks = BK * 2 / 16;        // 16-byte chunks per staged row
-    constexpr int kRowsPerPass = kThreads / kChunks;
-    constexpr int NP = (MT * 16 + kRowsPerPass - 1) / kRowsPerPass;   // staging loads per thread
-    constexpr int kPeriod = (DEPTH == 1) ? 2 : (DEPTH == 2) ? 6 : 12; // lcm(NW, DEPTH, 2)
-    static_assert(DEPTH >= 1 && DEPTH <= 3, "prefetch distance");
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);        // wave index, kept in a scalar register
-    const int r16 = lane & 15, q = lane >> 4;
-    const int H = a.H, I = a.I;
-    const int K = kGateUp ? H : I;
-    const int n_steps = K / BK;
-    const int mt_count = (t.rows + 15) >> 4;
-    const int n_out = kGateUp ? I : H;          // output columns of this stage
-    const int cols_per_wave = kGateUp ? NB * 8 : NB * 16;
-    const int col0 = nt * 4 * cols_per_wave + wv * cols_per_wave;     // first output column of the wave
-
-    // Addresses are a uniform base (scalar registers) plus a 32-bit per-lane offset, which keeps the
-    // vector registers for data in flight.  Weight row of block b: gate/up pairs block b (gate) with
-    // block b + NB/2 (up).
-    const char* wslot = reinterpret_cast<const char*>(a.w) + (size_t)t.slot * (kGateUp ? 2 * I : H) * a.ldw * 2;
-    const uint32_t w_lane = (uint32_t)(r16 * a.ldw + q * 8) * 2u;
-    const char* pw[NB];                                               // uniform: first row of block b
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        int col = kGateUp ? col0 + (b % (NB / 2)) * 16 : col0 + b * 16;
-        col = col < n_out ? col : n_out - 16;   // a block past the last column repeats the last block
-        const int row = (kGateUp && b >= NB / 2) ? I + col : col;
-        pw[b] = wslot + (size_t)row * a.ldw * 2;
-    }
-
-    // activation staging: thread (frow, fchunk) copies 16 bytes of rows frow, frow + kRowsPerPass, ...
-    // (the host only takes this path while every activation byte offset fits 32 bits)
-    const int frow = tid / kChunks, fchunk = tid % kChunks;
-    const char* xbase = reinterpret_cast<const char*>(a.src);
-    uint32_t x_lane[NP];
-#pragma unroll
-    for (int pz = 0; pz < NP; ++pz) {
-        int row = pz * kRowsPerPass + frow;
-        row = row < t.rows ? row : t.rows - 1;  // rows past the tile repeat its last row
-        const uint32_t src_row = kGateUp ? (uint32_t)min(max(a.perm_pair[t.row0 + row] / a.k, 0), a.T - 1)
-                                         : (uint32_t)(t.row0 + row);
-        x_lane[pz] = src_row * (uint32_t)(K * 2) + fchunk * 16;
-    }
-    const int wr_off = frow * kLdsRow + fchunk * 16;
-    const int rd_off = r16 * kLdsRow + q * 16;
-    constexpr int kLdsBuf = NP * kRowsPerPass * kLdsRow;   // staged rows past 16*MT are never read
-
-    floatx4 acc[NB][MT];
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[b][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-    u32x4 w[NW][NB * NJ];
-    u32x4 xr[DEPTH][NP];
-
-    auto load_w = [&](int buf, int step) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                w[buf][b * NJ + j] = *reinterpret_cast<const u32x4*>(pw[b] + (size_t)step * (BK * 2) + w_lane + j * 64);
-    };
-    auto load_x = [&](int set, int step) {
-#pragma unroll
-        for (int pz = 0; pz < NP; ++pz)
-            xr[set][pz] = *reinterpret_cast<const u32x4*>(xbase + (size_t)step * (BK * 2) + x_lane[pz]);
-    };
-    auto park_x = [&](int set, int buf) {
-#pragma unroll
-        for (int pz = 0; pz < NP; ++pz)
-            *reinterpret_cast<u32x4*>(lds + buf * kLdsBuf + wr_off + pz * kRowsPerPass * kLdsRow) = xr[set][pz];
-    };
-
-    // Every load below is unconditional (past the last step the index is clamped, which re-reads
-    // the last step): the compiler can then count outstanding loads exactly and waits only for
-    // the ones a step consumes, instead of draining the queue at every branch join.
-    const int last = n_steps - 1;
-    // (the weight addresses need only the tile, the activation addresses also need perm_pair: the
-    // weight loads go out first so that they overlap that extra round trip)
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) load_w(d, min(d, last));
-    load_x(0, 0);
-#pragma unroll
-    for (int d = 1; d < DEPTH; ++d) load_x(d % DEPTH, min(d, last));
-    park_x(0, 0);
-    __syncthreads();
-
-    // One K step with compile-time buffer indices u (= step s mod kPeriod).
-    auto do_step = [&](auto U, const int s) {
-        constexpr int u = decltype(U)::value;
-        // Loads retire in issue order: the activations go first so that waiting for them (to park
-        // them one step later) never waits for the younger weight loads.
-        const int ps = min(s + DEPTH, last);                          // past the end: re-read the last step
-        load_x(u % DEPTH, ps);
-        load_w((u + DEPTH) % NW, ps);
-        const char* cur = lds + (u % 2) * kLdsBuf + rd_off;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            if (mt < mt_count) {
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    const bf16x8 xb = *reinterpret_cast<const bf16x8*>(cur + mt * 16 * kLdsRow + j * 64);
-#pragma unroll
-                    for (int b = 0; b < NB; ++b)
-                        acc[b][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            __builtin_bit_cast(bf16x8, w[u % NW][b * NJ + j]), xb, acc[b][mt], 0, 0, 0);
-                }
-            }
-        }
-        // activations of the next step were loaded DEPTH-1 steps ago (set (u+1) % DEPTH)
-        park_x((u + 1) % DEPTH, (u + 1) % 2);
-        __syncthreads();
-    };
-
-    int s0 = 0;
-    for (; s0 + kPeriod <= n_steps; s0 += kPeriod) run_steps(std::make_integer_sequence<int, kPeriod>{}, do_step, s0);
-    run_steps_tail(std::make_integer_sequence<int, kPeriod - 1>{}, do_step, s0, n_steps);
-    store_tile<kGateUp, NB, MT>(a, t, acc, col0, n_out, mt_count, r16, q);
-}
-
-constexpr int kLdsSplit = 4 * 4 * (kNarrowMost / 16) * 64 * (int)sizeof(floatx4);      // partial sums of four waves
-constexpr int kLdsStream = 2 * 64 * (128 * 2 + 16);
-constexpr int kLdsWide = 2 * 128 * (64 * 2 + 16);
-constexpr int kLdsBytes = std::max(kLdsSplit, std::max(kLdsWide, kLdsStream));
 
 // Narrow tiles.  Measured against tiles staged through LDS with a barrier per K step (gate/up + down, us): 8 tokens of the
 // 2048 x 768 shape 21 + 10 -> 13 + 6.5 (twice the workgroups for the same bytes, nobody waits for a sibling wave's loads);
@@ -244,46 +120,38 @@ constexpr int kNarrowGrid = 1536;
 template <bool kGateUp>
 __global__ __launch_bounds__(kThreads, 2) void ffn_mfma_kernel(FfnArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    // Work items = (tile, column tile), wide items first: a wide workgroup lives several times longer
-    // than a stream one, so it has to start early for the other items to fill in around it.
-    // (Measured alternatives that lost: spreading the wide items through the launch order,
-    // alternating wide and stream items, and per-XCD work queues.)  Everything here is uniform per
-    // workgroup.
+    // Work items = (tile, column tile), tall tiles first: their workgroups live longest, so they start early for the
+    // narrow ones to fill in around them.  Everything here is uniform per workgroup.
     WorkList wl;
-    wl.read(a.group_offsets, a.spr, a.T * a.k, a.tile_rows, a.single_rows, a.stream_rows, a.narrow_rows);
-    const int wide_items = wl.n_wide * a.ntw, tall_items = wide_items + (wl.n_tall - wl.n_wide) * a.nts;
-    if ((int)blockIdx.x >= tall_items) {
-        const SplitArgs sa{a.src, a.perm_pair, a.w, a.dst, a.T, a.k, a.H, a.I, a.ldw};
-        const int n = (wl.n_tiles - wl.n_tall) * a.ntn, stride = gridDim.x - tall_items;
-        for (int id = blockIdx.x - tall_items; id < n; id += stride) {
-            const int ti = id / a.ntn;
-            const Tile t = wl.tile(wl.n_tall + ti, id - ti * a.ntn);
-            if (t.rows <= 16) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 1, 4, KRows::kWhole>(sa, t, lds);
-            else if (t.rows <= 32) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 2, 3, KRows::kWhole>(sa, t, lds);
-            else if (t.rows <= 48) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 3, 2, KRows::kWhole>(sa, t, lds);
-            else split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 4, 2, KRows::kWhole>(sa, t, lds);
-            __syncthreads();                                             // the next item's sums reuse the LDS
-        }
+    wl.read(a.group_offsets, a.spr, a.T * a.k, a.ntn);
+    const int tall_items = wl.n_tall * a.ntt;
+    int id = blockIdx.x;
+    if (id < tall_items) {
+        const int ti = id / a.ntt;
+        const Tile t = wl.tile(ti, id - ti * a.ntt);
+        if (t.rows <= 64) dense_tile<kGateUp, 2>(a, t, lds);
+        else if (t.rows <= 96) dense_tile<kGateUp, 3>(a, t, lds);
+        else dense_tile<kGateUp, 4>(a, t, lds);
         return;
     }
-    const int id = blockIdx.x;
-    const bool wide = id < wide_items;
-    const int nt = wide ? a.ntw : a.nts, r = wide ? id : id - wide_items, tl = r / nt;
-    const Tile t = wl.tile(wide ? tl : wl.n_wide + tl, r - tl * nt);
-    // partial wide tiles stage only the rows they have; with half the accumulators the 64-row variant
-    // also affords a second K step of weights in flight (token-balanced rank: gate/up 401 -> 390 us)
-    if (wide && t.rows <= 64) ffn_tile<kGateUp, 4, 4, 64, 2>(a, t, t.col, lds);
-    else if (wide && t.rows <= 96) ffn_tile<kGateUp, 4, 6, 64, 1>(a, t, t.col, lds);
-    else if (wide) ffn_tile<kGateUp, 4, 8, 64, 1>(a, t, t.col, lds);
-    else if (t.rows <= 64) ffn_tile<kGateUp, 2, 4, 128, 2>(a, t, t.col, lds);
-    else ffn_tile<kGateUp, 2, 8, 64, 3>(a, t, t.col, lds);
+    const SplitArgs sa{a.src, a.perm_pair, a.w, a.dst, a.T, a.k, a.H, a.I, a.ldw};
+    const int n = (wl.n_tiles - wl.n_tall) * a.ntn, stride = gridDim.x - tall_items;
+    for (id -= tall_items; id < n; id += stride) {
+        const int ti = id / a.ntn;
+        const Tile t = wl.tile(wl.n_tall + ti, id - ti * a.ntn);
+        if (t.rows <= 16) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 1, 4, KRows::kWhole>(sa, t, lds);
+        else if (t.rows <= 32) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 2, 3, KRows::kWhole>(sa, t, lds);
+        else if (t.rows <= 48) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 3, 2, KRows::kWhole>(sa, t, lds);
+        else split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 4, 2, KRows::kWhole>(sa, t, lds);
+        __syncthreads();                                                 // the next item's sums reuse the LDS
+    }
 }
 
-// Tall workgroups for the most tall tiles `cap` rows can make, and the narrow ones.
+// Workgroups: one per item of the most tall tiles `cap` rows can make, and the narrow ones.
 inline int mfma_grid(const FfnArgs& a, int cap, int spr) {
-    const int tall = a.tile_rows > a.narrow_rows ? std::min(cap / a.narrow_rows, max_tiles(cap, spr, a.tile_rows, a.single_rows > 0)) : 0;
-    const int narrow = std::min(a.ntn * (std::min(spr, cap) + cap / a.narrow_rows), kNarrowGrid);
-    return tall * std::max(a.ntw, a.nts) + narrow;
+    const int tall = std::min(cap / (kNarrowRows + 1), max_tiles(cap, spr, kTallRows));
+    const int narrow = std::min(a.ntn * (std::min(spr, cap) + cap / kNarrowRows), kNarrowGrid);
+    return tall * a.ntt + narrow;
 }
 
 // ------------------------------------------------------------------------------------------ general path
@@ -322,7 +190,7 @@ template <bool kGateUp>
 int launch_general(const SplitArgs& a, const int32_t* group_offsets, int spr, int dtype, hipStream_t st) {
     const int n_out = kGateUp ? a.I : a.H, K = kGateUp ? a.H : a.I;
     const int cols = kGateUp ? kGenGateUpCols : kGenDownCols, n_cols = (n_out + cols - 1) / cols;
-    const int64_t n_items = (int64_t)max_tiles(a.T * a.k, spr, kGenRows, false) * n_cols;
+    const int64_t n_items = (int64_t)max_tiles(a.T * a.k, spr, kGenRows) * n_cols;
     const uint32_t grid = (uint32_t)(n_items < kGenGrid ? n_items : kGenGrid);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, st, a, group_offsets, spr, n_cols, n_items);
@@ -377,27 +245,6 @@ int enable_large_lds() {                            // opt in to > 64 KB of dyna
         return e;
     });
 }
-
-// Tall remainders of at most this many rows become stream tiles.  A wide workgroup prefetches one step
-// ahead, so its K loop runs at about one memory latency per step: at large shapes that hides behind
-// the narrow items, at mid ones (short launches, HBM not saturated) it is the critical path, and they keep tall tiles on
-// the deep-prefetch stream path, whose narrower column tile costs more activation re-reads.
-inline bool large_shape(int H, int I) { return (size_t)H * I >= (size_t)4096 * 2048; }
-inline int stream_rows_for(int H, int I) { return large_shape(H, I) ? 32 : kWideRows; }
-
-// Tiles above this many rows stage their activations through LDS.  A narrow tile reads each activation once per 64 weight
-// rows, which at 33..64 rows is as much L2 traffic as the weights themselves: large shapes, at the fabric's rate
-// already, lose by it (7168 x 2048, 1024 tokens, METRO rank: 399 + 205 us with 64, 383 + 201 with 32); shorter launches
-// gain from the smaller work items (4096 x 1536: 103 + 57 with 64, 107 + 57 with 32; 2048 x 768 has only these tiles).
-inline int narrow_rows_for(int H, int I) { return large_shape(H, I) ? 32 : kNarrowMost; }
-
-// Rows of a full tile.  128 amortises a slot's weights over the most rows (one HBM pass per 128 rows; all
-// tiles narrow at 4096 x 1536: 116 + 59 instead of 103 + 57 us).
-// The smallest FFNs finish in a few tens of microseconds and are bound by their longest workgroup, not
-// by bytes: a 128-row tile spends longer in its matrix instructions than the whole launch should take,
-// while re-reading a small slot's weights from L2 is cheap, so they cut groups into narrow tiles (2048 x 768: 256 tokens
-// 30 + 16 us with 64 rows, 35 + 16 with 32; 4096 tokens 110 + 63 with 64, 159 + 83 with 32).
-inline int tile_rows_for(int H, int I) { return (size_t)H * I < (size_t)2048 * 1024 ? kNarrowMost : kWideRows; }
 
 inline int launched() { return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP; }
 
@@ -458,15 +305,7 @@ extern "C" int moe_grouped_ffn_gate_up(const void* x, const int32_t* perm_pair, 
     a.dst = (__bf16*)act;
     a.group_offsets = group_offsets;
     a.T = T; a.k = k; a.spr = spr; a.H = H; a.I = I;
-    a.stream_rows = stream_rows_for(H, I);
-    a.tile_rows = tile_rows_for(H, I);
-    a.narrow_rows = narrow_rows_for(H, I);
-    // mid shapes (every tile on the stream path, 128-row tiles): a one-tile slot of 65..128 rows is the
-    // longest workgroup of a launch that has fewer workgroups than the chip has slots; two 64-row tiles
-    // balance it (token-balanced rank of the 4096 x 1536 shape: gate/up 109 -> 101 us; no gain for down)
-    a.single_rows = (a.stream_rows >= kWideRows && a.tile_rows == kWideRows) ? 64 : 0;
-    a.ntw = I / 128;
-    a.nts = I / 64;
+    a.ntt = I / 64;
     a.ntn = I / (kNarrowBlocks * 8);
     hipLaunchKernelGGL(ffn_mfma_kernel<true>, dim3(mfma_grid(a, cap, spr)), dim3(kThreads), kLdsBytes, st, a);
     return launched();
@@ -497,17 +336,7 @@ extern "C" int moe_grouped_ffn_down(const int32_t* group_offsets, int T, int k, 
     a.dst = (__bf16*)y_perm;
     a.group_offsets = group_offsets;
     a.T = T; a.k = k; a.spr = spr; a.H = H; a.I = I;
-    a.stream_rows = stream_rows_for(H, I);
-    a.tile_rows = tile_rows_for(H, I);
-    a.narrow_rows = narrow_rows_for(H, I);
-    a.single_rows = 0;
-    // mid shapes: the full 128-row tiles of a several-tile slot take the wide path in this stage (half
-    // the column tiles, each activation fragment feeding four matrix instructions); smaller tiles stay
-    // on the stream path (METRO rank of the 4096 x 1536 shape: down 71 -> 60 us; a 113-row one-tile
-    // slot on the wide path costs the token-balanced rank 8 us, hence "full tiles only")
-    if (a.stream_rows >= kWideRows && a.tile_rows == kWideRows) a.stream_rows = kWideRows - 1;
-    a.ntw = (H + 255) / 256;
-    a.nts = H / 128;
+    a.ntt = H / 128;
     a.ntn = H / (kNarrowBlocks * 16);
     hipLaunchKernelGGL(ffn_mfma_kernel<false>, dim3(mfma_grid(a, cap, spr)), dim3(kThreads), kLdsBytes, st, a);
     return launched();

@@ -11,33 +11,39 @@ namespace {
 
 constexpr int kMaxSpr = 64;
 
-constexpr int kNarrowMost = 64;             // rows of a narrow tile at most
+constexpr int kTallRows = 128;              // rows of a full tall tile
+constexpr int kNarrowRows = 32;             // tiles of at most this many rows are narrow,
+constexpr int kCutRows = 64;                // or of this many where a launch is cut into narrow tiles only
 
 struct Tile {
     int slot, row0, rows, col;              // rows [row0, row0 + rows) of a slot x column tile `col`
 };
 
-// Upper bound of the tile count: cap / tile_rows full tiles, and per slot one remainder -- or two tiles where one-tile
-// slots are cut finer (each at least half a tile).
-inline int max_tiles(int cap, int spr, int tile_rows, bool finer_singles) {
-    return (finer_singles ? 2 : 1) * spr + cap / tile_rows;
-}
+// Upper bound of the tile count: cap / tile_rows full tiles, and per slot one remainder.
+inline int max_tiles(int cap, int spr, int tile_rows) { return spr + cap / tile_rows; }
 
 // ------------------------------------------------------------------------------------------ work items
-// A slot of m rows gives m / tile_rows full tiles and one tile for the remainder; a remainder is tall if it has more
-// than `narrow_rows` rows, wide if it has more than `stream_rows` (>= narrow_rows).  Tile order: full tiles, then the
-// remainders, larger classes of rows first (ties: lower slot first); so wide tiles come first, then the other tall
-// ones, then the narrow ones.  Work item = (tile, column tile), tile-major.
+// A slot of m rows gives m / th full tiles of th rows and one tile for the remainder.  Launches of few work items cut all
+// slots into narrow tiles (th = 64); the others cut 128-row tiles, of which the full ones and the remainders above 32 rows
+// are tall.  Tile order: full tiles, then the remainders, larger classes of rows first (ties: lower slot first), so tall
+// ones come first.  Work item = (tile, column tile), tile-major.
 // Every workgroup derives its own items from group_offsets (65 integers, one memory round trip, some
 // hundred scalar-ish instructions): no planning kernel, no list in memory.  Each wave computes the
 // same result with lane = local slot.
+
+// A narrow launch is bound by the latency of one workgroup, a dense tile's K loop with a barrier per 64 k is longer (256
+// tokens at 2048 x 768, 480 narrow items: 30 + 16 us, with dense tiles 35 + 16); from about one and a half rounds of
+// the 512 resident workgroups on, the dense tile's reuse wins (512 tokens at 4096 x 1536, about 1000 narrow items: gate/up
+// 112 us against 92; 4096 tokens at 2048 x 768, 1700 items: 111 + 63 us against 54 + 35).
+constexpr int kFewItems = 768;
+
 // The slots' tiles in the registers of a wave (lane = local slot), from which any item can be picked.
 struct WorkList {
-    int begin, th, full, part, incl, rank;      // per lane
-    int n_full, n_wide, n_tall, n_tiles;        // uniform
+    int begin, full, part, incl, rank;          // per lane
+    int th, n_full, n_tall, n_tiles;            // uniform
 
-    __device__ __forceinline__ void read(const int32_t* __restrict__ group_offsets, int spr, int cap, int tile_rows,
-                                         int single_rows, int stream_rows, int narrow_rows) {
+    // narrow_cols: column tiles of a narrow tile
+    __device__ __forceinline__ void read(const int32_t* __restrict__ group_offsets, int spr, int cap, int narrow_cols) {
         const int l = lane_id();
         int m = 0;
         begin = 0;
@@ -45,28 +51,26 @@ struct WorkList {
             begin = min(max(group_offsets[l], 0), cap);
             m = min(max(group_offsets[l + 1], begin), cap) - begin;
         }
-        // one-tile slots may be cut finer than the slots that re-read their weights once per tile
-        th = (single_rows > 0 && m <= tile_rows) ? single_rows : tile_rows;
+        const int cut = __builtin_amdgcn_readlane(wave_inclusive_sum((m + kCutRows - 1) / kCutRows), kWave - 1);
+        const bool narrow_only = cut <= kFewItems / narrow_cols;
+        th = narrow_only ? kCutRows : kTallRows;
         full = m / th;
-        part = m % th;
+        part = m - full * th;
         incl = wave_inclusive_sum(full);
         n_full = __builtin_amdgcn_readlane(incl, kWave - 1);
         // remainders: in classes of rows, larger ones first, inside a class by slot
         const uint64_t below = lanes_below();
         rank = 0;
         uint64_t larger = 0;
-        constexpr int kEdges[] = {96, 64, 32, 16, 0};
+        constexpr int kEdges[] = {96, 64, kNarrowRows, 16, 0};
 #pragma unroll
         for (int c = 0; c < 5; ++c) {
             const uint64_t in = __ballot(part > kEdges[c]) & ~larger;
             if (part > kEdges[c] && !((larger >> l) & 1)) rank = __popcll(larger) + __popcll(in & below);
             larger |= in;
         }
-        // stream_rows >= tile_rows: no wide class at all, full tiles take the stream path too
-        n_wide = stream_rows >= tile_rows ? 0 : n_full + __popcll(__ballot(part > stream_rows));
-        // full tiles run as tall ones unless no tile is tall (those of slots cut finer too, to keep the order simple)
-        n_tall = (tile_rows > narrow_rows ? n_full : 0) + __popcll(__ballot(part > narrow_rows));
-        n_tiles = n_full + __popcll(__ballot(part > 0));
+        n_tall = narrow_only ? 0 : n_full + __popcll(__ballot(part > kNarrowRows));
+        n_tiles = n_full + __popcll(larger);
     }
 
     __device__ __forceinline__ Tile tile(int ti, int col) const {
@@ -75,10 +79,9 @@ struct WorkList {
         if (ti < n_full) {
             const uint64_t owner = __ballot(incl - full <= ti && ti < incl);      // exactly one lane
             const int o = __ffsll((unsigned long long)owner) - 1;
-            const int first = __builtin_amdgcn_readlane(incl - full, o);
             t.slot = o;
-            t.rows = __builtin_amdgcn_readlane(th, o);
-            t.row0 = __builtin_amdgcn_readlane(begin, o) + (ti - first) * t.rows;
+            t.rows = th;
+            t.row0 = __builtin_amdgcn_readlane(begin, o) + (ti - __builtin_amdgcn_readlane(incl - full, o)) * th;
         } else {
             const uint64_t owner = __ballot(part > 0 && n_full + rank == ti);     // exactly one lane
             const int o = __ffsll((unsigned long long)owner) - 1;
