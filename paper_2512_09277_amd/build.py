@@ -5,11 +5,13 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmetro.so")
+CALL = os.path.join(HERE, "_call.so")
 SOURCES = ["route.hip", "permute.hip", "ffn.hip", "unpermute.hip", "gate.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -19,8 +21,25 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared", "-fno
 RESOURCES: dict = {}        # kernel symbol -> {"VGPRs": .., "AGPRs": .., "Occupancy": .., "LDS": .., "Scratch": ..} of the last build
 
 
+def build_call(verbose: bool = False) -> str:
+    """Compile the native argument marshalling of api.py (host code only) against the installed torch."""
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    lib = os.path.join(root, "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-sign-compare",
+           "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           os.path.join(CSRC, "call.cpp"), "-o", CALL, "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    return CALL
+
+
 def build(verbose: bool = False, extra=()) -> str:
-    """Compile the library; fails if any kernel spills registers to scratch memory (a spill in a
+    """Compile the library and the binding's native part; fails if any kernel spills registers to scratch memory (a spill in a
     streaming loop costs more HBM traffic than the kernel is allowed to waste)."""
     cmd = ["hipcc", *FLAGS, "-Rpass-analysis=kernel-resource-usage", *extra, "-I", os.path.join(ROOT, "include"),
            "-I", CSRC, *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB]
@@ -53,6 +72,7 @@ def build(verbose: bool = False, extra=()) -> str:
                 print(f"  {name[:70]:70s} VGPRs {val}")
     if spilled:
         raise RuntimeError(f"kernels spill to scratch: {spilled}")
+    build_call(verbose)
     return LIB
 
 
