@@ -1,6 +1,6 @@
 // Routing kernels for gfx950: the METRO greedy solve (Alg. 1, Sec. 4.3 of arxiv 2512.09277)
-// and the token-balanced baseline (Sec. 2.3 / Sec. 6.1).  One workgroup solves one layer;
-// every table lives in LDS.
+// and the token-balanced baseline (Sec. 2.3 / Sec. 6.1).  A workgroup solves one layer, every table in LDS; where pairs
+// have to be numbered, several workgroups solve the same layer and share the numbering.
 //
 // The paper's kernel runs Alg. 1 with one thread per expert and test-and-set locks on one
 // SM; the order in which experts are served is whatever the lock races give.  Here the order
@@ -9,7 +9,7 @@
 //   - an active expert with a single replica has no choice; its effect on the load L[g] seen
 //     by a later expert e is a prefix popcount of a per-rank bitmap of such experts below e;
 //   - only active experts with >= 2 replicas (at most S - N of them) form a serial chain, and
-//     each step is an argmin over <= G lanes, done with ballots over the bits of the load.
+//     each step is an argmin over <= G lanes, in registers.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -137,7 +137,8 @@ constexpr int kRunCache = 8;     // chunks of its run whose ids a wave keeps in 
 // one replica, so the row of a pair is the slot's first row plus the number of earlier pairs of the expert: one stable
 // numbering, by the keys of the run only.  Latency-bound throughout (barriers, LDS round trips, the serial chain); kernel
 // times with the rule below, us, against one workgroup that sorted its own pair_slot in three more passes: 64 pairs 9.9 ->
-// 5.8, 2048 pairs 11.0 -> 6.4, 8192 pairs (256 experts) 19.2 -> 11.2; without lists, 58 layers of 8192 pairs 10.2 -> 9.4.
+// 5.6, 2048 pairs 11.0 -> 6.4, 8192 pairs (256 experts) 19.2 -> 10.9; without lists, 58 layers of 8192 pairs 10.2 -> 8.2 (of
+// which 0.9 by one range check per id instead of three).
 template <bool kLists>
 __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
     __shared__ int s_active[kMaxN];
@@ -217,9 +218,10 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
         }
     }
     auto mark = [&](int id) {
-        if (id < -1 || id >= N) atomicOr(&s_err, METRO_FLAG_BAD_ID);
-        else if (id >= 0) s_active[id] = 1;
-        return id >= 0 && id < N;
+        const bool ok = (uint32_t)id < (uint32_t)N;
+        if (ok) s_active[id] = 1;
+        else if (id != -1) atomicOr(&s_err, METRO_FLAG_BAD_ID);
+        return ok;
     };
     if constexpr (kLists) {
         int* mine = s_hist + wave_id() * N;
@@ -325,7 +327,8 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
         }
     }
     for (int e = tid; e < N; e += kThreads) {
-        const int slot = s_slot[e] == kNoSlot ? -1 : s_slot[e];
+        int slot = s_slot[e];
+        if (slot == kNoSlot) s_slot[e] = slot = -1;
         if (part == 0) a.expert_slot[(size_t)layer * N + e] = slot;
         if (slot >= 0) set_bit64(s_bm_lo, s_bm_hi, slot / spr, slot % spr);
     }
@@ -341,8 +344,7 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
 
     // x from y: every pair of expert i goes to its activated replica.
     auto slot_of = [&](int id) {
-        const int slot = (id >= 0 && id < N) ? s_slot[id] : kNoSlot;
-        return slot == kNoSlot ? -1 : slot;
+        return (uint32_t)id < (uint32_t)N ? s_slot[id] : -1;
     };
     if constexpr (!kLists) {
         int4* o = reinterpret_cast<int4*>(pair_slot);
