@@ -9,6 +9,7 @@ namespace metro {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kMaxThreads = 1024;
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
 __device__ __forceinline__ uint32_t f32_to_bf16_bits(float v) {
@@ -47,10 +48,12 @@ struct Columns {
 
 // Rows of whole 16-byte vectors: every thread owns one vector's columns (one 128-bit load per row).  KMAX > 0:
 // k <= KMAX, the token's rows and weights sit in registers and the row loads of a column go out
-// together; KMAX == 0: any k.  Bound by HBM (1024 tokens x 7168 in bf16: 45 MB in 12.6 us) and, in small batches, by
-// the two dependent loads; fp32 rows took one column per thread and 15 us at 256 tokens x 2048, now 4.8.
+// together; KMAX == 0: any k.  Bound by HBM (1024 tokens x 7168 in bf16: 45 MB in 10.1 us) and, in small batches, by
+// the two dependent loads; fp32 rows took one column per thread and 15 us at 256 tokens x 2048, now 4.8.  A workgroup
+// has a thread for every vector of the row (256 to 1024): with 256 threads a row of 896 vectors took four turns, one
+// memory round trip each, and the launch 12.6 us.
 template <bool kBf16, int KMAX>
-__global__ __launch_bounds__(kThreads) void unpermute_vec_kernel(const uint4* __restrict__ y,
+__global__ __launch_bounds__(kMaxThreads) void unpermute_vec_kernel(const uint4* __restrict__ y,
                                                                  const int32_t* __restrict__ pair_row,
                                                                  const float* __restrict__ topk_w, int k, int HV,
                                                                  uint4* __restrict__ out) {
@@ -66,7 +69,7 @@ __global__ __launch_bounds__(kThreads) void unpermute_vec_kernel(const uint4* __
             if (rows[j] >= cap) rows[j] = -1;
             ws[j] = j < k ? topk_w[(size_t)t * k + j] : 0.f;
         }
-        for (int c = threadIdx.x; c < HV; c += kThreads) {
+        for (int c = threadIdx.x; c < HV; c += blockDim.x) {
             uint4 v[KMAX > 0 ? KMAX : 1];
 #pragma unroll
             for (int j = 0; j < KMAX; ++j)
@@ -78,7 +81,7 @@ __global__ __launch_bounds__(kThreads) void unpermute_vec_kernel(const uint4* __
             out[(size_t)t * HV + c] = C::pack(acc);
         }
     } else {
-        for (int c = threadIdx.x; c < HV; c += kThreads) {
+        for (int c = threadIdx.x; c < HV; c += blockDim.x) {
             float acc[C::kN] = {};
             for (int j = 0; j < k; ++j) {
                 const int r = pair_row[(size_t)t * k + j];
@@ -127,7 +130,8 @@ extern "C" int moe_unpermute(const void* y_perm, const int32_t* pair_row, const 
     const bool bf16 = dtype == METRO_DTYPE_BF16;
     const int per = bf16 ? 8 : 4;                 // columns of a 16-byte vector
     auto vec = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(T), dim3(kThreads), 0, st, (const uint4*)y_perm, pair_row, topk_w, k, H / per,
+        const int hv = H / per, threads = hv <= kThreads ? kThreads : hv >= kMaxThreads ? kMaxThreads : (hv + 63) / 64 * 64;
+        hipLaunchKernelGGL(kernel, dim3(T), dim3(threads), 0, st, (const uint4*)y_perm, pair_row, topk_w, k, hv,
                            (uint4*)out);
     };
     if (H % per == 0 && aligned) {
