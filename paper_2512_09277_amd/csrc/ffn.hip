@@ -160,8 +160,8 @@ inline int mfma_grid(const FfnArgs& a, int cap, int spr) {
 // occupancy (fp32 matrix instructions take about a third of the time at 32 rows), so the tiles are small -- many
 // workgroups -- and registers are kept low enough for three workgroups per CU.  Measured on the 17-slot, 362-row
 // fp32 rank of the 2048 x 768 shape, gate/up + down: 94 + 42 us with 64 rows x 32/64 columns at two workgroups per CU,
-// 71 + 39 us with 32 rows x 16/32 columns, 73 + 35 us with three per CU (this one); on 2000 x 712 in bf16
-// 30 + 21 us against 33 + 28 us.  (The vector-ALU kernels these replaced: 328 + 119 and 440 + 137 us.)
+// 71 + 39 us with 32 rows x 16/32 columns, 73 + 36 us with three per CU and weight loads ahead of the token list's
+// (this one; 77 + 37 without the latter on the same box); on 2000 x 712 in bf16 30 + 22 us against 33 + 28 us.  (The vector-ALU kernels these replaced: 328 + 119 and 440 + 137 us.)
 constexpr int kGenRows = 32;
 constexpr int kGenBlocks = 2;               // 16-row weight blocks of a workgroup
 constexpr int kGenGateUpCols = kGenBlocks * 8, kGenDownCols = kGenBlocks * 16;

@@ -59,18 +59,23 @@ __device__ __forceinline__ void split_tile(const SplitArgs& a, const Tile t, cha
         pw[b] = wslot + (size_t)((kGateUp && b >= kUnits) ? a.I + col : col) * a.ldw;
     }
     const uint32_t w_lane = (uint32_t)(r16 * a.ldw + q * kVec);
-    const XT* px[MT];
-    uint32_t x_lane[MT];
+    int token[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         const int row = t.row0 + min(mt * 16 + r16, t.rows - 1);    // rows past the tile repeat its last row
-        const int src = kGateUp ? min(max(a.perm_pair[row] / a.k, 0), a.T - 1) : row;
-        px[mt] = reinterpret_cast<const XT*>(a.src) + (kWhole ? 0 : (size_t)src * K);
-        x_lane[mt] = (uint32_t)src * (uint32_t)K + q * kVec;
+        token[mt] = kGateUp ? a.perm_pair[row] : row;
     }
+    auto x_rows = [&](const XT* (&px)[MT], uint32_t (&x_lane)[MT]) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const int src = kGateUp ? min(max(token[mt] / a.k, 0), a.T - 1) : token[mt];
+            px[mt] = reinterpret_cast<const XT*>(a.src) + (kWhole ? 0 : (size_t)src * K);
+            x_lane[mt] = (uint32_t)src * (uint32_t)K + q * kVec;
+        }
+    };
 
     floatx4 acc[NB][MT];
-    split_dot<WT, XT, NB, MT, DEPTH, kRows>(pw, px, w_lane, x_lane, K, wv, 4, mine, acc);
+    split_dot<WT, XT, NB, MT, DEPTH, kRows>(pw, w_lane, x_rows, K, wv, 4, mine, acc);
 
     // partial sums of the four waves, [wave][b][mt][lane]; the sums of a block are formed in wave order
     floatx4* part = reinterpret_cast<floatx4*>(lds);

@@ -253,14 +253,14 @@ __global__ __launch_bounds__(kSplit * kWave) void gate_logits_split_kernel(GateA
     const T* pw[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) pw[b] = (const T*)a.w_gate + (size_t)min(e0 + b * 16 + r16, a.N - 1) * a.ldw;
-    const T* px[MT];
-    const uint32_t none[MT] = {};
+    auto x_rows = [&](const T* (&px)[MT], uint32_t (&)[MT]) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) px[mt] = (const T*)a.x + (size_t)min(t0 + mt * 16 + r16, a.T - 1) * a.H;
+        for (int mt = 0; mt < MT; ++mt) px[mt] = (const T*)a.x + (size_t)min(t0 + mt * 16 + r16, a.T - 1) * a.H;
+    };
     floatx4 acc[NB][MT];
     // fp32 logits decide the top-k: chains of additions about as short as those of one product per lane and a tree
     constexpr int kChains = sizeof(T) == 2 ? 2 : NB * MT > 4 ? 2 : 8;
-    split_dot<T, T, NB, MT, DEPTH, kRows, kChains>(pw, px, 0u, none, a.H, wv, kSplit, max(n_steps - wv + kSplit - 1, 0) / kSplit, acc);
+    split_dot<T, T, NB, MT, DEPTH, kRows, kChains>(pw, 0u, x_rows, a.H, wv, kSplit, max(n_steps - wv + kSplit - 1, 0) / kSplit, acc);
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll

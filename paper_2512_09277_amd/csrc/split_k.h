@@ -39,11 +39,10 @@ enum class KRows { kWhole, kRagged, kTiny };  // K a multiple of a step; any K >
 
 // pw / px: first element of this lane's row of every block (kWhole: of the block, uniform, and w_lane / x_lane the lane's
 // offset in elements, which keeps the vector registers for data in flight).  The wave's steps are s0, s0 + stride, ...
-// (`mine` of them).  WT weights, XT activations.  kChains accumulators per block shorten the chains of additions.
-template <typename WT, typename XT, int NB, int MT, int DEPTH, KRows kRows, int kChains = 1>
-__device__ __forceinline__ void split_dot(const WT* const (&pw)[NB], const XT* const (&px)[MT], uint32_t w_lane,
-                                          const uint32_t (&x_lane)[MT], int K, int s0, int stride, int mine,
-                                          floatx4 (&sum)[NB][MT]) {
+// (`mine` of them).  x_rows(px, x_lane) fills the last two.  WT weights, XT activations.  kChains accumulators per block shorten the chains of additions.
+template <typename WT, typename XT, int NB, int MT, int DEPTH, KRows kRows, int kChains = 1, typename XRows>
+__device__ __forceinline__ void split_dot(const WT* const (&pw)[NB], uint32_t w_lane, XRows x_rows, int K, int s0, int stride,
+                                          int mine, floatx4 (&sum)[NB][MT]) {
     constexpr int kVec = 16 / (int)sizeof(WT);              // k per lane and load
     constexpr int kStep = 8 * kVec;                         // k per step
     constexpr int XV = kVec * (int)sizeof(XT) / 16;         // 16-byte loads of activations per weight load
@@ -69,18 +68,34 @@ __device__ __forceinline__ void split_dot(const WT* const (&pw)[NB], const XT* c
     };
     // Every lane's vector stays inside its row: one that would pass the end is moved back to end with the row, and
     // the elements it then repeats are zeroed (in both operands) when the partial step is consumed.
-    auto load = [&](auto B, int s) {
+    const XT* px[MT];
+    uint32_t x_lane[MT];
+    // Past the wave's last step every lane reads the same 16 bytes of a line that is there already.
+    auto load_w = [&](auto B, int s) {
         constexpr int buf = decltype(B)::value;
         const int step = s0 + stride * min(s, mine - 1);
-        // past the wave's last step: every lane the same 16 bytes of a line that is there already
-        const uint32_t w_off = s < mine ? w_lane : 0u;
-        uint32_t x_off[MT];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) x_off[mt] = s < mine ? x_lane[mt] : 0u;
+        const uint32_t off = s < mine ? w_lane : 0u;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const int k = step * kStep + j * 4 * kVec + q * kVec;
-            const int at = min(k, K - kVec);
+            const int k = step * kStep + j * 4 * kVec + q * kVec, at = min(k, K - kVec);
+            const size_t whole_at = (size_t)step * kStep + j * 4 * kVec;      // uniform
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                if constexpr (kRows == KRows::kTiny) w[buf][j][b] = guarded(pw[b], k);
+                else if constexpr (kWhole) w[buf][j][b] = *reinterpret_cast<const u32x4*>(pw[b] + whole_at + off);
+                else w[buf][j][b] = *reinterpret_cast<const u32x4_any*>(pw[b] + at);
+            }
+        }
+    };
+    auto load_x = [&](auto B, int s) {
+        constexpr int buf = decltype(B)::value;
+        const int step = s0 + stride * min(s, mine - 1);
+        uint32_t off[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) off[mt] = s < mine ? x_lane[mt] : 0u;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int k = step * kStep + j * 4 * kVec + q * kVec, at = min(k, K - kVec);
             const size_t whole_at = (size_t)step * kStep + j * 4 * kVec;      // uniform
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
@@ -88,15 +103,9 @@ __device__ __forceinline__ void split_dot(const WT* const (&pw)[NB], const XT* c
                 for (int v = 0; v < XV; ++v) {
                     constexpr int n = 16 / (int)sizeof(XT);
                     if constexpr (kRows == KRows::kTiny) x[buf][j][mt][v] = guarded(px[mt], k + v * n);
-                    else if constexpr (kWhole) x[buf][j][mt][v] = *reinterpret_cast<const u32x4*>(px[mt] + whole_at + x_off[mt] + v * n);
+                    else if constexpr (kWhole) x[buf][j][mt][v] = *reinterpret_cast<const u32x4*>(px[mt] + whole_at + off[mt] + v * n);
                     else x[buf][j][mt][v] = *reinterpret_cast<const u32x4_any*>(px[mt] + at + v * n);
                 }
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                if constexpr (kRows == KRows::kTiny) w[buf][j][b] = guarded(pw[b], k);
-                else if constexpr (kWhole) w[buf][j][b] = *reinterpret_cast<const u32x4*>(pw[b] + whole_at + w_off);
-                else w[buf][j][b] = *reinterpret_cast<const u32x4_any*>(pw[b] + at);
-            }
         }
     };
     auto consume = [&](auto B, int step, auto Masked) {
@@ -146,11 +155,22 @@ __device__ __forceinline__ void split_dot(const WT* const (&pw)[NB], const XT* c
         // Buffer s % DEPTH holds the wave's step s.  Loads are unconditional (past the end: the last step again) so
         // that the compiler counts what is outstanding exactly and waits for the consumed step only; the last
         // DEPTH steps load nothing.
-        run_steps(std::make_integer_sequence<int, DEPTH>{}, [&](auto U, int s) { load(U, s); }, 0);
+        // The rows of activations may hang on a load of their own: weights that need not wait for it go out first (the
+        // kernels of the general path; in the 16-bit ones, with more bytes in flight, it makes no difference).
+        if constexpr (kWhole) {
+            x_rows(px, x_lane);
+            run_steps(std::make_integer_sequence<int, DEPTH>{}, [&](auto U, int s) { load_x(U, s); load_w(U, s); }, 0);
+        } else {
+            run_steps(std::make_integer_sequence<int, DEPTH>{}, load_w, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            x_rows(px, x_lane);
+            run_steps(std::make_integer_sequence<int, DEPTH>{}, load_x, 0);
+        }
         auto step = [&](auto U, int s) {
             consume(U, s0 + stride * s, std::false_type{});
             __builtin_amdgcn_sched_barrier(0);              // the loads refill the registers just read, none earlier
-            load(U, s + DEPTH);
+            load_x(U, s + DEPTH);
+            load_w(U, s + DEPTH);
             __builtin_amdgcn_sched_barrier(0);
         };
         auto final_step = [&](auto U, int s) { consume(U, s0 + stride * s, std::true_type{}); };
