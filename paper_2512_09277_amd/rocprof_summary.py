@@ -99,7 +99,8 @@ def l2_table(path: str, stats, cmd):
 
 def source_sha16() -> str:
     h = hashlib.sha256()
-    for name in ("ffn.hip", "device_utils.h", "host_utils.h"):
+    for name in ("ffn.hip", "ffn_common.h", "ffn_split.h", "split_k.h", "dense_k.h", "mfma_common.h", "device_utils.h",
+                 "host_utils.h"):
         with open(os.path.join(ROOT, "paper_2512_09277_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -125,7 +126,7 @@ def main() -> None:
     cmd = lambda opts, sub: (f"rocprofv3 {opts} --output-format csv -d {args.dir}/{sub} -o {sub} -- python3 bench.py "
                              f"{args.bench_args}")
     lines = [f"# rocprofv3 summary: hot path of {args.workload}, {args.routing} routing, rank {args.rank}", "",
-             f"Kernel source hash (ffn.hip, device_utils.h, host_utils.h): `{source_sha16()}`.",
+             f"Kernel source hash (ffn.hip and its headers): `{source_sha16()}`.",
              "Commands (run from /tmp with TMPDIR=/tmp on the MI355X box, one rocprofv3 run each):", "",
              "    " + cmd("--kernel-trace --stats", "kt"), "    " + cmd("--pmc FETCH_SIZE", "fetch"),
              "    " + cmd("--pmc WRITE_SIZE", "write"),
