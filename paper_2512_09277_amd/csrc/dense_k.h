@@ -25,12 +25,14 @@ constexpr int kDenseLds = 2 * kDenseBuf;
 
 // x + x_lane[p] / w[p] + w_lane: this thread's 16 bytes (piece tid & 7) of activation / weight row p * 32 + (tid >> 3) at
 // k = 0 (x, w[p] uniform).  wave_x: first staged activation row of the wave; wave_w[b]: staged weight row of
-// block b.  acc[b][mt]: lane (r16, q) holds weight rows 4 q + v of block b, activation row r16 of sub-tile mt.
-template <int MT>
+// block b.  kHalves: the two halves of a K step have accumulators of their own (chains of additions half as long), added at the
+// end.  sum[b][mt]: lane (r16, q) holds weight rows 4 q + v of block b, activation row r16 of sub-tile mt.
+template <int MT, bool kHalves = false>
 __device__ __forceinline__ void dense_dot(const char* x, const uint32_t (&x_lane)[MT], const char* const (&w)[4],
                                           size_t w_lane, int wave_x,
                                           const int (&wave_w)[4], int s_begin, int s_end, char* lds,
-                                          floatx4 (&acc)[4][MT]) {
+                                          floatx4 (&sum)[4][MT]) {
+    floatx4 acc[kHalves ? 2 : 1][4][MT];
     const int tid = threadIdx.x, lane = tid & 63;
     const int r16 = lane & 15, q = lane >> 4;
     const int last = s_end - 1;
@@ -55,9 +57,11 @@ __device__ __forceinline__ void dense_dot(const char* x, const uint32_t (&x_lane
 #pragma unroll
     for (int b = 0; b < 4; ++b) w_off[b] = (kDenseRows + wave_w[b]) * kDenseRow + rd;
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int h = 0; h < (kHalves ? 2 : 1); ++h)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[b][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[h][b][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     // step U of a period of 6 (register set U % 3, LDS buffer U % 2 known at compile time)
     auto step = [&](auto Uc, int s) {
@@ -75,7 +79,7 @@ __device__ __forceinline__ void dense_dot(const char* x, const uint32_t (&x_lane
             for (int b = 0; b < 4; ++b)
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
-                    acc[b][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[b], xb[mt], acc[b][mt], 0, 0, 0);
+                    acc[kHalves ? j : 0][b][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[b], xb[mt], acc[kHalves ? j : 0][b][mt], 0, 0, 0);
         }
         park((U + 1) % 3, (U + 1) % 2);                           // step s + 1, loaded two steps ago
         __syncthreads();
@@ -88,6 +92,10 @@ __device__ __forceinline__ void dense_dot(const char* x, const uint32_t (&x_lane
     int s = s_begin;
     for (; s + 6 <= s_end; s += 6) run_steps(std::make_integer_sequence<int, 6>{}, step, s);
     run_steps_tail(std::make_integer_sequence<int, 5>{}, step, s, s_end);
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) sum[b][mt] = kHalves ? acc[0][b][mt] + acc[kHalves ? 1 : 0][b][mt] : acc[0][b][mt];
 }
 
 }  // namespace

@@ -22,6 +22,7 @@
 
 #include <type_traits>
 
+#include "dense_k.h"
 #include "device_utils.h"
 #include "host_utils.h"
 #include "metro.h"
@@ -126,111 +127,33 @@ __global__ __launch_bounds__(kThreads, 2) void gate_logits_mfma_kernel(GateArgs 
     }
 }
 
-// Large batches: one workgroup = 128 tokens x 128 experts x one K chunk, both operands staged through
-// LDS.  Global loads are fully coalesced (8 lanes read the 128 contiguous bytes a row contributes to a
-// K step of 64: a wave instruction covers 8 whole cache lines instead of 16 half lines), each operand
-// byte enters the CU once per workgroup, and the 2 x 2 waves (64 x 64 each, 16 accumulator tiles) read
-// their fragments from LDS in operand layout.  Double-buffered: the loads of step s + 1 are in flight
-// while step s is multiplied.
-constexpr int kBigTile = 128, kBigBK = 64;
-constexpr int kBigRow = kBigBK * 2 + 16;                         // LDS bytes per staged row (+16 spreads the banks)
-constexpr int kBigBuf = 2 * kBigTile * kBigRow;                  // x tile + w tile of one step
-constexpr int kBigLds = 2 * kBigBuf;
+// Large batches: one workgroup = 32 MT tokens x 128 experts x one K chunk, both operands staged through LDS (dense_k.h).
+constexpr int kBigTile = kDenseRows;                             // experts of a workgroup
 
+template <int MT>
 __global__ __launch_bounds__(kThreads, 2) void gate_logits_lds_kernel(GateArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int r16 = lane & 15, q = lane >> 4;
-    const int chunk = blockIdx.x, t0 = blockIdx.y * kBigTile, e0 = blockIdx.z * kBigTile;
-    const int n_steps = a.H / kBigBK;                             // the host takes this path only if H % 64 == 0
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, q = lane >> 4, srow = tid >> 3;
+    const int chunk = blockIdx.x, t0 = blockIdx.y * (32 * MT), e0 = blockIdx.z * kBigTile;
+    const int n_steps = a.H / kDenseBK;                           // the host takes this path only if H % 64 == 0
     const int s_begin = chunk * a.steps_per_chunk, s_end = min(s_begin + a.steps_per_chunk, n_steps);
-    const int last = s_end - 1;
-
-    // staging: thread (row, piece) copies 16 bytes of rows row, row + 32, row + 64, row + 96 of both tiles
-    const int srow = tid >> 3, piece = tid & 7;
-    const char* xg[4];
-    const char* wg[4];
+    uint32_t x_lane[MT];                                          // from the tile's first token
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const int tok = min(t0 + p * 32 + srow, a.T - 1);         // rows past the batch repeat the last token
-        xg[p] = reinterpret_cast<const char*>(a.x) + ((size_t)tok * a.H) * 2 + piece * 16;
-        wg[p] = reinterpret_cast<const char*>(a.w_gate) + ((size_t)(e0 + p * 32 + srow) * a.ldw) * 2 + piece * 16;
-    }
-    const int st_off = srow * kBigRow + piece * 16;
-    // Three register sets: the loads of steps s + 1 .. s + 3 are in flight while step s is multiplied
-    // (one workgroup per CU at most at these sizes, so the prefetch distance is all the latency hiding
-    // there is).  Loads are unconditional -- past the chunk they re-read its last step -- so that the
-    // compiler counts outstanding loads exactly.
-    u32x4 xr[3][4], wr[3][4];
-    auto load = [&](int set, int s) {
+    for (int p = 0; p < MT; ++p)                                  // rows past the batch repeat the last token
+        x_lane[p] = (uint32_t)(min(t0 + p * 32 + srow, a.T - 1) - t0) * (uint32_t)(a.H * 2) + (tid & 7) * 16;
+    const char* w[4];
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            xr[set][p] = *reinterpret_cast<const u32x4*>(xg[p] + (size_t)s * (kBigBK * 2));
-            wr[set][p] = *reinterpret_cast<const u32x4*>(wg[p] + (size_t)s * (kBigBK * 2));
-        }
-    };
-    auto park = [&](int set, int buf) {
-        char* base = lds + buf * kBigBuf + st_off;
+    for (int p = 0; p < 4; ++p) w[p] = reinterpret_cast<const char*>(a.w_gate) + (size_t)(e0 + p * 32) * a.ldw * 2;
+    const int ty = wv >> 1, tx = wv & 1;                          // wave: tokens [16 MT ty, ..), experts [64 tx, +64)
+    const int wave_w[4] = {tx * 64, tx * 64 + 16, tx * 64 + 32, tx * 64 + 48};
+    floatx4 acc[4][MT];
+    dense_dot<MT, MT == 2>(      // the smaller tile has K chunks twice as long: as many additions in a chain as the larger
+        reinterpret_cast<const char*>(a.x) + (size_t)t0 * a.H * 2, x_lane, w, (size_t)srow * a.ldw * 2 + (tid & 7) * 16,
+        ty * 16 * MT, wave_w, s_begin, s_end, lds, acc);
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            *reinterpret_cast<u32x4*>(base + p * 32 * kBigRow) = xr[set][p];
-            *reinterpret_cast<u32x4*>(base + kBigTile * kBigRow + p * 32 * kBigRow) = wr[set][p];
-        }
-    };
-
-    const int ty = wv >> 1, tx = wv & 1;                          // wave: tokens [64 ty, +64), experts [64 tx, +64)
-    const int rd = r16 * kBigRow + q * 16;
-    floatx4 acc[4][4];
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) acc[b][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-    // step U of a period of 6 (register set U % 3, LDS buffer U % 2 known at compile time)
-    auto step = [&](auto Uc, int s) {
-        constexpr int U = decltype(Uc)::value;
-        load(U % 3, min(s + 3, last));                            // set U % 3 was parked one step ago
-        const char* xt = lds + (U % 2) * kBigBuf + ty * 64 * kBigRow + rd;
-        const char* wt = lds + (U % 2) * kBigBuf + kBigTile * kBigRow + tx * 64 * kBigRow + rd;
-#pragma unroll
-        for (int j = 0; j < kBigBK / 32; ++j) {
-            bf16x8 xb[4], wa[4];
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) xb[mt] = *reinterpret_cast<const bf16x8*>(xt + mt * 16 * kBigRow + j * 64);
-#pragma unroll
-            for (int b = 0; b < 4; ++b) wa[b] = *reinterpret_cast<const bf16x8*>(wt + b * 16 * kBigRow + j * 64);
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int mt = 0; mt < 4; ++mt)
-                    acc[b][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[b], xb[mt], acc[b][mt], 0, 0, 0);
-        }
-        park((U + 1) % 3, (U + 1) % 2);                           // step s + 1, loaded two steps ago
-        __syncthreads();
-    };
-    load(0, min(s_begin, last));
-    load(1, min(s_begin + 1, last));
-    load(2, min(s_begin + 2, last));
-    park(0, 0);
-    __syncthreads();
-    int s = s_begin;
-    for (; s + 6 <= s_end; s += 6) {
-        step(std::integral_constant<int, 0>{}, s);
-        step(std::integral_constant<int, 1>{}, s + 1);
-        step(std::integral_constant<int, 2>{}, s + 2);
-        step(std::integral_constant<int, 3>{}, s + 3);
-        step(std::integral_constant<int, 4>{}, s + 4);
-        step(std::integral_constant<int, 5>{}, s + 5);
-    }
-    // tail: at most five steps; once one is past the end nothing after it is tested
-    (void)((s + 0 < s_end && (step(std::integral_constant<int, 0>{}, s + 0), true)) &&
-           (s + 1 < s_end && (step(std::integral_constant<int, 1>{}, s + 1), true)) &&
-           (s + 2 < s_end && (step(std::integral_constant<int, 2>{}, s + 2), true)) &&
-           (s + 3 < s_end && (step(std::integral_constant<int, 3>{}, s + 3), true)) &&
-           (s + 4 < s_end && (step(std::integral_constant<int, 4>{}, s + 4), true)));
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-        const int t = t0 + ty * 64 + mt * 16 + r16;
+    for (int mt = 0; mt < MT; ++mt) {
+        const int t = t0 + (ty * MT + mt) * 16 + r16;
         if (t < a.T) {
             float* out = a.part + ((size_t)chunk * a.T + t) * a.N + e0 + tx * 64 + q * 4;
 #pragma unroll
@@ -438,9 +361,15 @@ inline bool gate_mfma_shape(int H, int N, int dtype) {
 }
 
 // The LDS-staged kernel takes batches of at least 1024 tokens when N % 128 == 0 and H % 64 == 0 (measured
-// against the direct kernel at N = 256, H = 7168: 17.0 vs 18.7 us at T = 1024, 28 vs 56 us at T = 4096;
+// against the direct kernel at N = 256, H = 7168: 12.0 vs 17.3 us at T = 1024, 28 vs 56 us at T = 4096;
 // below that the direct kernel's smaller workgroups win).
-inline bool gate_big(int T, int H, int N) { return T >= 1024 && N % kBigTile == 0 && H % kBigBK == 0; }
+inline bool gate_big(int T, int H, int N) { return T >= 1024 && N % kBigTile == 0 && H % kDenseBK == 0; }
+
+// Tokens of its workgroups: 128 where that still makes two workgroups per CU at 8 K chunks, else 64, which takes 8 chunks
+// where 128 would need 16 to fill the chip -- half the partial sums to write and for the top-k kernel to read.  Measured,
+// logits + top-k, us, 128 / 64: 1024 tokens x 256 experts x 7168 13.2 + 6.9 / 12.0 + 5.0, 1500 x 256 x 4096 14.4 + 7.6 /
+// 13.1 + 6.0, 3000 x 256 x 4096 18.0 + 7.9 / 16.8 + 7.9, 4096 x 256 x 7168 27.6 + 9.3 / 33.1 + 9.6.
+inline int gate_big_tokens(int T, int N) { return ((T + 127) / 128) * (N / kBigTile) * 8 >= 512 ? 128 : 64; }
 
 // Tokens per workgroup: 64 (four sub-tiles) unless the batch is a single sub-tile.
 inline int gate_tok_tile(int T) { return T > kTokTile ? 4 * kTokTile : kTokTile; }
@@ -448,8 +377,8 @@ inline int gate_tok_tile(int T) { return T > kTokTile ? 4 * kTokTile : kTokTile;
 // K chunks: enough workgroups for two per CU (~512), each chunk at least kMinChunkSteps steps per wave.
 inline int gate_steps_per_chunk(int T, int H, int N) {
     if (gate_big(T, H, N)) {                    // steps of 64; ~8 chunks (one K range per XCD), >= 4 steps each
-        const int n_steps = H / kBigBK;
-        const int tiles = ((T + kBigTile - 1) / kBigTile) * (N / kBigTile);
+        const int n_steps = H / kDenseBK, rows = gate_big_tokens(T, N);
+        const int tiles = ((T + rows - 1) / rows) * (N / kBigTile);
         const int want = tiles * 8 < 256 ? 16 : 8;               // at least one workgroup per CU
         int chunks = n_steps / 4 >= want ? want : n_steps / 4 >= 8 ? 8 : n_steps / 4 > 0 ? n_steps / 4 : 1;
         return (n_steps + chunks - 1) / chunks;
@@ -466,7 +395,7 @@ inline int gate_steps_per_chunk(int T, int H, int N) {
 inline int gate_chunks(int T, int H, int N, int dtype) {
     if (!gate_mfma_shape(H, N, dtype)) return 1;
     const int spc = gate_steps_per_chunk(T, H, N);
-    const int n_steps = gate_big(T, H, N) ? H / kBigBK : H / 32;
+    const int n_steps = gate_big(T, H, N) ? H / kDenseBK : H / 32;
     return (n_steps + spc - 1) / spc;
 }
 
@@ -516,12 +445,18 @@ extern "C" int moe_gate_topk(const void* x, const void* w_gate, int ldw, int T, 
         if (gate_big(T, H, N)) {
             static PerDeviceOnce lds_ok;                          // opt in to > 64 KB of dynamic LDS, once per device
             if (lds_ok.run([] {
-                    return hipFuncSetAttribute((const void*)gate_logits_lds_kernel,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, kBigLds);
+                    hipError_t e = hipFuncSetAttribute((const void*)gate_logits_lds_kernel<2>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, kDenseLds);
+                    if (e == hipSuccess)
+                        e = hipFuncSetAttribute((const void*)gate_logits_lds_kernel<4>,
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, kDenseLds);
+                    return e;
                 }) != METRO_OK)
                 return METRO_ERR_HIP;
-            const dim3 grid(n_chunks, (T + kBigTile - 1) / kBigTile, N / kBigTile);
-            hipLaunchKernelGGL(gate_logits_lds_kernel, grid, dim3(kThreads), kBigLds, st, a);
+            const int rows = gate_big_tokens(T, N);
+            const dim3 grid(n_chunks, (T + rows - 1) / rows, N / kBigTile);
+            if (rows == 64) hipLaunchKernelGGL(gate_logits_lds_kernel<2>, grid, dim3(kThreads), kDenseLds, st, a);
+            else hipLaunchKernelGGL(gate_logits_lds_kernel<4>, grid, dim3(kThreads), kDenseLds, st, a);
         } else {
         const int tile = gate_tok_tile(T);
         const dim3 grid(n_chunks, (T + tile - 1) / tile, N / kExpTile);

@@ -197,3 +197,17 @@ def test_nan_and_infinite_logits(api):
     assert got["topk_ids"].cpu().tolist() == [want] * T
     low = api.moe_gate_topk(x[:1].cuda(), wg[[7, 50, 7, 50, 1]].cuda(), 5)
     assert low["topk_ids"].cpu().tolist() == [[4, 0, 2, 1, 3]]
+
+
+@pytest.mark.parametrize("T,H,N,k", [(1024, 64, 128, 8), (1087, 320, 128, 4), (4033, 128, 256, 8), (4225, 576, 256, 8),
+                                     (8130, 64, 128, 8), (8200, 448, 128, 2)])
+def test_large_batches(api, oracle, T, H, N, k):
+    """The LDS-staged logits kernel on both sides of its tile rule (64 or 128 tokens), last tiles of one to all rows, K chunks
+    of one to several steps."""
+    import torch
+
+    print(f"gate large T={T} H={H} N={N} k={k}", flush=True)
+    x, wg = W.activations(T, H, 95, "bf16"), W.gate_weights(N, H, 96, "bf16")
+    got = api.moe_gate_topk(dev(x), dev(wg), k)
+    torch.cuda.synchronize()
+    check(got, oracle.gate_topk(x, wg, k, want_logits=True), k, N, "bf16")
