@@ -553,10 +553,13 @@ __global__ __launch_bounds__(kThreads) void token_balanced_kernel(RouteArgs a) {
 // Workgroups per layer for the calls that number pairs: runs of at least 2048 pairs (one workgroup numbers these in less time
 // than reading the other runs' ids takes: 2048 pairs 6.4 us as one run, 8.1 us as two; 8192 pairs 11.2 us as four runs,
 // 10.5 as eight), no more workgroups than CUs, and no more than 64 readers of one layer's ids.
-inline int split_for(int L, int T, int k) {
-    const int64_t runs = ((int64_t)T * k + kRunPairs - 1) / kRunPairs;
+inline int split_for(const RouteArgs& a, int L) {
+    const int64_t n = (int64_t)a.T * a.k;
+    // a caller that writes over its ids gets one workgroup per layer: the others would read what it has written
+    auto over_ids = [&](const int32_t* out) { return out && out < a.ids + L * n && a.ids < out + L * n; };
+    if (over_ids(a.pair_slot) || over_ids(a.perm_pair) || over_ids(a.pair_row)) return 1;
     const int64_t most = L >= 256 ? 1 : std::min(256 / L, 64);
-    return (int)std::max<int64_t>(1, std::min(runs, most));
+    return (int)std::max<int64_t>(1, std::min((n + kRunPairs - 1) / kRunPairs, most));
 }
 
 int check_route_args(const void* ids, const void* s2e, int L, int T, int k, int N, int G, int spr,
@@ -627,7 +630,7 @@ extern "C" int metro_route_token_balanced(const int32_t* topk_ids, const int32_t
     if (rc != METRO_OK) return rc;
     RouteArgs a = pack(topk_ids, slot_to_expert, T, k, N, G, spr, pair_slot, nullptr, rank_active, rank_bitmap,
                        err_flag);
-    a.split = split_for(L, T, k);
+    a.split = split_for(a, L);
     hipLaunchKernelGGL(token_balanced_kernel, dim3(L * a.split), dim3(kThreads), 0, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP;
 }
@@ -645,7 +648,7 @@ extern "C" int metro_route_permute(const int32_t* topk_ids, const int32_t* slot_
                        rank_bitmap, err_flag);
     rc = add_lists(a, rank, group_offsets, perm_pair, pair_row, n_pairs);
     if (rc != METRO_OK) return rc;
-    a.split = split_for(1, T, k);
+    a.split = split_for(a, 1);
     hipLaunchKernelGGL(metro_route_kernel<true>, dim3(a.split), dim3(kThreads), 0, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP;
 }
@@ -663,7 +666,7 @@ extern "C" int metro_route_token_balanced_permute(const int32_t* topk_ids, const
                        err_flag);
     rc = add_lists(a, rank, group_offsets, perm_pair, pair_row, n_pairs);
     if (rc != METRO_OK) return rc;
-    a.split = split_for(1, T, k);
+    a.split = split_for(a, 1);
     hipLaunchKernelGGL(token_balanced_kernel, dim3(a.split), dim3(kThreads), 0, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP;
 }

@@ -63,3 +63,30 @@ def test_runs_of_many_layers(oracle, L, T):
         ref = oracle.route_token_balanced(ids[l], s2e, w.N, w.G, w.spr)
         assert np.array_equal(out["pair_slot"][l].cpu().numpy(), ref["pair_slot"]), l
         assert np.array_equal(out["rank_bitmap"][l].cpu().numpy().view(np.uint64), ref["rank_bitmap"]), l
+
+
+@pytest.mark.parametrize("T", [1024, 4096])
+def test_slots_written_over_the_ids(oracle, T):
+    """pair_slot may be the id tensor itself."""
+    from paper_2512_09277_amd import api
+
+    api.load()
+    w = W.QWEN3_30B
+    p = W.popularity(w.N, 1.0, T)
+    s2e, ids = W.placement(p, w.G, w.spr), W.topk_trace(p, T, w.k, T)
+    for plain, fused, ref in ((api.metro_route, api.metro_route_permute, oracle.route_metro),
+                              (api.metro_route_token_balanced, api.metro_route_token_balanced_permute,
+                               oracle.route_token_balanced)):
+        want = ref(ids, s2e, w.N, w.G, w.spr)["pair_slot"]
+        for lists in (False, True):
+            d = dev(ids)
+            out = api.route_buffers(1, T, w.k, w.N, w.G, "cuda")
+            out["pair_slot"] = d.unsqueeze(0)
+            if lists:
+                _, got = fused(d, dev(s2e), w.N, w.G, w.spr, 3, out=out)
+                rows = oracle.permute(want, 3, w.spr)
+                assert np.array_equal(got["pair_row"].cpu().numpy(), rows["pair_row"])
+                assert np.array_equal(got["perm_pair"].cpu().numpy()[:rows["n_pairs"]], rows["perm_pair"])
+            else:
+                plain(d, dev(s2e), w.N, w.G, w.spr, out=out)
+            assert np.array_equal(d.cpu().numpy(), want), lists
