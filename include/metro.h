@@ -64,6 +64,10 @@ const char* metro_status_string(int status);
  *   rank_bitmap    [L,G]   uint64 out: bit l set iff local slot l of the rank is activated
  *   err_flag       [L]     int32  out: 0, or METRO_FLAG_* bits; outputs of a flagged layer are
  *                                 unspecified apart from being in range
+ *
+ * Shared memory, here and in the other routing calls: pair_slot may be the id tensor itself; outputs of the token
+ * lists (see moe_permute) may lie anywhere in the ids or the placement of a call that routes and lists in one.
+ * Apart from that an output must not overlap an input or another output.
  */
 int metro_route(const int32_t* topk_ids, const int32_t* slot_to_expert, int L, int T, int k, int N, int G,
                 int spr, int32_t* pair_slot, int32_t* expert_slot, int32_t* rank_active,
@@ -97,9 +101,9 @@ int moe_permute(const int32_t* pair_slot, int T, int k, int rank, int spr, int32
 /*
  * metro_route_permute / metro_route_token_balanced_permute -- one layer's routing solve followed, in the same
  * launch, by the token lists of one rank ("route tokens", Sec. 4.3): exactly metro_route (or
- * metro_route_token_balanced) with L = 1 and then moe_permute(pair_slot, rank), without the second launch --
- * the workgroup that has just written pair_slot sorts it.  Arguments and results as in those calls;
- * 0 <= rank < G.
+ * metro_route_token_balanced) with L = 1 and then moe_permute(pair_slot, rank), without the second launch: a
+ * pair's row follows from its place among the pairs of its expert.  Arguments and results as in those calls;
+ * 0 <= rank < G.  Where buffers share memory (see metro_route) it is the two calls, in two launches.
  */
 int metro_route_permute(const int32_t* topk_ids, const int32_t* slot_to_expert, int T, int k, int N, int G, int spr,
                         int rank, int32_t* pair_slot, int32_t* expert_slot, int32_t* rank_active,

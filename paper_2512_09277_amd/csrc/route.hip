@@ -41,9 +41,9 @@ struct RouteArgs {
     int32_t* rank_active;
     uint64_t* rank_bitmap;
     int32_t* err_flag;
-    // token lists of one rank, emitted by the same workgroup after pair_slot (single-layer calls only)
-    int list_rank;            // < 0: no lists
     int split;                // workgroups per layer, each numbers and emits its own run of pairs
+    // token lists of one rank (single-layer calls only), each workgroup emits the rows of its run
+    int list_rank;            // < 0: no lists
     int32_t* group_offsets;
     int32_t* perm_pair;
     int32_t* pair_row;
@@ -555,11 +555,28 @@ __global__ __launch_bounds__(kThreads) void token_balanced_kernel(RouteArgs a) {
 // 10.5 as eight), no more workgroups than CUs, and no more than 64 readers of one layer's ids.
 inline int split_for(const RouteArgs& a, int L) {
     const int64_t n = (int64_t)a.T * a.k;
-    // a caller that writes over its ids gets one workgroup per layer: the others would read what it has written
-    auto over_ids = [&](const int32_t* out) { return out && out < a.ids + L * n && a.ids < out + L * n; };
-    if (over_ids(a.pair_slot) || over_ids(a.perm_pair) || over_ids(a.pair_row)) return 1;
     const int64_t most = L >= 256 ? 1 : std::min(256 / L, 64);
     return (int)std::max<int64_t>(1, std::min((n + kRunPairs - 1) / kRunPairs, most));
+}
+
+// Whether an output shares memory with an input or with another output.  Workgroups of a layer read its inputs while others
+// already write, and so do the waves of one workgroup with the ids that do not fit its registers (runs of more than 8192
+// pairs), whose list rows go to any place.  Such a call gets one workgroup per layer, and its token lists come from a
+// second launch, once the routing has consumed its inputs.
+bool shares_memory(const RouteArgs& a, int L) {
+    struct Range {
+        uintptr_t begin, end;
+        Range(const void* p, int64_t words) : begin((uintptr_t)p), end(p ? begin + 4 * (uintptr_t)words : begin) {}
+    };
+    const int64_t n = (int64_t)a.T * a.k, lists = a.list_rank >= 0;
+    const Range all[] = {{a.ids, L * n}, {a.slot_to_expert, (int64_t)L * a.G * a.spr},        // the inputs
+                         {a.pair_slot, L * n}, {a.expert_slot, (int64_t)L * a.N}, {a.rank_active, (int64_t)L * a.G},
+                         {a.rank_bitmap, (int64_t)L * a.G * 2}, {a.err_flag, L}, {a.group_offsets, lists * (a.spr + 1)},
+                         {a.perm_pair, lists * n}, {a.pair_row, lists * n}, {a.n_pairs, lists}};
+    for (int out = 2; out < (int)(sizeof(all) / sizeof(all[0])); ++out)
+        for (int other = 0; other < out; ++other)
+            if (all[out].begin < all[other].end && all[other].begin < all[out].end) return true;
+    return false;
 }
 
 int check_route_args(const void* ids, const void* s2e, int L, int T, int k, int N, int G, int spr,
@@ -630,7 +647,7 @@ extern "C" int metro_route_token_balanced(const int32_t* topk_ids, const int32_t
     if (rc != METRO_OK) return rc;
     RouteArgs a = pack(topk_ids, slot_to_expert, T, k, N, G, spr, pair_slot, nullptr, rank_active, rank_bitmap,
                        err_flag);
-    a.split = split_for(a, L);
+    a.split = shares_memory(a, L) ? 1 : split_for(a, L);
     hipLaunchKernelGGL(token_balanced_kernel, dim3(L * a.split), dim3(kThreads), 0, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP;
 }
@@ -648,6 +665,11 @@ extern "C" int metro_route_permute(const int32_t* topk_ids, const int32_t* slot_
                        rank_bitmap, err_flag);
     rc = add_lists(a, rank, group_offsets, perm_pair, pair_row, n_pairs);
     if (rc != METRO_OK) return rc;
+    if (shares_memory(a, 1)) {
+        rc = metro_route(topk_ids, slot_to_expert, 1, T, k, N, G, spr, pair_slot, expert_slot, rank_active, rank_bitmap,
+                         err_flag, stream);
+        return rc != METRO_OK ? rc : moe_permute(pair_slot, T, k, rank, spr, group_offsets, perm_pair, pair_row, n_pairs, stream);
+    }
     a.split = split_for(a, 1);
     hipLaunchKernelGGL(metro_route_kernel<true>, dim3(a.split), dim3(kThreads), 0, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP;
@@ -666,6 +688,11 @@ extern "C" int metro_route_token_balanced_permute(const int32_t* topk_ids, const
                        err_flag);
     rc = add_lists(a, rank, group_offsets, perm_pair, pair_row, n_pairs);
     if (rc != METRO_OK) return rc;
+    if (shares_memory(a, 1)) {
+        rc = metro_route_token_balanced(topk_ids, slot_to_expert, 1, T, k, N, G, spr, pair_slot, rank_active, rank_bitmap,
+                                        err_flag, stream);
+        return rc != METRO_OK ? rc : moe_permute(pair_slot, T, k, rank, spr, group_offsets, perm_pair, pair_row, n_pairs, stream);
+    }
     a.split = split_for(a, 1);
     hipLaunchKernelGGL(token_balanced_kernel, dim3(a.split), dim3(kThreads), 0, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP;

@@ -90,3 +90,53 @@ def test_slots_written_over_the_ids(oracle, T):
             else:
                 plain(d, dev(s2e), w.N, w.G, w.spr, out=out)
             assert np.array_equal(d.cpu().numpy(), want), lists
+
+
+def routed(routing, T, place=None):
+    """The fused call on T tokens, with `place` = (output, input, offset): that output in the input's memory, `offset` entries in.
+    Returns every output (on the host) and the oracle's arguments."""
+    import torch
+
+    from paper_2512_09277_amd import api
+
+    w = W.QWEN3_30B
+    p = W.popularity(w.N, 1.0, T)
+    s2e, ids = W.placement(p, w.G, w.spr), W.topk_trace(p, T, w.k, T)
+    inputs = dict(ids=dev(ids), s2e=dev(s2e))
+    out, lists = api.route_buffers(1, T, w.k, w.N, w.G, "cuda"), api.permute_buffers(T, w.k, w.spr, "cuda")
+    if place:
+        name, host, offset = place
+        into = out if name in out else lists
+        old = into[name]
+        words = old.numel() * old.element_size() // 4
+        into[name] = inputs[host].view(-1)[offset:offset + words].view(old.dtype).view(old.shape)
+    fused = api.metro_route_permute if routing == "metro" else api.metro_route_token_balanced_permute
+    fused(inputs["ids"], inputs["s2e"], w.N, w.G, w.spr, 3, out=out, lists=lists)
+    torch.cuda.synchronize()
+    return {n: t.cpu().numpy() for n, t in {**out, **lists}.items()}, ids, s2e
+
+
+# 8192 pairs: the ids of a single workgroup fit its registers; 8200 and 16384: they do not; 16: one run
+@pytest.mark.parametrize("T,place", [(T, (name, "ids", 0)) for T in (2, 1024, 1025, 2048) for name in ("pair_slot", "perm_pair", "pair_row")] +
+                         [(1024, (name, host, offset)) for host in ("ids", "s2e") for offset in (0, 8)
+                          for name in ("expert_slot", "rank_active", "rank_bitmap", "err_flag", "group_offsets", "n_pairs")])
+@pytest.mark.parametrize("routing", ["metro", "token_balanced"])
+def test_outputs_in_the_inputs_memory(oracle, routing, T, place):
+    """An output in the memory of the ids or of the placement: every output as with memory of its own, at any batch size."""
+    from paper_2512_09277_amd import api
+
+    api.load()
+    print(f"shared memory {routing} T={T} {place}", flush=True)
+    w = W.QWEN3_30B
+    got, ids, s2e = routed(routing, T, place)
+    ref = (oracle.route_metro if routing == "metro" else oracle.route_token_balanced)(ids, s2e, w.N, w.G, w.spr)
+    want = oracle.permute(ref["pair_slot"], 3, w.spr)
+    assert not got["err_flag"].any()
+    for name in ("pair_slot", "rank_active") + (("expert_slot",) if routing == "metro" else ()):
+        assert np.array_equal(got[name][0], ref[name]), name
+    assert np.array_equal(got["rank_bitmap"][0].view(np.uint64), ref["rank_bitmap"])
+    n = want["n_pairs"]
+    assert int(got["n_pairs"][0]) == n
+    assert np.array_equal(got["group_offsets"], want["group_offsets"])
+    assert np.array_equal(got["perm_pair"][:n], want["perm_pair"])
+    assert np.array_equal(got["pair_row"], want["pair_row"])
