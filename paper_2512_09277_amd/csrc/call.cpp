@@ -54,12 +54,16 @@ struct Args {
     const at::Tensor* field(PyObject* dict, const char* name) {
         return as_tensor(dict && PyDict_CheckExact(dict) ? PyDict_GetItemString(dict, name) : nullptr);
     }
-    // Pointer of a contiguous tensor of one dtype.
-    void* data(const at::Tensor* t, at::ScalarType type) {
+    // Pointer of a contiguous tensor of one dtype: of an input, and of a buffer that is written (which may be a lazy clone:
+    // its mutable pointer gives it memory of its own first).
+    void* in(const at::Tensor* t, at::ScalarType type = at::kInt) {
         if (!ok || t->scalar_type() != type || !t->is_contiguous()) return ok = false, nullptr;
         return const_cast<void*>(t->const_data_ptr());
     }
-    void* i32(const at::Tensor* t) { return data(t, at::kInt); }
+    void* out(const at::Tensor* t, at::ScalarType type = at::kInt) {
+        if (!ok || t->scalar_type() != type || !t->is_contiguous()) return ok = false, nullptr;
+        return t->mutable_data_ptr();
+    }
 };
 
 PyObject *get_device, *get_raw_stream;                  // of torch._C; held for the life of the process
@@ -112,9 +116,9 @@ PyObject* route(PyObject*, PyObject* const* v, Py_ssize_t n) {
     const int64_t L = ids->dim() == 3 ? ids->size(0) : 1, T = ids->size(-2), k = ids->size(-1);
     if (!fits(L) || !fits(T) || !fits(k) || (s2e->dim() == 2 ? s2e->size(0) : 1) != L || s2e->size(-1) != (int64_t)G * spr)
         return unusual();
-    void *pi = a.i32(ids), *ps = a.i32(s2e), *slot = a.i32(a.field(out, "pair_slot")), *active = a.i32(a.field(out, "rank_active")),
-         *bitmap = a.data(a.field(out, "rank_bitmap"), at::kLong), *err = a.i32(a.field(out, "err_flag"));
-    void* expert = metro ? a.i32(a.field(out, "expert_slot")) : nullptr;
+    void *pi = a.in(ids), *ps = a.in(s2e), *slot = a.out(a.field(out, "pair_slot")), *active = a.out(a.field(out, "rank_active")),
+         *bitmap = a.out(a.field(out, "rank_bitmap"), at::kLong), *err = a.out(a.field(out, "err_flag"));
+    void* expert = metro ? a.out(a.field(out, "expert_slot")) : nullptr;
     void* stream = current_stream(a);
     if (!a.ok) return unusual();
     using P = void*;
@@ -134,11 +138,11 @@ PyObject* route_permute(PyObject*, PyObject* const* v, Py_ssize_t n) {
     if (!a.ok || ids->dim() != 2 || s2e->dim() != 1 || s2e->numel() != (int64_t)G * spr) return unusual();
     const int64_t T = ids->size(0), k = ids->size(1);
     if (!fits(T) || !fits(k)) return unusual();
-    void *pi = a.i32(ids), *ps = a.i32(s2e), *slot = a.i32(a.field(out, "pair_slot")), *active = a.i32(a.field(out, "rank_active")),
-         *bitmap = a.data(a.field(out, "rank_bitmap"), at::kLong), *err = a.i32(a.field(out, "err_flag")),
-         *offsets = a.i32(a.field(lists, "group_offsets")), *perm = a.i32(a.field(lists, "perm_pair")),
-         *row = a.i32(a.field(lists, "pair_row")), *pairs = a.i32(a.field(lists, "n_pairs"));
-    void* expert = metro ? a.i32(a.field(out, "expert_slot")) : nullptr;
+    void *pi = a.in(ids), *ps = a.in(s2e), *slot = a.out(a.field(out, "pair_slot")), *active = a.out(a.field(out, "rank_active")),
+         *bitmap = a.out(a.field(out, "rank_bitmap"), at::kLong), *err = a.out(a.field(out, "err_flag")),
+         *offsets = a.out(a.field(lists, "group_offsets")), *perm = a.out(a.field(lists, "perm_pair")),
+         *row = a.out(a.field(lists, "pair_row")), *pairs = a.out(a.field(lists, "n_pairs"));
+    void* expert = metro ? a.out(a.field(out, "expert_slot")) : nullptr;
     void* stream = current_stream(a);
     if (!a.ok) return unusual();
     using P = void*;
@@ -170,8 +174,8 @@ PyObject* ffn(PyObject*, PyObject* const* v, Py_ssize_t n) {
     const int code = dtype_code(a, x);
     int ld13 = 0, ld2 = 0;
     void *p13 = weights(a, w13, x->scalar_type(), spr, 2 * I, H, ld13), *p2 = weights(a, w2, x->scalar_type(), spr, H, I, ld2);
-    void *px = a.data(x, x->scalar_type()), *pp = a.i32(perm), *po = a.i32(offsets), *py = a.data(y, x->scalar_type()),
-         *pws = a.data(ws, at::kByte);
+    void *px = a.in(x, x->scalar_type()), *pp = a.in(perm), *po = a.in(offsets), *py = a.out(y, x->scalar_type()),
+         *pws = a.out(ws, at::kByte);
     void* stream = current_stream(a);
     if (!a.ok) return unusual();
     using P = void*;
@@ -187,7 +191,7 @@ PyObject* unpermute(PyObject*, PyObject* const* v, Py_ssize_t n) {
     const int64_t T = row->size(0), k = row->size(1), H = y->size(1);
     if (!fits(T) || !fits(k) || !fits(H)) return unusual();
     const int code = dtype_code(a, y);
-    void *py = a.data(y, y->scalar_type()), *pr = a.i32(row), *pw = a.data(w, at::kFloat), *po = a.data(out, y->scalar_type());
+    void *py = a.in(y, y->scalar_type()), *pr = a.in(row), *pw = a.in(w, at::kFloat), *po = a.out(out, y->scalar_type());
     void* stream = current_stream(a);
     if (!a.ok) return unusual();
     using P = void*;
@@ -210,9 +214,9 @@ PyObject* gate_topk(PyObject*, PyObject* const* v, Py_ssize_t n) {
     const int64_t T = x->size(0), H = x->size(1), N = w->size(0), ldw = N > 1 ? w->stride(0) : H;
     if (!fits(T) || !fits(H) || !fits(N) || !fits(ldw)) return unusual();
     const int code = dtype_code(a, x);
-    void *px = a.data(x, x->scalar_type()), *ids = a.i32(a.field(out, "topk_ids")),
-         *tw = a.data(a.field(out, "topk_w"), at::kFloat), *cnt = a.i32(a.field(out, "expert_count")),
-         *pws = a.data(ws, at::kByte), *pnv = nv ? a.i32(nv) : nullptr;
+    void *px = a.in(x, x->scalar_type()), *ids = a.out(a.field(out, "topk_ids")),
+         *tw = a.out(a.field(out, "topk_w"), at::kFloat), *cnt = a.out(a.field(out, "expert_count")),
+         *pws = a.out(ws, at::kByte), *pnv = nv ? a.in(nv) : nullptr;
     void* stream = current_stream(a);
     if (!a.ok) return unusual();
     using P = void*;

@@ -168,3 +168,36 @@ def test_the_plain_case_is_native(monkeypatch):
             call(a)
     torch.cuda.synchronize()
     assert int(a["out"]["err_flag"].item()) == 0
+
+
+@pytest.mark.parametrize("native", [True, False])
+def test_lazily_cloned_buffers(monkeypatch, native):
+    """A written buffer that is a lazy (copy-on-write) clone gets memory of its own: the tensor that it was cloned from stays."""
+    import torch
+
+    from paper_2512_09277_amd import api
+
+    api.load()
+    if not native:
+        monkeypatch.setattr(api, "_native", OnlyPython())
+    for name, call in calls().items():
+        plain, a = made(), made()
+        for args in (plain, a):
+            calls()["route_permute"](args)                               # lists the FFN and the combine can read
+        torch.cuda.synchronize()
+        sources = []
+
+        def lazy(t):
+            sources.append((t, t.clone()))
+            return torch._lazy_clone(t)
+
+        for group in ("out", "lists", "gate"):
+            if not (group == "lists" and "permute" not in name):         # those are inputs of the FFN and the combine
+                a[group] = {n: lazy(t) for n, t in a[group].items()}
+        for n in ("ws", "gws", "comb") + (("y",) if name == "ffn" else ()):
+            a[n] = lazy(a[n])
+        got, want = outcome(call, a), outcome(call, plain)
+        assert not isinstance(got, tuple), (name, got)
+        assert all(torch.equal(p, q) for p, q in zip(got, want)), name
+        for source, before in sources:
+            assert torch.equal(source, before), name
