@@ -4,7 +4,7 @@
 // arxiv 2512.09277).  Every activated weight row is streamed from HBM once per tile, with 128-bit loads that
 // land directly in the matrix-core operand layout (16 rows x 64 contiguous bytes per instruction).
 // Work is cut into tiles of one slot's rows:
-//   narrow tiles (at most 32 rows, 64 where the launch is short; the bulk of the bytes): ffn_split.h -- K split over the
+//   narrow tiles (at most 16 rows, 64 where the launch is short; the bulk of the bytes): ffn_split.h -- K split over the
 //       four waves, 64 weight rows per workgroup, activations straight into registers, no barrier in the K loop;
 //   tall tiles (up to 128 rows, the popular experts and large batches): dense_k.h -- both operands through LDS, 128 weight
 //       rows per workgroup.  They are listed first.
@@ -41,6 +41,7 @@ struct FfnArgs {
     int ldw;                  // elements between consecutive weight rows (>= K)
     int ntt;                  // column tiles per tall tile
     int ntn;                  // column tiles per narrow tile
+    CutRule rule;
 };
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }
@@ -53,8 +54,7 @@ constexpr int kLdsBytes = std::max(kDenseLds, kLdsSplit);
 // elsewhere.  It replaced tiles whose weights went straight to registers, every wave reading all activations from
 // LDS: one K step in flight behind 128 accumulator registers, or 64 weight rows per workgroup.  Measured, gate/up + down,
 // us: 4096 tokens at 2048 x 768 111 + 63 -> 54 + 35; 512 tokens at 4096 x 1536 102 + 57 -> 92 + 49; 1024 tokens at
-// 7168 x 2048 (METRO rank) 381 + 200 -> 373 + 195.  Remainders of 33..64 rows are tall too (as narrow tiles 391 + 200 in
-// the last case, 97 + 51 in the one before).  Contiguous runs of items per XCD, so that its L2 sees fewer slots:
+// 7168 x 2048 (METRO rank) 381 + 200 -> 373 + 195.  Contiguous runs of items per XCD, so that its L2 sees fewer slots:
 // 395 + 203 in the last case, no gain in the others.
 template <bool kGateUp, int MT>
 __device__ __forceinline__ void dense_tile(const FfnArgs& a, const Tile t, char* lds) {
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_mfma_kernel(FfnArgs a) {
     // Work items = (tile, column tile), tall tiles first: their workgroups live longest, so they start early for the
     // narrow ones to fill in around them.  Everything here is uniform per workgroup.
     WorkList wl;
-    wl.read(a.group_offsets, a.spr, a.T * a.k, a.ntn);
+    wl.read(a.group_offsets, a.spr, a.T * a.k, a.rule);
     const int tall_items = wl.n_tall * a.ntt;
     int id = blockIdx.x;
     if (id < tall_items) {
@@ -307,6 +307,7 @@ extern "C" int moe_grouped_ffn_gate_up(const void* x, const int32_t* perm_pair, 
     a.T = T; a.k = k; a.spr = spr; a.H = H; a.I = I;
     a.ntt = I / 64;
     a.ntn = I / (kNarrowBlocks * 8);
+    a.rule = CutRule(a.ntn, a.ntt);
     hipLaunchKernelGGL(ffn_mfma_kernel<true>, dim3(mfma_grid(a, cap, spr)), dim3(kThreads), kLdsBytes, st, a);
     return launched();
 }
@@ -338,6 +339,7 @@ extern "C" int moe_grouped_ffn_down(const int32_t* group_offsets, int T, int k, 
     a.T = T; a.k = k; a.spr = spr; a.H = H; a.I = I;
     a.ntt = H / 128;
     a.ntn = H / (kNarrowBlocks * 16);
+    a.rule = CutRule(a.ntn, a.ntt);
     hipLaunchKernelGGL(ffn_mfma_kernel<false>, dim3(mfma_grid(a, cap, spr)), dim3(kThreads), kLdsBytes, st, a);
     return launched();
 }

@@ -11,8 +11,11 @@ namespace {
 
 constexpr int kMaxSpr = 64;
 
+// From 17 rows on a tile is better tall: a narrow one reads its rows once per 64 weight rows, straight into registers.
+// Measured, gate/up + down, us, weights from HBM, narrow / tall: 36 slots of 17 / 24 / 32 rows at 7168 x 2048 565 / 602 / 640
+// against 560 / 566 / 575, 18 slots of them at 4096 x 1536 142 / 152 / 163 against 138 / 141 / 145.
 constexpr int kTallRows = 128;              // rows of a full tall tile
-constexpr int kNarrowRows = 32;             // tiles of at most this many rows are narrow,
+constexpr int kNarrowRows = 16;             // tiles of at most this many rows are narrow,
 constexpr int kCutRows = 64;                // or of this many where a launch is cut into narrow tiles only
 
 struct Tile {
@@ -24,26 +27,37 @@ inline int max_tiles(int cap, int spr, int tile_rows) { return spr + cap / tile_
 
 // ------------------------------------------------------------------------------------------ work items
 // A slot of m rows gives m / th full tiles of th rows and one tile for the remainder.  Launches of few work items cut all
-// slots into narrow tiles (th = 64); the others cut 128-row tiles, of which the full ones and the remainders above 32 rows
+// slots into narrow tiles (th = 64); the others cut 128-row tiles, of which the full ones and the remainders above 16 rows
 // are tall.  Tile order: full tiles, then the remainders, larger classes of rows first (ties: lower slot first), so tall
 // ones come first.  Work item = (tile, column tile), tile-major.
 // Every workgroup derives its own items from group_offsets (65 integers, one memory round trip, some
 // hundred scalar-ish instructions): no planning kernel, no list in memory.  Each wave computes the
 // same result with lane = local slot.
 
-// A narrow launch is bound by the latency of one workgroup, a dense tile's K loop with a barrier per 64 k is longer (256
-// tokens at 2048 x 768, 480 narrow items: 30 + 16 us, with dense tiles 35 + 16); from about one and a half rounds of
-// the 512 resident workgroups on, the dense tile's reuse wins (512 tokens at 4096 x 1536, about 1000 narrow items: gate/up
-// 112 us against 92; 4096 tokens at 2048 x 768, 1700 items: 111 + 63 us against 54 + 35).
-constexpr int kFewItems = 768;
+// Narrow tiles only, where that gives at most
+//   kOneRound items: each has a CU for itself and ends earlier than the longer K loop of a tall tile; a second workgroup on a
+//     CU costs more than that.  Measured as above, narrow only / with tall tiles: one slot of 128 rows at 2048 x 768 (48 items)
+//     28 / 40, one of 256 rows at 7168 x 2048 (256 items) 89 / 107; past it, 3 slots of 96 rows at 4096 x 1536 (288) 77 / 61,
+//     6 slots of 96 rows at 2048 x 768 (288) 44 / 38, of 32 and 64 rows at 4096 x 1536 (288) 74 / 60 and 95 / 67, 18 slots of 64
+//     rows at 2048 x 768 (432) 63 / 52;
+//   kFewItems items, if the tall tiles would be few (below kTallItems items) and not nearly alone (3 in 4): few long workgroups
+//     beside many short ones leave CUs idle at the end.  A whole layer of 2048 x 768 at 256, 320, 384 and 512 tokens (skewed
+//     popularity, 480 to 768 items, 60 to 170 of them would be tall) 56 / 61, 59 / 65, 60 / 67 and 65 / 70.
+constexpr int kOneRound = 256, kFewItems = 768, kTallItems = 170;
+
+struct CutRule {
+    int one_round, few, tall;               // the limits in tiles: of 64 rows, of 64 rows, tall
+    CutRule() = default;
+    CutRule(int narrow_cols, int tall_cols)
+        : one_round(kOneRound / narrow_cols), few(kFewItems / narrow_cols), tall((kTallItems + tall_cols - 1) / tall_cols) {}
+};
 
 // The slots' tiles in the registers of a wave (lane = local slot), from which any item can be picked.
 struct WorkList {
     int begin, full, part, incl, rank;          // per lane
     int th, n_full, n_tall, n_tiles;            // uniform
 
-    // narrow_cols: column tiles of a narrow tile
-    __device__ __forceinline__ void read(const int32_t* __restrict__ group_offsets, int spr, int cap, int narrow_cols) {
+    __device__ __forceinline__ void read(const int32_t* __restrict__ group_offsets, int spr, int cap, const CutRule& rule) {
         const int l = lane_id();
         int m = 0;
         begin = 0;
@@ -51,8 +65,13 @@ struct WorkList {
             begin = min(max(group_offsets[l], 0), cap);
             m = min(max(group_offsets[l + 1], begin), cap) - begin;
         }
-        const int cut = __builtin_amdgcn_readlane(wave_inclusive_sum((m + kCutRows - 1) / kCutRows), kWave - 1);
-        const bool narrow_only = cut <= kFewItems / narrow_cols;
+        // narrow and tall tiles in one scan; a clamped count is past every limit by itself
+        static_assert(kFewItems < 1023 && 64 * 1023 < 65536, "the packed sums");
+        const int counts = __builtin_amdgcn_readlane(wave_inclusive_sum(min((m + kCutRows - 1) / kCutRows, 1023) |
+                                min((m + kTallRows - 1 - kNarrowRows) / kTallRows, 1023) << 16), kWave - 1);
+        const int cut = counts & 0xffff, tall = (int)((uint32_t)counts >> 16), rest = m & (kTallRows - 1);
+        const int small = __popcll(__ballot(rest > 0 && rest <= kNarrowRows));
+        const bool narrow_only = cut <= rule.one_round || (cut <= rule.few && tall < rule.tall && 3 * small > tall);
         th = narrow_only ? kCutRows : kTallRows;
         full = m / th;
         part = m - full * th;
@@ -62,7 +81,7 @@ struct WorkList {
         const uint64_t below = lanes_below();
         rank = 0;
         uint64_t larger = 0;
-        constexpr int kEdges[] = {96, 64, kNarrowRows, 16, 0};
+        constexpr int kEdges[] = {96, 64, 32, kNarrowRows, 0};
 #pragma unroll
         for (int c = 0; c < 5; ++c) {
             const uint64_t in = __ballot(part > kEdges[c]) & ~larger;

@@ -73,6 +73,14 @@ def test_matrix_path_edges(oracle, H, I):
           extra=128)
 
 
+# the rule that cuts a launch, at 384 x 640 (20 gate/up column tiles of a narrow tile, 10 of a tall one): 12 | 13 tiles of 64 rows
+# fill the CUs once; up to 38 the launch is narrow only if fewer than 17 tiles would be tall and more than a third as many small
+@pytest.mark.parametrize("sizes", [[16] * 12, [16] * 13, [33] * 12, [33] * 13, [65] * 6 + [1], [5] * 20 + [64] * 16, [5] * 20 + [64] * 17,
+                                   [1] * 5 + [40] * 15, [1] * 6 + [40] * 15, [16] * 38, [16] * 39, [16] * 10 + [64] * 28, [144] * 5])
+def test_cut_rule_edges(oracle, sizes):
+    check(oracle, "bf16", 384, 640, sizes, T=1000)
+
+
 # combine: vectors of 8 bf16 or 4 fp32 columns, k in registers (<= 8) or not, rows that are no whole vectors, pairs of other
 # ranks.  Sums of k products in fp32 in the oracle's order: fp32 within k * 2^-24 of the sum of magnitudes, bf16 one rounding.
 @pytest.mark.parametrize("dtype,tol", [("f32", 2e-6), ("bf16", 8e-3)])
