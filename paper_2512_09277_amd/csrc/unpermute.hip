@@ -49,9 +49,8 @@ struct Columns {
 // Rows of whole 16-byte vectors: every thread owns one vector's columns (one 128-bit load per row).  KMAX > 0:
 // k <= KMAX, the token's rows and weights sit in registers and the row loads of a column go out
 // together; KMAX == 0: any k.  Bound by HBM (1024 tokens x 7168 in bf16: 45 MB in 10.1 us) and, in small batches, by
-// the two dependent loads; fp32 rows took one column per thread and 15 us at 256 tokens x 2048, now 4.8.  A workgroup
-// has a thread for every vector of the row (256 to 1024): with 256 threads a row of 896 vectors took four turns, one
-// memory round trip each, and the launch 12.6 us.
+// the two dependent loads; fp32 rows took one column per thread and 15 us at 256 tokens x 2048, now 4.8.  How many
+// threads a workgroup has: row_threads.
 template <bool kBf16, int KMAX>
 __global__ __launch_bounds__(kMaxThreads) void unpermute_vec_kernel(const uint4* __restrict__ y,
                                                                  const int32_t* __restrict__ pair_row,
@@ -114,6 +113,20 @@ __global__ __launch_bounds__(kThreads) void unpermute_scalar_kernel(const void* 
     }
 }
 
+// Threads of a workgroup: the row's vectors split evenly over as few turns as `most` allows, in whole waves.  Up to 1024
+// tokens a row takes one turn if it can (1024 tokens x 896 vectors 10.1 us; 12.6 with four turns of 256 threads, a memory round
+// trip each).  More tokens than that come in several rounds of resident workgroups, and a workgroup of 1024 threads keeps its
+// places until its last wave is done: smaller ones do better.  Measured, an eighth of the pairs here, us, 1024 / 512 / 256
+// threads: 8192 tokens x 896 vectors (bf16, k = 8) 47.9 / 35.7 / 37.0, 4096 x 640 19.7 / 16.5 / 16.7, 8192 x 640 with k = 10 40.7 /
+// 35.9 / 34.9, 2048 x 4096 (fp32, k = 8) 42.6 / 44.9 / 50.3; rows of up to 512 vectors, whose loads go out together for k <= 8, gain
+// 4 to 12 % with 256 over 512.  A row of 16 vectors took four waves for the work of one (8192 tokens in fp32, k = 8: 7.1 us, now
+// 4.8).  A launch has fewer than 2^32 threads.
+inline int row_threads(int T, int k, int hv) {
+    const int most = T <= 1024 ? kMaxThreads : (k <= 8 && hv <= 512) || T >= (1 << 23) ? kThreads : 512;
+    const int turns = (hv + most - 1) / most, each = (hv + turns - 1) / turns;
+    return (each + 63) / 64 * 64;
+}
+
 }  // namespace
 }  // namespace metro
 
@@ -130,8 +143,8 @@ extern "C" int moe_unpermute(const void* y_perm, const int32_t* pair_row, const 
     const bool bf16 = dtype == METRO_DTYPE_BF16;
     const int per = bf16 ? 8 : 4;                 // columns of a 16-byte vector
     auto vec = [&](auto kernel) {
-        const int hv = H / per, threads = hv <= kThreads ? kThreads : hv >= kMaxThreads ? kMaxThreads : (hv + 63) / 64 * 64;
-        hipLaunchKernelGGL(kernel, dim3(T), dim3(threads), 0, st, (const uint4*)y_perm, pair_row, topk_w, k, hv,
+        const int hv = H / per;
+        hipLaunchKernelGGL(kernel, dim3(T), dim3(row_threads(T, k, hv)), 0, st, (const uint4*)y_perm, pair_row, topk_w, k, hv,
                            (uint4*)out);
     };
     if (H % per == 0 && aligned) {

@@ -103,3 +103,47 @@ def test_unpermute_edges(oracle, dtype, tol, H, k):
     want = oracle.unpermute(as_f64, row.reshape(T, k), tw)
     got = out.float().cpu().numpy().astype(np.float64)
     assert np.abs(got - want).max() <= tol * max(np.abs(want).max(), 1e-30)
+
+
+# the combine's workgroups on both sides of 1024 tokens: rows of less than a wave, of uneven turns, past 512 and 1024 vectors
+@pytest.mark.parametrize("dtype,tol", [("f32", 2e-6), ("bf16", 8e-3)])
+@pytest.mark.parametrize("T,H,k", [(1024, 40, 3), (1025, 40, 3), (1024, 7176, 2), (1025, 2600, 8), (1025, 4136, 9), (1100, 5208, 1)])
+def test_unpermute_workgroups(oracle, dtype, tol, T, H, k):
+    from paper_2512_09277_amd import api
+
+    api.load()
+    print(f"unpermute {dtype} T={T} H={H} k={k}", flush=True)
+    rng = np.random.default_rng(T + H)
+    row = np.full(T * k, -1, np.int32)
+    here = np.flatnonzero(rng.random(T * k) < 0.2)
+    row[here] = rng.permutation(here.size)
+    y = W.activations(here.size, H, 3, dtype)
+    tw = W.gating_weights(T, k, 4)
+    out = api.moe_unpermute(dev(y), dev(row.reshape(T, k)), dev(tw))
+    as_f64 = np.zeros((T * k, H))
+    as_f64[:here.size] = W.bf16_bits_to_f32(y) if dtype == "bf16" else y
+    want = oracle.unpermute(as_f64, row.reshape(T, k), tw)
+    got = out.float().cpu().numpy().astype(np.float64)
+    assert np.abs(got - want).max() <= tol * max(np.abs(want).max(), 1e-30)
+
+
+def test_unpermute_of_millions_of_tokens():
+    """2^22 tokens whose rows would fill a workgroup of 1024 threads: more threads than one launch may have."""
+    import torch
+
+    from paper_2512_09277_amd import api
+
+    api.load()
+    T, H = 1 << 22, 8192
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 70 GB of device memory")
+    out = torch.empty((T, H), dtype=torch.bfloat16, device="cuda")
+    some = [0, 1, T // 2, T - 2, T - 1]
+    out[some] = 7.0
+    row = torch.full((T, 1), -1, dtype=torch.int32, device="cuda")
+    row[T - 1] = 0
+    y = torch.ones((1, H), dtype=torch.bfloat16, device="cuda")
+    api.moe_unpermute(y, row, torch.full((T, 1), 2.0, device="cuda"), out=out)
+    assert torch.equal(out[some].float().cpu(), torch.tensor([0.0, 0.0, 0.0, 0.0, 2.0])[:, None].expand(5, H))
+    del out
+    torch.cuda.empty_cache()
