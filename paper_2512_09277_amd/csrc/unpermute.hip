@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "metro.h"
 
 namespace metro {
@@ -113,18 +115,21 @@ __global__ __launch_bounds__(kThreads) void unpermute_scalar_kernel(const void* 
     }
 }
 
-// Threads of a workgroup: the row's vectors split evenly over as few turns as `most` allows, in whole waves.  Up to 1024
-// tokens a row takes one turn if it can (1024 tokens x 896 vectors 10.1 us; 12.6 with four turns of 256 threads, a memory round
-// trip each).  More tokens than that come in several rounds of resident workgroups, and a workgroup of 1024 threads keeps its
-// places until its last wave is done: smaller ones do better.  Measured, an eighth of the pairs here, us, 1024 / 512 / 256
-// threads: 8192 tokens x 896 vectors (bf16, k = 8) 47.9 / 35.7 / 37.0, 4096 x 640 19.7 / 16.5 / 16.7, 8192 x 640 with k = 10 40.7 /
-// 35.9 / 34.9, 2048 x 4096 (fp32, k = 8) 42.6 / 44.9 / 50.3; rows of up to 512 vectors, whose loads go out together for k <= 8, gain
-// 4 to 12 % with 256 over 512.  A row of 16 vectors took four waves for the work of one (8192 tokens in fp32, k = 8: 7.1 us, now
-// 4.8).  A launch has fewer than 2^32 threads.
+// Threads of a workgroup.  Up to 1024 tokens, a thread for every vector of the row, 256 to 1024 (1024 tokens x 896 vectors 10.1 us;
+// 12.6 with four turns of 256 threads, a memory round trip each).  More tokens than that come in several rounds of resident
+// workgroups, and a workgroup keeps its places until its last wave is done: smaller ones do better, the vectors split evenly
+// over their turns.  Measured, an eighth of the pairs here, us, 1024 / 512 / 256 threads: 8192 tokens x 896 vectors (bf16, k = 8)
+// 47.9 / 35.7 / 37.0, 4096 x 640 19.7 / 16.5 / 16.7, 2048 x 4096 (fp32, k = 8) 42.6 / 44.9 / 50.3; rows of up to 512 vectors gain 4 to
+// 12 % with 256 over 512.  Past k = 8 a vector's rows are loaded one after the other, and more threads hide that until the rounds
+// are many: 1500 x 640 (bf16, k = 10, all pairs here) 26.4 with 1024, 30.1 with 512; 8192 x 640, an eighth here, 40.7 and 35.9.  A
+// row of 16 vectors took four waves for the work of one (8192 tokens in fp32, k = 8: 7.1 us, now 4.8).  A launch has fewer
+// than 2^32 threads.
 inline int row_threads(int T, int k, int hv) {
-    const int most = T <= 1024 ? kMaxThreads : (k <= 8 && hv <= 512) || T >= (1 << 23) ? kThreads : 512;
-    const int turns = (hv + most - 1) / most, each = (hv + turns - 1) / turns;
-    return (each + 63) / 64 * 64;
+    auto waves = [](int n) { return (n + 63) / 64 * 64; };
+    if (T <= 1024) return std::min(std::max(waves(hv), kThreads), kMaxThreads);
+    const int most = T >= (1 << 23) ? kThreads : k > 8 ? (T <= 4096 ? kMaxThreads : 512) : hv <= 512 ? kThreads : 512;
+    const int turns = (hv + most - 1) / most;
+    return waves((hv + turns - 1) / turns);
 }
 
 }  // namespace
