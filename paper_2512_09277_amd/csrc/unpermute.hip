@@ -155,6 +155,7 @@ extern "C" int moe_unpermute(const void* y_perm, const int32_t* pair_row, const 
     if (H % per == 0 && aligned) {
         if (bf16 && k <= 8) vec(unpermute_vec_kernel<true, 8>);
         else if (bf16) vec(unpermute_vec_kernel<true, 0>);
+        else if (k <= 2) vec(unpermute_vec_kernel<false, 2>);          // 8192 tokens x 64, k = 1: 3.8 us, 4.4 with slots for eight
         else if (k <= 8) vec(unpermute_vec_kernel<false, 8>);
         else vec(unpermute_vec_kernel<false, 0>);
     } else if (bf16) {
