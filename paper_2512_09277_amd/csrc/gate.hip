@@ -15,11 +15,13 @@
 //      top-k by k rounds of a wave-wide arg-max over (logit, -id) and forms the softmax weights;
 //   3. (only when the caller wants expert_count) gate_count_kernel: pairs per expert, one workgroup.
 // Shapes these kernels do not take (fp32, N not a multiple of 64, H not a multiple of 32, misaligned operands) use
-// gate_logits_split_kernel instead, K split over the waves of a workgroup.
+// gate_logits_split_kernel instead, K split over the waves of a workgroup, or, for few fp32 logits of long rows,
+// gate_logits_wave_kernel.
 #include <hip/hip_runtime.h>
 #include <float.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "dense_k.h"
@@ -207,6 +209,18 @@ __global__ __launch_bounds__(kSplit * kWave) void gate_logits_split_kernel(GateA
     }
 }
 
+// fp32, few logits of long rows: one wave per logit (long_rows says when).
+__global__ __launch_bounds__(kThreads) void gate_logits_wave_kernel(GateArgs a) {
+    const int t = blockIdx.x, e = blockIdx.y * (kThreads / kWave) + wave_id();
+    if (e >= a.N) return;
+    const float *x = (const float*)a.x + (size_t)t * a.H, *w = (const float*)a.w_gate + (size_t)e * a.ldw;
+    float acc = 0.f;
+    for (int h = lane_id(); h < a.H; h += kWave) acc = fmaf(x[h], w[h], acc);
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) acc += __shfl_xor(acc, d);
+    if (lane_id() == 0) a.part[(size_t)t * a.N + e] = acc;
+}
+
 // Position of a float (no NaN) in an order of unsigned integers; 0 comes before all of them.  -0 and +0 are one value.
 __device__ __forceinline__ uint32_t order_of(float v) {
     const uint32_t u = __float_as_uint(v + 0.0f);
@@ -337,6 +351,20 @@ __global__ __launch_bounds__(kCountThreads) void gate_count_kernel(const int32_t
     for (int e = threadIdx.x; e < N; e += kCountThreads) cnt[e] = hist[e];
 }
 
+// Whether fp32 logits take one wave each.  A tile's workgroup pulls its rows (the distinct ones of 16 tokens and 16 experts) into
+// one CU at about 45 GB/s, which a wave per logit spreads over the chip; that wave costs a longer chain of loads, and all
+// of them read the weights through L2, so these have to stay there.  Measured, whole call, us, tile / wave: H = 7168, 64 experts,
+// 1 / 16 / 64 / 128 tokens 22 / 31 / 32 / 32 against 21 / 22 / 23 / 25, 128 experts, 24 / 32 tokens 32 / 32 against 23 / 33; H = 4096, 128
+// experts, 4 / 16 / 64 / 128 tokens 17 / 21 / 22 / 22 against 17 / 18 / 20 / 27, 256 experts, 8 tokens 19 against 31; H = 2048, 64
+// experts, 8 / 16 / 128 tokens 13 / 14 / 14.5 against 13 / 13 / 15.
+inline bool long_rows(int T, int H, int N) {
+    const int64_t logits = (int64_t)T * N, weights = (int64_t)N * H * (int)sizeof(float);
+    if ((int64_t)H * (std::min(T, kTokTile) + std::min(N, kTokTile) - 11) < 32768) return false;
+    if (weights > 2 << 20)
+        return (T <= 24 && logits <= 24 * 128 && weights <= 15 << 18) || (T <= 4 && logits <= 1024 && weights <= 15 << 19);
+    return logits <= std::min<int64_t>(2 * (int64_t)H, 8192);
+}
+
 template <typename T>
 void launch_general_logits(const GateArgs& a, hipStream_t st) {
     auto tiles = [&](int rows) { return (int64_t)((a.T + rows - 1) / rows) * ((a.N + rows - 1) / rows); };
@@ -349,8 +377,11 @@ void launch_general_logits(const GateArgs& a, hipStream_t st) {
     // 512 tokens (16 / 64 / 256) 41 / 18 / 11.  The 32-wide tile pays from 64 tiles in bf16 (H = 2000, 200 experts, 512
     // tokens, 112 tiles: 8.3 against 13.7) and, its fp32 matrix instructions being the longer part, from 256 in fp32.
     // Short loops want little code: 8 waves two steps deep beat 16 waves four deep at 64 tokens, H = 1000, 5.1 to 7.6.
-    // (One wave per logit, which this replaced: 1887, 460, 83 us for the first, second and third, 93 for the fourth.)
-    if (a.H < 16 / (int)sizeof(T)) go(gate_logits_split_kernel<T, 2, 2, 4, 1, KRows::kTiny>, 32, 4);
+    // (One wave per logit: 1887, 460, 83 us for the first, second and third, 93 for the fourth.)
+    if (std::is_same_v<T, float> && long_rows(a.T, a.H, a.N)) {
+        constexpr int per = kThreads / kWave;
+        hipLaunchKernelGGL(gate_logits_wave_kernel, dim3(a.T, (a.N + per - 1) / per), dim3(kThreads), 0, st, a);
+    } else if (a.H < 16 / (int)sizeof(T)) go(gate_logits_split_kernel<T, 2, 2, 4, 1, KRows::kTiny>, 32, 4);
     else if (tiles(64) >= 256) go(gate_logits_split_kernel<T, 4, 4, 4, 1, KRows::kRagged>, 64, 4);
     else if (tiles(32) >= (sizeof(T) == 2 ? 64 : 256)) go(gate_logits_split_kernel<T, 2, 2, 8, 2, KRows::kRagged>, 32, 8);
     else go(gate_logits_split_kernel<T, 1, 1, 8, 2, KRows::kRagged>, 16, 8);

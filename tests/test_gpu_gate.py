@@ -211,3 +211,20 @@ def test_large_batches(api, oracle, T, H, N, k):
     got = api.moe_gate_topk(dev(x), dev(wg), k)
     torch.cuda.synchronize()
     check(got, oracle.gate_topk(x, wg, k, want_logits=True), k, N, "bf16")
+
+
+@pytest.mark.parametrize("T,H,N", [(1, 7168, 64), (3, 7168, 8), (24, 7168, 128), (25, 7168, 128), (16, 4096, 128), (64, 4096, 128),
+                                   (65, 4096, 128), (4, 7168, 256), (5, 7168, 256), (15, 2049, 63), (512, 4099, 16), (513, 4099, 16)])
+def test_few_logits_of_long_rows(api, oracle, T, H, N):
+    """fp32 on both sides of the rule between one wave per logit and tiles of 16 tokens x 16 experts."""
+    import torch
+
+    print(f"gate long rows T={T} H={H} N={N}", flush=True)
+    x, wg = W.activations(T, H, 93, "f32"), W.gate_weights(N, H, 94, "f32")
+    ref = oracle.gate_topk(x, wg, min(8, N), want_logits=True)
+    buf = torch.full((N, H + 3), 3.0, device="cuda")
+    buf[:, :H].copy_(dev(wg))
+    for w in (dev(wg), buf[:, :H]):
+        got = api.moe_gate_topk(dev(x), w, min(8, N))
+        torch.cuda.synchronize()
+        check(got, ref, min(8, N), N, "f32")
