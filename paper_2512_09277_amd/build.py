@@ -21,17 +21,23 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared", "-fno
 RESOURCES: dict = {}        # kernel symbol -> {"VGPRs": .., "AGPRs": .., "Occupancy": .., "LDS": .., "Scratch": ..} of the last build
 
 
-def build_call(verbose: bool = False) -> str:
-    """Compile the native argument marshalling of api.py (host code only) against the installed torch."""
+def call_flags(include: str = os.path.join(ROOT, "include")) -> list:
+    """Compiler and flags for call.cpp against the installed torch; include: the folder of metro.h."""
     import torch
 
     root = os.path.dirname(torch.__file__)
-    lib = os.path.join(root, "lib")
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-sign-compare",
-           "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
-           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
-           os.path.join(CSRC, "call.cpp"), "-o", CALL, "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-Wno-sign-compare", "-I", include,
+            "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+            "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", os.path.join(CSRC, "call.cpp")]
+
+
+def build_call(verbose: bool = False) -> str:
+    """Compile the native argument marshalling of api.py (host code only)."""
+    import torch
+
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [*call_flags(), "-shared", "-o", CALL, "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)

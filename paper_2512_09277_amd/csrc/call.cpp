@@ -11,11 +11,22 @@
 #include <ATen/core/Tensor.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <algorithm>
 #include <cstdint>
+
+#include "metro.h"
 
 namespace {
 
 constexpr long kUnusual = 1;                            // no status of the library is positive
+static_assert(METRO_OK == 0, "statuses are zero or negative");
+
+// An address that has passed the checks; converts to the pointer type that a prototype asks for.
+struct Ptr {
+    void* p = nullptr;
+    template <typename T>
+    operator T*() const { return static_cast<T*>(p); }
+};
 
 struct Args {
     PyObject* const* v;
@@ -56,13 +67,13 @@ struct Args {
     }
     // Pointer of a contiguous tensor of one dtype: of an input, and of a buffer that is written (which may be a lazy clone:
     // its mutable pointer gives it memory of its own first).
-    void* in(const at::Tensor* t, at::ScalarType type = at::kInt) {
-        if (!ok || t->scalar_type() != type || !t->is_contiguous()) return ok = false, nullptr;
-        return const_cast<void*>(t->const_data_ptr());
+    Ptr in(const at::Tensor* t, at::ScalarType type = at::kInt) {
+        if (!ok || t->scalar_type() != type || !t->is_contiguous()) return ok = false, Ptr{};
+        return Ptr{const_cast<void*>(t->const_data_ptr())};
     }
-    void* out(const at::Tensor* t, at::ScalarType type = at::kInt) {
-        if (!ok || t->scalar_type() != type || !t->is_contiguous()) return ok = false, nullptr;
-        return t->mutable_data_ptr();
+    Ptr out(const at::Tensor* t, at::ScalarType type = at::kInt) {
+        if (!ok || t->scalar_type() != type || !t->is_contiguous()) return ok = false, Ptr{};
+        return Ptr{t->mutable_data_ptr()};
     }
 };
 
@@ -81,21 +92,21 @@ void* current_stream(Args& a) {
 }
 
 int32_t dtype_code(Args& a, const at::Tensor* t) {      // METRO_DTYPE_*
-    if (a.ok && t->scalar_type() == at::kBFloat16) return 1;
-    if (a.ok && t->scalar_type() == at::kFloat) return 0;
+    if (a.ok && t->scalar_type() == at::kBFloat16) return METRO_DTYPE_BF16;
+    if (a.ok && t->scalar_type() == at::kFloat) return METRO_DTYPE_F32;
     a.ok = false;
-    return 0;
+    return METRO_DTYPE_F32;
 }
 
 bool fits(int64_t v) { return v >= 0 && v <= INT32_MAX; }
 
 PyObject* answer(long status) { return PyLong_FromLong(status); }
-// The library call itself runs without the interpreter lock, as through ctypes.
-template <typename R, typename... A>
-PyObject* call(R (*f)(A...), A... args) {
-    R status;
+// fn: address of a library function, called as its prototype F in metro.h, without the interpreter lock, as through ctypes.
+template <typename F, typename... A>
+PyObject* call(void* fn, A... args) {
+    int status;
     Py_BEGIN_ALLOW_THREADS
-    status = f(args...);
+    status = reinterpret_cast<F>(fn)(args...);
     Py_END_ALLOW_THREADS
     return answer(status);
 }
@@ -116,15 +127,14 @@ PyObject* route(PyObject*, PyObject* const* v, Py_ssize_t n) {
     const int64_t L = ids->dim() == 3 ? ids->size(0) : 1, T = ids->size(-2), k = ids->size(-1);
     if (!fits(L) || !fits(T) || !fits(k) || (s2e->dim() == 2 ? s2e->size(0) : 1) != L || s2e->size(-1) != (int64_t)G * spr)
         return unusual();
-    void *pi = a.in(ids), *ps = a.in(s2e), *slot = a.out(a.field(out, "pair_slot")), *active = a.out(a.field(out, "rank_active")),
-         *bitmap = a.out(a.field(out, "rank_bitmap"), at::kLong), *err = a.out(a.field(out, "err_flag"));
-    void* expert = metro ? a.out(a.field(out, "expert_slot")) : nullptr;
+    const Ptr pi = a.in(ids), ps = a.in(s2e), slot = a.out(a.field(out, "pair_slot")), active = a.out(a.field(out, "rank_active")),
+         bitmap = a.out(a.field(out, "rank_bitmap"), at::kLong), err = a.out(a.field(out, "err_flag"));
+    const Ptr expert = metro ? a.out(a.field(out, "expert_slot")) : Ptr{};
     void* stream = current_stream(a);
     if (!a.ok) return unusual();
-    using P = void*;
     if (metro)
-        return call((int (*)(P, P, int, int, int, int, int, int, P, P, P, P, P, P))fn, pi, ps, (int)L, (int)T, (int)k, N, G, spr, slot, expert, active, bitmap, err, stream);
-    return call((int (*)(P, P, int, int, int, int, int, int, P, P, P, P, P))fn, pi, ps, (int)L, (int)T, (int)k, N, G, spr, slot, active, bitmap, err, stream);
+        return call<decltype(&metro_route)>(fn, pi, ps, (int)L, (int)T, (int)k, N, G, spr, slot, expert, active, bitmap, err, stream);
+    return call<decltype(&metro_route_token_balanced)>(fn, pi, ps, (int)L, (int)T, (int)k, N, G, spr, slot, active, bitmap, err, stream);
 }
 
 // route_permute(fn, metro, topk_ids, slot_to_expert, N, G, spr, rank, out, lists)
@@ -138,27 +148,26 @@ PyObject* route_permute(PyObject*, PyObject* const* v, Py_ssize_t n) {
     if (!a.ok || ids->dim() != 2 || s2e->dim() != 1 || s2e->numel() != (int64_t)G * spr) return unusual();
     const int64_t T = ids->size(0), k = ids->size(1);
     if (!fits(T) || !fits(k)) return unusual();
-    void *pi = a.in(ids), *ps = a.in(s2e), *slot = a.out(a.field(out, "pair_slot")), *active = a.out(a.field(out, "rank_active")),
-         *bitmap = a.out(a.field(out, "rank_bitmap"), at::kLong), *err = a.out(a.field(out, "err_flag")),
-         *offsets = a.out(a.field(lists, "group_offsets")), *perm = a.out(a.field(lists, "perm_pair")),
-         *row = a.out(a.field(lists, "pair_row")), *pairs = a.out(a.field(lists, "n_pairs"));
-    void* expert = metro ? a.out(a.field(out, "expert_slot")) : nullptr;
+    const Ptr pi = a.in(ids), ps = a.in(s2e), slot = a.out(a.field(out, "pair_slot")), active = a.out(a.field(out, "rank_active")),
+         bitmap = a.out(a.field(out, "rank_bitmap"), at::kLong), err = a.out(a.field(out, "err_flag")),
+         offsets = a.out(a.field(lists, "group_offsets")), perm = a.out(a.field(lists, "perm_pair")),
+         row = a.out(a.field(lists, "pair_row")), pairs = a.out(a.field(lists, "n_pairs"));
+    const Ptr expert = metro ? a.out(a.field(out, "expert_slot")) : Ptr{};
     void* stream = current_stream(a);
     if (!a.ok) return unusual();
-    using P = void*;
     if (metro)
-        return call((int (*)(P, P, int, int, int, int, int, int, P, P, P, P, P, P, P, P, P, P))fn, pi, ps, (int)T, (int)k, N, G, spr, rank, slot, expert, active, bitmap, err, offsets, perm, row, pairs, stream);
-    return call((int (*)(P, P, int, int, int, int, int, int, P, P, P, P, P, P, P, P, P))fn, pi, ps, (int)T, (int)k, N, G, spr, rank, slot, active, bitmap, err, offsets, perm, row, pairs, stream);
+        return call<decltype(&metro_route_permute)>(fn, pi, ps, (int)T, (int)k, N, G, spr, rank, slot, expert, active, bitmap, err, offsets, perm, row, pairs, stream);
+    return call<decltype(&metro_route_token_balanced_permute)>(fn, pi, ps, (int)T, (int)k, N, G, spr, rank, slot, active, bitmap, err, offsets, perm, row, pairs, stream);
 }
 
 // Weights [slots, rows, K]: K contiguous, rows `ld` elements apart, slots rows * ld apart.
-void* weights(Args& a, const at::Tensor* t, at::ScalarType type, int64_t slots, int64_t rows, int64_t K, int& ld) {
+Ptr weights(Args& a, const at::Tensor* t, at::ScalarType type, int64_t slots, int64_t rows, int64_t K, int& ld) {
     if (!a.ok || t->scalar_type() != type || t->dim() != 3 || t->size(0) != slots || t->size(1) != rows || t->size(2) != K)
-        return a.ok = false, nullptr;
+        return a.ok = false, Ptr{};
     const int64_t pitch = rows > 1 ? t->stride(1) : std::max(K, t->stride(1));
-    if (t->stride(2) != 1 || pitch < K || !fits(pitch) || (slots > 1 && t->stride(0) != rows * pitch)) return a.ok = false, nullptr;
+    if (t->stride(2) != 1 || pitch < K || !fits(pitch) || (slots > 1 && t->stride(0) != rows * pitch)) return a.ok = false, Ptr{};
     ld = (int)pitch;
-    return const_cast<void*>(t->const_data_ptr());
+    return Ptr{const_cast<void*>(t->const_data_ptr())};
 }
 
 // ffn(fn, x, perm_pair, group_offsets, k, w13, w2, y_perm, ws)
@@ -173,13 +182,12 @@ PyObject* ffn(PyObject*, PyObject* const* v, Py_ssize_t n) {
     if (!fits(T) || !fits(H) || !fits(spr) || !fits(I) || perm->numel() < T * k || offsets->numel() != spr + 1) return unusual();
     const int code = dtype_code(a, x);
     int ld13 = 0, ld2 = 0;
-    void *p13 = weights(a, w13, x->scalar_type(), spr, 2 * I, H, ld13), *p2 = weights(a, w2, x->scalar_type(), spr, H, I, ld2);
-    void *px = a.in(x, x->scalar_type()), *pp = a.in(perm), *po = a.in(offsets), *py = a.out(y, x->scalar_type()),
-         *pws = a.out(ws, at::kByte);
+    const Ptr p13 = weights(a, w13, x->scalar_type(), spr, 2 * I, H, ld13), p2 = weights(a, w2, x->scalar_type(), spr, H, I, ld2);
+    const Ptr px = a.in(x, x->scalar_type()), pp = a.in(perm), po = a.in(offsets), py = a.out(y, x->scalar_type()),
+         pws = a.out(ws, at::kByte);
     void* stream = current_stream(a);
     if (!a.ok) return unusual();
-    using P = void*;
-    return call((int (*)(P, P, P, int, int, int, int, int, int, P, int, P, int, P, P, size_t, P))fn, px, pp, po, (int)T, k, (int)spr, (int)H, (int)I, code, p13, ld13, p2, ld2, py, pws, (size_t)ws->numel(), stream);
+    return call<decltype(&moe_grouped_ffn)>(fn, px, pp, po, (int)T, k, (int)spr, (int)H, (int)I, code, p13, ld13, p2, ld2, py, pws, (size_t)ws->numel(), stream);
 }
 
 // unpermute(fn, y_perm, pair_row, topk_w, out)
@@ -191,11 +199,10 @@ PyObject* unpermute(PyObject*, PyObject* const* v, Py_ssize_t n) {
     const int64_t T = row->size(0), k = row->size(1), H = y->size(1);
     if (!fits(T) || !fits(k) || !fits(H)) return unusual();
     const int code = dtype_code(a, y);
-    void *py = a.in(y, y->scalar_type()), *pr = a.in(row), *pw = a.in(w, at::kFloat), *po = a.out(out, y->scalar_type());
+    const Ptr py = a.in(y, y->scalar_type()), pr = a.in(row), pw = a.in(w, at::kFloat), po = a.out(out, y->scalar_type());
     void* stream = current_stream(a);
     if (!a.ok) return unusual();
-    using P = void*;
-    return call((int (*)(P, P, P, int, int, int, int, P, P))fn, py, pr, pw, (int)T, (int)k, (int)H, code, po, stream);
+    return call<decltype(&moe_unpermute)>(fn, py, pr, pw, (int)T, (int)k, (int)H, code, po, stream);
 }
 
 // gate_topk(fn, x, w_gate, k, out, ws, n_valid or None)
@@ -214,13 +221,12 @@ PyObject* gate_topk(PyObject*, PyObject* const* v, Py_ssize_t n) {
     const int64_t T = x->size(0), H = x->size(1), N = w->size(0), ldw = N > 1 ? w->stride(0) : H;
     if (!fits(T) || !fits(H) || !fits(N) || !fits(ldw)) return unusual();
     const int code = dtype_code(a, x);
-    void *px = a.in(x, x->scalar_type()), *ids = a.out(a.field(out, "topk_ids")),
-         *tw = a.out(a.field(out, "topk_w"), at::kFloat), *cnt = a.out(a.field(out, "expert_count")),
-         *pws = a.out(ws, at::kByte), *pnv = nv ? a.in(nv) : nullptr;
+    const Ptr px = a.in(x, x->scalar_type()), ids = a.out(a.field(out, "topk_ids")),
+         tw = a.out(a.field(out, "topk_w"), at::kFloat), cnt = a.out(a.field(out, "expert_count")),
+         pws = a.out(ws, at::kByte), pnv = nv ? a.in(nv) : Ptr{};
     void* stream = current_stream(a);
     if (!a.ok) return unusual();
-    using P = void*;
-    return call((int (*)(P, P, int, int, int, int, int, int, P, P, P, P, P, size_t, P))fn, px, const_cast<void*>(w->const_data_ptr()), (int)ldw, (int)T, (int)H, (int)N, k, code, pnv, ids, tw, cnt, pws, (size_t)ws->numel(), stream);
+    return call<decltype(&moe_gate_topk)>(fn, px, Ptr{const_cast<void*>(w->const_data_ptr())}, (int)ldw, (int)T, (int)H, (int)N, k, code, pnv, ids, tw, cnt, pws, (size_t)ws->numel(), stream);
 }
 
 template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)>

@@ -104,3 +104,21 @@ def test_binding_fails_loudly_without_the_library(monkeypatch):
     monkeypatch.setattr(api, "LIB_PATH", "/nonexistent/libmetro.so")
     with pytest.raises(RuntimeError):
         api.load()
+
+
+@pytest.mark.parametrize("edit", [None, ("int k, int N, int G,\n                int spr", "int k, int N, int G"),
+                                  ("const void* w13, int ldw13, const void* w2, int ldw2,\n                    void* y_perm, void* ws",
+                                   "const void* w13, const void* w2, int ldw13, int ldw2,\n                    void* y_perm, void* ws")])
+def test_native_calls_follow_the_header(tmp_path, edit):
+    """The binding's native calls are compiled against metro.h's prototypes: a changed one does not compile."""
+    import subprocess
+
+    from paper_2512_09277_amd import build
+
+    text = open(HEADER).read()
+    if edit:
+        assert edit[0] in text
+        text = text.replace(*edit)
+    (tmp_path / "metro.h").write_text(text)
+    done = subprocess.run([*build.call_flags(str(tmp_path)), "-fsyntax-only"], capture_output=True, text=True)
+    assert (done.returncode == 0) == (edit is None), done.stderr[-2000:]
