@@ -14,7 +14,7 @@ HEADER = os.path.join(ROOT, "include", "metro.h")
 def lib():
     from paper_2512_09277_amd import api
 
-    if not os.path.exists(api.LIB_PATH):
+    if not (os.path.exists(api.LIB_PATH) and os.path.exists(api.CALL_PATH)):
         from paper_2512_09277_amd import build
 
         build.build()
@@ -97,12 +97,13 @@ def test_size_queries_take_every_batch_size(lib):
     assert lib.moe_grouped_ffn_static_ws(one, one, one, 4, 2, 65, 256, 128, 1, one, 256, one, 128, one, None) == -2
 
 
-def test_binding_fails_loudly_without_the_library(monkeypatch):
+@pytest.mark.parametrize("part", ["LIB_PATH", "CALL_PATH"])
+def test_binding_fails_loudly_without_the_library(monkeypatch, lib, part):
     from paper_2512_09277_amd import api
 
     monkeypatch.setattr(api, "_lib", None)
-    monkeypatch.setattr(api, "LIB_PATH", "/nonexistent/libmetro.so")
-    with pytest.raises(RuntimeError):
+    monkeypatch.setattr(api, part, "/nonexistent/part.so")
+    with pytest.raises(RuntimeError, match="part.so is missing"):
         api.load()
 
 
