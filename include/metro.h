@@ -136,7 +136,7 @@ int metro_route_token_balanced_permute(const int32_t* topk_ids, const int32_t* s
  *   dtype  METRO_DTYPE_BF16: bf16 operands, fp32 accumulation on the matrix cores when H % 32 == 0,
  *          N % 64 == 0, ldw % 8 == 0 and x, w_gate are 16-byte aligned; other shapes and
  *          METRO_DTYPE_F32 (fp32 products and sums) take a general kernel.  Logits are summed in a fixed order, so the
- *          result is deterministic; NaN logits sort below every number.
+ *          result is deterministic; a NaN logit counts as the lowest finite number (above -infinity).
  * Limits: N <= 512, k <= min(N, 64), T*k < 2^24.  T == 0 writes nothing but expert_count (all zero).
  */
 size_t moe_gate_topk_workspace_bytes(int T, int H, int N, int dtype);

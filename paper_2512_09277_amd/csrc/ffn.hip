@@ -54,7 +54,7 @@ constexpr int kLdsBytes = std::max(kDenseLds, kLdsSplit);
 // elsewhere.  It replaced tiles whose weights went straight to registers, every wave reading all activations from
 // LDS: one K step in flight behind 128 accumulator registers, or 64 weight rows per workgroup.  Measured, gate/up + down,
 // us: 4096 tokens at 2048 x 768 111 + 63 -> 54 + 35; 512 tokens at 4096 x 1536 102 + 57 -> 92 + 49; 1024 tokens at
-// 7168 x 2048 (METRO rank) 381 + 200 -> 373 + 195.  Contiguous runs of items per XCD, so that its L2 sees fewer slots:
+// 7168 x 2048 (METRO rank) 381 + 200 -> 373 + 195, 369 + 194 since tiles of 17 to 32 rows are tall as well.  Contiguous runs of items per XCD, so that its L2 sees fewer slots:
 // 395 + 203 in the last case, no gain in the others.
 template <bool kGateUp, int MT>
 __device__ __forceinline__ void dense_tile(const FfnArgs& a, const Tile t, char* lds) {

@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kThreads) void gate_topk_kernel(const float* __rest
     uint32_t ord[kPerLane];                                      // 0: no expert, or already selected
 #pragma unroll
     for (int j = 0; j < kPerLane; ++j) {
-        if (v[j] != v[j]) v[j] = -FLT_MAX;                       // NaN sorts below every number
+        if (v[j] != v[j]) v[j] = -FLT_MAX;                       // NaN counts as the lowest finite number
         ord[j] = j * kWave + l < N ? order_of(v[j]) : 0u;
     }
     float my_v = 0.f;
@@ -353,10 +353,12 @@ __global__ __launch_bounds__(kCountThreads) void gate_count_kernel(const int32_t
 
 // Whether fp32 logits take one wave each.  A tile's workgroup pulls its rows (the distinct ones of 16 tokens and 16 experts) into
 // one CU at about 45 GB/s, which a wave per logit spreads over the chip; that wave costs a longer chain of loads, and all
-// of them read the weights through L2, so these have to stay there.  Measured, whole call, us, tile / wave: H = 7168, 64 experts,
-// 1 / 16 / 64 / 128 tokens 22 / 31 / 32 / 32 against 21 / 22 / 23 / 25, 128 experts, 24 / 32 tokens 32 / 32 against 23 / 33; H = 4096, 128
-// experts, 4 / 16 / 64 / 128 tokens 17 / 21 / 22 / 22 against 17 / 18 / 20 / 27, 256 experts, 8 tokens 19 against 31; H = 2048, 64
-// experts, 8 / 16 / 128 tokens 13 / 14 / 14.5 against 13 / 13 / 15.
+// of them read the weights through L2, so these have to stay there.  Measured, whole call, us, tiles against waves: H = 7168,
+// 64 experts, 1 / 16 / 64 / 128 tokens 22.1 / 31.2 / 31.9 / 31.8 against 17.8 / 18.6 / 19.8 / 22.9; 128 experts, 24 tokens 31.8
+// against 19.7, 256 experts, 4 tokens 25.3 against 19.0; H = 4096, 128 experts, 4 / 16 / 64 tokens 17.4 / 21.3 / 21.8 against
+// 13.3 / 13.7 / 16.2; H = 2048, 64 experts, 16 / 64 tokens 14.0 / 14.2 against 9.9 / 10.6.  Past the rule the waves lose (their
+// figures with a top-k kernel 3 us slower): H = 7168, 256 experts, 8 tokens 27.9 against 46.2; H = 4096, 128 experts, 128 tokens
+// 22.2 against 26.9, 256 experts, 8 tokens 19.4 against 31.0.
 inline bool long_rows(int T, int H, int N) {
     const int64_t logits = (int64_t)T * N, weights = (int64_t)N * H * (int)sizeof(float);
     if ((int64_t)H * (std::min(T, kTokTile) + std::min(N, kTokTile) - 11) < 32768) return false;

@@ -550,9 +550,11 @@ __global__ __launch_bounds__(kThreads) void token_balanced_kernel(RouteArgs a) {
     for (int c = kRunCache; c < run.per_wave; ++c) emit(run.item(c), run.item(c) < run.hi ? ids[run.item(c)] : -1);
 }
 
-// Workgroups per layer for the calls that number pairs: runs of at least 2048 pairs (one workgroup numbers these in less time
-// than reading the other runs' ids takes: 2048 pairs 6.4 us as one run, 8.1 us as two; 8192 pairs 11.2 us as four runs,
-// 10.5 as eight), no more workgroups than CUs, and no more than 64 readers of one layer's ids.
+// Workgroups per layer for the calls that number pairs: runs of at least 2048 pairs, no more workgroups than CUs, and no more
+// than 64 readers of one layer's ids.  Counting the other runs' ids costs a workgroup about 1 us whatever their number, so
+// that one run is the better up to 2048 pairs; beyond, shorter runs would gain a little more.  Measured, 256 experts, us, runs of
+// at least 1024 / 2048 / 4096 pairs, METRO and token-balanced: 2048 pairs 8.9 / 7.9 / 7.9 and 7.9 / 7.5 / 7.5, 4096 pairs 9.1 / 9.5 / 9.2
+// and 8.0 / 8.8 / 9.5, 8192 pairs 9.6 / 10.1 / 11.0 and 8.6 / 9.4 / 11.0, 32768 pairs 13.6 / 14.1 / 15.0 and 11.8 / 12.6 / 14.4.
 inline int split_for(const RouteArgs& a, int L) {
     const int64_t n = (int64_t)a.T * a.k;
     const int64_t most = L >= 256 ? 1 : std::min(256 / L, 64);

@@ -64,9 +64,9 @@ def test_general_path_edges(oracle, dtype, H, I):
     check(oracle, dtype, H, I, [1, 16, 0, 17, 32, 33, 15, 65])
 
 
-# matrix-core path: rows at the edges of every tile class (16, 32, 48, 64 narrow; 96, 128 tall; beyond one tile), K of 2
-# steps (two of the four waves without any) and of step counts that end inside the prefetch ring, one shape of each
-# size class (tiles of 64 rows; 128 rows on the stream path; 128 rows on the wide path)
+# matrix-core path: rows at the edges of every tile class (16, 32, 48, 64 in a launch cut into narrow tiles; 16 narrow, 64, 96, 128
+# tall in the others; beyond one tile), K of 2 steps (two of the four waves without any) and of step counts that end inside
+# the prefetch ring.  At 128 x 128 both stages, at 1152 x 256 gate/up are cut into narrow tiles; the others have tall ones.
 @pytest.mark.parametrize("H,I", [(128, 128), (384, 640), (1152, 256), (2048, 1024), (4096, 2048)])
 def test_matrix_path_edges(oracle, H, I):
     check(oracle, "bf16", H, I, [1, 15, 16, 17, 31, 32, 33, 0, 47, 48, 49, 63, 64, 65, 96, 97, 128, 129, 200], T=700,

@@ -183,7 +183,8 @@ def test_shapes_beside_the_matrix_tiles(api, oracle, T, H, N, k, dtype):
 
 
 def test_nan_and_infinite_logits(api):
-    """NaN sorts below every number, +-infinity in their places, equal values to the lower id (also across the 64 lanes)."""
+    """A NaN logit counts as the lowest finite number, above -infinity; +-infinity in their places, equal values to the lower id
+    (also across the 64 lanes)."""
     import torch
 
     N, k, T = 200, 9, 4
