@@ -65,16 +65,18 @@ struct WorkList {
             begin = min(max(group_offsets[l], 0), cap);
             m = min(max(group_offsets[l + 1], begin), cap) - begin;
         }
-        // narrow and tall tiles in one scan; a clamped count is past every limit by itself
+        // narrow and tall tiles in one scan; a clamped slot is past every limit by itself
+        constexpr uint32_t kClamp = 1023 * kCutRows;
         static_assert(kFewItems < 1023 && 64 * 1023 < 65536, "the packed sums");
-        const int counts = __builtin_amdgcn_readlane(wave_inclusive_sum(min((m + kCutRows - 1) / kCutRows, 1023) |
-                                min((m + kTallRows - 1 - kNarrowRows) / kTallRows, 1023) << 16), kWave - 1);
-        const int cut = counts & 0xffff, tall = (int)((uint32_t)counts >> 16), rest = m & (kTallRows - 1);
+        const uint32_t u = min((uint32_t)m, kClamp);
+        const uint32_t counts = __builtin_amdgcn_readlane(wave_inclusive_sum((int)((u + kCutRows - 1) / kCutRows |
+                                    (u + kTallRows - 1 - kNarrowRows) / kTallRows << 16)), kWave - 1);
+        const int cut = (int)(counts & 0xffff), tall = (int)(counts >> 16), rest = m & (kTallRows - 1);
         const int small = __popcll(__ballot(rest > 0 && rest <= kNarrowRows));
         const bool narrow_only = cut <= rule.one_round || (cut <= rule.few && tall < rule.tall && 3 * small > tall);
         th = narrow_only ? kCutRows : kTallRows;
-        full = m / th;
-        part = m - full * th;
+        full = (uint32_t)m >> (narrow_only ? __builtin_ctz(kCutRows) : __builtin_ctz(kTallRows));
+        part = m & (th - 1);
         incl = wave_inclusive_sum(full);
         n_full = __builtin_amdgcn_readlane(incl, kWave - 1);
         // remainders: in classes of rows, larger ones first, inside a class by slot
