@@ -13,9 +13,11 @@ constexpr int kMaxSpr = 64;
 
 // From 17 rows on a tile is better tall: a narrow one reads its rows once per 64 weight rows, straight into registers.
 // Measured, gate/up + down, us, weights from HBM, narrow / tall: 36 slots of 17 / 24 / 32 rows at 7168 x 2048 565 / 602 / 640
-// against 560 / 566 / 575, 18 slots of them at 4096 x 1536 142 / 152 / 163 against 138 / 141 / 145.
+// against 560 / 566 / 575, 18 slots of them at 4096 x 1536 142 / 152 / 163 against 138 / 141 / 145.  Where a long launch has only
+// a few such tiles, they would start first and stand alone (a layer of 256 token-balanced tokens at 4096 x 1536 149.0 / 151.4).
 constexpr int kTallRows = 128;              // rows of a full tall tile
 constexpr int kNarrowRows = 16;             // tiles of at most this many rows are narrow,
+constexpr int kNarrowIfFew = 32;            // or of this many in launches past kFewItems of which few would be tall (kTallItems),
 constexpr int kCutRows = 64;                // or of this many where a launch is cut into narrow tiles only
 
 struct Tile {
@@ -83,14 +85,14 @@ struct WorkList {
         const uint64_t below = lanes_below();
         rank = 0;
         uint64_t larger = 0;
-        constexpr int kEdges[] = {96, 64, 32, kNarrowRows, 0};
+        constexpr int kEdges[] = {96, 64, kNarrowIfFew, kNarrowRows, 0};
 #pragma unroll
         for (int c = 0; c < 5; ++c) {
             const uint64_t in = __ballot(part > kEdges[c]) & ~larger;
             if (part > kEdges[c] && !((larger >> l) & 1)) rank = __popcll(larger) + __popcll(in & below);
             larger |= in;
         }
-        n_tall = narrow_only ? 0 : n_full + __popcll(__ballot(part > kNarrowRows));
+        n_tall = narrow_only ? 0 : n_full + __popcll(__ballot(part > (cut > rule.few && tall < rule.tall ? kNarrowIfFew : kNarrowRows)));
         n_tiles = n_full + __popcll(larger);
     }
 

@@ -74,9 +74,11 @@ def test_matrix_path_edges(oracle, H, I):
 
 
 # the rule that cuts a launch, at 384 x 640 (20 gate/up column tiles of a narrow tile, 10 of a tall one): 12 | 13 tiles of 64 rows
-# fill the CUs once; up to 38 the launch is narrow only if fewer than 17 tiles would be tall and more than a third as many small
+# fill the CUs once; up to 38 the launch is narrow only if fewer than 17 tiles would be tall and more than a third as many small;
+# past 38 tiles of 17 to 32 rows are narrow if fewer than 17 would be tall
 @pytest.mark.parametrize("sizes", [[16] * 12, [16] * 13, [33] * 12, [33] * 13, [65] * 6 + [1], [5] * 20 + [64] * 16, [5] * 20 + [64] * 17,
-                                   [1] * 5 + [40] * 15, [1] * 6 + [40] * 15, [16] * 38, [16] * 39, [16] * 10 + [64] * 28, [144] * 5])
+                                   [1] * 5 + [40] * 15, [1] * 6 + [40] * 15, [16] * 38, [16] * 39, [16] * 10 + [64] * 28, [144] * 5,
+                                   [5] * 30 + [24] * 7 + [32, 33, 40, 90], [5] * 22 + [24] * 17])
 def test_cut_rule_edges(oracle, sizes):
     check(oracle, "bf16", 384, 640, sizes, T=1000)
 
