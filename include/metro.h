@@ -66,8 +66,8 @@ const char* metro_status_string(int status);
  *                                 unspecified apart from being in range
  *
  * Shared memory, here and in the other routing calls: pair_slot may be the id tensor itself; outputs of the token
- * lists (see moe_permute) may lie anywhere in the ids or the placement of a call that routes and lists in one.
- * Apart from that an output must not overlap an input or another output.
+ * lists (see moe_permute) may lie anywhere in the ids or the placement of a call that routes and lists in one;
+ * n_pairs may be group_offsets + spr.  Apart from that an output must not overlap an input or another output.
  */
 int metro_route(const int32_t* topk_ids, const int32_t* slot_to_expert, int L, int T, int k, int N, int G,
                 int spr, int32_t* pair_slot, int32_t* expert_slot, int32_t* rank_active,

@@ -571,10 +571,11 @@ bool shares_memory(const RouteArgs& a, int L) {
         Range(const void* p, int64_t words) : begin((uintptr_t)p), end(p ? begin + 4 * (uintptr_t)words : begin) {}
     };
     const int64_t n = (int64_t)a.T * a.k, lists = a.list_rank >= 0;
+    const bool own_count = lists && a.n_pairs != a.group_offsets + a.spr;       // else the last offset itself, the same value
     const Range all[] = {{a.ids, L * n}, {a.slot_to_expert, (int64_t)L * a.G * a.spr},        // the inputs
                          {a.pair_slot, L * n}, {a.expert_slot, (int64_t)L * a.N}, {a.rank_active, (int64_t)L * a.G},
                          {a.rank_bitmap, (int64_t)L * a.G * 2}, {a.err_flag, L}, {a.group_offsets, lists * (a.spr + 1)},
-                         {a.perm_pair, lists * n}, {a.pair_row, lists * n}, {a.n_pairs, lists}};
+                         {a.perm_pair, lists * n}, {a.pair_row, lists * n}, {a.n_pairs, own_count}};
     for (int out = 2; out < (int)(sizeof(all) / sizeof(all[0])); ++out)
         for (int other = 0; other < out; ++other)
             if (all[out].begin < all[other].end && all[other].begin < all[out].end) return true;

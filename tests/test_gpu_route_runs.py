@@ -93,7 +93,8 @@ def test_slots_written_over_the_ids(oracle, T):
 
 
 def routed(routing, T, place=None):
-    """The fused call on T tokens, with `place` = (output, input, offset): that output in the input's memory, `offset` entries in.
+    """The fused call on T tokens, with `place` = (output, input, offset): that output in the input's memory, `offset` entries in;
+    or "count": n_pairs as the last entry of group_offsets.
     Returns every output (on the host) and the oracle's arguments."""
     import torch
 
@@ -104,7 +105,9 @@ def routed(routing, T, place=None):
     s2e, ids = W.placement(p, w.G, w.spr), W.topk_trace(p, T, w.k, T)
     inputs = dict(ids=dev(ids), s2e=dev(s2e))
     out, lists = api.route_buffers(1, T, w.k, w.N, w.G, "cuda"), api.permute_buffers(T, w.k, w.spr, "cuda")
-    if place:
+    if place == "count":                                     # n_pairs is the last offset
+        lists["n_pairs"] = lists["group_offsets"][w.spr:]
+    elif place:
         name, host, offset = place
         into = out if name in out else lists
         old = into[name]
@@ -117,7 +120,7 @@ def routed(routing, T, place=None):
 
 
 # 8192 pairs: the ids of a single workgroup fit its registers; 8200 and 16384: they do not; 16: one run
-@pytest.mark.parametrize("T,place", [(T, (name, "ids", 0)) for T in (2, 1024, 1025, 2048) for name in ("pair_slot", "perm_pair", "pair_row")] +
+@pytest.mark.parametrize("T,place", [(2, "count"), (2048, "count")] + [(T, (name, "ids", 0)) for T in (2, 1024, 1025, 2048) for name in ("pair_slot", "perm_pair", "pair_row")] +
                          [(1024, (name, host, offset)) for host in ("ids", "s2e") for offset in (0, 8)
                           for name in ("expert_slot", "rank_active", "rank_bitmap", "err_flag", "group_offsets", "n_pairs")])
 @pytest.mark.parametrize("routing", ["metro", "token_balanced"])
