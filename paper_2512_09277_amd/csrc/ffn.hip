@@ -1,12 +1,12 @@
 // moe_grouped_ffn for gfx950: SwiGLU expert FFN over one rank's per-slot token lists.
 //
 // Decode is HBM-bound: runtime follows the bytes of the activated experts' weights (Sec. 3.2 of
-// arxiv 2512.09277).  Every activated weight row is streamed from HBM once per tile, with 128-bit loads that
-// land directly in the matrix-core operand layout (16 rows x 64 contiguous bytes per instruction).
+// arxiv 2512.09277).  Every activated weight row is streamed from HBM once per tile, with loads of whole lines that get their
+// matrix-core operand layout in LDS.
 // Work is cut into tiles of one slot's rows:
 //   narrow tiles (at most 16 rows, 64 where the launch is short; the bulk of the bytes): ffn_split.h -- K split over the
-//       four waves, 64 weight rows per workgroup, activations straight into registers, no barrier in the K loop;
-//   tall tiles (up to 128 rows, the popular experts and large batches): dense_k.h -- both operands through LDS, 128 weight
+//       four waves, 64 weight rows per workgroup, each wave's operands through its own LDS, no barrier in the K loop;
+//   tall tiles (up to 128 rows, the popular experts and large batches): ring_k.h -- both operands through LDS, 128 weight
 //       rows per workgroup.  They are listed first.
 //   gate/up: a wave owns gate rows and the matching up rows, so silu(gate)*up is formed in
 //            registers and written once as bf16;   down: same structure over K = I.
@@ -16,14 +16,14 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 #include <utility>
 
-#include "dense_k.h"
 #include "ffn_common.h"
 #include "ffn_split.h"
-#include "host_utils.h"
 #include "metro.h"
+#include "ring_k.h"
 
 namespace metro {
 namespace {
@@ -46,67 +46,61 @@ struct FfnArgs {
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }
 
-constexpr int kLdsSplit = 4 * 4 * (kCutRows / 16) * 64 * (int)sizeof(floatx4);         // partial sums of four waves
-constexpr int kLdsBytes = std::max(kDenseLds, kLdsSplit);
-
-// Tall tile: 32 MT rows x 64 gate/up columns or 128 down columns, both operands through LDS (dense_k.h).  Bound by what the
-// L2s deliver (a 128 x 128 tile reads 32 KB per 2 MFLOP) at large batches and by latency times resident workgroups
-// elsewhere.  It replaced tiles whose weights went straight to registers, every wave reading all activations from
-// LDS: one K step in flight behind 128 accumulator registers, or 64 weight rows per workgroup.  Measured, gate/up + down,
-// us: 4096 tokens at 2048 x 768 111 + 63 -> 54 + 35; 512 tokens at 4096 x 1536 102 + 57 -> 92 + 49; 1024 tokens at
-// 7168 x 2048 (METRO rank) 381 + 200 -> 373 + 195, 369 + 194 since tiles of 17 to 32 rows are tall as well.  Contiguous runs of items per XCD, so that its L2 sees fewer slots:
-// 395 + 203 in the last case, no gain in the others.
+// Tall tile: 16 MT rows x 64 gate/up columns or 128 down columns, both operands through LDS (ring_k.h).  Bound, in launches of many
+// rows, by the work of a step inside a CU (with operands that cost no memory traffic 33 instead of 44 us for 4096 tokens at
+// 2048 x 768, of which the matrix instructions need 14), elsewhere by what the fabric delivers.  It replaced tiles with both operands
+// through registers, three steps deep, two LDS buffers with padded rows and the loads of a step behind its products.  Measured with
+// weights from HBM, gate/up + down, us: 4096 tokens at 2048 x 768 57 + 38.5 -> 51.3 + 35.2, 512 tokens at 4096 x 1536 108.7 + 56.7 ->
+// 108.4 + 53.6, 1024 tokens at 7168 x 2048 (METRO rank) 388.5 + 209 -> 388.3 + 205.1.  Weights straight to registers in operand layout:
+// slower than either (weights in the Infinity Cache, 50 + 34 against 44 + 31; 130 + 63; 425 + 218), see ring_k.h.
 template <bool kGateUp, int MT>
-__device__ __forceinline__ void dense_tile(const FfnArgs& a, const Tile t, char* lds) {
+__device__ __forceinline__ void ring_tile(const FfnArgs& a, const Tile t) {
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, q = lane >> 4, srow = tid >> 3;
     const int K = kGateUp ? a.H : a.I, n_out = kGateUp ? a.I : a.H;
     const int col0 = t.col * (kGateUp ? 64 : 128);
-    uint32_t x_lane[MT];                    // every activation byte offset fits 32 bits on this path
-    const char* wb[4];
+    uint32_t x_lane[MT / 2];                // every activation byte offset fits 32 bits on this path
+#pragma unroll
+    for (int p = 0; p < MT / 2; ++p) {
+        const int at = p * 32 + srow, row = t.row0 + min(at, t.rows - 1);          // rows past the tile repeat its last row
+        const int src = kGateUp ? min(max(a.perm_pair[row] / a.k, 0), a.T - 1) : row;
+        x_lane[p] = (uint32_t)src * (uint32_t)(K * 2) + ring_piece(at);
+    }
     const __bf16* wslot = a.w + (size_t)t.slot * (kGateUp ? 2 * a.I : a.H) * a.ldw;
+    const char* wb[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         const int row = kGateUp ? (p >> 1) * a.I + col0 + (p & 1) * 32 : col0 + p * 32;
         wb[p] = reinterpret_cast<const char*>(wslot + (size_t)row * a.ldw);
     }
-#pragma unroll
-    for (int p = 0; p < MT; ++p) {
-        const int row = t.row0 + min(p * 32 + srow, t.rows - 1);          // rows past the tile repeat its last row
-        const int src = kGateUp ? min(max(a.perm_pair[row] / a.k, 0), a.T - 1) : row;
-        x_lane[p] = (uint32_t)src * (uint32_t)(K * 2) + (tid & 7) * 16;
-    }
+    floatx4 acc[4][MT / 2];
+    ring_dot<MT>(reinterpret_cast<const char*>(a.src), x_lane, wb, (size_t)srow * a.ldw * 2 + (tid & 7) * 16, 0, K / kRingStep, acc);
     const int ty = wv >> 1, tx = wv & 1;
-    int wave_w[4];
 #pragma unroll
-    for (int b = 0; b < 4; ++b) wave_w[b] = kGateUp ? (b >> 1) * 64 + tx * 32 + (b & 1) * 16 : tx * 64 + b * 16;
-    floatx4 acc[4][MT];
-    dense_dot<MT>(reinterpret_cast<const char*>(a.src), x_lane, wb, (size_t)srow * a.ldw * 2 + (tid & 7) * 16, ty * 16 * MT, wave_w, 0, K / kDenseBK, lds, acc);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int row = (ty * MT + mt) * 16 + r16;
+    for (int mt = 0; mt < MT / 2; ++mt) {
+        const int row = (mt * 2 + ty) * 16 + r16;
         if (row >= t.rows) continue;
-        __bf16* out = a.dst + (size_t)(t.row0 + row) * n_out + q * 4;
+        __bf16* out = a.dst + (size_t)(t.row0 + row) * n_out + col0 + tx * 32 + q * 4;
         if (kGateUp) {
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
                 const floatx4 g = acc[b][mt], u = acc[b + 2][mt];
-                *reinterpret_cast<u32x2*>(out + col0 + tx * 32 + b * 16) =
+                *reinterpret_cast<u32x2*>(out + b * 16) =
                     u32x2{pack_bf16x2(silu(g[0]) * u[0], silu(g[1]) * u[1]), pack_bf16x2(silu(g[2]) * u[2], silu(g[3]) * u[3])};
             }
         } else {
 #pragma unroll
             for (int b = 0; b < 4; ++b)
-                *reinterpret_cast<u32x2*>(out + col0 + tx * 64 + b * 16) =
+                *reinterpret_cast<u32x2*>(out + (b >> 1) * 64 + (b & 1) * 16) =
                     u32x2{pack_bf16x2(acc[b][mt][0], acc[b][mt][1]), pack_bf16x2(acc[b][mt][2], acc[b][mt][3])};
         }
     }
 }
 
-// Narrow tiles.  Measured against tiles staged through LDS with a barrier per K step (gate/up + down, us): 8 tokens of the
-// 2048 x 768 shape 21 + 10 -> 13 + 6.5 (twice the workgroups for the same bytes, nobody waits for a sibling wave's loads);
-// 256 tokens of it 38 + 18 -> 30 + 16; 97 tokens of the 7168 x 2048 shape (token-balanced) 288 + 152 -> 268 + 138; 1024
-// tokens of it (METRO, whose time is in the tall tiles) 384 + 205 -> 383 + 201.
+// Narrow tiles: K split over the waves, whole lines loaded, operand layout through the wave's LDS (split_k.h).  Measured against
+// loads in operand layout, which left a CU at 38 GB/s for both operands together (gate/up + down, us, weights from HBM): 256 tokens of
+// the 2048 x 768 shape 29.2 + 16.0 -> 24.9 + 14.7, 512 tokens at 4096 x 1536 (about half of the time narrow tiles) 108.5 + 53.6 ->
+// 94.9 + 48.6, 1024 tokens at 7168 x 2048 (METRO rank) 388 + 205 -> 378 + 201, 97 tokens of it 291 + 145.5 -> 288 + 145.
 //   Blocks: 2 instead of 4 weight blocks per workgroup re-read the activations twice as often and lose everywhere (97 tokens:
 //   276 + 177).
 //   Depth: what 256 registers hold.
@@ -117,71 +111,89 @@ constexpr int kNarrowBlocks = 4;
 // tokens, gate/up).
 constexpr int kNarrowGrid = 1536;
 
+// The ring's LDS as split_tile uses it: per wave a step of weights and of activations, then the partial sums.
+struct NarrowLds {
+    __device__ __forceinline__ char* wave_w(int wave) const { return ring_buf_at(2 * wave); }
+    __device__ __forceinline__ char* wave_x(int wave) const { return ring_buf_at(2 * wave + 1); }
+    __device__ __forceinline__ floatx4* part(int u) const { return reinterpret_cast<floatx4*>(ring_buf_at(u >> 1) + (u & 1) * (kRingBuf / 2)); }
+};
+
 template <bool kGateUp>
 __global__ __launch_bounds__(kThreads, 2) void ffn_mfma_kernel(FfnArgs a) {
-    extern __shared__ __attribute__((aligned(16))) char lds[];
-    // Work items = (tile, column tile), tall tiles first: their workgroups live longest, so they start early for the
-    // narrow ones to fill in around them.  Everything here is uniform per workgroup.
+    // Work items = (tile, column tile).  Every XCD has a list of them, tall tiles first: their workgroups live longest, so they
+    // start early for the narrow ones to fill in around them.  Everything here is uniform per workgroup.
     WorkList wl;
     wl.read(a.group_offsets, a.spr, a.T * a.k, a.rule);
-    const int tall_items = wl.n_tall * a.ntt;
-    int id = blockIdx.x;
-    if (id < tall_items) {
-        const int ti = id / a.ntt;
-        const Tile t = wl.tile(ti, id - ti * a.ntt);
-        if (t.rows <= 64) dense_tile<kGateUp, 2>(a, t, lds);
-        else if (t.rows <= 96) dense_tile<kGateUp, 3>(a, t, lds);
-        else dense_tile<kGateUp, 4>(a, t, lds);
+    const int xcd = blockIdx.x & 7, tall = wl.list_tall(xcd, a.ntt);
+    int id = blockIdx.x >> 3;
+    if (id < tall) {
+        const Tile t = wl.tall(id);
+        if (t.rows <= 32) ring_tile<kGateUp, 2>(a, t);
+        else if (t.rows <= 64) ring_tile<kGateUp, 4>(a, t);
+        else if (t.rows <= 96) ring_tile<kGateUp, 6>(a, t);
+        else ring_tile<kGateUp, 8>(a, t);
         return;
     }
+    const NarrowLds lds;
     const SplitArgs sa{a.src, a.perm_pair, a.w, a.dst, a.T, a.k, a.H, a.I, a.ldw};
-    const int n = (wl.n_tiles - wl.n_tall) * a.ntn, stride = gridDim.x - tall_items;
-    for (id -= tall_items; id < n; id += stride) {
+    const int n = wl.n_narrow * a.ntn, stride = gridDim.x - tall * 8;
+    for (id = (id - tall) * 8 + xcd; id < n; id += stride) {
         const int ti = id / a.ntn;
-        const Tile t = wl.tile(wl.n_tall + ti, id - ti * a.ntn);
-        if (t.rows <= 16) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 1, 4, KRows::kWhole>(sa, t, lds);
-        else if (t.rows <= 32) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 2, 3, KRows::kWhole>(sa, t, lds);
-        else if (t.rows <= 48) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 3, 2, KRows::kWhole>(sa, t, lds);
-        else split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 4, 2, KRows::kWhole>(sa, t, lds);
+        const Tile t = wl.narrow(ti, id - ti * a.ntn);
+        if (t.rows <= 16) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 1, 3, KRows::kWhole>(sa, t, lds);
+        else if (t.rows <= 32) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 2, 2, KRows::kWhole>(sa, t, lds);
+        else if (t.rows <= 48) split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 3, 1, KRows::kWhole>(sa, t, lds);
+        else split_tile<kGateUp, __bf16, __bf16, __bf16, kNarrowBlocks, 4, 1, KRows::kWhole>(sa, t, lds);
         __syncthreads();                                                 // the next item's sums reuse the LDS
     }
 }
 
-// Workgroups: one per item of the most tall tiles `cap` rows can make, and the narrow ones.
+// Workgroups, a multiple of 8: per XCD one for each of the most tall items that `cap` rows can make, and the narrow ones.
 inline int mfma_grid(const FfnArgs& a, int cap, int spr) {
     const int tall = std::min(cap / (kNarrowRows + 1), max_tiles(cap, spr, kTallRows));
     const int narrow = std::min(a.ntn * (std::min(spr, cap) + cap / kNarrowRows), kNarrowGrid);
-    return tall * a.ntt + narrow;
+    return tall * ((a.ntt + 7) & ~7) + ((narrow + 7) & ~7);
 }
 
 // ------------------------------------------------------------------------------------------ general path
 // fp32 storage, and 16-bit shapes whose H or I is no multiple of 128 (activations between the stages in fp32): K-split
-// tiles (ffn_split.h) of at most 32 rows x 16 gate/up columns or 32 down columns.  What bounds it is HBM latency times
-// occupancy (fp32 matrix instructions take about a third of the time at 32 rows), so the tiles are small -- many
-// workgroups -- and registers are kept low enough for three workgroups per CU.  Measured on the 17-slot, 362-row
-// fp32 rank of the 2048 x 768 shape, gate/up + down: 94 + 42 us with 64 rows x 32/64 columns at two workgroups per CU,
-// 71 + 39 us with 32 rows x 16/32 columns, 73 + 36 us with three per CU and weight loads ahead of the token list's
-// (this one; 77 + 37 without the latter on the same box); on 2000 x 712 in bf16 30 + 22 us against 33 + 28 us.  (The vector-ALU kernels these replaced: 328 + 119 and 440 + 137 us.)
-constexpr int kGenRows = 32;
+// tiles (ffn_split.h) of at most 32 rows x 16 gate/up columns or 32 down columns, of 16 rows where 16-bit weights meet fp32
+// activations.  What bounds it is latency and, in fp32, the matrix instructions (46 % of the time at 362 rows over 17 slots), so
+// registers are kept low enough for four workgroups per CU, a single step of loads in flight per wave (three and two steps at three
+// workgroups per CU: 57.5 + 30.3 us against 54.0 + 30.2; 64 rows or four weight blocks a tile lose 5 %).  Measured, gate/up + down, us,
+// weights from HBM: 362 rows of the 2048 x 768 shape in fp32 72.6 + 36.5 -> 54.0 + 30.2, 2000 x 712 in bf16 27.0 + 22.6 -> 24.4 + 20.9,
+// with operands loaded in operand layout (both stages then took what a CU gets of such loads, see ring_k.h).
+constexpr int kGenRows = 32, kGenWideRows = 16;
 constexpr int kGenBlocks = 2;               // 16-row weight blocks of a workgroup
 constexpr int kGenGateUpCols = kGenBlocks * 8, kGenDownCols = kGenBlocks * 16;
-constexpr int kGenLds = 4 * kGenBlocks * (kGenRows / 16) * 64 * (int)sizeof(floatx4);
-// Two rounds of the 768 resident workgroups; more items loop.  (The grid can only be sized for a rank that gets every
+// One and a half rounds of the 1024 resident workgroups; more items loop.  (The grid can only be sized for a rank that gets every
 // pair of the batch; a workgroup that finds no item costs about 2 ns.)
 constexpr int kGenGrid = 1536;
 
+template <bool kGateUp, typename WT>
+constexpr int gen_rows() { return !kGateUp && sizeof(WT) == 2 ? kGenWideRows : kGenRows; }
+
 template <bool kGateUp, typename WT, KRows kRows>
-__global__ __launch_bounds__(kThreads, 3) void general_ffn_kernel(SplitArgs a, const int32_t* __restrict__ group_offsets,
+__global__ __launch_bounds__(kThreads, kRows == KRows::kTiny ? 3 : 4) void general_ffn_kernel(SplitArgs a, const int32_t* __restrict__ group_offsets,
                                                                   int spr, int n_cols, int64_t n_items) {
-    __shared__ __attribute__((aligned(16))) char lds[kGenLds];
     using XT = std::conditional_t<kGateUp, WT, float>;
     using OT = std::conditional_t<kGateUp, float, WT>;
+    constexpr int kRowsMax = gen_rows<kGateUp, WT>(), MT = kRowsMax / 16;
+    constexpr int kW = split_w_bytes<WT, XT, kGenBlocks, MT>(), kWave = kW + split_x_bytes<WT, XT, kGenBlocks, MT>();
+    __shared__ __attribute__((aligned(16))) char mem[4 * kWave];
+    static_assert(sizeof(mem) >= 4 * kGenBlocks * MT * 64 * sizeof(floatx4), "the partial sums");
+    struct Lds {
+        char* mem;
+        __device__ __forceinline__ char* wave_w(int wave) const { return mem + wave * kWave; }
+        __device__ __forceinline__ char* wave_x(int wave) const { return mem + wave * kWave + kW; }
+        __device__ __forceinline__ floatx4* part(int u) const { return reinterpret_cast<floatx4*>(mem) + u * 4 * 64; }
+    };
+    const Lds lds{mem};
     for (int64_t id = blockIdx.x; id < n_items; id += gridDim.x) {
-        const Item it = locate_in_order(group_offsets, spr, a.T * a.k, kGenRows, n_cols, id);
+        const Item it = locate_in_order(group_offsets, spr, a.T * a.k, kRowsMax, n_cols, id);
         if (!it.valid) return;                                       // uniform; items are consecutive
-        if constexpr (kRows == KRows::kTiny) split_tile<kGateUp, WT, XT, OT, kGenBlocks, 2, 1, kRows>(a, it.tile, lds);
-        else if (it.tile.rows <= 16) split_tile<kGateUp, WT, XT, OT, kGenBlocks, 1, 3, kRows>(a, it.tile, lds);
-        else split_tile<kGateUp, WT, XT, OT, kGenBlocks, 2, 2, kRows>(a, it.tile, lds);
+        if (kRows != KRows::kTiny && it.tile.rows <= 16) split_tile<kGateUp, WT, XT, OT, kGenBlocks, 1, 1, kRows>(a, it.tile, lds);
+        else split_tile<kGateUp, WT, XT, OT, kGenBlocks, MT, 1, kRows>(a, it.tile, lds);
         __syncthreads();                                             // the next item's sums reuse the LDS
     }
 }
@@ -190,7 +202,8 @@ template <bool kGateUp>
 int launch_general(const SplitArgs& a, const int32_t* group_offsets, int spr, int dtype, hipStream_t st) {
     const int n_out = kGateUp ? a.I : a.H, K = kGateUp ? a.H : a.I;
     const int cols = kGateUp ? kGenGateUpCols : kGenDownCols, n_cols = (n_out + cols - 1) / cols;
-    const int64_t n_items = (int64_t)max_tiles(a.T * a.k, spr, kGenRows) * n_cols;
+    const int rows = dtype == METRO_DTYPE_F32 ? gen_rows<kGateUp, float>() : gen_rows<kGateUp, __bf16>();
+    const int64_t n_items = (int64_t)max_tiles(a.T * a.k, spr, rows) * n_cols;
     const uint32_t grid = (uint32_t)(n_items < kGenGrid ? n_items : kGenGrid);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, st, a, group_offsets, spr, n_cols, n_items);
@@ -232,18 +245,6 @@ int check_common(const int32_t* group_offsets, int T, int k, int spr, int H, int
     if (((uintptr_t)ws & 255) != 0) return METRO_ERR_INVALID_ARG;
     if (ws_bytes < moe_grouped_ffn_workspace_bytes(T, k, spr, H, I, dtype)) return METRO_ERR_WORKSPACE;
     return METRO_OK;
-}
-
-int enable_large_lds() {                            // opt in to > 64 KB of dynamic LDS, once per device
-    static PerDeviceOnce once;
-    return once.run([] {
-        hipError_t e = hipFuncSetAttribute((const void*)ffn_mfma_kernel<true>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void*)ffn_mfma_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    kLdsBytes);
-        return e;
-    });
 }
 
 inline int launched() { return hipGetLastError() == hipSuccess ? METRO_OK : METRO_ERR_HIP; }
@@ -296,7 +297,6 @@ extern "C" int moe_grouped_ffn_gate_up(const void* x, const int32_t* perm_pair, 
         const SplitArgs g{x, perm_pair, w13, act, T, k, H, I, ldw13};
         return launch_general<true>(g, group_offsets, spr, dtype, st);
     }
-    if (enable_large_lds() != METRO_OK) return METRO_ERR_HIP;
     FfnArgs a;
     a.src = (const __bf16*)x;
     a.perm_pair = perm_pair;
@@ -308,7 +308,7 @@ extern "C" int moe_grouped_ffn_gate_up(const void* x, const int32_t* perm_pair, 
     a.ntt = I / 64;
     a.ntn = I / (kNarrowBlocks * 8);
     a.rule = CutRule(a.ntn, a.ntt);
-    hipLaunchKernelGGL(ffn_mfma_kernel<true>, dim3(mfma_grid(a, cap, spr)), dim3(kThreads), kLdsBytes, st, a);
+    hipLaunchKernelGGL(ffn_mfma_kernel<true>, dim3(mfma_grid(a, cap, spr)), dim3(kThreads), 0, st, a);
     return launched();
 }
 
@@ -328,7 +328,6 @@ extern "C" int moe_grouped_ffn_down(const int32_t* group_offsets, int T, int k, 
         const SplitArgs g{act, nullptr, w2, y_perm, T, k, H, I, ldw2};
         return launch_general<false>(g, group_offsets, spr, dtype, st);
     }
-    if (enable_large_lds() != METRO_OK) return METRO_ERR_HIP;
     FfnArgs a;
     a.src = (const __bf16*)act;
     a.perm_pair = nullptr;
@@ -340,7 +339,7 @@ extern "C" int moe_grouped_ffn_down(const int32_t* group_offsets, int T, int k, 
     a.ntt = H / 128;
     a.ntn = H / (kNarrowBlocks * 16);
     a.rule = CutRule(a.ntn, a.ntt);
-    hipLaunchKernelGGL(ffn_mfma_kernel<false>, dim3(mfma_grid(a, cap, spr)), dim3(kThreads), kLdsBytes, st, a);
+    hipLaunchKernelGGL(ffn_mfma_kernel<false>, dim3(mfma_grid(a, cap, spr)), dim3(kThreads), 0, st, a);
     return launched();
 }
 

@@ -11,10 +11,10 @@ namespace {
 
 constexpr int kMaxSpr = 64;
 
-// From 17 rows on a tile is better tall: a narrow one reads its rows once per 64 weight rows, straight into registers.
-// Measured, gate/up + down, us, weights from HBM, narrow / tall: 36 slots of 17 / 24 / 32 rows at 7168 x 2048 565 / 602 / 640
-// against 560 / 566 / 575, 18 slots of them at 4096 x 1536 142 / 152 / 163 against 138 / 141 / 145.  Where a long launch has only
-// a few such tiles, they would start first and stand alone (a layer of 256 token-balanced tokens at 4096 x 1536 149.0 / 151.4).
+// From 17 rows on a tile is better tall: a narrow one reads its rows once per 64 weight rows.  Measured, a layer, us, narrow up to
+// 16 / 32 / 48 / 64 rows: 1024 tokens at 7168 x 2048 (METRO rank) 606 / 607 / 611 / 615, 97 tokens of it 443.3 / 445.0 / 444.8 / 445.4,
+// 512 tokens at 4096 x 1536 150.7 / 151.7 / 152.9 / 151.6.  Where a long launch has only a few such tiles, they would start first
+// and stand alone (a layer of 256 token-balanced tokens at 4096 x 1536 149.0 / 151.4 with tiles that loaded in operand layout).
 constexpr int kTallRows = 128;              // rows of a full tall tile
 constexpr int kNarrowRows = 16;             // tiles of at most this many rows are narrow,
 constexpr int kNarrowIfFew = 32;            // or of this many in launches past kFewItems of which few would be tall (kTallItems),
@@ -30,8 +30,8 @@ inline int max_tiles(int cap, int spr, int tile_rows) { return spr + cap / tile_
 // ------------------------------------------------------------------------------------------ work items
 // A slot of m rows gives m / th full tiles of th rows and one tile for the remainder.  Launches of few work items cut all
 // slots into narrow tiles (th = 64); the others cut 128-row tiles, of which the full ones and the remainders above 16 rows
-// are tall.  Tile order: full tiles, then the remainders, larger classes of rows first (ties: lower slot first), so tall
-// ones come first.  Work item = (tile, column tile), tile-major.
+// are tall.  Tall ones come first, slot by slot; of the narrow ones full tiles, then the remainders, larger classes of rows
+// first (ties: lower slot first).  Work item = (tile, column tile), for narrow ones tile-major.
 // Every workgroup derives its own items from group_offsets (65 integers, one memory round trip, some
 // hundred scalar-ish instructions): no planning kernel, no list in memory.  Each wave computes the
 // same result with lane = local slot.
@@ -56,8 +56,11 @@ struct CutRule {
 
 // The slots' tiles in the registers of a wave (lane = local slot), from which any item can be picked.
 struct WorkList {
-    int begin, full, part, incl, rank;          // per lane
-    int th, n_full, n_tall, n_tiles;            // uniform
+    int begin, rows;                            // per lane: the slot's rows
+    int tall_tiles;                             // tall tiles of the slot
+    int tall_first, tall_mine, tall_incl;       // in the XCD's list: first column, items of the slot, of the slots up to it
+    int full, part, incl, rank, narrow_begin;   // full narrow tiles, rows of the remainder; narrow rows start here
+    int n_full, n_narrow;                       // uniform
 
     __device__ __forceinline__ void read(const int32_t* __restrict__ group_offsets, int spr, int cap, const CutRule& rule) {
         const int l = lane_id();
@@ -76,40 +79,72 @@ struct WorkList {
         const int cut = (int)(counts & 0xffff), tall = (int)(counts >> 16), rest = m & (kTallRows - 1);
         const int small = __popcll(__ballot(rest > 0 && rest <= kNarrowRows));
         const bool narrow_only = cut <= rule.one_round || (cut <= rule.few && tall < rule.tall && 3 * small > tall);
-        th = narrow_only ? kCutRows : kTallRows;
-        full = (uint32_t)m >> (narrow_only ? __builtin_ctz(kCutRows) : __builtin_ctz(kTallRows));
-        part = m & (th - 1);
+        const int limit = cut > rule.few && tall < rule.tall ? kNarrowIfFew : kNarrowRows;
+        rows = m;
+        full = narrow_only ? (uint32_t)m / kCutRows : (uint32_t)m / kTallRows;
+        part = narrow_only ? m & (kCutRows - 1) : rest;
+        tall_tiles = narrow_only ? 0 : full + (part > limit);
+        narrow_begin = begin;
+        if (!narrow_only) {                     // what the tall tiles leave: remainders up to the limit
+            narrow_begin += full * kTallRows;
+            full = 0;
+            if (part > limit) part = 0;
+        }
         incl = wave_inclusive_sum(full);
         n_full = __builtin_amdgcn_readlane(incl, kWave - 1);
         // remainders: in classes of rows, larger ones first, inside a class by slot
         const uint64_t below = lanes_below();
         rank = 0;
         uint64_t larger = 0;
-        constexpr int kEdges[] = {96, 64, kNarrowIfFew, kNarrowRows, 0};
+        constexpr int kEdges[] = {48, 32, 16, 0};
 #pragma unroll
-        for (int c = 0; c < 5; ++c) {
+        for (int c = 0; c < 4; ++c) {
             const uint64_t in = __ballot(part > kEdges[c]) & ~larger;
             if (part > kEdges[c] && !((larger >> l) & 1)) rank = __popcll(larger) + __popcll(in & below);
             larger |= in;
         }
-        n_tall = narrow_only ? 0 : n_full + __popcll(__ballot(part > (cut > rule.few && tall < rule.tall ? kNarrowIfFew : kNarrowRows)));
-        n_tiles = n_full + __popcll(larger);
+        n_narrow = n_full + __popcll(larger);
     }
 
-    __device__ __forceinline__ Tile tile(int ti, int col) const {
+    // The tall items of an XCD; returns their number.  Workgroup i runs on XCD i mod 8, each with an L2 of its own.  The tiles of a
+    // column of one slot read the same weights: they are neighbours in the list of one XCD.  The columns of a slot go round the XCDs, so
+    // that each has the same share of every slot.  Measured, gate/up + down, us, against items by tile, columns inside: 4096 tokens
+    // at 2048 x 768 47.6 + 31.9 / 54.1 + 34.3, 512 tokens at 4096 x 1536 107.9 + 53.0 / 108.6 + 53.4, 1024 tokens at 7168 x 2048 376.9 +
+    // 201.1 / 375.0 + 202.4.  Columns round 4 or 2 XCDs, whose L2s then take fewer rows, but unequal shares of the slots, are slower
+    // (by 4 to 7 and 15 to 23 %), and so is an eighth of the items in one piece (4096 x 1536: 112.8 + 59.4).
+    __device__ __forceinline__ int list_tall(int xcd, int n_cols) {
+        tall_first = (xcd - lane_id() * n_cols) & 7;
+        tall_mine = tall_tiles * ((n_cols - tall_first + 7) >> 3);
+        tall_incl = wave_inclusive_sum(tall_mine);
+        return __builtin_amdgcn_readlane(tall_incl, kWave - 1);
+    }
+    __device__ __forceinline__ Tile tall(int i) const {
+        const uint64_t owner = __ballot(tall_incl - tall_mine <= i && i < tall_incl);      // exactly one lane
+        const int o = __ffsll((unsigned long long)owner) - 1;
+        const int tiles = __builtin_amdgcn_readlane(tall_tiles, o), at = i - __builtin_amdgcn_readlane(tall_incl - tall_mine, o);
+        const int c = (uint32_t)at / (uint32_t)tiles, row = (at - c * tiles) * kTallRows;
+        Tile t;
+        t.slot = o;
+        t.col = __builtin_amdgcn_readlane(tall_first, o) + c * 8;
+        t.row0 = __builtin_amdgcn_readlane(begin, o) + row;
+        t.rows = min(kTallRows, __builtin_amdgcn_readlane(rows, o) - row);
+        return t;
+    }
+
+    __device__ __forceinline__ Tile narrow(int ti, int col) const {
         Tile t;
         t.col = col;
         if (ti < n_full) {
             const uint64_t owner = __ballot(incl - full <= ti && ti < incl);      // exactly one lane
             const int o = __ffsll((unsigned long long)owner) - 1;
             t.slot = o;
-            t.rows = th;
-            t.row0 = __builtin_amdgcn_readlane(begin, o) + (ti - __builtin_amdgcn_readlane(incl - full, o)) * th;
+            t.rows = kCutRows;
+            t.row0 = __builtin_amdgcn_readlane(narrow_begin, o) + (ti - __builtin_amdgcn_readlane(incl - full, o)) * kCutRows;
         } else {
             const uint64_t owner = __ballot(part > 0 && n_full + rank == ti);     // exactly one lane
             const int o = __ffsll((unsigned long long)owner) - 1;
             t.slot = o;
-            t.row0 = __builtin_amdgcn_readlane(begin + full * th, o);
+            t.row0 = __builtin_amdgcn_readlane(narrow_begin + full * kCutRows, o);
             t.rows = __builtin_amdgcn_readlane(part, o);
         }
         return t;

@@ -32,8 +32,8 @@ struct SplitArgs {
 };
 
 // WT weights, XT activations, OT output.
-template <bool kGateUp, typename WT, typename XT, typename OT, int NB, int MT, int DEPTH, KRows kRows>
-__device__ __forceinline__ void split_tile(const SplitArgs& a, const Tile t, char* lds) {
+template <bool kGateUp, typename WT, typename XT, typename OT, int NB, int MT, int DEPTH, KRows kRows, typename Lds>
+__device__ __forceinline__ void split_tile(const SplitArgs& a, const Tile t, Lds lds) {
     constexpr int kVec = 16 / (int)sizeof(WT);              // k per lane and load
     constexpr int kStep = 8 * kVec;                         // k per step
     constexpr int kUnits = kGateUp ? NB / 2 : NB;           // 16-column blocks of the output
@@ -47,48 +47,39 @@ __device__ __forceinline__ void split_tile(const SplitArgs& a, const Tile t, cha
     const int mt_count = (t.rows + 15) >> 4;
     const int col0 = t.col * kUnits * 16;
 
-    // Whole rows (the host checks that activation offsets fit): a uniform base per block and 32-bit lane offsets, which
-    // leaves the vector registers to the data in flight.  Otherwise a pointer per lane, rows past the last column
-    // repeating it.
-    constexpr bool kWhole = kRows == KRows::kWhole;
-    const WT* wslot = reinterpret_cast<const WT*>(a.w) + (size_t)t.slot * (kGateUp ? 2 * a.I : a.H) * a.ldw;
-    const WT* pw[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int at = col0 + (b % kUnits) * 16, col = kWhole ? at : min(at + r16, n_out - 1);
-        pw[b] = wslot + (size_t)((kGateUp && b >= kUnits) ? a.I + col : col) * a.ldw;
-    }
-    const uint32_t w_lane = (uint32_t)(r16 * a.ldw + q * kVec);
-    int token[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int row = t.row0 + min(mt * 16 + r16, t.rows - 1);    // rows past the tile repeat its last row
-        token[mt] = kGateUp ? a.perm_pair[row] : row;
-    }
-    auto x_rows = [&](const XT* (&px)[MT], uint32_t (&x_lane)[MT]) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const int src = kGateUp ? min(max(token[mt] / a.k, 0), a.T - 1) : token[mt];
-            px[mt] = reinterpret_cast<const XT*>(a.src) + (kWhole ? 0 : (size_t)src * K);
-            x_lane[mt] = (uint32_t)src * (uint32_t)K + q * kVec;
-        }
+    auto w_block = [&](int b) { return (kGateUp && b >= kUnits ? a.I : 0) + col0 + (b % kUnits) * 16; };
+    auto w_row = [&](int b, int r) { return w_block(b) + min(r, n_out - 1 - (col0 + (b % kUnits) * 16)); };  // past the last column: that one
+    auto x_row = [&](int mt, int r) {
+        const int row = t.row0 + min(mt * 16 + r, t.rows - 1);      // past the tile: its last row
+        return kGateUp ? min(max(a.perm_pair[row] / a.k, 0), a.T - 1) : row;
     };
-
+    struct Rows {
+        const WT* w_base;
+        const XT* x_base;
+        int w_pitch, x_pitch;
+        decltype(w_block) w_block;
+        decltype(w_row) w_row;
+        decltype(x_row) x_row;
+    };
+    const WT* wslot = reinterpret_cast<const WT*>(a.w) + (size_t)t.slot * (kGateUp ? 2 * a.I : a.H) * a.ldw;
     floatx4 acc[NB][MT];
-    split_dot<WT, XT, NB, MT, DEPTH, kRows>(pw, w_lane, x_rows, K, wv, 4, mine, acc);
+    split_dot<WT, XT, NB, MT, DEPTH, kRows>(Rows{wslot, reinterpret_cast<const XT*>(a.src), a.ldw, K, w_block, w_row, x_row}, K, wv, 4,
+                                            mine, lds.wave_w(wv), lds.wave_x(wv), acc);
+    __syncthreads();                                        // the partial sums take the LDS of all waves
 
-    // partial sums of the four waves, [wave][b][mt][lane]; the sums of a block are formed in wave order
-    floatx4* part = reinterpret_cast<floatx4*>(lds);
+    // partial sums of the four waves, [block][row sub-tile][wave][lane]; a sum is formed in wave order.  lds.part(u): the LDS of
+    // (block, sub-tile) u.
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
-            if (mt < mt_count) part[((wv * NB + b) * MT + mt) * 64 + lane] = acc[b][mt];
+            if (mt < mt_count) lds.part(b * MT + mt)[wv * 64 + lane] = acc[b][mt];
     __syncthreads();
-    auto total = [&](int b, int mt) {
-        floatx4 s = part[(b * MT + mt) * 64 + lane];
+    auto total = [&](int u) {
+        const floatx4* p = lds.part(u) + lane;
+        floatx4 s = p[0];
 #pragma unroll
-        for (int o = 1; o < 4; ++o) s += part[((o * NB + b) * MT + mt) * 64 + lane];
+        for (int o = 1; o < 4; ++o) s += p[o * 64];
         return s;
     };
 #pragma unroll
@@ -97,11 +88,11 @@ __device__ __forceinline__ void split_tile(const SplitArgs& a, const Tile t, cha
         if (u >= kUnits * MT || mt >= mt_count) continue;
         const int row = mt * 16 + r16, col = col0 + b * 16 + q * 4;
         float o[4];
-        const floatx4 g = total(b, mt);
+        const floatx4 g = total(u);
         if (kGateUp) {
-            const floatx4 up = total(b + kUnits, mt);
+            const floatx4 h = total(u + kUnits * MT);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) o[v] = g[v] / (1.0f + (sizeof(OT) == 4 ? expf(-g[v]) : __expf(-g[v]))) * up[v];
+            for (int v = 0; v < 4; ++v) o[v] = g[v] / (1.0f + (sizeof(OT) == 4 ? expf(-g[v]) : __expf(-g[v]))) * h[v];
         } else {
 #pragma unroll
             for (int v = 0; v < 4; ++v) o[v] = g[v];

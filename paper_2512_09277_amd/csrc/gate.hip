@@ -24,10 +24,9 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "dense_k.h"
 #include "device_utils.h"
-#include "host_utils.h"
 #include "metro.h"
+#include "ring_k.h"
 #include "split_k.h"
 
 namespace metro {
@@ -129,37 +128,34 @@ __global__ __launch_bounds__(kThreads, 2) void gate_logits_mfma_kernel(GateArgs 
     }
 }
 
-// Large batches: one workgroup = 32 MT tokens x 128 experts x one K chunk, both operands staged through LDS (dense_k.h).
-constexpr int kBigTile = kDenseRows;                             // experts of a workgroup
+// Large batches: one workgroup = 16 MT tokens x 128 experts x one K chunk, both operands staged through LDS (ring_k.h).
+constexpr int kBigTile = kRingRows;                              // experts of a workgroup
 
 template <int MT>
 __global__ __launch_bounds__(kThreads, 2) void gate_logits_lds_kernel(GateArgs a) {
-    extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, q = lane >> 4, srow = tid >> 3;
-    const int chunk = blockIdx.x, t0 = blockIdx.y * (32 * MT), e0 = blockIdx.z * kBigTile;
-    const int n_steps = a.H / kDenseBK;                           // the host takes this path only if H % 64 == 0
+    const int chunk = blockIdx.x, t0 = blockIdx.y * (16 * MT), e0 = blockIdx.z * kBigTile;
+    const int n_steps = a.H / kRingStep;                          // the host takes this path only if H % 64 == 0
     const int s_begin = chunk * a.steps_per_chunk, s_end = min(s_begin + a.steps_per_chunk, n_steps);
-    uint32_t x_lane[MT];                                          // from the tile's first token
+    uint32_t x_lane[MT / 2];                                      // from the tile's first token
 #pragma unroll
-    for (int p = 0; p < MT; ++p)                                  // rows past the batch repeat the last token
-        x_lane[p] = (uint32_t)(min(t0 + p * 32 + srow, a.T - 1) - t0) * (uint32_t)(a.H * 2) + (tid & 7) * 16;
+    for (int p = 0; p < MT / 2; ++p)                              // rows past the batch repeat the last token
+        x_lane[p] = (uint32_t)(min(t0 + p * 32 + srow, a.T - 1) - t0) * (uint32_t)(a.H * 2) + ring_piece(p * 32 + srow);
     const char* w[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) w[p] = reinterpret_cast<const char*>(a.w_gate) + (size_t)(e0 + p * 32) * a.ldw * 2;
-    const int ty = wv >> 1, tx = wv & 1;                          // wave: tokens [16 MT ty, ..), experts [64 tx, +64)
-    const int wave_w[4] = {tx * 64, tx * 64 + 16, tx * 64 + 32, tx * 64 + 48};
-    floatx4 acc[4][MT];
-    dense_dot<MT, MT == 2>(      // the smaller tile has K chunks twice as long: as many additions in a chain as the larger
-        reinterpret_cast<const char*>(a.x) + (size_t)t0 * a.H * 2, x_lane, w, (size_t)srow * a.ldw * 2 + (tid & 7) * 16,
-        ty * 16 * MT, wave_w, s_begin, s_end, lds, acc);
+    floatx4 acc[4][MT / 2];
+    ring_dot<MT, MT == 4>(       // the smaller tile has K chunks twice as long: as many additions in a chain as the larger
+        reinterpret_cast<const char*>(a.x) + (size_t)t0 * a.H * 2, x_lane, w, (size_t)srow * a.ldw * 2 + (tid & 7) * 16, s_begin, s_end, acc);
+    const int ty = wv >> 1, tx = wv & 1;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int t = t0 + (ty * MT + mt) * 16 + r16;
+    for (int mt = 0; mt < MT / 2; ++mt) {
+        const int t = t0 + (mt * 2 + ty) * 16 + r16;
         if (t < a.T) {
-            float* out = a.part + ((size_t)chunk * a.T + t) * a.N + e0 + tx * 64 + q * 4;
+            float* out = a.part + ((size_t)chunk * a.T + t) * a.N + e0 + tx * 32 + q * 4;
 #pragma unroll
-            for (int b = 0; b < 4; ++b) *reinterpret_cast<floatx4*>(out + b * 16) = acc[b][mt];
+            for (int b = 0; b < 4; ++b) *reinterpret_cast<floatx4*>(out + (b >> 1) * 64 + (b & 1) * 16) = acc[b][mt];
         }
     }
 }
@@ -169,23 +165,31 @@ __global__ __launch_bounds__(kThreads, 2) void gate_logits_lds_kernel(GateArgs a
 // of busy CUs; which tile when: launch_general_logits.
 template <typename T, int NB, int MT, int kSplit, int DEPTH, KRows kRows>
 __global__ __launch_bounds__(kSplit * kWave) void gate_logits_split_kernel(GateArgs a) {
-    __shared__ floatx4 part[kSplit][NB * MT][kWave];
+    constexpr int kLdsW = split_w_bytes<T, T, NB, MT>(), kLds = kLdsW + split_x_bytes<T, T, NB, MT>();   // of a wave
+    __shared__ __attribute__((aligned(16))) char lds[kSplit * kLds];
+    static_assert(kLds >= NB * MT * kWave * (int)sizeof(floatx4), "the partial sums");
+    floatx4 (*part)[NB * MT][kWave] = reinterpret_cast<floatx4 (*)[NB * MT][kWave]>(lds);
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
     const int r16 = lane & 15, q = lane >> 4;
     const int t0 = blockIdx.x * (16 * MT), e0 = blockIdx.y * (16 * NB);
     constexpr int kStep = 8 * (16 / (int)sizeof(T));
     const int n_steps = (a.H + kStep - 1) / kStep;
-    const T* pw[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) pw[b] = (const T*)a.w_gate + (size_t)min(e0 + b * 16 + r16, a.N - 1) * a.ldw;
-    auto x_rows = [&](const T* (&px)[MT], uint32_t (&)[MT]) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) px[mt] = (const T*)a.x + (size_t)min(t0 + mt * 16 + r16, a.T - 1) * a.H;
+    auto w_block = [&](int b) { return e0 + b * 16; };
+    auto w_row = [&](int b, int r) { return min(e0 + b * 16 + r, a.N - 1); };
+    auto x_row = [&](int mt, int r) { return min(t0 + mt * 16 + r, a.T - 1); };
+    struct Rows {
+        const T *w_base, *x_base;
+        int w_pitch, x_pitch;
+        decltype(w_block) w_block;
+        decltype(w_row) w_row;
+        decltype(x_row) x_row;
     };
     floatx4 acc[NB][MT];
     // fp32 logits decide the top-k: chains of additions about as short as those of one product per lane and a tree
     constexpr int kChains = sizeof(T) == 2 ? 2 : NB * MT > 4 ? 2 : 8;
-    split_dot<T, T, NB, MT, DEPTH, kRows, kChains>(pw, 0u, x_rows, a.H, wv, kSplit, max(n_steps - wv + kSplit - 1, 0) / kSplit, acc);
+    split_dot<T, T, NB, MT, DEPTH, kRows, kChains>(Rows{(const T*)a.w_gate, (const T*)a.x, a.ldw, a.H, w_block, w_row, x_row}, a.H, wv, kSplit,
+                                                   max(n_steps - wv + kSplit - 1, 0) / kSplit, lds + wv * kLds, lds + wv * kLds + kLdsW, acc);
+    __syncthreads();                                        // the partial sums take the LDS of all waves
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -378,7 +382,8 @@ void launch_general_logits(const GateArgs& a, hipStream_t st) {
     // tokens (256 / 896 / 3328 tiles) 25 / 42 / 75, 1024 tokens (64 / 224 / 832) 25 / 14 / 24; fp32, H = 2048, 128 experts,
     // 512 tokens (16 / 64 / 256) 41 / 18 / 11.  The 32-wide tile pays from 64 tiles in bf16 (H = 2000, 200 experts, 512
     // tokens, 112 tiles: 8.3 against 13.7) and, its fp32 matrix instructions being the longer part, from 256 in fp32.
-    // Short loops want little code: 8 waves two steps deep beat 16 waves four deep at 64 tokens, H = 1000, 5.1 to 7.6.
+    // (Operands loaded in operand layout; as whole lines through LDS the last takes 6.7 us at 256 tokens, H = 2048, 128 experts in
+    // fp32 against 10.8.)  Short loops want little code: 8 waves two steps deep beat 16 waves four deep at 64 tokens, H = 1000, 5.1 to 7.6.
     // (One wave per logit: 1887, 460, 83 us for the first, second and third, 93 for the fourth.)
     if (std::is_same_v<T, float> && long_rows(a.T, a.H, a.N)) {
         constexpr int per = kThreads / kWave;
@@ -394,9 +399,9 @@ inline bool gate_mfma_shape(int H, int N, int dtype) {
 }
 
 // The LDS-staged kernel takes batches of at least 1024 tokens when N % 128 == 0 and H % 64 == 0 (measured
-// against the direct kernel at N = 256, H = 7168: 12.0 vs 17.3 us at T = 1024, 28 vs 56 us at T = 4096;
+// against the direct kernel at N = 256, H = 7168: 11.7 vs 17.3 us at T = 1024, 28 vs 56 us at T = 4096;
 // below that the direct kernel's smaller workgroups win).
-inline bool gate_big(int T, int H, int N) { return T >= 1024 && N % kBigTile == 0 && H % kDenseBK == 0; }
+inline bool gate_big(int T, int H, int N) { return T >= 1024 && N % kBigTile == 0 && H % kRingStep == 0; }
 
 // Tokens of its workgroups: 128 where that still makes two workgroups per CU at 8 K chunks, else 64, which takes 8 chunks
 // where 128 would need 16 to fill the chip -- half the partial sums to write and for the top-k kernel to read.  Measured,
@@ -410,7 +415,7 @@ inline int gate_tok_tile(int T) { return T > kTokTile ? 4 * kTokTile : kTokTile;
 // K chunks: enough workgroups for two per CU (~512), each chunk at least kMinChunkSteps steps per wave.
 inline int gate_steps_per_chunk(int T, int H, int N) {
     if (gate_big(T, H, N)) {                    // steps of 64; ~8 chunks (one K range per XCD), >= 4 steps each
-        const int n_steps = H / kDenseBK, rows = gate_big_tokens(T, N);
+        const int n_steps = H / kRingStep, rows = gate_big_tokens(T, N);
         const int tiles = ((T + rows - 1) / rows) * (N / kBigTile);
         const int want = tiles * 8 < 256 ? 16 : 8;               // at least one workgroup per CU
         int chunks = n_steps / 4 >= want ? want : n_steps / 4 >= 8 ? 8 : n_steps / 4 > 0 ? n_steps / 4 : 1;
@@ -428,7 +433,7 @@ inline int gate_steps_per_chunk(int T, int H, int N) {
 inline int gate_chunks(int T, int H, int N, int dtype) {
     if (!gate_mfma_shape(H, N, dtype)) return 1;
     const int spc = gate_steps_per_chunk(T, H, N);
-    const int n_steps = gate_big(T, H, N) ? H / kDenseBK : H / 32;
+    const int n_steps = gate_big(T, H, N) ? H / kRingStep : H / 32;
     return (n_steps + spc - 1) / spc;
 }
 
@@ -476,20 +481,10 @@ extern "C" int moe_gate_topk(const void* x, const void* w_gate, int ldw, int T, 
         a.steps_per_chunk = gate_steps_per_chunk(T, H, N);
         n_chunks = gate_chunks(T, H, N, dtype);
         if (gate_big(T, H, N)) {
-            static PerDeviceOnce lds_ok;                          // opt in to > 64 KB of dynamic LDS, once per device
-            if (lds_ok.run([] {
-                    hipError_t e = hipFuncSetAttribute((const void*)gate_logits_lds_kernel<2>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, kDenseLds);
-                    if (e == hipSuccess)
-                        e = hipFuncSetAttribute((const void*)gate_logits_lds_kernel<4>,
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, kDenseLds);
-                    return e;
-                }) != METRO_OK)
-                return METRO_ERR_HIP;
             const int rows = gate_big_tokens(T, N);
             const dim3 grid(n_chunks, (T + rows - 1) / rows, N / kBigTile);
-            if (rows == 64) hipLaunchKernelGGL(gate_logits_lds_kernel<2>, grid, dim3(kThreads), kDenseLds, st, a);
-            else hipLaunchKernelGGL(gate_logits_lds_kernel<4>, grid, dim3(kThreads), kDenseLds, st, a);
+            if (rows == 64) hipLaunchKernelGGL(gate_logits_lds_kernel<4>, grid, dim3(kThreads), 0, st, a);
+            else hipLaunchKernelGGL(gate_logits_lds_kernel<8>, grid, dim3(kThreads), 0, st, a);
         } else {
         const int tile = gate_tok_tile(T);
         const dim3 grid(n_chunks, (T + tile - 1) / tile, N / kExpTile);

@@ -99,8 +99,7 @@ def l2_table(path: str, stats, cmd):
 
 def source_sha16() -> str:
     h = hashlib.sha256()
-    for name in ("ffn.hip", "ffn_common.h", "ffn_split.h", "split_k.h", "dense_k.h", "mfma_common.h", "device_utils.h",
-                 "host_utils.h"):
+    for name in ("ffn.hip", "ffn_common.h", "ffn_split.h", "split_k.h", "ring_k.h", "mfma_common.h", "device_utils.h"):
         with open(os.path.join(ROOT, "paper_2512_09277_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

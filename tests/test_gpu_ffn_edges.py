@@ -83,6 +83,13 @@ def test_cut_rule_edges(oracle, sizes):
     check(oracle, "bf16", 384, 640, sizes, T=1000)
 
 
+# lists of tall tiles per XCD: 1, 2, 4, 7, 11 and 14 column tiles (fewer than the XCDs, no multiple of them), slots of one to sixteen
+# tiles, empty ones between them, K of 2 and 4 steps (shorter than the prefetch ring) and of 14 and 22
+@pytest.mark.parametrize("H,I", [(256, 128), (128, 256), (896, 512), (1408, 896)])
+def test_tall_lists(oracle, H, I):
+    check(oracle, "bf16", H, I, [0, 2000, 1, 0, 1500, 700, 65, 97, 33, 17, 0, 130, 128, 16, 300], T=2600)
+
+
 # combine: vectors of 8 bf16 or 4 fp32 columns, k in registers (<= 8) or not, rows that are no whole vectors, pairs of other
 # ranks.  Sums of k products in fp32 in the oracle's order: fp32 within k * 2^-24 of the sum of magnitudes, bf16 one rounding.
 @pytest.mark.parametrize("dtype,tol", [("f32", 2e-6), ("bf16", 8e-3)])
