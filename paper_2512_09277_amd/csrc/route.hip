@@ -29,6 +29,7 @@ constexpr int kWords = kMaxN / 64;
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
 constexpr int kNoSlot = 0x7fffffff;
+constexpr int kChain = 64, kChainRow = kChain + 4;   // chain steps prepared at a time; the row ends off a bank period
 constexpr int kRunPairs = 2048;   // pairs a workgroup numbers at least: two 64-item chunks per wave
 
 struct RouteArgs {
@@ -58,17 +59,27 @@ __device__ __forceinline__ void set_bit64(uint32_t* lo, uint32_t* hi, int idx, i
 }
 
 // ------------------------------------------------------------------------------------------ shared pieces
-// Smallest value over the lanes of the first 16 (narrow) or all 64 lanes, in every lane's scalar view.
-__device__ __forceinline__ uint32_t wave_min(uint32_t v, bool narrow) {
+// Smallest value over the wave, in every lane's scalar view.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
     constexpr int kNone = -1;                        // identity of the unsigned minimum
     v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x111, 0xf, 0xf, false));      // row_shr:1
     v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x112, 0xf, 0xf, false));
     v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x114, 0xf, 0xf, false));
     v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x118, 0xf, 0xf, false));
-    if (narrow) return __builtin_amdgcn_readlane(v, 15);
     v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x142, 0xa, 0xf, false));      // row_bcast:15
     v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x143, 0xc, 0xf, false));      // row_bcast:31
     return __builtin_amdgcn_readlane(v, kWave - 1);
+}
+
+// Smallest value over this lane's aligned group of 8 or 16 lanes, in every lane of it.
+template <int kGroup>
+__device__ __forceinline__ uint32_t group_min(uint32_t v) {
+    constexpr int kNone = -1;
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0xb1, 0xf, 0xf, false));      // quad_perm: lane ^ 1
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x4e, 0xf, 0xf, false));      // quad_perm: lane ^ 2
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x141, 0xf, 0xf, false));     // row_half_mirror: lane ^ 7
+    if (kGroup == 16) v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(kNone, (int)v, 0x140, 0xf, 0xf, false));  // row_mirror
+    return v;
 }
 
 // The run of pairs [lo, hi) of one of the workgroups of a layer, in chunks of 64; wave w of it owns the chunks
@@ -106,6 +117,7 @@ __device__ __forceinline__ void for_other_ids(const int32_t* __restrict__ ids, i
             }
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
+                if (i0 + u * kThreads >= n / 4) break;   // uniform
                 const bool before = 4 * (i0 + u * kThreads + tid) < run.lo;
                 f(q[u].x, before); f(q[u].y, before); f(q[u].z, before); f(q[u].w, before);
             }
@@ -118,38 +130,45 @@ __device__ __forceinline__ void for_other_ids(const int32_t* __restrict__ ids, i
 
 // Per-wave counts of the run -> what precedes each wave's chunks; returns the count over the whole layer.
 __device__ __forceinline__ int run_bases(int* hist, int n_keys, int e, int before, int after) {
-    int running = before;
+    int c[kWaves], running = before;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) c[w] = hist[w * n_keys + e];      // all reads first: one LDS round trip, not one per wave
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-        const int c = hist[w * n_keys + e];
         hist[w * n_keys + e] = running;
-        running += c;
+        running += c[w];
     }
     return running + after;
 }
 
 // ------------------------------------------------------------------------------------------ METRO
 constexpr int kIdCache = 8;      // int4 loads of ids a thread keeps in registers between the two passes
+constexpr int kOtherCache = 4;   // int4 loads of the ids outside its run
 constexpr int kRunCache = 8;     // chunks of its run whose ids a wave keeps in registers
 
 // One workgroup per layer solves; with kLists, `split` workgroups solve the same layer and each emits its own run of
 // pairs and the rows these get in the token lists of one rank ("route tokens", Sec. 4.3).  All pairs of an expert go to
 // one replica, so the row of a pair is the slot's first row plus the number of earlier pairs of the expert: one stable
-// numbering, by the keys of the run only.  Latency-bound throughout (barriers, LDS round trips, the serial chain); kernel
-// times with the rule below, us, against one workgroup that sorted its own pair_slot in three more passes: 64 pairs 9.9 ->
-// 5.6, 2048 pairs 11.0 -> 6.4, 8192 pairs (256 experts) 19.2 -> 10.9; without lists, 58 layers of 8192 pairs 10.2 -> 8.2 (of
-// which 0.9 by one range check per id instead of three).
+// numbering, by the keys of the run only.  Bound by latency (barriers, LDS round trips, the serial chain), by the instructions of the
+// passes over the ids (16 waves on four issue ports: an instruction of all of them takes 16 cycles) and, where other kernels ran
+// before, by fetching its code (14 KB with lists), so loops are not unrolled.  Kernel times with the rule below, us, against one
+// workgroup that sorted its own pair_slot in three more passes: 64 pairs 9.9 -> 5.6, 2048 pairs 11.0 -> 6.9, 8192 pairs (256 experts)
+// 19.2 -> 10.5; without lists, 58 layers of 8192 pairs 10.2 -> 5.9 a pass (7.9 with flags set behind a branch per id and the masks
+// inside the chain).
 template <bool kLists>
 __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
-    __shared__ int s_active[kMaxN];
+    __shared__ uint32_t s_active4[kMaxN / 4 + 1];  // a byte per expert: has pairs (kLists: of the run)
     __shared__ uint32_t s_host_lo[kMaxN], s_host_hi[kMaxN];
     __shared__ int s_rank[kMaxN];                  // chosen rank g* of every active expert
-    __shared__ int s_slot[kMaxN];                  // chosen slot
+    __shared__ int s_slot[kMaxN + 1];              // chosen slot
     __shared__ uint32_t s_forced_lo[kWords][kMaxG], s_forced_hi[kWords][kMaxG];
-    __shared__ uint32_t s_multi_lo[kWords], s_multi_hi[kWords];
+    __shared__ uint32_t s_multi_lo[kWords], s_multi_hi[kWords];     // per word: active experts with several replicas
     __shared__ uint32_t s_bm_lo[kMaxG], s_bm_hi[kMaxG];
     __shared__ int s_err;
-    __shared__ int s_hist[kLists ? kWaves * kMaxN : 1];             // pairs per expert: the run's, by wave
+    __shared__ __attribute__((aligned(16))) uint32_t s_key[kMaxG][kChainRow];     // of a run of chain steps, by rank
+    __shared__ __attribute__((aligned(16))) uint32_t s_best[kChain];
+    __shared__ int s_list[kChain];                                  // their experts
+    __shared__ __attribute__((aligned(16))) int s_hist[kLists ? kWaves * kMaxN : 1];             // pairs per expert: the run's, by wave
     __shared__ int s_before[kLists ? kMaxN : 1], s_after[kLists ? kMaxN : 1];
     __shared__ int s_off[kLists ? kMaxSpr : 1];                     // first row of every slot of list_rank
 
@@ -166,13 +185,21 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
     const int4* v = reinterpret_cast<const int4*>(ids);
     const int n4 = a.vec4 ? n_pairs / 4 : 0;
     const Run run(n_pairs, part, kLists ? a.split : 1);
-    int4 idc[kLists ? 1 : kIdCache];
+    int4 idc[kLists ? kOtherCache : kIdCache];       // kLists: of the ids outside the run
     int key[kLists ? kRunCache : 1];
+    uint8_t* s_active = reinterpret_cast<uint8_t*>(s_active4);
+    auto outside = [&](int p) { return p < n_pairs && (p < run.lo || p >= run.hi); };
     if constexpr (kLists) {
 #pragma unroll
         for (int c = 0; c < kRunCache; ++c) {
             const int p = run.item(c);
             key[c] = c < run.per_wave && p < run.hi ? ids[p] : -1;
+        }
+#pragma unroll
+        for (int c = 0; c < kOtherCache; ++c) {
+            const int i = tid + c * kThreads;
+            idc[c] = make_int4(-1, -1, -1, -1);
+            if (a.vec4 && outside(4 * i)) idc[c] = v[i];
         }
     } else {
 #pragma unroll
@@ -190,22 +217,24 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
     }
 
     for (int e = tid; e < N; e += kThreads) {
-        s_active[e] = 0;
         s_host_lo[e] = 0;
         s_host_hi[e] = 0;
         s_rank[e] = -1;
         s_slot[e] = kNoSlot;
         if constexpr (kLists) s_before[e] = s_after[e] = 0;
     }
+    if (tid <= kMaxN / 4) s_active4[tid] = 0;
     if constexpr (kLists)
-        for (int i = tid; i < kWaves * N; i += kThreads) s_hist[i] = 0;
+        for (int i = tid; i < kWaves * N / 4; i += kThreads) reinterpret_cast<int4*>(s_hist)[i] = make_int4(0, 0, 0, 0);
     for (int i = tid; i < ((N + 63) >> 6) * kMaxG; i += kThreads) {
         (&s_forced_lo[0][0])[i] = 0;
         (&s_forced_hi[0][0])[i] = 0;
     }
-    if (tid < kWords) { s_multi_lo[tid] = 0; s_multi_hi[tid] = 0; }
     if (tid < kMaxG) { s_bm_lo[tid] = 0; s_bm_hi[tid] = 0; }
-    if (tid == 0) s_err = 0;
+    if (tid == 0) {
+        s_err = 0;
+        s_slot[N] = -1;
+    }
     __syncthreads();
 
     // Ranks hosting each expert (matrix A) and T[i] > 0 for every expert.
@@ -217,27 +246,55 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
             else if (se[j] >= 0) set_bit64(s_host_lo, s_host_hi, se[j], sl / spr);
         }
     }
+    // The 16 waves share four issue ports, so what counts in the passes over the ids is their instructions: flags are set
+    // without a branch (every id outside [0, N) sets one past the experts'), ids out of range show in a maximum.
+    uint32_t top = 0;                                    // of id + 1: more than N only if an id is out of range
     auto mark = [&](int id) {
-        const bool ok = (uint32_t)id < (uint32_t)N;
-        if (ok) s_active[id] = 1;
-        else if (id != -1) atomicOr(&s_err, METRO_FLAG_BAD_ID);
-        return ok;
+        s_active[min((uint32_t)id, (uint32_t)N)] = 1;
+        top = max(top, (uint32_t)id + 1u);
+    };
+    // f(id, whether it precedes the run) for the ids outside the run: the first from registers
+    auto others = [&](auto f) {
+        if (run.lo == 0 && run.hi >= n_pairs) return;    // uniform
+        auto four = [&](const int4& q, int i) {
+            const bool before = 4 * i < run.lo;
+            f(q.x, before); f(q.y, before); f(q.z, before); f(q.w, before);
+        };
+        if (a.vec4) {
+#pragma unroll
+            for (int c = 0; c < kOtherCache; ++c)
+                if (c * kThreads < n4) four(idc[kLists ? c : 0], tid + c * kThreads);      // uniform
+            for (int i = tid + kOtherCache * kThreads; i < n4; i += kThreads)
+                if (outside(4 * i)) four(v[i], i);
+        } else {
+            for (int p = tid; p < n_pairs; p += kThreads)
+                if (outside(p)) f(ids[p], p < run.lo);
+        }
     };
     if constexpr (kLists) {
         int* mine = s_hist + wave_id() * N;
+        auto count = [&](int id, int* counts) {
+            if ((uint32_t)id < (uint32_t)N) atomicAdd(&counts[id], 1);
+        };
 #pragma unroll
         for (int c = 0; c < kRunCache; ++c)
-            if (mark(key[c])) atomicAdd(&mine[key[c]], 1);
+            if (c < run.per_wave) {                      // uniform per wave
+                mark(key[c]);
+                count(key[c], mine);
+            }
         for (int c = kRunCache; c < run.per_wave; ++c) {
             const int id = run.item(c) < run.hi ? ids[run.item(c)] : -1;
-            if (mark(id)) atomicAdd(&mine[id], 1);
+            mark(id);
+            count(id, mine);
         }
-        for_other_ids(ids, n_pairs, a.vec4, run, [&](int id, bool before) {
-            if (mark(id)) atomicAdd(before ? &s_before[id] : &s_after[id], 1);
+        others([&](int id, bool before) {
+            top = max(top, (uint32_t)id + 1u);
+            count(id, before ? s_before : s_after);
         });
     } else {
 #pragma unroll
         for (int c = 0; c < kIdCache; ++c) {
+            if (c * kThreads >= n4) break;               // uniform
             mark(idc[c].x); mark(idc[c].y); mark(idc[c].z); mark(idc[c].w);   // padding (-1) where not loaded
         }
         for (int i = tid + kIdCache * kThreads; i < n4; i += kThreads) {
@@ -247,66 +304,101 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
         if (!a.vec4)
             for (int i = tid; i < n_pairs; i += kThreads) mark(ids[i]);
     }
+    if (top > (uint32_t)N) atomicOr(&s_err, METRO_FLAG_BAD_ID);
     __syncthreads();
 
-    // Split the active experts: single replica (forced) or several (the serial chain).
-    for (int e = tid; e < N; e += kThreads) {
-        if (!s_active[e]) continue;
-        const uint64_t host = join64(s_host_lo[e], s_host_hi[e]);
+    // Split the active experts: single replica (forced) or several (the serial chain).  Wave w has the experts of word w.
+    const int word = wave_id(), n_words = (N + 63) >> 6;
+    if (word < n_words) {
+        uint64_t host = 0;
+        const bool active = tid < N && (kLists ? s_active[tid] | s_before[tid] | s_after[tid] : s_active[tid]);
+        if (active) host = join64(s_host_lo[tid], s_host_hi[tid]);
         const int r = __popcll(host);
-        if (r == 0) {
-            atomicOr(&s_err, METRO_FLAG_NO_REPLICA);
-        } else if (r == 1) {
+        if (r == 1) {
             const int g = __ffsll((unsigned long long)host) - 1;
-            s_rank[e] = g;
-            set_bit64(&s_forced_lo[e >> 6][0], &s_forced_hi[e >> 6][0], g, e & 63);
-        } else {
-            set_bit64(s_multi_lo, s_multi_hi, e >> 6, e & 63);
+            s_rank[tid] = g;
+            set_bit64(&s_forced_lo[word][0], &s_forced_hi[word][0], g, lane_id());
+        } else if (r == 0 && active) {
+            atomicOr(&s_err, METRO_FLAG_NO_REPLICA);
+        }
+        const uint64_t multi = __ballot(r > 1);
+        if (lane_id() == 0) {
+            s_multi_lo[word] = (uint32_t)multi;
+            s_multi_hi[word] = (uint32_t)(multi >> 32);
         }
     }
     __syncthreads();
 
-    // The chain: wave 0, lane g keeps L[g].  Load of rank g when expert e is served =
-    //   L (all experts of lower words) + forced experts of this word below e + chain picks of this word.
-    // Per 64-expert word the lanes first fetch the host masks of the word's experts (lane b <-> expert
-    // 64w+b), so that the serial loop reads them with readlane instead of waiting for LDS each step.  The choice is a
-    // minimum over (load, rank) in registers: about 100 cycles per expert (ballots over the bits of the load: 300).
-    if (tid < kWave) {
-        const int g = tid;
-        int L = 0;
-        const int n_words = (N + 63) >> 6;
-        for (int w = 0; w < n_words; ++w) {
-            const uint64_t forced = g < G ? join64(s_forced_lo[w][g], s_forced_hi[w][g]) : 0ull;
-            const int my_e = min((w << 6) + g, N - 1);
-            const uint32_t hl = s_host_lo[my_e], hh = s_host_hi[my_e];
-            uint64_t multi = join64(__builtin_amdgcn_readfirstlane(s_multi_lo[w]),
-                                    __builtin_amdgcn_readfirstlane(s_multi_hi[w]));
-            int picked = 0;
-            uint32_t best_of = 0xffffffffu;              // lane b: rank chosen for expert 64w+b
-            while (multi) {
-                const int b = __ffsll((unsigned long long)multi) - 1;
-                multi &= multi - 1;
-                const uint64_t cand = join64(__builtin_amdgcn_readlane(hl, b), __builtin_amdgcn_readlane(hh, b));
-                const int cur = L + __popcll(forced & ((1ull << b) - 1ull)) + picked;
-                const uint32_t order = ((cand >> g) & 1ull) ? ((uint32_t)cur << 6) | (uint32_t)g : 0xffffffffu;
-                const int best = (int)(wave_min(order, G <= 16) & 63u);      // least load, lowest rank among equals
-                if (g == best) ++picked;
-                if (g == b) best_of = best;
+    // The chain: wave 0.  Load of rank g when expert e is served = forced experts below e (known beforehand) + chain picks so far.
+    // The known part becomes a key per step and rank, (load, rank), beyond every load where the rank does not host the expert, which all
+    // waves prepare for up to kChain steps; what remains in the chain is an add, a minimum over the ranks in registers and a
+    // compare, about 55 cycles per expert up to 16 ranks, where every lane of a group of 8 or 16 learns the minimum
+    // (150 to 230 with the masks and popcounts inside the chain).
+    const int group = G <= 8 ? 8 : G <= 16 ? 16 : kWave;
+    // every word has `parts` waves: each prepares every parts-th of its steps
+    const int parts = kWaves / n_words, of = wave_id() / parts, part_of = wave_id() - of * parts;
+    const int lw = min(lane_id(), n_words - 1);
+    const uint32_t my_lo = s_multi_lo[lw], my_hi = s_multi_hi[lw];
+    const int upto = wave_inclusive_sum(lane_id() < n_words ? __popc(my_lo) + __popc(my_hi) : 0);      // lane w: up to word w
+    const int steps = __builtin_amdgcn_readlane(upto, kWords - 1);
+    uint32_t picked = 0;                                 // of this lane's rank, in units of the key
+#pragma clang loop unroll(disable)
+    for (int first = 0; first < max(steps, 1); first += kChain) {        // once, unless more than kChain experts have a choice
+        if (of < n_words) {
+            const int g = lane_id();                     // masks of ranks past G are zero
+            uint64_t left = join64(__builtin_amdgcn_readlane(my_lo, of), __builtin_amdgcn_readlane(my_hi, of)), forced = 0;
+            int load = 0;
+#pragma clang loop unroll(disable)
+            for (int w = 0; w <= of; ++w) {
+                load += __popcll(forced);
+                forced = join64(s_forced_lo[w][g], s_forced_hi[w][g]);
             }
-            if (best_of != 0xffffffffu) s_rank[(w << 6) + g] = (int)best_of;
-            L += __popcll(forced) + picked;
+            int i = (of > 0 ? __builtin_amdgcn_readlane(upto, of - 1) : 0) - first;
+            for (int turn = part_of; left; left &= left - 1, ++i, turn = turn ? turn - 1 : parts - 1) {
+                if (turn || i < 0 || i >= kChain) continue;              // uniform
+                const int b = __ffsll((unsigned long long)left) - 1, e = (of << 6) + b;
+                const uint64_t hosts = join64(s_host_lo[e], s_host_hi[e]);
+                const uint32_t known = (uint32_t)(load + __popcll(forced & ((1ull << b) - 1ull)));
+                s_key[g][i] = (((hosts >> g) & 1ull) ? known << 6 : 0x40000000u) | (uint32_t)g;
+                if (g == 0) s_list[i] = e;
+            }
         }
-    } else if constexpr (kLists) {                       // meanwhile: what precedes each wave's chunks, and T[i]
-        for (int e = tid - kWave; e < N; e += kThreads - kWave) s_after[e] = run_bases(s_hist, N, e, s_before[e], s_after[e]);
+        __syncthreads();
+        if (tid < kWave) {
+            const int n = min(steps - first, kChain);
+            const uint32_t* keys = s_key[tid & (group - 1)];
+            auto chain = [&](auto least) {
+                uint4 ahead = *reinterpret_cast<const uint4*>(keys);
+#pragma clang loop unroll(disable)                     // the code of a call is fetched anew, so what loops is cheaper
+                for (int i = 0; i < n; i += 4) {         // past the last step: keys of no step, whose picks nobody asks for
+                    const uint32_t k[4] = {ahead.x, ahead.y, ahead.z, ahead.w};
+                    ahead = *reinterpret_cast<const uint4*>(keys + min(i + 4, kChain - 4));
+                    uint32_t m[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const uint32_t v = k[u] + picked;
+                        m[u] = least(v);
+                        picked += v == m[u] ? 64u : 0u;
+                    }
+                    *reinterpret_cast<uint4*>(s_best + i) = make_uint4(m[0], m[1], m[2], m[3]);
+                }
+            };
+            if (group == 8) chain([](uint32_t v) { return group_min<8>(v); });
+            else if (group == 16) chain([](uint32_t v) { return group_min<16>(v); });
+            else chain([](uint32_t v) { return wave_min(v); });
+            if (tid < n) s_rank[s_list[tid]] = (int)(s_best[tid] & 63u);     // a wave's LDS accesses are done in order
+        } else if (kLists && first == 0) {               // meanwhile: what precedes each wave's chunks, and T[i]
+            for (int e = tid - kWave; e < N; e += kThreads - kWave) s_after[e] = run_bases(s_hist, N, e, s_before[e], s_after[e]);
+        }
+        __syncthreads();
     }
-    __syncthreads();
 
     // y[i][g*] = 1 -> the lowest slot of expert i on rank g*.
 #pragma unroll
     for (int j = 0; j < kMaxS / kThreads; ++j) {
         const int sl = tid + j * kThreads;
         const int e = se[j];
-        if (sl < S && e >= 0 && s_active[e] && s_rank[e] == sl / spr) atomicMin(&s_slot[e], sl);
+        if (sl < S && e >= 0 && s_rank[e] == sl / spr) atomicMin(&s_slot[e], sl);         // rank -1: not active, or no replica
     }
     __syncthreads();
     const int lo = a.list_rank * spr;
@@ -343,9 +435,7 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
     }
 
     // x from y: every pair of expert i goes to its activated replica.
-    auto slot_of = [&](int id) {
-        return (uint32_t)id < (uint32_t)N ? s_slot[id] : -1;
-    };
+    auto slot_of = [&](int id) { return s_slot[min((uint32_t)id, (uint32_t)N)]; };      // the one past the experts': -1
     if constexpr (!kLists) {
         int4* o = reinterpret_cast<int4*>(pair_slot);
 #pragma unroll
@@ -440,14 +530,16 @@ __global__ __launch_bounds__(kThreads) void token_balanced_kernel(RouteArgs a) {
             else if (se[j] >= 0) set_bit64(s_host_lo, s_host_hi, se[j], sl / spr);
         }
     }
+    bool bad = false;
     auto valid = [&](int id) {
-        if (id < -1 || id >= N) atomicOr(&s_err, METRO_FLAG_BAD_ID);
-        return id >= 0 && id < N;
+        const bool ok = (uint32_t)id < (uint32_t)N;
+        bad |= !ok && id != -1;
+        return ok;
     };
     int* mine = s_hist + wave_id() * N;
 #pragma unroll
     for (int c = 0; c < kRunCache; ++c)
-        if (valid(key[c])) atomicAdd(&mine[key[c]], 1);
+        if (c < run.per_wave && valid(key[c])) atomicAdd(&mine[key[c]], 1);      // the first half is uniform
     for (int c = kRunCache; c < run.per_wave; ++c) {
         const int id = run.item(c) < run.hi ? ids[run.item(c)] : -1;
         if (valid(id)) atomicAdd(&mine[id], 1);
@@ -455,6 +547,7 @@ __global__ __launch_bounds__(kThreads) void token_balanced_kernel(RouteArgs a) {
     for_other_ids(ids, n_pairs, a.vec4, run, [&](int id, bool before) {
         if (valid(id)) atomicAdd(before ? &s_before[id] : &s_cnt[id], 1);
     });
+    if (bad) atomicOr(&s_err, METRO_FLAG_BAD_ID);
     __syncthreads();
 
     // T[i], the bases of the run's chunks, and an exclusive scan of the replica counts r_e = popcount(host[e]) -> s_base

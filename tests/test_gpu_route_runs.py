@@ -48,6 +48,40 @@ def test_runs_of_one_layer(oracle, routing, N, k, G, spr, T):
         assert np.array_equal(lists["pair_row"].cpu().numpy(), want["pair_row"])
 
 
+# experts with a choice on both sides of a batch of 8 and of the 64 prepared at a time, up to all 512; ranks in groups of 8, of 16 and
+# more; ids out of range and experts without a replica beside them
+@pytest.mark.parametrize("N,G,spr,choices", [(70, 3, 32, 0), (70, 8, 18, 7), (70, 8, 18, 8), (70, 9, 18, 9), (200, 16, 32, 63), (200, 17, 32, 64),
+                                             (200, 8, 36, 65), (300, 32, 20, 129), (512, 16, 64, 512), (512, 64, 32, 300)])
+def test_chain_lengths(oracle, N, G, spr, choices):
+    from paper_2512_09277_amd import api
+
+    api.load()
+    print(f"chain N={N} G={G} spr={spr} choices={choices}", flush=True)
+    rng = np.random.default_rng(N * G + choices)
+    slots = [[] for _ in range(G)]
+    for e in rng.permutation(N):
+        if e != 5:                                        # expert 5 has no replica
+            slots[min(range(G), key=lambda g: len(slots[g]))].append(e)
+    for e in rng.permutation(N)[:choices]:
+        for g in rng.permutation(G)[:int(rng.integers(2, 4))]:
+            if e != 5 and e not in slots[g] and len(slots[g]) < spr:
+                slots[g].append(e)
+    s2e = np.concatenate([(s + [-1] * spr)[:spr] for s in slots]).astype(np.int32)
+    for T in (3, 600):
+        ids = np.stack([rng.permutation(N)[:4] for _ in range(T)]).astype(np.int32)
+        ids[0, 0] = -1
+        for bad in (None, N, -2, 2**31 - 1):
+            if bad is not None:
+                ids[T - 1, 3] = bad
+            served = np.where((ids < 0) | (ids >= N) | (ids == 5), -1, ids)              # the others get no slot
+            ref = oracle.route_metro(served, s2e, N, G, spr)
+            flag = (api.FLAG_BAD_ID if bad is not None else 0) | (api.FLAG_NO_REPLICA if (ids == 5).any() else 0)
+            for got in (api.metro_route(dev(ids), dev(s2e), N, G, spr), api.metro_route_permute(dev(ids), dev(s2e), N, G, spr, 1)[0]):
+                assert int(got["err_flag"].item()) == flag
+                for name in ("pair_slot", "expert_slot", "rank_active"):
+                    assert np.array_equal(got[name][0].cpu().numpy(), ref[name]), (name, T, bad)
+
+
 @pytest.mark.parametrize("L,T", [(3, 1500), (58, 1024), (129, 700), (300, 300)])
 def test_runs_of_many_layers(oracle, L, T):
     from paper_2512_09277_amd import api
