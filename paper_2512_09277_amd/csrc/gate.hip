@@ -131,7 +131,8 @@ __global__ __launch_bounds__(kThreads, 2) void gate_logits_mfma_kernel(GateArgs 
 // Large batches: one workgroup = 16 MT tokens x 128 experts x one K chunk, both operands staged through LDS (ring_k.h).
 constexpr int kBigTile = kRingRows;                              // experts of a workgroup
 
-template <int MT>
+// kChains: accumulators per block, see gate_big.  The smaller tile has K chunks twice as long.
+template <int MT, int kChains>
 __global__ __launch_bounds__(kThreads, 2) void gate_logits_lds_kernel(GateArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, q = lane >> 4, srow = tid >> 3;
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(kThreads, 2) void gate_logits_lds_kernel(GateArgs a
 #pragma unroll
     for (int p = 0; p < 4; ++p) w[p] = reinterpret_cast<const char*>(a.w_gate) + (size_t)(e0 + p * 32) * a.ldw * 2;
     floatx4 acc[4][MT / 2];
-    ring_dot<MT, MT == 4>(       // the smaller tile has K chunks twice as long: as many additions in a chain as the larger
+    ring_dot<MT, kChains>(
         reinterpret_cast<const char*>(a.x) + (size_t)t0 * a.H * 2, x_lane, w, (size_t)srow * a.ldw * 2 + (tid & 7) * 16, s_begin, s_end, acc);
     const int ty = wv >> 1, tx = wv & 1;
 #pragma unroll
@@ -398,10 +399,16 @@ inline bool gate_mfma_shape(int H, int N, int dtype) {
     return dtype == METRO_DTYPE_BF16 && H % 32 == 0 && N % kExpTile == 0 && N <= kMaxN;
 }
 
-// The LDS-staged kernel takes batches of at least 1024 tokens when N % 128 == 0 and H % 64 == 0 (measured
-// against the direct kernel at N = 256, H = 7168: 11.7 vs 17.3 us at T = 1024, 28 vs 56 us at T = 4096;
-// below that the direct kernel's smaller workgroups win).
-inline bool gate_big(int T, int H, int N) { return T >= 1024 && N % kBigTile == 0 && H % kRingStep == 0; }
+// The LDS-staged kernel needs N % 128 == 0 and H % 64 == 0.  It takes batches of at least 1024 tokens and smaller ones, from its tile
+// of 64 on, of more than 2^28 products, where what the direct kernel reads in operand layout (64 tokens x 64 experts a workgroup, 38 GB/s per CU) is more than
+// a launch's latency.  Measured, whole call, us, direct / staged: 256 experts x 7168, 192 / 256 / 512 / 1000 tokens 18.1 / 18.1 /
+// 18.6 / 24.1 against 14.6 / 14.7 / 15.2 / 17.1, 512 x 4096, 192 tokens 18.2 / 16.3, 128 x 4096, 768 tokens 15.3 / 13.5, 256 x 2048, 768
+// tokens 16.2 / 14.5; below the line nothing to win (128 x 2048 and 256 x 1024 up to 1000 tokens within 0.2 us, either way).
+// The staged kernel has four accumulators per block there: with two the error of the weights against 64 bits would grow (1000 tokens
+// x 256 x 7168 1.51e-7 -> 1.72e-7, now 1.51e-7; they cost 0.2 us).
+inline bool gate_big(int T, int H, int N) {
+    return (T >= 1024 || (T >= 64 && (int64_t)T * N * H > 1 << 28)) && N % kBigTile == 0 && H % kRingStep == 0;
+}
 
 // Tokens of its workgroups: 128 where that still makes two workgroups per CU at 8 K chunks, else 64, which takes 8 chunks
 // where 128 would need 16 to fill the chip -- half the partial sums to write and for the top-k kernel to read.  Measured,
@@ -417,7 +424,7 @@ inline int gate_steps_per_chunk(int T, int H, int N) {
     if (gate_big(T, H, N)) {                    // steps of 64; ~8 chunks (one K range per XCD), >= 4 steps each
         const int n_steps = H / kRingStep, rows = gate_big_tokens(T, N);
         const int tiles = ((T + rows - 1) / rows) * (N / kBigTile);
-        const int want = tiles * 8 < 256 ? 16 : 8;               // at least one workgroup per CU
+        const int want = tiles * 8 >= 256 ? 8 : 16;               // at least one workgroup per CU
         int chunks = n_steps / 4 >= want ? want : n_steps / 4 >= 8 ? 8 : n_steps / 4 > 0 ? n_steps / 4 : 1;
         return (n_steps + chunks - 1) / chunks;
     }
@@ -483,8 +490,9 @@ extern "C" int moe_gate_topk(const void* x, const void* w_gate, int ldw, int T, 
         if (gate_big(T, H, N)) {
             const int rows = gate_big_tokens(T, N);
             const dim3 grid(n_chunks, (T + rows - 1) / rows, N / kBigTile);
-            if (rows == 64) hipLaunchKernelGGL(gate_logits_lds_kernel<4>, grid, dim3(kThreads), 0, st, a);
-            else hipLaunchKernelGGL(gate_logits_lds_kernel<8>, grid, dim3(kThreads), 0, st, a);
+            if (rows == 128) hipLaunchKernelGGL((gate_logits_lds_kernel<8, 1>), grid, dim3(kThreads), 0, st, a);
+            else if (T >= 1024) hipLaunchKernelGGL((gate_logits_lds_kernel<4, 2>), grid, dim3(kThreads), 0, st, a);
+            else hipLaunchKernelGGL((gate_logits_lds_kernel<4, 4>), grid, dim3(kThreads), 0, st, a);
         } else {
         const int tile = gate_tok_tile(T);
         const dim3 grid(n_chunks, (T + tile - 1) / tile, N / kExpTile);

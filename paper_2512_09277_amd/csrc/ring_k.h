@@ -61,13 +61,13 @@ __device__ __forceinline__ uint32_t ring_piece(int row) { return (uint32_t)(((th
 
 // x + x_lane[p]: the 16 bytes that this lane stages of activation row p * 32 + tid / 8 (ring_piece); w[p] + w_lane: those of weight row
 // p * 32 + tid / 8 (piece tid & 7).  x, w[p] uniform.  acc[b][mt]: lane (r16, q) of wave (ty, tx) holds weight rows
-// (b >> 1) * 64 + tx * 32 + (b & 1) * 16 + 4 q + v, activation row (2 mt + ty) * 16 + r16.  kHalves: the two halves of a step have
-// accumulators of their own (chains of additions half as long), added at the end.
-template <int MT, bool kHalves = false>
+// (b >> 1) * 64 + tx * 32 + (b & 1) * 16 + 4 q + v, activation row (2 mt + ty) * 16 + r16.  kChains = 2: the two halves of a step have
+// accumulators of their own (chains of additions half as long), added at the end; 4: even and odd steps too.
+template <int MT, int kChains = 1>
 __device__ __forceinline__ void ring_dot(const char* x, const uint32_t (&x_lane)[MT / 2], const char* const (&w)[4],
                                          size_t w_lane, int s_begin, int s_end, floatx4 (&sum)[4][MT / 2]) {
     constexpr int D = MT <= 4 ? 4 : 3, kHalf = MT <= 4 ? 1 : 2, kWBuf = D * kHalf;
-    static_assert(MT % 2 == 0 && kWBuf + 4 <= kRingBufs, "");
+    static_assert(MT % 2 == 0 && kWBuf + 4 <= kRingBufs && (kChains < 4 || D % 2 == 0), "");
     constexpr int M2 = MT / 2, kX = MT / 2, kW = 4;              // loads of a step
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, q = lane >> 4, ty = wv >> 1, tx = wv & 1;
@@ -99,13 +99,7 @@ __device__ __forceinline__ void ring_dot(const char* x, const uint32_t (&x_lane)
         };
         run_steps(std::make_integer_sequence<int, kX>{}, piece, 0);
     };
-    floatx4 acc[kHalves ? 2 : 1][4][M2];
-#pragma unroll
-    for (int h = 0; h < (kHalves ? 2 : 1); ++h)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-            for (int mt = 0; mt < M2; ++mt) acc[h][b][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    floatx4 acc[kChains][4][M2];
 
     struct Fragments { bf16x8 x[M2], w[4]; } f[2];
     auto read = [&](auto U, auto J) {
@@ -117,8 +111,8 @@ __device__ __forceinline__ void ring_dot(const char* x, const uint32_t (&x_lane)
         for (int mt = 0; mt < M2; ++mt)
             f[j].x[mt] = *reinterpret_cast<const bf16x8*>((mt < 2 ? ring_buf<set * kHalf>() : ring_buf<set * kHalf + kHalf - 1>()) + (mt & 1) * 4096 + x_rd[j]);
     };
-    auto multiply = [&](auto J) {
-        constexpr int j = decltype(J)::value, h = kHalves ? j : 0;
+    auto multiply = [&](auto U, auto J) {
+        constexpr int j = decltype(J)::value, h = (decltype(U)::value % 2 * 2 + j) % kChains;
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -140,7 +134,7 @@ __device__ __forceinline__ void ring_dot(const char* x, const uint32_t (&x_lane)
         // Fragment reads first, then stores and loads between the products: a wave issues in order, and a burst of loads from four
         // waves holds the products behind it back for some 500 cycles (4096 tokens at 2048 x 768 53.2 + 38.3 -> 51.3 + 35.2 us).
         read(U, j1);
-        multiply(j0);
+        multiply(U, j0);
         park_w(next);
         __builtin_amdgcn_sched_group_barrier(kDsRead, 4 + M2, 0);
         __builtin_amdgcn_sched_group_barrier(kMatrix, M2, 0);
@@ -154,7 +148,7 @@ __device__ __forceinline__ void ring_dot(const char* x, const uint32_t (&x_lane)
         read(next, j0);
         load_x(U, s + D);
         load_w(next, s + 1 + D);
-        multiply(j1);
+        multiply(U, j1);
         __builtin_amdgcn_sched_group_barrier(kDsRead, 4 + M2, 0);
 #pragma unroll
         for (int i = 0; i < kX + kW; ++i) {
@@ -164,6 +158,13 @@ __device__ __forceinline__ void ring_dot(const char* x, const uint32_t (&x_lane)
         __builtin_amdgcn_sched_barrier(0);
     };
     run_steps(std::make_integer_sequence<int, D>{}, [&](auto U, int s) { load_w(U, s); load_x(U, s); }, s_begin);
+    __builtin_amdgcn_sched_barrier(0);                           // up to 128 registers to clear, while the first loads are on their way
+#pragma unroll
+    for (int h = 0; h < kChains; ++h)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int mt = 0; mt < M2; ++mt) acc[h][b][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
     park_w(j0);
     load_w(j0, s_begin + D);
     arrive(std::integral_constant<int, (D - 1) * (kW + kX) + kW>{});
@@ -176,7 +177,11 @@ __device__ __forceinline__ void ring_dot(const char* x, const uint32_t (&x_lane)
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
-        for (int mt = 0; mt < M2; ++mt) sum[b][mt] = kHalves ? acc[0][b][mt] + acc[kHalves ? 1 : 0][b][mt] : acc[0][b][mt];
+        for (int mt = 0; mt < M2; ++mt) {
+            sum[b][mt] = acc[0][b][mt];
+            if constexpr (kChains > 1) sum[b][mt] += acc[1][b][mt];
+            if constexpr (kChains > 2) sum[b][mt] += acc[2][b][mt] + acc[3][b][mt];
+        }
 }
 
 }  // namespace

@@ -201,10 +201,11 @@ def test_nan_and_infinite_logits(api):
 
 
 @pytest.mark.parametrize("T,H,N,k", [(1024, 64, 128, 8), (1087, 320, 128, 4), (4033, 128, 256, 8), (4225, 576, 256, 8),
-                                     (8130, 64, 128, 8), (8200, 448, 128, 2)])
+                                     (8130, 64, 128, 8), (8200, 448, 128, 2), (63, 8384, 512, 8), (64, 8256, 512, 8),
+                                     (128, 8192, 256, 8), (129, 8192, 256, 8), (1000, 2112, 128, 4)])
 def test_large_batches(api, oracle, T, H, N, k):
-    """The LDS-staged logits kernel on both sides of its tile rule (64 or 128 tokens), last tiles of one to all rows, K chunks
-    of one to several steps."""
+    """The LDS-staged logits kernel on both sides of its tile rule (64 or 128 tokens) and of the rule that gives it batches below
+    1024 tokens (2^28 products), last tiles of one to all rows, K chunks of one to several steps."""
     import torch
 
     print(f"gate large T={T} H={H} N={N} k={k}", flush=True)
