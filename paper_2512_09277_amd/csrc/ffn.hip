@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_mfma_kernel(FfnArgs a) {
     const int xcd = blockIdx.x & 7, tall = wl.list_tall(xcd, a.ntt);
     int id = blockIdx.x >> 3;
     if (id < tall) {
-        const Tile t = wl.tall(id);
+        const Tile t = wl.tall(id, xcd);
         if (t.rows <= 32) ring_tile<kGateUp, 2>(a, t);
         else if (t.rows <= 64) ring_tile<kGateUp, 4>(a, t);
         else if (t.rows <= 96) ring_tile<kGateUp, 6>(a, t);
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(kThreads, 2) void ffn_mfma_kernel(FfnArgs a) {
 inline int mfma_grid(const FfnArgs& a, int cap, int spr) {
     const int tall = std::min(cap / (kNarrowRows + 1), max_tiles(cap, spr, kTallRows));
     const int narrow = std::min(a.ntn * (std::min(spr, cap) + cap / kNarrowRows), kNarrowGrid);
-    return tall * ((a.ntt + 7) & ~7) + ((narrow + 7) & ~7);
+    return ((tall * (a.ntt < 8 ? a.ntt : (a.ntt + 7) & ~7) + 7) & ~7) + ((narrow + 7) & ~7);
 }
 
 // ------------------------------------------------------------------------------------------ general path

@@ -60,7 +60,7 @@ struct WorkList {
     int tall_tiles;                             // tall tiles of the slot
     int tall_first, tall_mine, tall_incl;       // in the XCD's list: first column, items of the slot, of the slots up to it
     int full, part, incl, rank, narrow_begin;   // full narrow tiles, rows of the remainder; narrow rows start here
-    int n_full, n_narrow;                       // uniform
+    int n_full, n_narrow, tall_stride;          // uniform
 
     __device__ __forceinline__ void read(const int32_t* __restrict__ group_offsets, int spr, int cap, const CutRule& rule) {
         const int l = lane_id();
@@ -112,20 +112,25 @@ struct WorkList {
     // at 2048 x 768 47.6 + 31.9 / 54.1 + 34.3, 512 tokens at 4096 x 1536 107.9 + 53.0 / 108.6 + 53.4, 1024 tokens at 7168 x 2048 376.9 +
     // 201.1 / 375.0 + 202.4.  Columns round 4 or 2 XCDs, whose L2s then take fewer rows, but unequal shares of the slots, are slower
     // (by 4 to 7 and 15 to 23 %), and so is an eighth of the items in one piece (4096 x 1536: 112.8 + 59.4).
+    // With fewer columns than XCDs the items themselves go round: the host cannot know the longest list, and a grid for 8 columns
+    // would be mostly empty workgroups (4096 tokens at 128 x 128 36 us a layer, 30 without).
     __device__ __forceinline__ int list_tall(int xcd, int n_cols) {
-        tall_first = (xcd - lane_id() * n_cols) & 7;
-        tall_mine = tall_tiles * ((n_cols - tall_first + 7) >> 3);
+        tall_stride = n_cols < 8 ? 1 : 8;
+        tall_first = n_cols < 8 ? 0 : (xcd - lane_id() * n_cols) & 7;
+        tall_mine = tall_tiles * (n_cols < 8 ? n_cols : (n_cols - tall_first + 7) >> 3);
         tall_incl = wave_inclusive_sum(tall_mine);
-        return __builtin_amdgcn_readlane(tall_incl, kWave - 1);
+        const int n = __builtin_amdgcn_readlane(tall_incl, kWave - 1);
+        return n_cols < 8 ? (n - xcd + 7) >> 3 : n;
     }
-    __device__ __forceinline__ Tile tall(int i) const {
+    __device__ __forceinline__ Tile tall(int nth, int xcd) const {
+        const int i = tall_stride == 1 ? nth * 8 + xcd : nth;
         const uint64_t owner = __ballot(tall_incl - tall_mine <= i && i < tall_incl);      // exactly one lane
         const int o = __ffsll((unsigned long long)owner) - 1;
         const int tiles = __builtin_amdgcn_readlane(tall_tiles, o), at = i - __builtin_amdgcn_readlane(tall_incl - tall_mine, o);
         const int c = (uint32_t)at / (uint32_t)tiles, row = (at - c * tiles) * kTallRows;
         Tile t;
         t.slot = o;
-        t.col = __builtin_amdgcn_readlane(tall_first, o) + c * 8;
+        t.col = __builtin_amdgcn_readlane(tall_first, o) + c * tall_stride;
         t.row0 = __builtin_amdgcn_readlane(begin, o) + row;
         t.rows = min(kTallRows, __builtin_amdgcn_readlane(rows, o) - row);
         return t;
