@@ -10,7 +10,9 @@
 // One barrier per step, in its middle: the first half step's fragments are in registers when a step begins, the second half's are
 // read while those are multiplied, and behind the barrier -- every wave has read all of step s, and step s + 1 has arrived -- the
 // next step's first half is read while the second half is multiplied.  The stage of step s then takes step s + D.
-// Loads are unconditional, past the end every lane takes the same 16 bytes, so that the count of outstanding loads is known.
+// A wait that lets newer loads stay in flight is a count of these, so what is counted must really be issued.  Loads are unconditional
+// (past the end every lane takes the same 16 bytes), but the compiler drops a load to registers that no path uses: in the steps
+// behind the unrolled loop, weights that no later step of them stores.  Those are not loaded there, and not counted.
 //
 // LDS: 128 bytes per staged row, its 16-byte piece p at place p ^ (row & 7), so that the 16 rows of a fragment read spread over the
 // banks.  A direct load puts lane i's 16 bytes at place i behind a common base, so the lane that fills place i reads piece
@@ -128,8 +130,9 @@ __device__ __forceinline__ void ring_dot(const char* x, const uint32_t (&x_lane)
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto step = [&](auto U, int s) {
-        constexpr int u = decltype(U)::value;
+    // Last: the last step, counted like U, whose weights are loaded, or stored by a step that follows in the code.
+    auto step = [&](auto U, int s, auto Last) {
+        constexpr int u = decltype(U)::value, newer = decltype(Last)::value - (u + 1);
         constexpr std::integral_constant<int, u + 1> next{};
         // Fragment reads first, then stores and loads between the products: a wave issues in order, and a burst of loads from four
         // waves holds the products behind it back for some 500 cycles (4096 tokens at 2048 x 768 53.2 + 38.3 -> 51.3 + 35.2 us).
@@ -143,11 +146,11 @@ __device__ __forceinline__ void ring_dot(const char* x, const uint32_t (&x_lane)
             __builtin_amdgcn_sched_group_barrier(kDsWrite, 1, 0);
             __builtin_amdgcn_sched_group_barrier(kMatrix, M2 > 1 ? M2 - 1 : 1, 0);
         }
-        // behind the activations of s + 1: the weights of s + 2 .. s + D and the activations of s + 2 .. s + D - 1
-        arrive(std::integral_constant<int, kW * (D - 1) + kX * (D - 2)>{});
+        // behind the activations of s + 1: those of s + 2 .. s + D - 1 and the weights of s + 2 .. s + D, as far as there are any
+        arrive(std::integral_constant<int, kW * (newer <= 0 ? 0 : newer < D - 1 ? newer : D - 1) + kX * (D - 2)>{});
         read(next, j0);
         load_x(U, s + D);
-        load_w(next, s + 1 + D);
+        if constexpr (newer >= D) load_w(next, s + 1 + D);
         multiply(U, j1);
         __builtin_amdgcn_sched_group_barrier(kDsRead, 4 + M2, 0);
 #pragma unroll
@@ -157,8 +160,13 @@ __device__ __forceinline__ void ring_dot(const char* x, const uint32_t (&x_lane)
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    run_steps(std::make_integer_sequence<int, D>{}, [&](auto U, int s) { load_w(U, s); load_x(U, s); }, s_begin);
-    __builtin_amdgcn_sched_barrier(0);                           // up to 128 registers to clear, while the first loads are on their way
+    asm volatile("; ring of %0 stages, %1 loads each" ::"i"(D), "i"(kX));          // a comment in the assembly, no instruction
+    run_steps(std::make_integer_sequence<int, D>{}, [&](auto U, int s) {
+        load_w(U, s);
+        load_x(U, s);
+        __builtin_amdgcn_sched_barrier(0);                       // the waits count on this order
+    }, s_begin);
+    // up to 128 registers to clear, while the first loads are on their way
 #pragma unroll
     for (int h = 0; h < kChains; ++h)
 #pragma unroll
@@ -171,9 +179,12 @@ __device__ __forceinline__ void ring_dot(const char* x, const uint32_t (&x_lane)
     read(j0, j0);
     constexpr int kPeriod = D % 2 ? 2 * D : D;
     int s = s_begin;
-    for (; s + kPeriod <= s_end; s += kPeriod) run_steps(std::make_integer_sequence<int, kPeriod>{}, step, s);
-    run_steps_tail(std::make_integer_sequence<int, kPeriod - 1>{}, step, s, s_end);
+    for (; s + kPeriod <= s_end; s += kPeriod)
+        run_steps(std::make_integer_sequence<int, kPeriod>{}, [&](auto U, int at) { step(U, at, std::integral_constant<int, 2 * kPeriod>{}); }, s);
+    run_steps_tail(std::make_integer_sequence<int, kPeriod - 1>{}, [&](auto U, int at) { step(U, at, std::integral_constant<int, kPeriod - 1>{}); },
+                   s, s_end);
     wait_loads<0>();                                             // nothing is on its way to LDS when the workgroup ends or goes on
+    asm volatile("; ring done");
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll

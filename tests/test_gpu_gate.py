@@ -215,6 +215,25 @@ def test_large_batches(api, oracle, T, H, N, k):
     check(got, oracle.gate_topk(x, wg, k, want_logits=True), k, N, "bf16")
 
 
+# K chunks (steps of 64, n of them; the last may be shorter) of every length around the ring's period.  1921 tokens x 512 experts: tiles of
+# 128 tokens, a period of 6 steps, one chunk up to 7 steps, 8 chunks from 32; 1100 x 128 and 512 x 512: tiles of 64, a period of 4.
+@pytest.mark.parametrize("T,N,n", [(1921, 512, n) for n in (1, 2, 3, 4, 5, 6, 7, 9, 64, 72, 80, 85, 88, 96)]
+                         + [(1100, 128, n) for n in (1, 2, 3, 4, 5, 6, 7, 9, 111, 128)]
+                         + [(512, 512, n) for n in (17, 21, 32, 33, 48, 49, 56, 64)] + [(512, 256, 112), (960, 256, 112)])
+def test_chunk_lengths(api, T, N, n):
+    """Staged logits against float64 products on the device (for the oracle's loop these are too many)."""
+    import torch
+
+    H, k = 64 * n, 8
+    print(f"gate chunks T={T} H={H} N={N}", flush=True)
+    x, wg = dev(W.activations(T, H, 97, "bf16")), dev(W.gate_weights(N, H, 98, "bf16"))
+    got = api.moe_gate_topk(x, wg, k)
+    torch.cuda.synchronize()
+    logits = torch.mm(x.double(), wg.double().t().contiguous())
+    ids = torch.sort(logits, dim=1, descending=True, stable=True)[1][:, :k]
+    check(got, dict(logits=logits.cpu().numpy(), ids=ids.cpu().numpy()), k, N, "bf16")
+
+
 @pytest.mark.parametrize("T,H,N", [(1, 7168, 64), (3, 7168, 8), (24, 7168, 128), (25, 7168, 128), (16, 4096, 128), (64, 4096, 128),
                                    (65, 4096, 128), (4, 7168, 256), (5, 7168, 256), (15, 2049, 63), (512, 4099, 16), (513, 4099, 16)])
 def test_few_logits_of_long_rows(api, oracle, T, H, N):
