@@ -132,7 +132,8 @@ int metro_route_token_balanced_permute(const int32_t* topk_ids, const int32_t* s
  *   topk_ids [T,k]   int32     out; valid input for metro_route / metro_route_token_balanced
  *   topk_w   [T,k]   float32   out; valid input for moe_unpermute
  *   expert_count [N] int32     out, may be NULL (asking for it adds one small launch)
- *   ws                         workspace of moe_gate_topk_workspace_bytes(); 256-byte aligned
+ *   ws                         workspace of moe_gate_topk_workspace_bytes(); 256-byte aligned.  The figure for T tokens is enough
+ *                              for every smaller batch; a call is refused only for less than its own batch needs
  *   dtype  METRO_DTYPE_BF16: bf16 operands, fp32 accumulation on the matrix cores when H % 32 == 0,
  *          N % 64 == 0, ldw % 8 == 0 and x, w_gate are 16-byte aligned; other shapes and
  *          METRO_DTYPE_F32 (fp32 products and sums) take a general kernel.  Logits are summed in a fixed order, so the

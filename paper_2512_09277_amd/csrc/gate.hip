@@ -131,7 +131,8 @@ __global__ __launch_bounds__(kThreads, 2) void gate_logits_mfma_kernel(GateArgs 
 // Large batches: one workgroup = 16 MT tokens x 128 experts x one K chunk, both operands staged through LDS (ring_k.h).
 constexpr int kBigTile = kRingRows;                              // experts of a workgroup
 
-// kChains: accumulators per block, see gate_big.  The smaller tile has K chunks twice as long.
+// kChains: accumulators per block, which keep the chains of additions short.  Tiles of 128 tokens: 1, at 8 chunks; of 64: 2 from 1024
+// tokens on, whose chunks are as many and as long, and 4 below, see gate_big.
 template <int MT, int kChains>
 __global__ __launch_bounds__(kThreads, 2) void gate_logits_lds_kernel(GateArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -400,14 +401,16 @@ inline bool gate_mfma_shape(int H, int N, int dtype) {
 }
 
 // The LDS-staged kernel needs N % 128 == 0 and H % 64 == 0.  It takes batches of at least 1024 tokens and smaller ones, from its tile
-// of 64 on, of more than 2^28 products, where what the direct kernel reads in operand layout (64 tokens x 64 experts a workgroup, 38 GB/s per CU) is more than
-// a launch's latency.  Measured, whole call, us, direct / staged: 256 experts x 7168, 192 / 256 / 512 / 1000 tokens 18.1 / 18.1 /
-// 18.6 / 24.1 against 14.6 / 14.7 / 15.2 / 17.1, 512 x 4096, 192 tokens 18.2 / 16.3, 128 x 4096, 768 tokens 15.3 / 13.5, 256 x 2048, 768
-// tokens 16.2 / 14.5; below the line nothing to win (128 x 2048 and 256 x 1024 up to 1000 tokens within 0.2 us, either way).
-// The staged kernel has four accumulators per block there: with two the error of the weights against 64 bits would grow (1000 tokens
-// x 256 x 7168 1.51e-7 -> 1.72e-7, now 1.51e-7; they cost 0.2 us).
+// of 64 on, of more than 2^28 products, where what the direct kernel reads in operand layout (64 tokens x 64 experts a workgroup, 38 GB/s
+// per CU) is more than a launch's latency.  Measured, whole call, us, direct / staged: 256 experts x 7168, 192 / 256 / 512 / 1000 tokens
+// 17.4 / 17.9 / 20.4 / 25.9 against 14.3 / 14.7 / 17.0 / 19.4, 512 x 4096, 192 tokens 18.7 / 17.1, 128 x 4096, 768 tokens 15.3 / 13.5,
+// 256 x 2048, 768 tokens 16.2 / 14.5; below the line nothing to win (128 x 2048 and 256 x 1024 up to 1000 tokens within 0.2 us, either
+// way).  The staged kernel has four accumulators per block there: with two the error of the weights against 64 bits would grow (1000
+// tokens x 256 x 7168 1.51e-7 -> 1.72e-7, now 1.51e-7; they cost 0.2 us).
+constexpr int kStagedAlways = 1024, kStagedMin = 64;
+constexpr int64_t kStagedProducts = 1 << 28;
 inline bool gate_big(int T, int H, int N) {
-    return (T >= 1024 || (T >= 64 && (int64_t)T * N * H > 1 << 28)) && N % kBigTile == 0 && H % kRingStep == 0;
+    return (T >= kStagedAlways || (T >= kStagedMin && (int64_t)T * N * H > kStagedProducts)) && N % kBigTile == 0 && H % kRingStep == 0;
 }
 
 // Tokens of its workgroups: 128 where that still makes two workgroups per CU at 8 K chunks, else 64, which takes 8 chunks
@@ -424,7 +427,11 @@ inline int gate_steps_per_chunk(int T, int H, int N) {
     if (gate_big(T, H, N)) {                    // steps of 64; ~8 chunks (one K range per XCD), >= 4 steps each
         const int n_steps = H / kRingStep, rows = gate_big_tokens(T, N);
         const int tiles = ((T + rows - 1) / rows) * (N / kBigTile);
-        const int want = tiles * 8 >= 256 ? 8 : 16;               // at least one workgroup per CU
+        // 16 chunks where 8 are less than one workgroup per CU; below 1024 tokens only as long as 16 are no more than that.  Measured,
+        // whole call, us, 16 / 8 chunks: 256 experts x 7168, 576 / 768 / 960 tokens 20.5 / 21.9 / 23.8 against 16.5 / 17.2 / 19.1 (direct
+        // kernel 24.0 / 24.5 / 25.8), 512 x 4096, 320 / 448 tokens 21.2 / 23.1 against 16.1 / 17.4 (20.2 / 21.7); error of the weights
+        // against 64 bits at 256 x 7168 and 768 tokens 1.67e-7 against 1.50e-7 (1.50e-7).
+        const int want = T < kStagedAlways ? (tiles * 16 <= 256 ? 16 : 8) : tiles * 8 >= 256 ? 8 : 16;
         int chunks = n_steps / 4 >= want ? want : n_steps / 4 >= 8 ? 8 : n_steps / 4 > 0 ? n_steps / 4 : 1;
         return (n_steps + chunks - 1) / chunks;
     }
@@ -446,14 +453,31 @@ inline int gate_chunks(int T, int H, int N, int dtype) {
 
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
+// What a batch of T tokens itself needs; an empty one has no partial sums.
+inline size_t gate_need(int T, int H, int N, int dtype) {
+    return T == 0 ? 256 : align256((size_t)gate_chunks(T, H, N, dtype) * T * N * sizeof(float)) + 256;
+}
+
 }  // namespace
 }  // namespace metro
 
+// The most that any batch of up to T tokens needs.  More tokens make more tiles, which take fewer K chunks, so the most is at T or at
+// the last batch before the chunks become fewer: the last of a tile of 64 or 128 tokens, of the tile of 16, or of a kernel.  From
+// 32768 tokens on (512 tiles of 64) there is one chunk, or the staged kernel's 8.
 extern "C" size_t moe_gate_topk_workspace_bytes(int T, int H, int N, int dtype) {
     using namespace metro;
     if (T < 0 || H < 1 || N < 1) return 0;
-    if (T == 0) return 256;                                       // an empty batch has no partial sums
-    return align256((size_t)gate_chunks(T, H, N, dtype) * T * N * sizeof(float)) + 256;
+    size_t most = gate_need(T, H, N, dtype);
+    if (!gate_mfma_shape(H, N, dtype)) return most;               // one chunk, whatever T
+    auto with = [&](int64_t t) {
+        if (t < T) most = std::max(most, gate_need((int)t, H, N, dtype));
+    };
+    with(kTokTile);
+    with(kStagedMin - 1);
+    with(kStagedProducts / ((int64_t)N * H));
+    with(kStagedAlways - 1);
+    for (int t = 64; t < T && t <= 32768; t += 64) with(t);
+    return most;
 }
 
 extern "C" int moe_gate_topk(const void* x, const void* w_gate, int ldw, int T, int H, int N, int k, int dtype,
@@ -474,7 +498,7 @@ extern "C" int moe_gate_topk(const void* x, const void* w_gate, int ldw, int T, 
     }
     if (!x || !w_gate || !topk_ids || !topk_w || !ws) return METRO_ERR_INVALID_ARG;
     if (((uintptr_t)ws & 255) != 0) return METRO_ERR_INVALID_ARG;
-    if (ws_bytes < moe_gate_topk_workspace_bytes(T, H, N, dtype)) return METRO_ERR_WORKSPACE;
+    if (ws_bytes < gate_need(T, H, N, dtype)) return METRO_ERR_WORKSPACE;
     const bool mfma = gate_mfma_shape(H, N, dtype) && ldw % 8 == 0 &&
                       (((uintptr_t)x | (uintptr_t)w_gate) & 15) == 0;
     hipStream_t st = (hipStream_t)stream;
@@ -491,7 +515,7 @@ extern "C" int moe_gate_topk(const void* x, const void* w_gate, int ldw, int T, 
             const int rows = gate_big_tokens(T, N);
             const dim3 grid(n_chunks, (T + rows - 1) / rows, N / kBigTile);
             if (rows == 128) hipLaunchKernelGGL((gate_logits_lds_kernel<8, 1>), grid, dim3(kThreads), 0, st, a);
-            else if (T >= 1024) hipLaunchKernelGGL((gate_logits_lds_kernel<4, 2>), grid, dim3(kThreads), 0, st, a);
+            else if (T >= kStagedAlways) hipLaunchKernelGGL((gate_logits_lds_kernel<4, 2>), grid, dim3(kThreads), 0, st, a);
             else hipLaunchKernelGGL((gate_logits_lds_kernel<4, 4>), grid, dim3(kThreads), 0, st, a);
         } else {
         const int tile = gate_tok_tile(T);

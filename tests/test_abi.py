@@ -97,6 +97,17 @@ def test_size_queries_take_every_batch_size(lib):
     assert lib.moe_grouped_ffn_static_ws(one, one, one, 4, 2, 65, 256, 128, 1, one, 256, one, 128, one, None) == -2
 
 
+@pytest.mark.parametrize("H", [64, 1024, 2048, 2560, 4096, 7168, 8384])
+@pytest.mark.parametrize("N", [16, 64, 128, 200, 256, 384, 512])
+def test_gate_workspace_serves_smaller_batches(lib, N, H):
+    """A workspace sized for the largest batch is enough for every smaller one, whichever kernels and K chunks these take."""
+    for dtype in (0, 1):
+        need = [lib.moe_gate_topk_workspace_bytes(T, H, N, dtype) for T in range(4300)]
+        assert need == sorted(need)
+    far = [lib.moe_gate_topk_workspace_bytes(T, H, N, 1) for T in range(4300, 70000, 61)]
+    assert far == sorted(far) and far[0] >= need[-1]
+
+
 @pytest.mark.parametrize("part", ["LIB_PATH", "CALL_PATH"])
 def test_binding_fails_loudly_without_the_library(monkeypatch, lib, part):
     from paper_2512_09277_amd import api

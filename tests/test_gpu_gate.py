@@ -215,6 +215,19 @@ def test_large_batches(api, oracle, T, H, N, k):
     check(got, oracle.gate_topk(x, wg, k, want_logits=True), k, N, "bf16")
 
 
+@pytest.mark.parametrize("most,T,H,N", [(1024, 960, 7168, 256), (1024, 513, 4096, 256), (512, 448, 4096, 512), (2048, 1984, 4096, 128)])
+def test_workspace_of_the_largest_batch(api, most, T, H, N):
+    """One workspace, sized for the largest batch, for a smaller one that takes more K chunks or other kernels."""
+    import torch
+
+    print(f"gate workspace of {most} for T={T} H={H} N={N}", flush=True)
+    ws = torch.empty((api.load().moe_gate_topk_workspace_bytes(most, H, N, api.DTYPE_BF16),), dtype=torch.uint8, device="cuda")
+    x, wg = dev(W.activations(T, H, 99, "bf16")), dev(W.gate_weights(N, H, 100, "bf16"))
+    got, want = api.moe_gate_topk(x, wg, 8, ws=ws), api.moe_gate_topk(x, wg, 8)
+    for key in want:
+        assert torch.equal(got[key], want[key]), key
+
+
 # K chunks (steps of 64, n of them; the last may be shorter) of every length around the ring's period.  1921 tokens x 512 experts: tiles of
 # 128 tokens, a period of 6 steps, one chunk up to 7 steps, 8 chunks from 32; 1100 x 128 and 512 x 512: tiles of 64, a period of 4.
 @pytest.mark.parametrize("T,N,n", [(1921, 512, n) for n in (1, 2, 3, 4, 5, 6, 7, 9, 64, 72, 80, 85, 88, 96)]
