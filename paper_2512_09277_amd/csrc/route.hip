@@ -143,18 +143,23 @@ __device__ __forceinline__ int run_bases(int* hist, int n_keys, int e, int befor
 
 // ------------------------------------------------------------------------------------------ METRO
 constexpr int kIdCache = 8;      // int4 loads of ids a thread keeps in registers between the two passes
-constexpr int kOtherCache = 4;   // int4 loads of the ids outside its run
 constexpr int kRunCache = 8;     // chunks of its run whose ids a wave keeps in registers
+
+// Fewer steps than this in the chain (no more than spare slots or pairs, unless experts have no slot): no keys.  Preparing them costs two
+// barriers' phases, 0.8 us; a call with lists, us, with keys / without: 16 experts, 4 spare slots 5.2 / 4.3 at 1 token, 128 experts, 16 spare
+// slots 5.7 / 5.3 at 32 tokens, 256 experts, 32 spare slots 6.4 / 6.4, 512 experts, 64 spare slots 7.4 / 7.8.  Without lists the keys are
+// the faster everywhere.
+constexpr int kFewSteps = 32;
 
 // One workgroup per layer solves; with kLists, `split` workgroups solve the same layer and each emits its own run of
 // pairs and the rows these get in the token lists of one rank ("route tokens", Sec. 4.3).  All pairs of an expert go to
 // one replica, so the row of a pair is the slot's first row plus the number of earlier pairs of the expert: one stable
 // numbering, by the keys of the run only.  Bound by latency (barriers, LDS round trips, the serial chain), by the instructions of the
-// passes over the ids (16 waves on four issue ports: an instruction of all of them takes 16 cycles) and, where other kernels ran
-// before, by fetching its code (14 KB with lists), so loops are not unrolled.  Kernel times with the rule below, us, against one
-// workgroup that sorted its own pair_slot in three more passes: 64 pairs 9.9 -> 5.6, 2048 pairs 11.0 -> 6.9, 8192 pairs (256 experts)
-// 19.2 -> 10.5; without lists, 58 layers of 8192 pairs 10.2 -> 5.9 a pass (7.9 with flags set behind a branch per id and the masks
-// inside the chain).
+// passes over the ids (16 waves on four issue ports: an instruction of all of them takes 16 cycles) and by fetching its code anew in
+// every call (15 KB with lists, of which a call runs one form of the chain), so loops are not unrolled.  Kernel times in a layer with the
+// rule below, us, against one workgroup that sorted its own pair_slot in three more passes: 64 pairs 9.9 -> 5.2, 2048 pairs 11.0 -> 6.2,
+// 8192 pairs (256 experts) 19.2 -> 10.0; without lists, 58 layers of 8192 pairs 10.2 -> 5.7 a pass (7.9 with flags set behind a branch
+// per id and the masks inside the chain).
 template <bool kLists>
 __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
     __shared__ uint32_t s_active4[kMaxN / 4 + 1];  // a byte per expert: has pairs (kLists: of the run)
@@ -185,21 +190,14 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
     const int4* v = reinterpret_cast<const int4*>(ids);
     const int n4 = a.vec4 ? n_pairs / 4 : 0;
     const Run run(n_pairs, part, kLists ? a.split : 1);
-    int4 idc[kLists ? kOtherCache : kIdCache];       // kLists: of the ids outside the run
+    int4 idc[kLists ? 1 : kIdCache];
     int key[kLists ? kRunCache : 1];
     uint8_t* s_active = reinterpret_cast<uint8_t*>(s_active4);
-    auto outside = [&](int p) { return p < n_pairs && (p < run.lo || p >= run.hi); };
     if constexpr (kLists) {
 #pragma unroll
         for (int c = 0; c < kRunCache; ++c) {
             const int p = run.item(c);
             key[c] = c < run.per_wave && p < run.hi ? ids[p] : -1;
-        }
-#pragma unroll
-        for (int c = 0; c < kOtherCache; ++c) {
-            const int i = tid + c * kThreads;
-            idc[c] = make_int4(-1, -1, -1, -1);
-            if (a.vec4 && outside(4 * i)) idc[c] = v[i];
         }
     } else {
 #pragma unroll
@@ -253,24 +251,6 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
         s_active[min((uint32_t)id, (uint32_t)N)] = 1;
         top = max(top, (uint32_t)id + 1u);
     };
-    // f(id, whether it precedes the run) for the ids outside the run: the first from registers
-    auto others = [&](auto f) {
-        if (run.lo == 0 && run.hi >= n_pairs) return;    // uniform
-        auto four = [&](const int4& q, int i) {
-            const bool before = 4 * i < run.lo;
-            f(q.x, before); f(q.y, before); f(q.z, before); f(q.w, before);
-        };
-        if (a.vec4) {
-#pragma unroll
-            for (int c = 0; c < kOtherCache; ++c)
-                if (c * kThreads < n4) four(idc[kLists ? c : 0], tid + c * kThreads);      // uniform
-            for (int i = tid + kOtherCache * kThreads; i < n4; i += kThreads)
-                if (outside(4 * i)) four(v[i], i);
-        } else {
-            for (int p = tid; p < n_pairs; p += kThreads)
-                if (outside(p)) f(ids[p], p < run.lo);
-        }
-    };
     if constexpr (kLists) {
         int* mine = s_hist + wave_id() * N;
         auto count = [&](int id, int* counts) {
@@ -287,7 +267,7 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
             mark(id);
             count(id, mine);
         }
-        others([&](int id, bool before) {
+        for_other_ids(ids, n_pairs, a.vec4, run, [&](int id, bool before) {
             top = max(top, (uint32_t)id + 1u);
             count(id, before ? s_before : s_after);
         });
@@ -330,67 +310,96 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
     __syncthreads();
 
     // The chain: wave 0.  Load of rank g when expert e is served = forced experts below e (known beforehand) + chain picks so far.
-    // The known part becomes a key per step and rank, (load, rank), beyond every load where the rank does not host the expert, which all
-    // waves prepare for up to kChain steps; what remains in the chain is an add, a minimum over the ranks in registers and a
-    // compare, about 55 cycles per expert up to 16 ranks, where every lane of a group of 8 or 16 learns the minimum
-    // (150 to 230 with the masks and popcounts inside the chain).
-    const int group = G <= 8 ? 8 : G <= 16 ? 16 : kWave;
-    // every word has `parts` waves: each prepares every parts-th of its steps
-    const int parts = kWaves / n_words, of = wave_id() / parts, part_of = wave_id() - of * parts;
-    const int lw = min(lane_id(), n_words - 1);
-    const uint32_t my_lo = s_multi_lo[lw], my_hi = s_multi_hi[lw];
-    const int upto = wave_inclusive_sum(lane_id() < n_words ? __popc(my_lo) + __popc(my_hi) : 0);      // lane w: up to word w
-    const int steps = __builtin_amdgcn_readlane(upto, kWords - 1);
-    uint32_t picked = 0;                                 // of this lane's rank, in units of the key
-#pragma clang loop unroll(disable)
-    for (int first = 0; first < max(steps, 1); first += kChain) {        // once, unless more than kChain experts have a choice
-        if (of < n_words) {
-            const int g = lane_id();                     // masks of ranks past G are zero
-            uint64_t left = join64(__builtin_amdgcn_readlane(my_lo, of), __builtin_amdgcn_readlane(my_hi, of)), forced = 0;
-            int load = 0;
-#pragma clang loop unroll(disable)
-            for (int w = 0; w <= of; ++w) {
-                load += __popcll(forced);
-                forced = join64(s_forced_lo[w][g], s_forced_hi[w][g]);
-            }
-            int i = (of > 0 ? __builtin_amdgcn_readlane(upto, of - 1) : 0) - first;
-            for (int turn = part_of; left; left &= left - 1, ++i, turn = turn ? turn - 1 : parts - 1) {
-                if (turn || i < 0 || i >= kChain) continue;              // uniform
-                const int b = __ffsll((unsigned long long)left) - 1, e = (of << 6) + b;
-                const uint64_t hosts = join64(s_host_lo[e], s_host_hi[e]);
-                const uint32_t known = (uint32_t)(load + __popcll(forced & ((1ull << b) - 1ull)));
-                s_key[g][i] = (((hosts >> g) & 1ull) ? known << 6 : 0x40000000u) | (uint32_t)g;
-                if (g == 0) s_list[i] = e;
-            }
-        }
-        __syncthreads();
+    // With lists, few steps: the masks of a word's experts in registers, lane b those of expert 64 w + b, 150 to 230 cycles per expert.
+    // Else the known part becomes a key per step and rank, (load, rank), beyond every load where the rank does not host the expert,
+    // which all waves prepare for up to kChain steps; what remains in the chain is an add, a minimum over the ranks in registers
+    // and a compare, about 55 cycles per expert up to 16 ranks, where every lane of a group of 8 or 16 learns the minimum.
+    const bool few = kLists && min(S - N, n_pairs) < kFewSteps;              // uniform; any number of steps is right both ways
+    if (__builtin_expect(few, 0)) {              // out of line: laid in between it costs the other way 0.1 us
         if (tid < kWave) {
-            const int n = min(steps - first, kChain);
-            const uint32_t* keys = s_key[tid & (group - 1)];
-            auto chain = [&](auto least) {
-                uint4 ahead = *reinterpret_cast<const uint4*>(keys);
-#pragma clang loop unroll(disable)                     // the code of a call is fetched anew, so what loops is cheaper
-                for (int i = 0; i < n; i += 4) {         // past the last step: keys of no step, whose picks nobody asks for
-                    const uint32_t k[4] = {ahead.x, ahead.y, ahead.z, ahead.w};
-                    ahead = *reinterpret_cast<const uint4*>(keys + min(i + 4, kChain - 4));
-                    uint32_t m[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const uint32_t v = k[u] + picked;
-                        m[u] = least(v);
-                        picked += v == m[u] ? 64u : 0u;
-                    }
-                    *reinterpret_cast<uint4*>(s_best + i) = make_uint4(m[0], m[1], m[2], m[3]);
+            const int g = tid;                           // masks of ranks past G are zero
+            int load = 0;
+            for (int w = 0; w < n_words; ++w) {
+                const uint64_t forced = join64(s_forced_lo[w][g], s_forced_hi[w][g]);
+                const int mine = min((w << 6) + g, N - 1);
+                const uint32_t host_lo = s_host_lo[mine], host_hi = s_host_hi[mine];
+                uint64_t left = join64(__builtin_amdgcn_readfirstlane(s_multi_lo[w]), __builtin_amdgcn_readfirstlane(s_multi_hi[w]));
+                int picked = 0;
+                uint32_t best_of = 0xffffffffu;          // lane b: rank chosen for expert 64 w + b
+                for (; left; left &= left - 1) {
+                    const int b = __ffsll((unsigned long long)left) - 1;
+                    const uint64_t hosts = join64(__builtin_amdgcn_readlane(host_lo, b), __builtin_amdgcn_readlane(host_hi, b));
+                    const int now = load + __popcll(forced & ((1ull << b) - 1ull)) + picked;
+                    const uint32_t best = wave_min(((hosts >> g) & 1ull) ? ((uint32_t)now << 6) | (uint32_t)g : 0xffffffffu) & 63u;
+                    if ((uint32_t)g == best) ++picked;
+                    if (g == b) best_of = best;
                 }
-            };
-            if (group == 8) chain([](uint32_t v) { return group_min<8>(v); });
-            else if (group == 16) chain([](uint32_t v) { return group_min<16>(v); });
-            else chain([](uint32_t v) { return wave_min(v); });
-            if (tid < n) s_rank[s_list[tid]] = (int)(s_best[tid] & 63u);     // a wave's LDS accesses are done in order
-        } else if (kLists && first == 0) {               // meanwhile: what precedes each wave's chunks, and T[i]
+                if (best_of != 0xffffffffu) s_rank[(w << 6) + g] = (int)best_of;
+                load += __popcll(forced) + picked;
+            }
+        } else if constexpr (kLists) {                   // meanwhile: what precedes each wave's chunks, and T[i]
             for (int e = tid - kWave; e < N; e += kThreads - kWave) s_after[e] = run_bases(s_hist, N, e, s_before[e], s_after[e]);
         }
         __syncthreads();
+    } else {
+        const int group = G <= 8 ? 8 : G <= 16 ? 16 : kWave;
+        // every word has `parts` waves: each prepares every parts-th of its steps
+        const int parts = kWaves / n_words, of = wave_id() / parts, part_of = wave_id() - of * parts;
+        const int lw = min(lane_id(), n_words - 1);
+        const uint32_t my_lo = s_multi_lo[lw], my_hi = s_multi_hi[lw];
+        const int upto = wave_inclusive_sum(lane_id() < n_words ? __popc(my_lo) + __popc(my_hi) : 0);      // lane w: up to word w
+        const int steps = __builtin_amdgcn_readlane(upto, kWords - 1);
+        uint32_t picked = 0;                                 // of this lane's rank, in units of the key
+#pragma clang loop unroll(disable)
+        for (int first = 0; first < max(steps, 1); first += kChain) {        // once, unless more than kChain experts have a choice
+            if (of < n_words) {
+                const int g = lane_id();                     // masks of ranks past G are zero
+                uint64_t left = join64(__builtin_amdgcn_readlane(my_lo, of), __builtin_amdgcn_readlane(my_hi, of)), forced = 0;
+                int load = 0;
+#pragma clang loop unroll(disable)
+                for (int w = 0; w <= of; ++w) {
+                    load += __popcll(forced);
+                    forced = join64(s_forced_lo[w][g], s_forced_hi[w][g]);
+                }
+                int i = (of > 0 ? __builtin_amdgcn_readlane(upto, of - 1) : 0) - first;
+                for (int turn = part_of; left; left &= left - 1, ++i, turn = turn ? turn - 1 : parts - 1) {
+                    if (turn || i < 0 || i >= kChain) continue;              // uniform
+                    const int b = __ffsll((unsigned long long)left) - 1, e = (of << 6) + b;
+                    const uint64_t hosts = join64(s_host_lo[e], s_host_hi[e]);
+                    const uint32_t known = (uint32_t)(load + __popcll(forced & ((1ull << b) - 1ull)));
+                    s_key[g][i] = (((hosts >> g) & 1ull) ? known << 6 : 0x40000000u) | (uint32_t)g;
+                    if (g == 0) s_list[i] = e;
+                }
+            }
+            __syncthreads();
+            if (tid < kWave) {
+                const int n = min(steps - first, kChain);
+                const uint32_t* keys = s_key[tid & (group - 1)];
+                auto chain = [&](auto least) {
+                    uint4 ahead = *reinterpret_cast<const uint4*>(keys);
+#pragma clang loop unroll(disable)                     // the code of a call is fetched anew, so what loops is cheaper
+                    for (int i = 0; i < n; i += 4) {         // past the last step: keys of no step, whose picks nobody asks for
+                        const uint32_t k[4] = {ahead.x, ahead.y, ahead.z, ahead.w};
+                        ahead = *reinterpret_cast<const uint4*>(keys + min(i + 4, kChain - 4));
+                        uint32_t m[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const uint32_t v = k[u] + picked;
+                            m[u] = least(v);
+                            picked += v == m[u] ? 64u : 0u;
+                        }
+                        *reinterpret_cast<uint4*>(s_best + i) = make_uint4(m[0], m[1], m[2], m[3]);
+                    }
+                };
+                if (group == 8) chain([](uint32_t v) { return group_min<8>(v); });
+                else if (group == 16) chain([](uint32_t v) { return group_min<16>(v); });
+                else chain([](uint32_t v) { return wave_min(v); });
+                if (tid < n) s_rank[s_list[tid]] = (int)(s_best[tid] & 63u);     // a wave's LDS accesses are done in order
+            } else if (kLists && first == 0) {               // meanwhile: what precedes each wave's chunks, and T[i]
+                for (int e = tid - kWave; e < N; e += kThreads - kWave) s_after[e] = run_bases(s_hist, N, e, s_before[e], s_after[e]);
+            }
+            __syncthreads();
+        }
     }
 
     // y[i][g*] = 1 -> the lowest slot of expert i on rank g*.

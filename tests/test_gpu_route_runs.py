@@ -82,6 +82,37 @@ def test_chain_lengths(oracle, N, G, spr, choices):
                     assert np.array_equal(got[name][0].cpu().numpy(), ref[name]), (name, T, bad)
 
 
+# With lists the chain has two forms; which one takes a call hangs on its spare slots (S - N) and pairs, on both sides of 32, and either has
+# to serve any number of experts with a choice: here more than the spare slots, as half of the experts have no slot and no pair.
+@pytest.mark.parametrize("N,G,spr,k,T", [(16, 4, 5, 2, 15), (16, 4, 5, 2, 400), (200, 8, 28, 4, 700), (205, 8, 29, 4, 700), (200, 8, 29, 4, 700),
+                                         (512, 17, 32, 1, 31), (512, 17, 32, 1, 32), (512, 32, 17, 8, 900), (480, 64, 8, 8, 900)])
+def test_chain_of_few_spare_slots(oracle, N, G, spr, k, T):
+    from paper_2512_09277_amd import api
+
+    api.load()
+    print(f"few N={N} G={G} spr={spr} k={k} T={T}", flush=True)
+    rng = np.random.default_rng(N + G + T)
+    there = np.sort(rng.permutation(N)[:N // 2])
+    slots = [[] for _ in range(G)]
+    for e in np.concatenate([rng.permutation(there), rng.permutation(there)]):            # two replicas of most
+        free = [g for g in range(G) if len(slots[g]) < spr and e not in slots[g]]
+        slots[min(free, key=lambda g: len(slots[g]))].append(e)
+    s2e = np.concatenate([(s + [-1] * spr)[:spr] for s in slots]).astype(np.int32)
+    ids = np.stack([there[rng.permutation(there.size)[:k]] for _ in range(T)]).astype(np.int32)
+    ref = oracle.route_metro(ids, s2e, N, G, spr)
+    for rank in (0, G - 1):
+        got, lists = api.metro_route_permute(dev(ids), dev(s2e), N, G, spr, rank)
+        want = oracle.permute(ref["pair_slot"], rank, spr)
+        assert int(got["err_flag"].item()) == 0
+        for name in ("pair_slot", "expert_slot", "rank_active"):
+            assert np.array_equal(got[name][0].cpu().numpy(), ref[name]), name
+        n = int(want["n_pairs"])
+        assert int(lists["n_pairs"].item()) == n
+        assert np.array_equal(lists["group_offsets"].cpu().numpy(), want["group_offsets"])
+        assert np.array_equal(lists["perm_pair"].cpu().numpy()[:n], want["perm_pair"][:n])
+        assert np.array_equal(lists["pair_row"].cpu().numpy(), want["pair_row"])
+
+
 @pytest.mark.parametrize("L,T", [(3, 1500), (58, 1024), (129, 700), (300, 300)])
 def test_runs_of_many_layers(oracle, L, T):
     from paper_2512_09277_amd import api
