@@ -147,9 +147,10 @@ constexpr int kRunCache = 8;     // chunks of its run whose ids a wave keeps in 
 
 // Fewer steps than this in the chain (no more than spare slots or pairs, unless experts have no slot): no keys.  Preparing them costs two
 // barriers' phases, 0.8 us; a call with lists, us, with keys / without: 16 experts, 4 spare slots 5.2 / 4.3 at 1 token, 128 experts, 16 spare
-// slots 5.7 / 5.3 at 32 tokens, 256 experts, 32 spare slots 6.4 / 6.4, 512 experts, 64 spare slots 7.4 / 7.8.  Without lists the keys are
-// the faster everywhere.
-constexpr int kFewSteps = 32;
+// slots 5.7 / 5.3 at 32 tokens, 256 experts, 32 spare slots 6.4 / 6.4, 512 experts, 64 spare slots 7.4 / 7.8.  Deciding by the steps
+// themselves, counted in LDS, costs 0.1 us everywhere.  Fewer slots than experts say nothing: keys.  Without lists the keys are the
+// faster everywhere.
+constexpr uint32_t kFewSteps = 32;
 
 // One workgroup per layer solves; with kLists, `split` workgroups solve the same layer and each emits its own run of
 // pairs and the rows these get in the token lists of one rank ("route tokens", Sec. 4.3).  All pairs of an expert go to
@@ -314,7 +315,7 @@ __global__ __launch_bounds__(kThreads) void metro_route_kernel(RouteArgs a) {
     // Else the known part becomes a key per step and rank, (load, rank), beyond every load where the rank does not host the expert,
     // which all waves prepare for up to kChain steps; what remains in the chain is an add, a minimum over the ranks in registers
     // and a compare, about 55 cycles per expert up to 16 ranks, where every lane of a group of 8 or 16 learns the minimum.
-    const bool few = kLists && min(S - N, n_pairs) < kFewSteps;              // uniform; any number of steps is right both ways
+    const bool few = kLists && min((uint32_t)(S - N), (uint32_t)n_pairs) < kFewSteps;    // uniform; any number of steps is right both ways
     if (__builtin_expect(few, 0)) {              // out of line: laid in between it costs the other way 0.1 us
         if (tid < kWave) {
             const int g = tid;                           // masks of ranks past G are zero

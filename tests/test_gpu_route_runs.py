@@ -85,7 +85,8 @@ def test_chain_lengths(oracle, N, G, spr, choices):
 # With lists the chain has two forms; which one takes a call hangs on its spare slots (S - N) and pairs, on both sides of 32, and either has
 # to serve any number of experts with a choice: here more than the spare slots, as half of the experts have no slot and no pair.
 @pytest.mark.parametrize("N,G,spr,k,T", [(16, 4, 5, 2, 15), (16, 4, 5, 2, 400), (200, 8, 28, 4, 700), (205, 8, 29, 4, 700), (200, 8, 29, 4, 700),
-                                         (512, 17, 32, 1, 31), (512, 17, 32, 1, 32), (512, 32, 17, 8, 900), (480, 64, 8, 8, 900)])
+                                         (512, 17, 32, 1, 31), (512, 17, 32, 1, 32), (512, 32, 17, 8, 900), (480, 64, 8, 8, 900), (300, 16, 18, 3, 200),
+                                         (300, 19, 16, 3, 200)])
 def test_chain_of_few_spare_slots(oracle, N, G, spr, k, T):
     from paper_2512_09277_amd import api
 
@@ -94,9 +95,10 @@ def test_chain_of_few_spare_slots(oracle, N, G, spr, k, T):
     rng = np.random.default_rng(N + G + T)
     there = np.sort(rng.permutation(N)[:N // 2])
     slots = [[] for _ in range(G)]
-    for e in np.concatenate([rng.permutation(there), rng.permutation(there)]):            # two replicas of most
+    for e in np.concatenate([rng.permutation(there), rng.permutation(there)]):            # two replicas of all or most
         free = [g for g in range(G) if len(slots[g]) < spr and e not in slots[g]]
-        slots[min(free, key=lambda g: len(slots[g]))].append(e)
+        if free:
+            slots[min(free, key=lambda g: len(slots[g]))].append(e)
     s2e = np.concatenate([(s + [-1] * spr)[:spr] for s in slots]).astype(np.int32)
     ids = np.stack([there[rng.permutation(there.size)[:k]] for _ in range(T)]).astype(np.int32)
     ref = oracle.route_metro(ids, s2e, N, G, spr)
