@@ -5,7 +5,8 @@
 // which is matrix-operand layout, take a CU four times as long, see ring_k.h), DEPTH steps of loads in registers per wave.  A step
 // then passes through the wave's own LDS, which turns it into operand layout: 128 bytes per row, its 16-byte piece p at place
 // p ^ (row & 7), so that the 16 rows of a fragment read spread over the banks.  LDS accesses of a wave are done in order, so the next
-// step can be stored as soon as the reads of the last are issued.  The waves of a workgroup share K (wave w takes steps w, w + waves,
+// step can be stored as soon as the reads of the last are issued; a fence of wave scope, which is no instruction, keeps the compiler
+// from moving a lane's reads of other lanes' data over the stores.  The waves of a workgroup share K (wave w takes steps w, w + waves,
 // ..., so that together they read contiguous bytes of a row) and add their partial sums up through LDS afterwards, in a fixed
 // order, so results are deterministic.
 //
@@ -149,6 +150,7 @@ __device__ __forceinline__ void split_dot(Rows rows, int K, int s0, int stride, 
             *reinterpret_cast<u32x4*>(lds_x + mt * (2048 * XV) + (x_p >> 3) * 2048 + place(r, x_p & 7)) = x[buf][i];
         }
     };
+    auto wave_fence = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
     auto consume = [&](int step, auto Masked) {
         constexpr bool masked = decltype(Masked)::value && kRows == KRows::kRagged;
 #pragma unroll
@@ -217,7 +219,9 @@ __device__ __forceinline__ void split_dot(Rows rows, int K, int s0, int stride, 
             run_steps(std::make_integer_sequence<int, DEPTH>{}, load_x, 0);
         }
         auto step = [&](auto U, int s) {
+            wave_fence();
             store(U);
+            wave_fence();
             __builtin_amdgcn_sched_barrier(0);              // the loads refill the registers just stored, none earlier
             load_x(U, s + DEPTH);
             load_w(U, s + DEPTH);
@@ -225,7 +229,9 @@ __device__ __forceinline__ void split_dot(Rows rows, int K, int s0, int stride, 
             consume(s0 + stride * s, std::false_type{});
         };
         auto final_step = [&](auto U, int s) {
+            wave_fence();
             store(U);
+            wave_fence();
             consume(s0 + stride * s, std::true_type{});
         };
         int s = 0;
