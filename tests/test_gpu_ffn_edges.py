@@ -156,3 +156,37 @@ def test_unpermute_of_millions_of_tokens():
     assert torch.equal(out[some].float().cpu(), torch.tensor([0.0, 0.0, 0.0, 0.0, 2.0])[:, None].expand(5, H))
     del out
     torch.cuda.empty_cache()
+
+
+def test_activations_past_2_gib():
+    """Tokens (first stage) and list rows (second) more than 2^31 bytes into their arrays, in tall and narrow tiles: addressed by unsigned
+    32-bit offsets up to 4 GiB.  Against float64 products of the rows on the device."""
+    import torch
+
+    from paper_2512_09277_amd import api
+
+    api.load()
+    T, H, I, sizes = 1_200_000, 1024, 1024, [700, 9, 700]
+    n = sum(sizes)
+    print(f"past 2 GiB T={T} H={H} I={I} sizes={sizes}", flush=True)
+    assert 2**31 < (T - n) * H * 2 and T * H * 2 < 2**32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    tokens = torch.cat([torch.arange(T - 1000, T), torch.arange(n - 1000)]).cuda()[torch.randperm(n, generator=g, device="cuda")]
+    x = torch.empty((T, H), dtype=torch.bfloat16, device="cuda")
+    x[tokens] = torch.randn((n, H), generator=g, device="cuda").bfloat16()
+    w13 = (0.02 * torch.randn((3, 2 * I, H), generator=g, device="cuda")).bfloat16()
+    w2 = (0.02 * torch.randn((3, H, I), generator=g, device="cuda")).bfloat16()
+    perm = torch.zeros((T,), dtype=torch.int32, device="cuda")
+    perm[T - n:] = tokens.int()
+    offsets = torch.tensor([T - n, T - n + sizes[0], T - sizes[2], T], dtype=torch.int32, device="cuda")     # the last rows of the list
+    y = torch.empty((T, H), dtype=torch.bfloat16, device="cuda")
+    api.moe_grouped_ffn(x, perm, offsets, 1, w13, w2, y_perm=y)
+    begin = 0
+    for slot, m in enumerate(sizes):
+        h = torch.mm(x[tokens[begin:begin + m]].double(), w13[slot].double().t().contiguous())
+        want = torch.mm(torch.nn.functional.silu(h[:, :I]) * h[:, I:], w2[slot].double().t().contiguous())
+        got = y[T - n + begin:T - n + begin + m].double()
+        err = ((got - want).abs().max() / want.abs().max()).item()
+        assert err <= TOL["bf16"], (slot, err)
+        begin += m
