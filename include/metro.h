@@ -159,8 +159,8 @@ int moe_gate_topk(const void* x, const void* w_gate, int ldw, int T, int H, int 
  *                              elements apart, slots H*ldw2
  *   ldw13, ldw2                row pitches in elements, multiples of 8.  The weights are the
  *                              library's to lay out: a pitch that is a multiple of 4096 bytes makes
- *                              the 16 rows of one load instruction fall on the same few HBM
- *                              channels (measured: 5.3 instead of 6.2 TB/s at a 4096-byte pitch),
+ *                              the rows that are read together fall on the same few HBM channels (36 slots
+ *                              of 8 rows at H = 4096, I = 2048, both matrices: 4.8 instead of 6.1 TB/s),
  *                              so pad such rows, e.g. by 128 elements.
  *   y_perm [T*k,H]     dtype   out: rows 0..n_pairs-1 are written
  *   ws                         workspace of moe_grouped_ffn_workspace_bytes(); 256-byte aligned

@@ -14,7 +14,8 @@ constexpr int kMaxSpr = 64;
 // From 17 rows on a tile is better tall: a narrow one reads its rows once per 64 weight rows.  Measured, a layer, us, narrow up to
 // 16 / 32 / 48 / 64 rows: 1024 tokens at 7168 x 2048 (METRO rank) 606 / 607 / 611 / 615, 97 tokens of it 443.3 / 445.0 / 444.8 / 445.4,
 // 512 tokens at 4096 x 1536 150.7 / 151.7 / 152.9 / 151.6.  Where a long launch has only a few such tiles, they would start first
-// and stand alone (a layer of 256 token-balanced tokens at 4096 x 1536 149.0 / 151.4 with tiles that loaded in operand layout).
+// and stand alone: a layer at 4096 x 1536 of 128 / 256 / 384 tokens, narrow up to 32 / 16 rows, METRO 122.6 / 134.9 / 144.4 against
+// 124.5 / 139.4 / 145.9, token-balanced 132.0 / 138.3 / 141.0 against 134.6 / 138.0 / 142.7.
 constexpr int kTallRows = 128;              // rows of a full tall tile
 constexpr int kNarrowRows = 16;             // tiles of at most this many rows are narrow,
 constexpr int kNarrowIfFew = 32;            // or of this many in launches past kFewItems of which few would be tall (kTallItems),
@@ -38,13 +39,15 @@ inline int max_tiles(int cap, int spr, int tile_rows) { return spr + cap / tile_
 
 // Narrow tiles only, where that gives at most
 //   kOneRound items: each has a CU for itself and ends earlier than the longer K loop of a tall tile; a second workgroup on a
-//     CU costs more than that.  Measured as above, narrow only / with tall tiles: one slot of 128 rows at 2048 x 768 (48 items)
-//     28 / 40, one of 256 rows at 7168 x 2048 (256 items) 89 / 107; past it, 3 slots of 96 rows at 4096 x 1536 (288) 77 / 61,
-//     6 slots of 96 rows at 2048 x 768 (288) 44 / 38, of 32 and 64 rows at 4096 x 1536 (288) 74 / 60 and 95 / 67, 18 slots of 64
-//     rows at 2048 x 768 (432) 63 / 52;
+//     CU may cost more than that.  Measured, gate/up + down, us, weights from HBM, narrow only / with tall tiles: one slot of 128 rows at
+//     2048 x 768 (48 items) 17.7 / 28.7, one of 256 rows at 7168 x 2048 (256 items) 58 / 93.  Past it items alone do not tell: 288 of
+//     them are 59 / 52 and 71 / 59 as 6 slots of 32 and 64 rows at 4096 x 1536 and 35 / 30 as 12 slots of 32 rows at 2048 x 768, but 43 / 60
+//     as 3 slots of 96 rows at 4096 x 1536 and 28 / 36 as 6 of them at 2048 x 768; 18 slots of 64 rows at 2048 x 768 (432) 51 / 47, 6 of
+//     96 rows at 7168 x 2048 (768) 188 / 129;
 //   kFewItems items, if the tall tiles would be few (below kTallItems items) and not nearly alone (3 in 4): few long workgroups
 //     beside many short ones leave CUs idle at the end.  A whole layer of 2048 x 768 at 256, 320, 384 and 512 tokens (skewed
-//     popularity, 480 to 768 items, 60 to 170 of them would be tall) 56 / 61, 59 / 65, 60 / 67 and 65 / 70.
+//     popularity, 480 to 768 items, 60 to 170 of them would be tall), METRO 52 / 58, 53 / 61, 55 / 64 and 59 / 65, token-balanced 50 / 54,
+//     52 / 56, 53 / 57 and 55 / 58; from 768 tokens on narrow tiles only lose (68.6 / 66.2 and 64.9 / 62.0).
 constexpr int kOneRound = 256, kFewItems = 768, kTallItems = 170;
 
 struct CutRule {

@@ -10,7 +10,8 @@
 // of busy CUs are.  Launches:
 //   1. gate_logits_mfma_kernel: 64 tokens x 64 experts x one K chunk per workgroup (split-K so that
 //      ~512 workgroups exist at any batch size); both operands go straight from global memory into
-//      the MFMA operand layout; fp32 partial sums land in the workspace, part[chunk][t][e];
+//      the MFMA operand layout; large batches: gate_logits_lds_kernel, both operands staged through LDS;
+//      fp32 partial sums land in the workspace, part[chunk][t][e];
 //   2. gate_topk_kernel: one wave per token sums the chunks in a fixed order (deterministic), picks the
 //      top-k by k rounds of a wave-wide arg-max over (logit, -id) and forms the softmax weights;
 //   3. (only when the caller wants expert_count) gate_count_kernel: pairs per expert, one workgroup.
@@ -357,14 +358,14 @@ __global__ __launch_bounds__(kCountThreads) void gate_count_kernel(const int32_t
     for (int e = threadIdx.x; e < N; e += kCountThreads) cnt[e] = hist[e];
 }
 
-// Whether fp32 logits take one wave each.  A tile's workgroup pulls its rows (the distinct ones of 16 tokens and 16 experts) into
-// one CU at about 45 GB/s, which a wave per logit spreads over the chip; that wave costs a longer chain of loads, and all
-// of them read the weights through L2, so these have to stay there.  Measured, whole call, us, tiles against waves: H = 7168,
-// 64 experts, 1 / 16 / 64 / 128 tokens 22.1 / 31.2 / 31.9 / 31.8 against 17.8 / 18.6 / 19.8 / 22.9; 128 experts, 24 tokens 31.8
-// against 19.7, 256 experts, 4 tokens 25.3 against 19.0; H = 4096, 128 experts, 4 / 16 / 64 tokens 17.4 / 21.3 / 21.8 against
-// 13.3 / 13.7 / 16.2; H = 2048, 64 experts, 16 / 64 tokens 14.0 / 14.2 against 9.9 / 10.6.  Past the rule the waves lose (their
-// figures with a top-k kernel 3 us slower): H = 7168, 256 experts, 8 tokens 27.9 against 46.2; H = 4096, 128 experts, 128 tokens
-// 22.2 against 26.9, 256 experts, 8 tokens 19.4 against 31.0.
+// Whether fp32 logits take one wave each.  The line was drawn for tiles whose rows came into a CU at 45 GB/s, in operand layout, which a
+// wave per logit spreads over the chip; that wave costs a longer chain of loads, and all of them read the weights through L2, so
+// these have to stay there.  Measured with the tiles as they are, whole call, us, tiles / waves, inside the rule: H = 2048, 16 tokens,
+// 16 / 64 / 128 experts 10.1 / 10.3 / 11.3 against 9.9 / 10.0 / 10.8; H = 4096, 64 experts, 4 / 64 tokens 13.5 / 13.9 against 13.3 /
+// 13.8, 128 experts, 64 tokens 14.1 / 15.0; H = 7168, 64 experts, 1 / 16 / 128 tokens 17.9 / 17.7 / 18.7 against 18.1 / 18.6 / 20.9, 256
+// experts, 2 / 4 tokens 18.9 / 18.8 against 19.2 / 33.5.  So the waves are still ahead, by at most 5 %, with rows up to 4096, and
+// behind with longer ones.  Past the rule they lose as before: H = 7168, 256 experts, 8 tokens 18.8 / 41.4; H = 4096, 128 experts,
+// 128 tokens 14.3 / 22.8, 256 experts, 8 tokens 14.4 / 26.6.
 inline bool long_rows(int T, int H, int N) {
     const int64_t logits = (int64_t)T * N, weights = (int64_t)N * H * (int)sizeof(float);
     if ((int64_t)H * (std::min(T, kTokTile) + std::min(N, kTokTile) - 11) < 32768) return false;
@@ -380,13 +381,13 @@ void launch_general_logits(const GateArgs& a, hipStream_t st) {
         hipLaunchKernelGGL(kernel, dim3((a.T + rows - 1) / rows, (a.N + rows - 1) / rows), dim3(waves * kWave), 0, st, a);
     };
     // The largest tile that gives the chip enough workgroups: larger tiles read each operand fewer times, smaller ones put
-    // more CUs and waves to work.  Measured, logits kernel, us, 64 / 32 / 16 wide tiles: bf16, H = 4000, 200 experts, 4096
-    // tokens (256 / 896 / 3328 tiles) 25 / 42 / 75, 1024 tokens (64 / 224 / 832) 25 / 14 / 24; fp32, H = 2048, 128 experts,
-    // 512 tokens (16 / 64 / 256) 41 / 18 / 11.  The 32-wide tile pays from 64 tiles in bf16 (H = 2000, 200 experts, 512
-    // tokens, 112 tiles: 8.3 against 13.7) and, its fp32 matrix instructions being the longer part, from 256 in fp32.
-    // (Operands loaded in operand layout; as whole lines through LDS the last takes 6.7 us at 256 tokens, H = 2048, 128 experts in
-    // fp32 against 10.8.)  Short loops want little code: 8 waves two steps deep beat 16 waves four deep at 64 tokens, H = 1000, 5.1 to 7.6.
-    // (One wave per logit: 1887, 460, 83 us for the first, second and third, 93 for the fourth.)
+    // more CUs and waves to work.  Measured, whole call, us, 64 / 32 / 16 wide tiles: bf16, H = 4000, 200 experts, 4096
+    // tokens (256 / 896 / 3328 tiles) 35.3 / 44.0 / 61.4, 1024 tokens (64 / 224 / 832) 29.9 / 15.8 / 19.5, 700 tokens (154 of 32) 29.9 /
+    // 17.0 / 17.1, 512 tokens (112) 29.5 / 14.8 / 14.2; H = 2048, 40 experts, 1024 tokens (64) 19.7 / 11.9 / 9.9: in bf16 the 32-wide
+    // tile pays from about 150 tiles on, the line at 64 is from loads in operand layout.  fp32, H = 2048, 128 experts, 512 / 1024 / 2048
+    // tokens (64 / 128 / 256 of 32) 52.7 / 21.1 / 12.2, 53.0 / 21.3 / 15.8, 54.4 / 22.8 / 24.4; H = 7168, 256 experts, 1024 tokens (256)
+    // 156 / 49.5 / 53.7: there, its fp32 matrix instructions being the longer part, from 256.  Short loops want little code: 8 waves
+    // two steps deep beat 16 waves four deep at 64 tokens, H = 1000, logits kernel 5.1 to 7.6 (loads in operand layout).
     if (std::is_same_v<T, float> && long_rows(a.T, a.H, a.N)) {
         constexpr int per = kThreads / kWave;
         hipLaunchKernelGGL(gate_logits_wave_kernel, dim3(a.T, (a.N + per - 1) / per), dim3(kThreads), 0, st, a);
@@ -415,8 +416,8 @@ inline bool gate_big(int T, int H, int N) {
 
 // Tokens of its workgroups: 128 where that still makes two workgroups per CU at 8 K chunks, else 64, which takes 8 chunks
 // where 128 would need 16 to fill the chip -- half the partial sums to write and for the top-k kernel to read.  Measured,
-// logits + top-k, us, 128 / 64: 1024 tokens x 256 experts x 7168 13.2 + 6.9 / 12.0 + 5.0, 1500 x 256 x 4096 14.4 + 7.6 /
-// 13.1 + 6.0, 3000 x 256 x 4096 18.0 + 7.9 / 16.8 + 7.9, 4096 x 256 x 7168 27.6 + 9.3 / 33.1 + 9.6.
+// whole call, us, 128 / 64: 1024 tokens x 256 experts x 7168 23.6 / 20.0, 1500 x 256 x 4096 26.2 / 22.5, 3000 x 256 x 4096 27.6 / 27.6,
+// 3900 x 256 x 4096 31.3 / 34.5, 4096 x 256 x 7168 39.7 / 43.0, 2048 x 512 x 4096 29.6 / 32.2.
 inline int gate_big_tokens(int T, int N) { return ((T + 127) / 128) * (N / kBigTile) * 8 >= 512 ? 128 : 64; }
 
 // Tokens per workgroup: 64 (four sub-tiles) unless the batch is a single sub-tile.

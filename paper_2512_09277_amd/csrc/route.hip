@@ -654,10 +654,10 @@ __global__ __launch_bounds__(kThreads) void token_balanced_kernel(RouteArgs a) {
 }
 
 // Workgroups per layer for the calls that number pairs: runs of at least 2048 pairs, no more workgroups than CUs, and no more
-// than 64 readers of one layer's ids.  Counting the other runs' ids costs a workgroup about 1 us whatever their number, so
-// that one run is the better up to 2048 pairs; beyond, shorter runs would gain a little more.  Measured, 256 experts, us, runs of
-// at least 1024 / 2048 / 4096 pairs, METRO and token-balanced: 2048 pairs 8.9 / 7.9 / 7.9 and 7.9 / 7.5 / 7.5, 4096 pairs 9.1 / 9.5 / 9.2
-// and 8.0 / 8.8 / 9.5, 8192 pairs 9.6 / 10.1 / 11.0 and 8.6 / 9.4 / 11.0, 32768 pairs 13.6 / 14.1 / 15.0 and 11.8 / 12.6 / 14.4.
+// than 64 readers of one layer's ids.  Counting the other runs' ids costs a workgroup up to 1 us whatever their number, numbering more
+// of its own pairs costs it more.  Measured, 256 experts, a call with lists, us, runs of at least 1024 / 2048 / 4096 pairs, METRO and
+// token-balanced: 2048 pairs 6.9 / 7.1 / 7.1 and 6.5 / 7.0 / 7.0, 4096 pairs 7.0 / 7.6 / 8.4 and 6.6 / 7.5 / 9.0, 8192 pairs 7.7 / 8.0 /
+// 9.1 and 7.3 / 8.1 / 9.8, 32768 pairs 11.1 / 11.5 / 12.4 and 10.6 / 11.4 / 13.1; from 64 runs of 2048 on no difference.
 inline int split_for(const RouteArgs& a, int L) {
     const int64_t n = (int64_t)a.T * a.k;
     const int64_t most = L >= 256 ? 1 : std::min(256 / L, 64);
