@@ -407,7 +407,9 @@ inline bool gate_mfma_shape(int H, int N, int dtype) {
 // 17.4 / 17.9 / 20.4 / 25.9 against 14.3 / 14.7 / 17.0 / 19.4, 512 x 4096, 192 tokens 18.7 / 17.1, 128 x 4096, 768 tokens 15.3 / 13.5,
 // 256 x 2048, 768 tokens 16.2 / 14.5; below the line nothing to win (128 x 2048 and 256 x 1024 up to 1000 tokens within 0.2 us, either
 // way).  The staged kernel has four accumulators per block there: with two the error of the weights against 64 bits would grow (1000
-// tokens x 256 x 7168 1.51e-7 -> 1.72e-7, now 1.51e-7; they cost 0.2 us).
+// tokens x 256 x 7168 1.51e-7 -> 1.72e-7, now 1.51e-7; they cost 0.2 us).  Over 40 inputs, direct / staged, 1e-7: 320 tokens x 256 x
+// 4096 1.673 / 1.665, x 7168 1.945 / 1.700, 768 x 128 x 7168 1.570 / 1.561, 512 x 256 x 7168 1.696 / 1.698; larger only where 8 chunks
+// replace 4, 1000 x 512 x 4096 1.495 / 1.508.
 constexpr int kStagedAlways = 1024, kStagedMin = 64;
 constexpr int64_t kStagedProducts = 1 << 28;
 inline bool gate_big(int T, int H, int N) {
